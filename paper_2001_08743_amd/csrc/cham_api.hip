@@ -886,11 +886,18 @@ static int32_t synth_impl(const void *Xv, int xbytes, int64_t ld, int32_t d, con
     // LDS histogram: room for every cluster if that fits in 96 KiB and beside the kernel's other
     // arrays; byte knobs: never less than one cluster (all knobs, which always fits); two-byte
     // knobs: never less than one knob of one cluster
-    int64_t words = (int64_t)pl.kmax * d * cmax;
+    int64_t per_cluster = cmax;                            // words of one cluster: the task with the most choices
+    for (int t = 0; t < T; ++t) {
+        int64_t sum = 0;
+        for (int j = 0; j < d; ++j) sum += cards[(int64_t)t * d + j];
+        if (sum > per_cluster) per_cluster = sum;
+    }
+    if (wide) per_cluster = (int64_t)d * cmax;             // (its histograms have one width for all knobs)
+    int64_t words = (int64_t)pl.kmax * per_cluster;
     if (words > 24576) words = 24576;
     const int64_t avail = (160 * 1024 - (int64_t)synth_lds_bytes(d, pl.kmax, 0, xbytes)) / 4;
     if (words > avail) words = avail;
-    if (xbytes == 1 && words < (int64_t)d * cmax) words = (int64_t)d * cmax;
+    if (xbytes == 1 && words < per_cluster) words = per_cluster;
     if (words < cmax) return CHAM_E_CARD;
     a.hist_words = (int)words;
     a.task_off = reinterpret_cast<const int64_t *>(ws + pl.off_task);
@@ -929,8 +936,8 @@ static int32_t synth_impl(const void *Xv, int xbytes, int64_t ld, int32_t d, con
         a.wide_hist = reinterpret_cast<unsigned *>(p);
         e = launch_synth_wide(a, total, s);
     } else {
-        int nt = pl.nt < 256 ? 256 : pl.nt;
-        if (nt > 1024) nt = 1024;
+        // one row per thread and step: as many threads as there is work for
+        const int nt = pl.n_max >= 1024 ? 1024 : (pl.n_max >= 512 ? 512 : 256);
         e = launch_synth(a, nt, s);
     }
     if (e != hipSuccess) return hip_fail(e);

@@ -238,6 +238,34 @@ __device__ __forceinline__ bool visited_has(const uint64_t *v, int64_t n, uint64
     return lo < n && v[lo] == key;
 }
 
+// The same for one key per group of eight neighbouring lanes (every lane of the wave takes part, `on`
+// is uniform within a group): eight probes cut the range into nine, so a lookup in 2^20 words takes
+// seven rounds of independent loads instead of twenty dependent ones.  The lookup is pure latency:
+// with one lane per key it was most of the synthesis of a task with few clusters.
+__device__ __forceinline__ bool visited_has8(const uint64_t *v, int64_t n, uint64_t key, bool on)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    const int sub = lane & 7, first = lane & ~7;
+    if (n < 0) {                                    // table: the chain is short, one lane walks it
+        const bool has = on && sub == 0 && visited_has(v, n, key);
+        return (__ballot(has) >> first) & 1ull;
+    }
+    int64_t lo = 0, hi = on ? n : 0;
+    while (__ballot(lo < hi)) {
+        const int64_t span = hi - lo;
+        const int64_t at = lo + span * (sub + 1) / 9;                 // < hi while span > 0
+        const bool less = span > 0 && v[at] < key;                    // true for a prefix of the group
+        const int cnt = __popc((unsigned)(__ballot(less) >> first) & 0xFFu);
+        if (span > 0) {
+            const int64_t nlo = cnt > 0 ? lo + span * cnt / 9 + 1 : lo;
+            const int64_t nhi = cnt < 8 ? lo + span * (cnt + 1) / 9 : hi;
+            lo = nlo;
+            hi = nhi;
+        }
+    }
+    return on && lo < n && v[lo] == key;
+}
+
 // Insert one hash: 1 = newly inserted, 2 = was there already, 0 = the table is full.
 __device__ __forceinline__ int table_insert_new(uint64_t *v, uint64_t mask, uint64_t h)
 {
@@ -367,11 +395,72 @@ __global__ void table_insert_configs_kernel(uint64_t *v, int64_t slots, const XT
     if (!table_insert(v, (uint64_t)slots - 1, h) && overflow) *overflow = 1;
 }
 
+// Value of the mode from the histogram of one (cluster, knob), by one wave: largest count, smallest
+// value on ties; every lane returns it.
+__device__ __forceinline__ int wave_mode(const unsigned *hv, int card)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    unsigned long long best = 0xFFFFull;             // count << 16 | (65535 - value): value 0 with no count
+    for (int v = lane; v < card; v += kWave) {
+        const unsigned long long key = ((unsigned long long)hv[v] << 16) | (unsigned)(0xFFFF - v);
+        best = key > best ? key : best;
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        const unsigned long long o = __shfl_xor(best, off, kWave);
+        best = o > best ? o : best;
+    }
+    return 0xFFFF - (int)(best & 0xFFFFull);
+}
+
+// The ordered accept / drop walk over the flagged clusters (ascending), by one wave.  Membership in the
+// visited set and the hashes are known already, so a step only asks whether the replacement equals a
+// kept pick or an accepted replacement: equal vectors have equal hashes, and a lane that finds an
+// equal hash compares the vectors themselves.  fl: flags (3 = flagged); cfg / hcfg: configurations and
+// hashes of the kept picks, joined by the accepted replacements; mode / hmode / vis: replacements.
+template <typename XT>
+__device__ __forceinline__ void accept_modes(int k, int d, int nf, const int *flagged, const uint8_t *hasv, const uint8_t *vis,
+                                             const uint64_t *hmode, const XT *mode, uint8_t *fl, uint64_t *hcfg, XT *cfg)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    for (int f = 0; f < nf; ++f) {
+        const int c = flagged[f];
+        if (!hasv[c] || vis[c]) continue;            // stays DROPPED
+        const uint64_t h = hmode[c];
+        const XT *m = mode + c * d;
+        bool dup = false;
+        for (int q = lane; q < k; q += kWave) {
+            const int fq = fl[q];
+            if ((fq == 1 || (fq == 2 && q < c)) && hcfg[q] == h) {
+                bool same = true;
+                for (int j = 0; j < d && same; ++j) same = cfg[q * d + j] == m[j];
+                dup = dup || same;
+            }
+        }
+        if (!__ballot(dup)) {
+            if (lane == 0) {
+                fl[c] = 2;                           // CHAM_OUT_SYNTH
+                hcfg[c] = h;
+            }
+            for (int j = lane; j < d; j += kWave) cfg[c * d + j] = m[j];
+        }
+        __builtin_amdgcn_wave_barrier();
+        __threadfence_block();
+    }
+}
+
 // Synthesis: one workgroup per task.
 //  A. flag picks (invalid row, or hash in the visited set); unflagged picks are KEPT.
 //  B. histograms value counts per (flagged cluster, knob) over the cluster's valid members, a
-//     chunk of clusters at a time (as many as fit the LDS histogram), and takes the mode.
-//  C. one wave walks the flagged clusters in ascending order and accepts or drops each mode.
+//     window of knobs and a chunk of clusters at a time (as many as fit the LDS histogram, every knob
+//     with as many words as it has choices), and takes the modes, one wave per (cluster, knob).
+//  C. hashes and looks up all modes at once; then one wave walks the flagged clusters in ascending
+//     order and accepts or drops each mode.
+// Bound by latency (visited lookups) and LDS atomics, not by bandwidth: a task's rows are read once
+// per window and chunk.  Histograms packed by cardinality and wave-wide modes: with cardinalities in
+// the thousands (16 tasks of up to 1900 rows x 27 knobs) 49 us; one lane per histogram scanned thousands
+// of words and took 3349 us.  Lookups by groups of eight lanes: 256 tasks x 4096 rows x 24 knobs with 2^20 visited
+// hashes 45 us, 81 us with one lane per lookup.
 template <typename XT>
 __global__ __launch_bounds__(1024) void synth_kernel(const SynthArgs a)
 {
@@ -387,95 +476,113 @@ __global__ __launch_bounds__(1024) void synth_kernel(const SynthArgs a)
     uint8_t *oflag = a.out_flag + (int64_t)t * kmax;
 
     // LDS carve
-    unsigned *hist = reinterpret_cast<unsigned *>(smem);                       // [hist_words]
-    unsigned char *p8 = smem + sizeof(unsigned) * (size_t)a.hist_words;
+    unsigned char *p8 = smem;
+    uint64_t *hcfg = reinterpret_cast<uint64_t *>(p8);    p8 += sizeof(uint64_t) * (size_t)kmax; // [kmax] hashes of kept / accepted
+    uint64_t *hmode = reinterpret_cast<uint64_t *>(p8);   p8 += sizeof(uint64_t) * (size_t)kmax; // [kmax] hashes of the modes
+    unsigned *hist = reinterpret_cast<unsigned *>(p8);    p8 += sizeof(unsigned) * (size_t)a.hist_words;
     int *slot_of = reinterpret_cast<int *>(p8);           p8 += sizeof(int) * (size_t)kmax;      // [kmax]
     int *flagged = reinterpret_cast<int *>(p8);           p8 += sizeof(int) * (size_t)kmax;      // compact list
     int *misc = reinterpret_cast<int *>(p8);              p8 += sizeof(int) * 8;
+    int *card = reinterpret_cast<int *>(p8);              p8 += sizeof(int) * 64;                // [d] cardinalities
+    int *coff = reinterpret_cast<int *>(p8);              p8 += sizeof(int) * 66;                // [d + 1] sums of the cardinalities before
     XT *cfg = reinterpret_cast<XT *>(p8);                 p8 += sizeof(XT) * (size_t)kmax * d;   // [kmax][d] kept / accepted
     XT *mode = reinterpret_cast<XT *>(p8);                p8 += sizeof(XT) * (size_t)kmax * d;   // [kmax][d] candidate modes
     uint8_t *fl = p8;                                     p8 += (size_t)kmax;                    // [kmax] flags
-    uint8_t *hasv = p8;                                                                           // [kmax] cluster has a valid member
+    uint8_t *hasv = p8;                                   p8 += (size_t)kmax;                    // [kmax] cluster has a valid member
+    uint8_t *vis = p8;                                                                            // [kmax] mode is visited
 
+    const int k = (ci >= 0 && ci < a.n_k) ? a.ks[ci] : 0;
+    const XT *picks = reinterpret_cast<const XT *>(a.pick_cfg) + (int64_t)t * kmax * d;
     for (int c = tid; c < kmax; c += blockDim.x) {
         fl[c] = 0;          // CHAM_OUT_EMPTY
         hasv[c] = 0;
+        vis[c] = 0;
         slot_of[c] = -1;
     }
-    for (int e = tid; e < kmax * d; e += blockDim.x) cfg[e] = 0;
+    for (int e = tid; e < kmax * d; e += blockDim.x) cfg[e] = e < k * d ? picks[e] : (XT)0;
+    if (tid < d) card[tid] = a.cards[(int64_t)t * d + tid];
     __syncthreads();
-    const int k = (ci >= 0 && ci < a.n_k) ? a.ks[ci] : 0;
+    if (tid == 0) {
+        int sum = 0, cmax = 1;
+        for (int j = 0; j < d; ++j) {
+            coff[j] = sum;
+            sum += card[j];
+            cmax = card[j] > cmax ? card[j] : cmax;
+        }
+        coff[d] = sum;
+        misc[1] = cmax;
+    }
     const uint64_t salt = a.salts[t];
-    const uint16_t *card = a.cards + (int64_t)t * d;
 
-    // A. flag picks
-    for (int c = tid; c < k; c += blockDim.x) {
-        const int row = a.pick_row[(int64_t)t * kmax + c];
-        if (row < 0) continue;
-        const XT *pc = reinterpret_cast<const XT *>(a.pick_cfg) + ((int64_t)t * kmax + c) * d;
+    // A. flag picks, eight lanes each
+    for (int c0 = 0; c0 < k; c0 += blockDim.x / 8) {
+        const int c = c0 + tid / 8;
+        const int row = c < k ? a.pick_row[(int64_t)t * kmax + c] : -1;
+        const bool on = row >= 0;
         uint64_t h = fnv_begin(salt);
-        for (int j = 0; j < d; ++j) h = fnv_step(h, pc[j]);
-        const bool invalid = a.valid && a.valid[r0 + row] == 0;
-        const bool bad = invalid || visited_has(a.visited, a.n_visited, h);
-        if (bad) {
-            fl[c] = 3;      // CHAM_OUT_DROPPED until a replacement is accepted
-        } else {
-            fl[c] = 1;      // CHAM_OUT_KEPT
-            for (int j = 0; j < d; ++j) cfg[c * d + j] = pc[j];
+        if (on)
+            for (int j = 0; j < d; ++j) h = fnv_step(h, cfg[c * d + j]);
+        const bool invalid = on && a.valid && a.valid[r0 + row] == 0;
+        const bool bad = visited_has8(a.visited, a.n_visited, h, on) || invalid;
+        if (on && (tid & 7) == 0) {
+            fl[c] = bad ? 3 : 1;      // CHAM_OUT_DROPPED until a replacement is accepted, or CHAM_OUT_KEPT
+            hcfg[c] = h;
         }
     }
     __syncthreads();
-    if (tid == 0) {
+    for (int e = tid; e < k * d; e += blockDim.x)
+        if (fl[e / d] != 1) cfg[e] = 0;
+    if (tid < kWave) {
         int nf = 0;
-        for (int c = 0; c < k; ++c)
-            if (fl[c] == 3) flagged[nf++] = c;
-        misc[0] = nf;
+        for (int c0 = 0; c0 < k; c0 += kWave) {
+            const int c = c0 + tid;
+            const uint64_t m = __ballot(c < k && fl[c] == 3);
+            if ((m >> tid) & 1ull) flagged[nf + __popcll(m & ((1ull << tid) - 1ull))] = c;
+            nf += __popcll(m);
+        }
+        if (tid == 0) misc[0] = nf;
     }
     __syncthreads();
     const int nf = misc[0];
+    const int cmax = misc[1];
 
     // B. modes, a window of knobs and a chunk of flagged clusters at a time (all knobs at once when
     // the histogram of a whole cluster fits)
-    int cmax = 1;
-    for (int j = 0; j < d; ++j) cmax = card[j] > cmax ? card[j] : cmax;
-    int jn = a.hist_words / cmax;                       // >= 1 by construction on the host
-    jn = jn > d ? d : jn;
-    const int per_cluster = jn * cmax;
-    const int chunk = a.hist_words / per_cluster;
-    for (int j0 = 0; j0 < d; j0 += jn) {
-        const int jw = (d - j0) < jn ? (d - j0) : jn;
+    for (int j0 = 0, j1 = 0; nf > 0 && j0 < d; j0 = j1) {
+        const int w0 = coff[j0];
+        j1 = j0 + 1;                                     // one knob fits by construction on the host
+        while (j1 < d && coff[j1 + 1] - w0 <= a.hist_words) ++j1;
+        const int jw = j1 - j0;
+        const int per_cluster = coff[j1] - w0;
+        const int chunk = a.hist_words / per_cluster;
         for (int f0 = 0; f0 < nf; f0 += chunk) {
             const int fn = (nf - f0) < chunk ? (nf - f0) : chunk;
             for (int e = tid; e < fn * per_cluster; e += blockDim.x) hist[e] = 0u;
             for (int q = tid; q < fn; q += blockDim.x) slot_of[flagged[f0 + q]] = q;
             __syncthreads();
             for (int64_t r = r0 + tid; r < r1; r += blockDim.x) {
-                const int s = slot_of[a.labels_sel[r]];
+                const int lab = a.labels_sel[r];
+                const int s = slot_of[lab];
                 if (s < 0) continue;
                 if (a.valid && a.valid[r] == 0) continue;
-                unsigned *hrow = hist + (size_t)s * per_cluster;
-                for (int j = 0; j < jw; ++j) {
-                    const unsigned v = X[(int64_t)(j0 + j) * a.ld + r];
-                    if (v < (unsigned)cmax) atomicAdd(&hrow[j * cmax + v], 1u);
+                const int base = s * per_cluster - w0;
+                const XT *xr = X + r;
+                // eight knob values under way at a time
+                for (int j = j0; j < j1; j += 8) {
+                    unsigned v[8];
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) v[i] = j + i < j1 ? (unsigned)xr[(int64_t)(j + i) * a.ld] : 0xFFFFFFFFu;
+#pragma unroll
+                    for (int i = 0; i < 8; ++i)
+                        if (j + i < j1 && v[i] < (unsigned)card[j + i]) atomicAdd(&hist[base + coff[j + i] + (int)v[i]], 1u);
+                    if (j == 0 && v[0] < (unsigned)cmax) hasv[lab] = 1;
                 }
             }
             __syncthreads();
-            for (int e = tid; e < fn * jw; e += blockDim.x) {
-                const int q = e / jw, j = e % jw;
-                const unsigned *hv = hist + (size_t)q * per_cluster + (size_t)j * cmax;
-                int bv = 0;
-                unsigned bc = hv[0];
-                unsigned total = hv[0];
-                for (int v = 1; v < cmax; ++v) {
-                    total += hv[v];
-                    if (v < card[j0 + j] && hv[v] > bc) {
-                        bc = hv[v];
-                        bv = v;
-                    }
-                }
-                const int c = flagged[f0 + q];
-                mode[c * d + j0 + j] = (XT)bv;
-                if (j0 + j == 0) hasv[c] = total > 0 ? 1 : 0;
+            for (int e = tid / kWave; e < fn * jw; e += blockDim.x / kWave) {
+                const int q = e / jw, j = j0 + e % jw;
+                const int mv = wave_mode(hist + (size_t)q * per_cluster + (coff[j] - w0), card[j]);
+                if ((tid & (kWave - 1)) == 0) mode[flagged[f0 + q] * d + j] = (XT)mv;
             }
             __syncthreads();
             for (int q = tid; q < fn; q += blockDim.x) slot_of[flagged[f0 + q]] = -1;
@@ -483,41 +590,32 @@ __global__ __launch_bounds__(1024) void synth_kernel(const SynthArgs a)
         }
     }
 
-    // C. accept or drop, in ascending cluster order, by the first wave
-    if (tid < kWave) {
-        const int lane = tid;
-        for (int f = 0; f < nf; ++f) {
-            const int c = flagged[f];
-            if (!hasv[c]) continue;
-            const XT *m = mode + c * d;
-            bool dup = false;
-            for (int q = lane; q < k; q += kWave) {
-                const int fq = fl[q];
-                if (fq == 1 || (fq == 2 && q < c)) {
-                    bool same = true;
-                    for (int j = 0; j < d && same; ++j) same = cfg[q * d + j] == m[j];
-                    dup = dup || same;
-                }
-            }
-            uint64_t h = fnv_begin(salt);
-            for (int j = 0; j < d; ++j) h = fnv_step(h, m[j]);
-            const bool vis = visited_has(a.visited, a.n_visited, h);
-            const bool any_dup = __ballot(dup) != 0ull;
-            if (!vis && !any_dup) {
-                if (lane == 0) fl[c] = 2;       // CHAM_OUT_SYNTH
-                for (int j = lane; j < d; j += kWave) cfg[c * d + j] = m[j];
-            }
-            __builtin_amdgcn_wave_barrier();
-            __threadfence_block();
+    // C. look up every mode, eight lanes each, then accept or drop them in ascending cluster order
+    for (int f0 = 0; f0 < nf; f0 += blockDim.x / 8) {
+        const int f = f0 + tid / 8;
+        const int c = f < nf ? flagged[f] : 0;
+        const bool on = f < nf && hasv[c];
+        uint64_t h = fnv_begin(salt);
+        if (on)
+            for (int j = 0; j < d; ++j) h = fnv_step(h, mode[c * d + j]);
+        const bool has = visited_has8(a.visited, a.n_visited, h, on);
+        if (on && (tid & 7) == 0) {
+            hmode[c] = h;
+            vis[c] = has ? 1 : 0;
         }
     }
     __syncthreads();
+    if (tid < kWave) accept_modes<XT>(k, d, nf, flagged, hasv, vis, hmode, mode, fl, hcfg, cfg);
+    __syncthreads();
     for (int e = tid; e < kmax * d; e += blockDim.x) ocfg[e] = cfg[e];
     for (int c = tid; c < kmax; c += blockDim.x) oflag[c] = fl[c];
-    if (tid == 0) {
+    if (tid < kWave) {
         int cnt = 0;
-        for (int c = 0; c < k; ++c) cnt += (fl[c] == 1 || fl[c] == 2) ? 1 : 0;
-        a.out_count[t] = cnt;
+        for (int c0 = 0; c0 < k; c0 += kWave) {
+            const int f = c0 + tid < k ? fl[c0 + tid] : 0;
+            cnt += __popcll(__ballot(f == 1 || f == 2));
+        }
+        if (tid == 0) a.out_count[t] = cnt;
     }
 }
 
@@ -699,7 +797,7 @@ __global__ void snap_wide_finish_kernel(const SnapArgs a)
 
 // Synthesis, wide: flag picks (one workgroup per task), value histograms of the flagged clusters
 // over row chunks, then modes and the ordered accept / drop per task.
-__global__ __launch_bounds__(256) void synth_wide_flag_kernel(const SynthArgs a)
+__global__ __launch_bounds__(1024) void synth_wide_flag_kernel(const SynthArgs a)
 {
     __shared__ int nf_sh;
     const int tid = threadIdx.x;
@@ -712,38 +810,40 @@ __global__ __launch_bounds__(256) void synth_wide_flag_kernel(const SynthArgs a)
     uint8_t *ocfg = a.out_cfg + (int64_t)t * kmax * d;
     uint8_t *oflag = a.out_flag + (int64_t)t * kmax;
     int *slot_of = a.wide_slot + (int64_t)t * kmax;
-    for (int e = tid; e < kmax * d; e += blockDim.x) ocfg[e] = 0;
-    for (int c = tid; c < kmax; c += blockDim.x) {
-        int f = 0;
-        slot_of[c] = -1;
-        if (c < k) {
-            const int row = a.pick_row[(int64_t)t * kmax + c];
-            if (row >= 0) {
-                const uint8_t *pc = a.pick_cfg + ((int64_t)t * kmax + c) * d;
-                uint64_t h = fnv_begin(salt);
-                for (int j = 0; j < d; ++j) h = fnv_step(h, pc[j]);
-                const bool invalid = a.valid && a.valid[r0 + row] == 0;
-                f = (invalid || visited_has(a.visited, a.n_visited, h)) ? 3 : 1;
-            }
+    for (int c0 = 0; c0 < kmax; c0 += blockDim.x / 8) {
+        const int c = c0 + tid / 8;
+        const int row = c < k ? a.pick_row[(int64_t)t * kmax + c] : -1;
+        const bool on = row >= 0;
+        const uint8_t *pc = a.pick_cfg + ((int64_t)t * kmax + c) * d;
+        uint64_t h = fnv_begin(salt);
+        if (on)
+            for (int j = 0; j < d; ++j) h = fnv_step(h, pc[j]);
+        const bool invalid = on && a.valid && a.valid[r0 + row] == 0;
+        const bool bad = visited_has8(a.visited, a.n_visited, h, on) || invalid;
+        if (c < kmax && (tid & 7) == 0) {
+            oflag[c] = on ? (bad ? 3 : 1) : 0;
+            slot_of[c] = -1;
         }
-        oflag[c] = (uint8_t)f;
+        if (c < kmax)
+            for (int j = tid & 7; j < d; j += 8) ocfg[c * d + j] = on && !bad ? pc[j] : (uint8_t)0;
     }
     __syncthreads();
-    for (int c = tid; c < k; c += blockDim.x) {
-        if (oflag[c] == 1) {
-            const uint8_t *pc = a.pick_cfg + ((int64_t)t * kmax + c) * d;
-            for (int j = 0; j < d; ++j) ocfg[c * d + j] = pc[j];
-        }
-    }
-    if (tid == 0) {
+    if (tid < kWave) {
         int nf = 0;
-        for (int c = 0; c < k; ++c)
-            if (oflag[c] == 3) {
-                a.wide_list[(int64_t)t * kmax + nf] = c;
-                slot_of[c] = nf++;
+        for (int c0 = 0; c0 < k; c0 += kWave) {
+            const int c = c0 + tid;
+            const uint64_t m = __ballot(c < k && oflag[c] == 3);
+            if ((m >> tid) & 1ull) {
+                const int f = nf + __popcll(m & ((1ull << tid) - 1ull));
+                a.wide_list[(int64_t)t * kmax + f] = c;
+                slot_of[c] = f;
             }
-        a.wide_nf[t] = nf;
-        nf_sh = nf;
+            nf += __popcll(m);
+        }
+        if (tid == 0) {
+            a.wide_nf[t] = nf;
+            nf_sh = nf;
+        }
     }
     __syncthreads();
     const int64_t words = (int64_t)nf_sh * d * a.wide_cmax;
@@ -796,7 +896,7 @@ __global__ __launch_bounds__(1024) void synth_wide_hist_kernel(const SynthArgs a
     }
 }
 
-__global__ __launch_bounds__(256) void synth_wide_finish_kernel(const SynthArgs a)
+__global__ __launch_bounds__(1024) void synth_wide_finish_kernel(const SynthArgs a)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     const int tid = threadIdx.x;
@@ -811,69 +911,63 @@ __global__ __launch_bounds__(256) void synth_wide_finish_kernel(const SynthArgs 
     uint8_t *oflag = a.out_flag + (int64_t)t * kmax;
     const int *flagged = a.wide_list + (int64_t)t * kmax;
     const unsigned *hist = a.wide_hist + (int64_t)t * kmax * d * cmax;
-    uint8_t *cfg = smem;                       // [kmax][d]
+    uint64_t *hcfg = reinterpret_cast<uint64_t *>(smem);   // [kmax] hashes of the kept picks and accepted modes
+    uint64_t *hmode = hcfg + kmax;                          // [kmax] hashes of the modes
+    uint8_t *cfg = reinterpret_cast<uint8_t *>(hmode + kmax);   // [kmax][d]
     uint8_t *mode = cfg + (size_t)kmax * d;    // [kmax][d]
     uint8_t *fl = mode + (size_t)kmax * d;     // [kmax]
     uint8_t *hasv = fl + kmax;                 // [kmax]
+    uint8_t *vis = hasv + kmax;                // [kmax]
     for (int e = tid; e < kmax * d; e += blockDim.x) cfg[e] = ocfg[e];
     for (int c = tid; c < kmax; c += blockDim.x) {
         fl[c] = oflag[c];
         hasv[c] = 0;
+        vis[c] = 0;
     }
     __syncthreads();
-    int tcmax = 1;
-    for (int j = 0; j < d; ++j) tcmax = card[j] > tcmax ? card[j] : tcmax;
-    for (int e = tid; e < nf * d; e += blockDim.x) {
+    for (int c = tid; c < k; c += blockDim.x) {
+        uint64_t h = fnv_begin(salt);
+        for (int j = 0; j < d; ++j) h = fnv_step(h, cfg[c * d + j]);
+        hcfg[c] = h;                           // (used for kept picks only)
+    }
+    // modes: one wave per (flagged cluster, knob); values from the knob's cardinality on are no choices, but a
+    // member that holds one in knob 0 still makes the cluster a usable one
+    for (int e = tid / kWave; e < nf * d; e += blockDim.x / kWave) {
         const int q = e / d, j = e % d;
         const unsigned *hv = hist + ((size_t)q * d + j) * cmax;
-        int bv = 0;
-        unsigned bc = hv[0], total = hv[0];
-        for (int v = 1; v < tcmax; ++v) {
-            total += hv[v];
-            if (v < card[j] && hv[v] > bc) {
-                bc = hv[v];
-                bv = v;
-            }
-        }
+        const int mv = wave_mode(hv, card[j]);
         const int c = flagged[q];
-        mode[c * d + j] = (uint8_t)bv;
-        if (j == 0) hasv[c] = total > 0 ? 1 : 0;
+        if ((tid & (kWave - 1)) == 0) mode[c * d + j] = (uint8_t)mv;
+        if (j == 0)
+            for (int v = tid & (kWave - 1); v < cmax; v += kWave)
+                if (hv[v] != 0u) hasv[c] = 1;
     }
     __syncthreads();
-    if (tid < kWave) {
-        const int lane = tid;
-        for (int f = 0; f < nf; ++f) {
-            const int c = flagged[f];
-            if (!hasv[c]) continue;
-            const uint8_t *m = mode + c * d;
-            bool dup = false;
-            for (int q = lane; q < k; q += kWave) {
-                const int fq = fl[q];
-                if (fq == 1 || (fq == 2 && q < c)) {
-                    bool same = true;
-                    for (int j = 0; j < d && same; ++j) same = cfg[q * d + j] == m[j];
-                    dup = dup || same;
-                }
-            }
-            uint64_t h = fnv_begin(salt);
-            for (int j = 0; j < d; ++j) h = fnv_step(h, m[j]);
-            const bool vis = visited_has(a.visited, a.n_visited, h);
-            const bool any_dup = __ballot(dup) != 0ull;
-            if (!vis && !any_dup) {
-                if (lane == 0) fl[c] = 2;
-                for (int j = lane; j < d; j += kWave) cfg[c * d + j] = m[j];
-            }
-            __builtin_amdgcn_wave_barrier();
-            __threadfence_block();
+    for (int f0 = 0; f0 < nf; f0 += blockDim.x / 8) {
+        const int f = f0 + tid / 8;
+        const int c = f < nf ? flagged[f] : 0;
+        const bool on = f < nf && hasv[c];
+        uint64_t h = fnv_begin(salt);
+        if (on)
+            for (int j = 0; j < d; ++j) h = fnv_step(h, mode[c * d + j]);
+        const bool has = visited_has8(a.visited, a.n_visited, h, on);
+        if (on && (tid & 7) == 0) {
+            hmode[c] = h;
+            vis[c] = has ? 1 : 0;
         }
     }
+    __syncthreads();
+    if (tid < kWave) accept_modes<uint8_t>(k, d, nf, flagged, hasv, vis, hmode, mode, fl, hcfg, cfg);
     __syncthreads();
     for (int e = tid; e < kmax * d; e += blockDim.x) ocfg[e] = cfg[e];
     for (int c = tid; c < kmax; c += blockDim.x) oflag[c] = fl[c];
-    if (tid == 0) {
+    if (tid < kWave) {
         int cnt = 0;
-        for (int c = 0; c < k; ++c) cnt += (fl[c] == 1 || fl[c] == 2) ? 1 : 0;
-        a.out_count[t] = cnt;
+        for (int c0 = 0; c0 < k; c0 += kWave) {
+            const int f = c0 + tid < k ? fl[c0 + tid] : 0;
+            cnt += __popcll(__ballot(f == 1 || f == 2));
+        }
+        if (tid == 0) a.out_count[t] = cnt;
     }
 }
 
@@ -971,18 +1065,19 @@ hipError_t launch_synth_wide(const SynthArgs &a, int total_wgs, hipStream_t s)
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(synth_wide_hist_kernel),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_hist);
     if (e != hipSuccess) return e;
-    const size_t lds_fin = (size_t)a.kmax * a.d * 2 + (size_t)a.kmax * 2 + 16;
-    hipLaunchKernelGGL(synth_wide_flag_kernel, dim3(a.T), dim3(256), 0, s, a);
+    const size_t lds_fin = (size_t)a.kmax * (2 * a.d + 2 * sizeof(uint64_t) + 3) + 16;
+    hipLaunchKernelGGL(synth_wide_flag_kernel, dim3(a.T), dim3(1024), 0, s, a);
     hipLaunchKernelGGL(synth_wide_hist_kernel, dim3(total_wgs), dim3(1024), lds_hist, s, a);
-    hipLaunchKernelGGL(synth_wide_finish_kernel, dim3(a.T), dim3(256), lds_fin, s, a);
+    hipLaunchKernelGGL(synth_wide_finish_kernel, dim3(a.T), dim3(1024), lds_fin, s, a);
     return hipGetLastError();
 }
 
 size_t synth_lds_bytes(int d, int kmax, int hist_words, int xbytes)
 {
     size_t b = sizeof(unsigned) * (size_t)hist_words;
-    b += sizeof(int) * (size_t)kmax * 2 + sizeof(int) * 8;
-    b += (size_t)xbytes * kmax * d * 2 + (size_t)kmax * 2;
+    b += sizeof(uint64_t) * (size_t)kmax * 2;
+    b += sizeof(int) * (size_t)kmax * 2 + sizeof(int) * (8 + 64 + 66);
+    b += (size_t)xbytes * kmax * d * 2 + (size_t)kmax * 3;
     return (b + 15) & ~(size_t)15;
 }
 
