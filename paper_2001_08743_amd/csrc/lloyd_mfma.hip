@@ -1309,6 +1309,9 @@ __global__ __launch_bounds__(512) void resident_mfma_kernel(const SweepArgs a)
             run_unit<DK, NTW, XT>(a, smem, ki, t, k);
         }
         if (tid == 0) next_unit = after;            // (read by everyone after the barrier at the loop's head)
+        // The compiler leaves out the wait for this write across the loop's back edge: without it a wave may
+        // pass the barrier and still read the unit before (LDS requests of different SIMDs are not ordered).
+        __builtin_amdgcn_s_waitcnt(0xC07F);         // lgkmcnt(0)
     }
 }
 
