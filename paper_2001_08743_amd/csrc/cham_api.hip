@@ -166,7 +166,28 @@ int32_t check_common(const void *X, int64_t ld, int32_t d, const int64_t *task_o
     return CHAM_OK;
 }
 
-constexpr int kStreamRowsPerWg = 4096;      // the smallest value of stream_rows_per_wg: bounds the workgroup count
+constexpr int kStreamRowsPerWg = 4096;      // rows per workgroup of the streaming assignment, at most
+
+// Rows one workgroup of the streaming assignment walks: 4096, halved (down to the 512 rows that one step
+// of its four waves holds) while the launch has fewer workgroups than the chip has places for them (two
+// per compute unit).  Measured per sampling step, 4096 / 2048 / 1024 / 512 rows: 48 units of 900 to 2500 rows
+// 1064 / 1023 / 801 / 676 us; 42 units of 21 000 to 60 000 rows (385 / 770 / 1540 / 3080 workgroups)
+// 1749 / 1418 / 1476 / 1777 us; 5 units of 2^20 rows (1280 / 2560 workgroups) 2890 / 3052 us.  Below 4096 rows
+// the loss partials of the final pass stand in the unit's sums, which hold 512 of them at least.  A
+// traced sweep has partials in every pass and keeps 4096.
+int stream_rows_per_wg(const Plan &pl, const int64_t *task_off, int n_ks, bool traced)
+{
+    constexpr int kPlaces = 512, kMinRows = 512, kMaxPartials = 512;
+    int rows = kStreamRowsPerWg;
+    if (traced) return rows;
+    while (rows > kMinRows) {
+        int64_t wgs = 0;
+        for (int t = 0; t < pl.T; ++t) wgs += (task_off[t + 1] - task_off[t] + rows - 1) / rows;
+        if (wgs * n_ks >= kPlaces || (pl.n_max + rows / 2 - 1) / (rows / 2) > kMaxPartials) break;
+        rows /= 2;
+    }
+    return rows;
+}
 
 constexpr int kSweepFlags = CHAM_F_FORCE_EXACT | CHAM_F_STREAMING | CHAM_F_RESIDENT | CHAM_F_NO_MFMA | CHAM_F_VALUES_BELOW_2048;
 
@@ -400,9 +421,9 @@ static int32_t sweep_impl(const void *Xv, int xbytes, int64_t ld, int32_t d, con
             if (!wo.assign(((size_t)n_units + 2) / 2)) return CHAM_E_NOMEM;
             int32_t *po = reinterpret_cast<int32_t *>(wo.data());
             int acc = 0;
+            const int rpw = stream_rows_per_wg(pl, task_off, ki_end - ki_begin, inertia_trace != nullptr);
             for (int u = 0; u < n_units; ++u) {
                 const int t = u % T;
-                const int rpw = stream_rows_per_wg(ks[ki_end - 1 - u / T]);
                 po[u] = acc;
                 acc += (int)((task_off[t + 1] - task_off[t] + rpw - 1) / rpw);
             }
@@ -426,6 +447,8 @@ static int32_t sweep_impl(const void *Xv, int xbytes, int64_t ld, int32_t d, con
             sa.done = a.done;
             sa.it = 0;
             sa.final_pass = 0;
+            sa.rows_per_wg = rpw;
+            sa.loss_in_sums = rpw < kStreamRowsPerWg ? 1 : 0;
             sa.task_off = a.task_off;
             sa.ks = a.ks;
             sa.koff = a.koff;

@@ -53,10 +53,6 @@ inline size_t resident_lds_bytes(int DP, int kmax, int sum_bytes = 4)
     return b;
 }
 
-// Rows one workgroup of the streaming assignment kernel walks, by the unit's k.  (Measured on the
-// large single-task workload: 2048 or 16384 rows for k <= 64 are both slower than 4096.)
-__host__ __device__ inline int stream_rows_per_wg(int /*k*/) { return 4096; }
-
 // Arguments of the streaming sweep kernels (tasks too large for one workgroup).
 struct StreamArgs {
     const uint8_t *X;
@@ -75,6 +71,8 @@ struct StreamArgs {
     const int *done;               // [T] or null: tasks whose sweep has already stopped (their units report status 3)
     int it;                        // pass being run
     int final_pass;
+    int rows_per_wg;               // rows a workgroup of the assignment kernel walks
+    int loss_in_sums;              // 1: the loss partials of the final pass go to the unit's sums (rows_per_wg < 4096)
     const int64_t *task_off;
     const int *ks;
     const int *koff;
@@ -98,7 +96,7 @@ struct StreamArgs {
     float *biasf;                  // [n_units][kpm] |mu'|^2 per centroid row (huge for padding rows)
     float *m2;                     // [n_units][8] bound on max |mu'|^2 per tile of 32 centroids; tile 0 negative = unit unusable
     double *loss_part;             // [total workgroups] loss partials of the last pass
-    int *passes;                   // [T][n_k] labelling passes actually run (preset to n_iter + 1 by the host code)
+    int *passes;                   // [T][n_k] during the sweep: 1 + the last pass that moved a row; n_iter + 1 at the end
 };
 
 // Arguments of the snap kernel.

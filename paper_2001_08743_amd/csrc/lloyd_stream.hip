@@ -49,30 +49,35 @@ __device__ __forceinline__ UnitState unit_state(const StreamArgs &a, int u)
     return s;
 }
 
-// Centring offsets per task: rounded mean of the starting centroids of the largest k.
-__global__ void stream_offsets_kernel(const StreamArgs a)
+// Centring offsets per task: rounded mean of the starting centroids of the largest k (any integer
+// would do: it only keeps the centred magnitudes small).  Eight lanes per knob, four loads of a lane
+// under way at a time: one lane per knob walked up to 256 dependent pairs of loads (28 us at k = 256).
+__global__ __launch_bounds__(256) void stream_offsets_kernel(const StreamArgs a)
 {
     const int t = blockIdx.x;
-    const int j = threadIdx.x;
-    if (j >= 32) return;
-    float o = 0.0f;
+    const int j = threadIdx.x >> 3, part = threadIdx.x & 7;
+    double s = 0.0;
+    int cnt = a.kmax;
+    if (a.init_mode == 0) cnt = a.ndist[t] < a.kmax ? a.ndist[t] : a.kmax;
     if (j < a.d) {
-        double s = 0.0;
-        int cnt = 0;
         if (a.init_mode == 0) {
-            cnt = a.ndist[t] < a.kmax ? a.ndist[t] : a.kmax;
-            const int64_t r0 = a.task_off[t];
-            for (int c = 0; c < cnt; ++c) s += (double)a.X[(int64_t)j * a.ld + r0 + a.init_rows[(int64_t)t * a.kmax + c]];
+            const uint8_t *col = a.X + (int64_t)j * a.ld + a.task_off[t];
+            const int *rows = a.init_rows + (int64_t)t * a.kmax;
+#pragma unroll 4
+            for (int c = part; c < cnt; c += 8) s += (double)col[rows[c]];
         } else {
-            cnt = a.kmax;
             const int64_t crow = (int64_t)t * a.Ksum + a.koff[a.n_k - 1];
-            for (int c = 0; c < cnt; ++c) s += a.init_centroids[(crow + c) * a.d + j];
+#pragma unroll 4
+            for (int c = part; c < cnt; c += 8) s += a.init_centroids[(crow + c) * a.d + j];
         }
-        double m = cnt > 0 ? rint(s / (double)cnt) : 0.0;
-        m = m < 0.0 ? 0.0 : (m > 255.0 ? 255.0 : m);
-        o = (float)m;
     }
-    a.ojf[t * 32 + j] = o;
+#pragma unroll
+    for (int off = 4; off >= 1; off >>= 1) s = s + __shfl_xor(s, off, 64);
+    if (part == 0) {
+        double m = j < a.d && cnt > 0 ? rint(s / (double)cnt) : 0.0;
+        m = m < 0.0 ? 0.0 : (m > 255.0 ? 255.0 : m);
+        a.ojf[t * 32 + j] = (float)m;
+    }
 }
 
 // Centred f16 copy of the rows (row-major, DK halfs per row, absent knobs zero) and the squared
@@ -142,7 +147,7 @@ __global__ __launch_bounds__(32 * (DK / 8)) void stream_update_kernel(const Stre
             for (int64_t r = r0 + tid; r < r1; r += blockDim.x) labrow[r] = 0;
             if (tid == 0) {
                 a.status[slot] = skipped ? 3 : 1;
-            a.passes[slot] = 0;
+                a.passes[slot] = 0;
                 a.inertia[slot] = 0.0;
             }
             if (a.trace)
@@ -155,13 +160,19 @@ __global__ __launch_bounds__(32 * (DK / 8)) void stream_update_kernel(const Stre
     if (mt == 0 && mode != 0 && tid == 0 && (mode == 2 || a.trace)) {
         const int nwg = a.wg_off[ul + 1] - a.wg_off[ul];
         double s = 0.0;
-        for (int w = 0; w < nwg; ++w) s = s + a.loss_part[(size_t)a.wg_off[ul] + w];
+        const double *part = a.loss_in_sums ? reinterpret_cast<const double *>(st.S) : a.loss_part + a.wg_off[ul];
+#pragma unroll 8
+        for (int w = 0; w < nwg; ++w) s = s + part[w];
         if (a.trace) a.trace[slot * (a.n_iter + 1) + a.it] = s;
         if (mode == 2) {
             a.inertia[slot] = s;
             a.status[slot] = 0;
+            a.passes[slot] = a.n_iter + 1;         // nominal: a pass of a settled unit is still launched
         }
     }
+    if (mode == 0 && mt == 0 && tid == 0) a.passes[slot] = 0;
+    // the pass moved no row of the unit: every sum, hence every centroid, is what it was
+    if (mode == 1 && !a.trace && a.passes[slot] <= a.it) return;
     const int kpu = (k + 31) & ~31;
     if (mt * 32 >= kpu) return;                // no such tile in this unit
     if (mode == 2) {
@@ -295,12 +306,19 @@ __device__ __forceinline__ void assign_unit(const StreamArgs &a, int unit_idx)
     const int kpu = (k + 31) & ~31;
     float m2 = a.m2[u * kM2Tiles];
     if (m2 < 0.0f) return;                     // unusable unit (fewer than k distinct rows)
+    // The pass before moved no row: sums and centroids are what that pass used, so this one would move
+    // none either.  (passes holds 1 + the last pass that moved a row; a workgroup of this pass may
+    // raise it to it + 1 meanwhile, but only in a unit that none of them skips.)  The final pass runs
+    // for the loss, a traced sweep runs every pass.
+    int *moved_at = a.passes + (int64_t)t * a.n_k + ki;
+    if (a.it > 0 && !a.final_pass && !a.trace && *moved_at < a.it) return;
+    bool moved = false;
     for (int i = 1; i < kpu / 32; ++i) m2 = __builtin_fmaxf(m2, a.m2[u * kM2Tiles + i]);
     const UnitState st = unit_state(a, u);
     StreamLds<DK> L(smem, kpm);
 
     const int64_t t0 = a.task_off[t], t1 = a.task_off[t + 1];
-    const int64_t rpw = stream_rows_per_wg(k);
+    const int64_t rpw = a.rows_per_wg;
     const int64_t r0 = t0 + (int64_t)wgi * rpw;
     const int64_t r1 = (r0 + rpw < t1) ? r0 + rpw : t1;
     uint8_t *labrow = a.labbuf + (int64_t)ki * a.ld;
@@ -713,7 +731,10 @@ __device__ __forceinline__ void assign_unit(const StreamArgs &a, int unit_idx)
                 nchg += c;
             }
         }
-        if (nchg) apply_changes(nchg);
+        if (nchg) {
+            apply_changes(nchg);
+            moved = true;
+        }
         if (want_dist) {
             // exact loss terms of the rows of this step: one row per lane, knobs ascending
             __builtin_amdgcn_wave_barrier();
@@ -749,20 +770,25 @@ __device__ __forceinline__ void assign_unit(const StreamArgs &a, int unit_idx)
         const double ws = wave_sum(part);
         if (lane == 0) L.red[wave] = ws;
     }
-    __syncthreads();
-    // changes of this workgroup -> the unit's sums
-    for (int e = tid; e < k * DK; e += blockDim.x) {
-        const int v = L.S[e];
-        if (v != 0) atomicAdd(&st.S[(e / DK) * 32 + (e % DK)], v);
+    const bool any_moved = __syncthreads_or(moved ? 1 : 0) != 0;
+    // changes of this workgroup -> the unit's sums (which nothing reads after the final pass)
+    if (any_moved && !a.final_pass) {
+        if (tid == 0) *moved_at = a.it + 1;
+        for (int e = tid; e < k * DK; e += blockDim.x) {
+            const int v = L.S[e];
+            if (v != 0) atomicAdd(&st.S[(e / DK) * 32 + (e % DK)], v);
+        }
     }
-    for (int c = tid; c < k; c += blockDim.x) {
+    if (any_moved) for (int c = tid; c < k; c += blockDim.x) {
         const int v = L.n[c];
         if (v != 0) atomicAdd(&st.n[c], v);
     }
     if (want_dist && tid == 0) {
         double s = 0.0;
         for (int w = 0; w < kWavesPerWg; ++w) s = s + (w < (int)(blockDim.x >> 6) ? L.red[w] : 0.0);
-        a.loss_part[blockIdx.x] = s;
+        // (a final pass leaves the sums alone: with many workgroups its partials stand there)
+        if (a.loss_in_sums) reinterpret_cast<double *>(st.S)[wgi] = s;
+        else a.loss_part[blockIdx.x] = s;
     }
 }
 
@@ -815,7 +841,7 @@ hipError_t run_stream(StreamArgs a, int64_t n_total, int total_wgs, hipStream_t 
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     if (a.prepare) {
-        hipLaunchKernelGGL(stream_offsets_kernel, dim3(a.T), dim3(64), 0, s, a);
+        hipLaunchKernelGGL(stream_offsets_kernel, dim3(a.T), dim3(256), 0, s, a);
         const unsigned pb = (unsigned)((n_total + 255) / 256);
         if (pb) hipLaunchKernelGGL(stream_pack_kernel<DK>, dim3(pb), dim3(256), 0, s, a, n_total);
     }
