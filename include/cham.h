@@ -130,7 +130,8 @@ int32_t cham_kmeans_sweep(const uint8_t *X, int64_t ld, int32_t d,
  * the choice depends only on d, the largest task, the largest k and flags (Sec. 3.3's k-means,
  * "K-means.run" of Algorithm 1, is the same computation on every path).
  *   CHAM_PATH_RESIDENT_MFMA    one workgroup per (task, k), distances on the matrix cores
- *                              (d <= 31, tasks of at most 4096 rows, k <= 64)
+ *                              (d <= 31, tasks of at most 4096 rows, k <= 64; d = 32: 4096 rows with
+ *                              k <= 32, or 2048 rows with k <= 64)
  *   CHAM_PATH_STREAM_MFMA      several workgroups per (task, k), one launch pair per pass (d <= 31)
  *   CHAM_PATH_RESIDENT_VECTOR  one workgroup per (task, k), vector ALU
  * cham_sweep_path_kernel gives the name of the family's dominant kernel (a static string).

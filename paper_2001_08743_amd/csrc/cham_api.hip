@@ -205,7 +205,12 @@ SweepPath choose_path(const Plan &pl, int d, int flags, int xbytes = 1)
         if (promised && !exact && !no_mfma && mfma_path_fits_u16(d, pl.kmax, pl.n_max)) return SweepPath::kMfmaResident;
         return SweepPath::kVectorResident;
     }
-    if (exact || no_mfma || d > 31) return SweepPath::kVectorResident;
+    if (exact || no_mfma) return SweepPath::kVectorResident;
+    // All 32 knobs in use: the matrix cores where registers allow the bias a step of its own (32 tasks x 2048 rows,
+    // k = 2..32: 487 us a step against 1004 on the vector kernel); no streaming variant
+    if (d > 31)
+        return !(flags & CHAM_F_STREAMING) && mfma_path_fits_d32(d, pl.kmax, pl.n_max) ? SweepPath::kMfmaResident
+                                                                                       : SweepPath::kVectorResident;
     if (flags & CHAM_F_STREAMING) return SweepPath::kStream;
     if (mfma_path_fits(d, pl.kmax, pl.n_max)) return SweepPath::kMfmaResident;
     if (flags & CHAM_F_RESIDENT) return SweepPath::kVectorResident;

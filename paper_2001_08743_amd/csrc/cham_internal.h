@@ -163,6 +163,7 @@ hipError_t launch_resident_sweep(const SweepArgs &a, int nt, hipStream_t s);
 int resident_dp16(int d);      // padded knob count the two-byte kernels use for d knobs
 // Matrix-core resident kernel: usable when every task has at most 4096 rows and k <= 64.
 bool mfma_path_fits(int d, int kmax, int64_t n_max);
+bool mfma_path_fits_d32(int d, int kmax, int64_t n_max);
 bool mfma_path_fits_u16(int d, int kmax, int64_t n_max);
 hipError_t launch_mfma_sweep(const SweepArgs &a, int64_t n_max, int64_t n_total, hipStream_t s);
 int64_t stream_lds_bytes(int d, int kpm);

@@ -5,7 +5,9 @@
 // Screen:  score(c, i) = |mu'_c|^2 - 2 x'_i . mu'_c   (x', mu' centred by an integer offset)
 //   A (32 centroids x K) = [ hi(w) | lo(w) ],  w = fl32(-2 mu'),  hi = f16(w), lo = f16(w - hi)
 //   B (K x 32 rows)      = [ x' ; x' ]        (x' is a small integer: exact in f16)
-//   the last knob slot (always unused: d < DK) carries the bias: B = 256, A = hi/lo of |mu'_c|^2 / 256
+//   the last knob slot (unused when d < DK) carries the bias: B = 256, A = hi/lo of |mu'_c|^2 / 256;
+//   with d = DK = 32 (SEP) the bias is a step of its own at the head of the chain, slots 0 and 1 of
+//   sixteen: one instruction in five more, against twice the row registers and steps of 64-wide rows
 // so every product is exact and only the fp32 accumulation and the 22-bit splits round.
 //
 // Centroid c sits in fragment row 8 (i / 4) + 4 (c & 1) + (i & 3), i = (c & 31) / 2, of m-tile c / 32,
@@ -93,13 +95,15 @@ __device__ __forceinline__ int frag_row(int c)
     return 8 * (i >> 2) + 4 * (c & 1) + (i & 3);
 }
 
-// LDS carve-up.  DK = padded knob count (16 or 32), KP = padded centroid count (32 or 64).
-template <int DK>
+// LDS carve-up.  DK = padded knob count (16, 32 or 64), KP = padded centroid count (32 or 64); SEP: the
+// bias has fragments of its own.
+template <int DK, bool SEP = false>
 struct MfmaLds {
     double *mu64T;      // [DK][KP]   exact centroids, transposed
     double *red;        // [16]       per-wave partial sums of the loss
     float *bias;        // [KP]       upper bound of |mu - o|^2 per centroid (0 for padding rows)
     half8 *afrag;       // [KP/32][2*DK/16][64]  A fragments: hi parts then lo parts
+    half8 *abias;       // [KP/32][64] A fragments of the bias step (SEP only; directly behind afrag)
     int *S;             // [KP][DK+1] integer cluster sums (row stride DK + 1: rows of different clusters fall into different banks)
     int *n;             // [KP]       cluster sizes
     int *dirty;         // [KP]       pass in which the cluster last changed
@@ -114,7 +118,7 @@ struct MfmaLds {
     __host__ __device__ static size_t bytes(int KP, int nwaves, int ntw)
     {
         size_t b = sizeof(double) * DK * KP + sizeof(double) * 16 + sizeof(float) * KP;
-        b += 16 * (size_t)(KP / 32) * (2 * DK / 16) * 64;
+        b += 16 * (size_t)(KP / 32) * (2 * DK / 16 + (SEP ? 1 : 0)) * 64;
         b += sizeof(int) * (size_t)KP * (DK + 1) + sizeof(int) * KP * 2 + sizeof(float) * DK + 32;
         b = (b + 15) & ~(size_t)15;
         return b + wave_bytes(ntw) * nwaves;
@@ -127,6 +131,7 @@ struct MfmaLds {
         red = reinterpret_cast<double *>(base + o);    o += sizeof(double) * 16;
         bias = reinterpret_cast<float *>(base + o);    o += sizeof(float) * KP;
         afrag = reinterpret_cast<half8 *>(base + o);   o += 16 * (size_t)(KP / 32) * (2 * DK / 16) * 64;
+        abias = reinterpret_cast<half8 *>(base + o);   o += SEP ? 16 * (size_t)(KP / 32) * 64 : 0;
         S = reinterpret_cast<int *>(base + o);         o += sizeof(int) * (size_t)KP * (DK + 1);
         n = reinterpret_cast<int *>(base + o);         o += sizeof(int) * KP;
         dirty = reinterpret_cast<int *>(base + o);     o += sizeof(int) * KP;
@@ -433,8 +438,9 @@ __device__ __forceinline__ void apply_changes(const WaveQueue<DK> &Q, int cnt, i
 // Needs 16-byte aligned rows (xw, ld) and reads whole groups of 64 rows: the caller makes sure
 // that the last group of the task still lies inside the matrix (rows of other tasks or padding
 // read there meet the label 0xFF, which matches no centroid).  NG = groups of 64 rows a wave owns
-// at most; the loads of four groups are under way at any time.
-template <int DK, int NG>
+// at most; the loads of four groups are under way at any time.  SEP: every knob row is in use, so the
+// sizes are counted from the labels.
+template <int DK, int NG, bool SEP>
 __device__ __forceinline__ void full_sums(const WaveQueue<DK> &Q, int *S, int *n, const uint8_t *xw, int64_t ld,
                                           int d, int k, int rows_here, int lane)
 {
@@ -515,9 +521,15 @@ __device__ __forceinline__ void full_sums(const WaveQueue<DK> &Q, int *S, int *n
             if (m32 < k) atomicAdd(&S[m32 * (DK + 1) + m], (int)acc0[i]);
             if (two && m32 + 32 < k) atomicAdd(&S[(m32 + 32) * (DK + 1) + m], (int)acc1[i]);
         }
-        if (i == 15 && kh == 1) {                              // knob row 31: 1024 per row of the cluster
+        if (!SEP && i == 15 && kh == 1) {                              // knob row 31: 1024 per row of the cluster
             if (m32 < k) atomicAdd(&n[m32], (int)acc0[i] >> 10);
             if (two && m32 + 32 < k) atomicAdd(&n[m32 + 32], (int)acc1[i] >> 10);
+        }
+    }
+    if (SEP) {
+        for (int e = lane; e < rows_here; e += 64) {
+            const int c = Q.lab()[e];
+            if (c < k) atomicAdd(&n[c], 1);
         }
     }
 }
@@ -525,14 +537,14 @@ __device__ __forceinline__ void full_sums(const WaveQueue<DK> &Q, int *S, int *n
 // Centroid update for the clusters touched in this pass, all threads: item (c, q) owns knobs
 // 4q..4q+3 of centroid c: mean = (double)S / (double)n, then the f16 hi/lo fragments of
 // w = -2 (mu - o) (one 8-byte store each).  The DK/4 items of a centroid sit in adjacent lanes and
-// add up |mu - o|^2 among themselves; the last of them owns the bias slot (knob slot DK - 1) and
-// stores the sum / 256 there as hi/lo, and its rounded-up value for the error bound.
+// add up |mu - o|^2 among themselves; the last of them owns the bias slot (knob slot DK - 1, or with
+// SEP slots 0 and 1 of the bias step) and stores the sum / 256 there as hi/lo, and its rounded-up value for the error bound.
 // all: fragments from the centroids as they are (no sums yet).  raw: the sums were rebuilt by
 // full_sums for every cluster (each still raised by 1024 n): every cluster is updated, and the sums
 // are left either corrected (the next pass applies label changes to them) or, with zero_after,
 // cleared together with the sizes (the next pass rebuilds them).
-template <int DK, bool BYTE_KNOBS = true>
-__device__ __forceinline__ void update_centroids(const MfmaLds<DK> &U, int k, int KP, int d, int stamp, bool all,
+template <int DK, bool BYTE_KNOBS, bool SEP>
+__device__ __forceinline__ void update_centroids(const MfmaLds<DK, SEP> &U, int k, int KP, int d, int stamp, bool all,
                                                  bool raw = false, bool zero_after = false)
 {
     constexpr int NS = DK / 16, NS2 = 2 * NS, QN = DK / 4;
@@ -594,8 +606,14 @@ __device__ __forceinline__ void update_centroids(const MfmaLds<DK> &U, int k, in
             if (q == QN - 1) {
                 const float bs = (float)b * (1.0f / kBiasScale);
                 const _Float16 bhi = (_Float16)bs;
-                hi4[3] = bhi;
-                lo4[3] = (_Float16)(bs - (float)bhi);
+                const _Float16 blo = (_Float16)(bs - (float)bhi);
+                if constexpr (SEP) {
+                    typedef _Float16 half2v __attribute__((ext_vector_type(2)));
+                    *reinterpret_cast<half2v *>(U.abias + (c >> 5) * 64 + frag_row(c)) = half2v{bhi, blo};
+                } else {
+                    hi4[3] = bhi;
+                    lo4[3] = blo;
+                }
                 U.bias[c] = __double2float_ru(b) * 1.0000005f;
             }
             const int mt = c >> 5, m32 = frag_row(c);
@@ -618,19 +636,21 @@ __device__ __forceinline__ void update_centroids(const MfmaLds<DK> &U, int k, in
 
 // Everything one workgroup does for its unit.  Units with more than 32 centroids use two 32-row
 // m-tiles per row tile; otherwise the two accumulators alternate between row tiles.
-template <int DK, int NTW, typename XT>
+template <int DK, int NTW, typename XT, bool SEP>
 __device__ __forceinline__ void run_unit(const SweepArgs &a, unsigned char *smem, int ki, int t, int k)
 {
     constexpr bool kByteKnobs = sizeof(XT) == 1;
     constexpr double kMaxValue = kByteKnobs ? 255.0 : 2047.0;
-    constexpr bool kAllowTwo = DK <= 32;     // 64-wide rows leave no registers for a second m-tile: k <= 32 there
+    // 64-wide rows leave no registers for a second m-tile, nor do 16 tiles of rows beside the bias step: k <= 32 there
+    constexpr bool kAllowTwo = DK <= 32 && !(SEP && NTW > 8);
     const XT *X = reinterpret_cast<const XT *>(a.X);
     const bool two = kAllowTwo && k > 32;
     constexpr int NS = DK / 16;          // distinct B fragments per row
-    constexpr int NS2 = 2 * NS;          // chained instructions per 32x32 tile
+    constexpr int NS2 = 2 * NS;          // chained instructions per 32x32 tile, without the bias step
+    constexpr int NSA = NS2 + (SEP ? 1 : 0);   // ... with it
     constexpr int CH = 16 / NS2;         // scores handled between two matrix instructions
     const int KP = a.kmax > 32 ? 64 : 32;
-    MfmaLds<DK> U(smem, KP);
+    MfmaLds<DK, SEP> U(smem, KP);
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -654,7 +674,7 @@ __device__ __forceinline__ void run_unit(const SweepArgs &a, unsigned char *smem
     const int64_t crow = (int64_t)t * a.Ksum + a.koff[ki];
     uint8_t *labrow = a.labbuf + (int64_t)ki * a.ld;
 
-    WaveQueue<DK> Q(U.wave_base + MfmaLds<DK>::wave_bytes(NTW) * wave);
+    WaveQueue<DK> Q(U.wave_base + MfmaLds<DK, SEP>::wave_bytes(NTW) * wave);
     const int wave_row0 = wave * NTW * 32;                 // first row (task-relative) of this wave
     const bool wave_live = wave_row0 < nrows;              // the wave owns at least one row
 
@@ -663,8 +683,8 @@ __device__ __forceinline__ void run_unit(const SweepArgs &a, unsigned char *smem
     const int kk_last = two ? k - 32 : k;                  // centroids in the last (or only) m-tile
     const int lregs = ((kk_last + 1) / 2 + 3) & ~3;        // 4, 8, 12 or 16
 
-    // The last knob slot of the fragments is reserved (d <= DK - 1): it carries the bias (256 in B,
-    // |mu'|^2 / 256 as hi/lo in A).
+    // Without SEP the last knob slot of the fragments is reserved (d <= DK - 1): it carries the bias (256
+    // in B, |mu'|^2 / 256 as hi/lo in A).
     constexpr int bstep = NS - 1, bhalf = 1, belem = 7;
     constexpr int kFullDivisor = 8;
 
@@ -699,12 +719,13 @@ __device__ __forceinline__ void run_unit(const SweepArgs &a, unsigned char *smem
         half8 z;
 #pragma unroll
         for (int i = 0; i < 8; ++i) z[i] = (_Float16)0.0f;
-        for (int e = tid; e < (KP / 32) * NS2 * 64; e += blockDim.x) U.afrag[e] = z;
+        for (int e = tid; e < (KP / 32) * NSA * 64; e += blockDim.x) U.afrag[e] = z;      // (abias included)
     }
     __syncthreads();
     // padding centroid rows (beyond k) carry a huge bias so that they never win
     for (int c = k + tid; c < KP; c += blockDim.x) {
-        _Float16 *bslot = reinterpret_cast<_Float16 *>(U.afrag + ((c >> 5) * NS2 + bstep) * 64 + 32 * bhalf + frag_row(c)) + belem;
+        _Float16 *bslot = SEP ? reinterpret_cast<_Float16 *>(U.abias + (c >> 5) * 64 + frag_row(c))
+                              : reinterpret_cast<_Float16 *>(U.afrag + ((c >> 5) * NS2 + bstep) * 64 + 32 * bhalf + frag_row(c)) + belem;
         bslot[0] = (_Float16)kPadBiasHi;
     }
     if (tid == 0) {
@@ -750,7 +771,7 @@ __device__ __forceinline__ void run_unit(const SweepArgs &a, unsigned char *smem
         }
     }
     __syncthreads();
-    update_centroids<DK, kByteKnobs>(U, k, KP, d, 0, true);
+    update_centroids<DK, kByteKnobs, SEP>(U, k, KP, d, 0, true);
 
     // ---- centre the rows; on the way, the sum of |x|^2 over the task's rows as an integer (for the loss
     // at a fixed point, see the end) and the squared norm of every centred row (for the error bound).
@@ -798,7 +819,7 @@ __device__ __forceinline__ void run_unit(const SweepArgs &a, unsigned char *smem
                 half8 cv = __builtin_bit_cast(half8, w);
                 part = sumsq(cv, part);
                 // the bias slot: a constant for every live row (after the norm, which excludes it)
-                if (f == bstep && live && h == bhalf) cv[belem] = (_Float16)kBiasScale;
+                if (!SEP && f == bstep && live && h == bhalf) cv[belem] = (_Float16)kBiasScale;
                 B[nt][f] = cv;
             }
             if (kByteKnobs) q2 += live ? (unsigned)raw : 0u;
@@ -819,7 +840,7 @@ __device__ __forceinline__ void run_unit(const SweepArgs &a, unsigned char *smem
         m2 = __builtin_fmaxf(m2, __int_as_float(U.stamp[1])) * 1.000001f;
 #pragma unroll
         for (int nt = 0; nt < NTW; ++nt)
-            if (h == 0) Q.eb()[nt * 32 + n32] = mfma_bound<NS2>(x2row[nt], m2);
+            if (h == 0) Q.eb()[nt * 32 + n32] = mfma_bound<NSA>(x2row[nt], m2);
     }
     __builtin_amdgcn_wave_barrier();
 
@@ -893,7 +914,7 @@ __device__ __forceinline__ void run_unit(const SweepArgs &a, unsigned char *smem
 #pragma unroll
                     for (int i = 0; i < 8; ++i) {
                         float xf = (float)bt[f][i] + of[f][i];
-                        if (f == bstep && i == belem) xf = h == bhalf ? 0.0f : xf;     // the bias slot is no knob
+                        if (!SEP && f == bstep && i == belem) xf = h == bhalf ? 0.0f : xf;     // the bias slot is no knob
                         const double tq = (double)xf - mu[f][i];
                         s = s + tq * tq;
                     }
@@ -924,18 +945,31 @@ __device__ __forceinline__ void run_unit(const SweepArgs &a, unsigned char *smem
             constexpr int LREGS = decltype(live_tag)::value;
             const int lane = opaque(lane_id), n32 = lane & 31;
             // A fragments of this pass (the bias slot included)
-            half8 A0[NS2], A1[NS2];
+            half8 A0[NSA], A1[NSA];
 #pragma unroll
             for (int s = 0; s < NS2; ++s) {
                 A0[s] = U.afrag[s * 64 + lane];
                 A1[s] = two ? U.afrag[(NS2 + s) * 64 + lane] : A0[s];
             }
+            // the bias step: 256 against hi (slot 0) and lo (slot 1), the same for every row
+            half8 bias_b;
+            if constexpr (SEP) {
+                A0[NS2] = U.abias[lane];
+                A1[NS2] = two ? U.abias[64 + lane] : A0[NS2];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) bias_b[i] = (_Float16)(i < 2 && lane < 32 ? kBiasScale : 0.0f);
+            }
 
             float16v accA, accB;
             const float16v zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 
-            // one matrix instruction of the chain of a 32x32 tile
-            auto mma = [&](float16v &acc, const half8 (&Af)[NS2], const half8 (&Bt)[NS], int s) {
+            // one matrix instruction of the chain of a 32x32 tile (the first one behind the bias step)
+            auto mma = [&](float16v &acc, const half8 (&Af)[NSA], const half8 (&Bt)[NS], int s) {
+                if constexpr (SEP) {
+                    if (s == 0) acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(Af[NS2], bias_b, zero16, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(Af[s], Bt[s % NS], acc, 0, 0, 0);
+                    return;
+                }
                 acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(Af[s], Bt[s % NS], s == 0 ? zero16 : acc, 0, 0, 0);
             };
             // mark scores [i0, i0 + CH): bit set = above the threshold (or padding)
@@ -1133,7 +1167,7 @@ __device__ __forceinline__ void run_unit(const SweepArgs &a, unsigned char *smem
             __builtin_amdgcn_wave_barrier();
             if (wave_live) {
                 const int left = nrows - wave_row0;
-                full_sums<DK, NTW / 2>(Q, U.S, U.n, xw, a.ld, d, k, left < NTW * 32 ? left : NTW * 32, lane);
+                full_sums<DK, NTW / 2, SEP>(Q, U.S, U.n, xw, a.ld, d, k, left < NTW * 32 ? left : NTW * 32, lane);
             }
         } else {
             // a dense queue of (previous, new, knob values), applied with one lane per (row, group of four
@@ -1192,7 +1226,7 @@ __device__ __forceinline__ void run_unit(const SweepArgs &a, unsigned char *smem
         if (last_pass || rows_changed == 0) break;
         if (tid == 0) U.stamp[2 + ((it + 1) & 1)] = 0;      // the next pass counts from zero (nobody adds before the barrier below)
         const bool full_next = x_aligned && rows_changed > full_above;
-        update_centroids<DK, kByteKnobs>(U, k, KP, d, it, false, full_mode, full_next);
+        update_centroids<DK, kByteKnobs, SEP>(U, k, KP, d, it, false, full_mode, full_next);
         full_mode = full_next;
         __syncthreads();
     }
@@ -1265,7 +1299,7 @@ __device__ __forceinline__ void run_unit(const SweepArgs &a, unsigned char *smem
 // Persistent workgroups (one per compute unit) take units from a counter until none is left: the
 // next unit starts as soon as the last one ends, without a new dispatch of a workgroup of this size.
 // Units are handed out in descending-k order so that the longest ones start first.
-template <int DK, int NTW, typename XT>
+template <int DK, int NTW, typename XT, bool SEP>
 __global__ __launch_bounds__(512) void resident_mfma_kernel(const SweepArgs a)
 {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -1306,7 +1340,7 @@ __global__ __launch_bounds__(512) void resident_mfma_kernel(const SweepArgs a)
             if (a.trace)
                 for (int e = tid; e <= a.n_iter; e += blockDim.x) a.trace[slot * (a.n_iter + 1) + e] = 0.0;
         } else {
-            run_unit<DK, NTW, XT>(a, smem, ki, t, k);
+            run_unit<DK, NTW, XT, SEP>(a, smem, ki, t, k);
         }
         if (tid == 0) next_unit = after;            // (read by everyone after the barrier at the loop's head)
         // The compiler leaves out the wait for this write across the loop's back edge: without it a wave may
@@ -1315,7 +1349,7 @@ __global__ __launch_bounds__(512) void resident_mfma_kernel(const SweepArgs a)
     }
 }
 
-template <int DK, int NTW, typename XT>
+template <int DK, int NTW, typename XT, bool SEP = false>
 hipError_t launch_mfma_t(const SweepArgs &a, int nwaves, int64_t n_total, hipStream_t s)
 {
     const unsigned pb = (unsigned)((n_total + 255) / 256);
@@ -1323,8 +1357,8 @@ hipError_t launch_mfma_t(const SweepArgs &a, int nwaves, int64_t n_total, hipStr
         hipLaunchKernelGGL((pack_rows_kernel<DK, XT>), dim3(pb), dim3(256), 0, s, reinterpret_cast<const XT *>(a.X), a.ld, a.d,
                            n_total, reinterpret_cast<_Float16 *>(a.xh), a.too_large);
     const int KP = a.kmax > 32 ? 64 : 32;
-    const size_t lds = MfmaLds<DK>::bytes(KP, nwaves, NTW);
-    auto kern = resident_mfma_kernel<DK, NTW, XT>;
+    const size_t lds = MfmaLds<DK, SEP>::bytes(KP, nwaves, NTW);
+    auto kern = resident_mfma_kernel<DK, NTW, XT, SEP>;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
@@ -1353,6 +1387,13 @@ bool mfma_path_fits(int d, int kmax, int64_t n_max)
     return d >= 1 && d <= 31 && kmax <= 64 && n_max <= 4096;
 }
 
+// All 32 byte knobs: the bias takes a step of its own, which 4096 rows leave registers for up to k = 32
+// only (one m-tile) and 2048 rows up to k = 64.
+bool mfma_path_fits_d32(int d, int kmax, int64_t n_max)
+{
+    return d == 32 && ((kmax <= 32 && n_max <= 4096) || (kmax <= 64 && n_max <= 2048));
+}
+
 // Two-byte knobs whose values the caller promises to be below 2048: the same limits up to 31 knobs;
 // up to 63 knobs in 64-wide rows, which leave registers for 2048 rows and one tile of 32 centroids.
 bool mfma_path_fits_u16(int d, int kmax, int64_t n_max)
@@ -1364,11 +1405,17 @@ bool mfma_path_fits_u16(int d, int kmax, int64_t n_max)
 template <typename XT>
 static hipError_t launch_mfma_sweep_t(const SweepArgs &a, int64_t n_max, int64_t n_total, hipStream_t s)
 {
-    const int DK = a.d <= 15 ? 16 : (a.d <= 31 ? 32 : 64);
-    const int ntw = n_max <= 1024 ? 4 : (DK == 64 ? 8 : 16);
+    const bool sep = sizeof(XT) == 1 && a.d == 32;
+    const int DK = a.d <= 15 ? 16 : (a.d <= 31 || sep ? 32 : 64);
+    const int ntw = n_max <= 1024 ? 4 : (DK == 64 || (sep && n_max <= 2048) ? 8 : 16);
     int nwaves = (int)((n_max + 32 * ntw - 1) / (32 * ntw));
     if (nwaves < 1) nwaves = 1;
     if (nwaves > 8) nwaves = 8;
+    if (sep) {
+        if (ntw == 4) return launch_mfma_t<32, 4, uint8_t, true>(a, nwaves, n_total, s);
+        return ntw == 8 ? launch_mfma_t<32, 8, uint8_t, true>(a, nwaves, n_total, s)
+                        : launch_mfma_t<32, 16, uint8_t, true>(a, nwaves, n_total, s);
+    }
     if (DK == 16) return ntw == 4 ? launch_mfma_t<16, 4, XT>(a, nwaves, n_total, s) : launch_mfma_t<16, 16, XT>(a, nwaves, n_total, s);
     if (DK == 32) return ntw == 4 ? launch_mfma_t<32, 4, XT>(a, nwaves, n_total, s) : launch_mfma_t<32, 16, XT>(a, nwaves, n_total, s);
     if (sizeof(XT) == 1) return hipErrorInvalidValue;        // (byte knobs never come with more than 32 knobs)
