@@ -95,6 +95,10 @@ __device__ __forceinline__ int frag_row(int c)
     return 8 * (i >> 2) + 4 * (c & 1) + (i & 3);
 }
 
+// Rows a wave's queue holds (a tile fills at most 32): with few tiles per wave, 40 let two workgroups of
+// 32-wide rows and 64 centroids share a compute unit (32 tasks x 1000 rows x 24 knobs, k = 2..48: 551 -> 458 us).
+__host__ __device__ constexpr int rec_cap(int DK, int ntw) { return DK == 32 && ntw <= 4 ? 40 : kRecCap; }
+
 // LDS carve-up.  DK = padded knob count (16, 32 or 64), KP = padded centroid count (32 or 64); SEP: the
 // bias has fragments of its own.
 template <int DK, bool SEP = false>
@@ -113,7 +117,7 @@ struct MfmaLds {
     unsigned char *wave_base;   // per-wave regions follow
     __host__ __device__ static size_t wave_bytes(int ntw)
     {
-        return ((size_t)kRecCap * DK * 2 + kRecCap * 8 + kRecCap * 2 + 4 * 32 * 8 + 512 + 512 + 512 * 4 + (size_t)ntw * 64 * 4 + 15) / 16 * 16;
+        return ((size_t)rec_cap(DK, ntw) * (DK * 2 + 8 + 2) + 4 * 32 * 8 + (size_t)ntw * 32 * 6 + (size_t)ntw * 64 * 4 + 15) / 16 * 16;
     }
     __host__ __device__ static size_t bytes(int KP, int nwaves, int ntw)
     {
@@ -143,26 +147,26 @@ struct MfmaLds {
     }
 };
 
-// Per-wave LDS region.  A queue of at most kRecCap rows (their centred knob values as f16, the
+// Per-wave LDS region.  A queue of at most kCap rows (their centred knob values as f16, the
 // candidate masks of both lane halves, the row index), used first for the rows the screen could
 // not decide and then for the label changes of the pass, in batches; behind it the current label of
 // every row, the labels the pass arrives at, the error bound of every row and, per (tile, lane),
 // the mask the lane had when its tile was last decided.
-template <int DK>
+template <int DK, int NTW>
 struct WaveQueue {
-    static constexpr int kRows = 512;                       // rows a wave owns at most
-    static constexpr size_t kOffMask = (size_t)kRecCap * DK * 2;
-    static constexpr size_t kOffPid = kOffMask + (size_t)kRecCap * 8;
-    static constexpr size_t kOffFew = kOffPid + (size_t)kRecCap * 2;
+    static constexpr int kRows = NTW * 32;                  // rows a wave owns at most
+    static constexpr int kCap = rec_cap(DK, NTW);
+    static constexpr size_t kOffMask = (size_t)kCap * DK * 2;
+    static constexpr size_t kOffPid = kOffMask + (size_t)kCap * 8;
+    static constexpr size_t kOffFew = kOffPid + (size_t)kCap * 2;
     static constexpr size_t kOffLab = kOffFew + 4 * 32 * 8;
     static constexpr size_t kOffNew = kOffLab + (size_t)kRows;
     static constexpr size_t kOffEb = kOffNew + (size_t)kRows;
     static constexpr size_t kOffSeen = kOffEb + (size_t)kRows * 4;
-    __host__ __device__ static constexpr size_t bytes(int ntw) { return (kOffSeen + (size_t)ntw * 64 * 4 + 15) / 16 * 16; }
     unsigned char *base;
     __device__ explicit WaveQueue(unsigned char *wb) : base(wb) {}
-    __device__ _Float16 *rec_x() const { return reinterpret_cast<_Float16 *>(base); }                    // [kRecCap][DK]
-    __device__ unsigned *rec_mask() const { return reinterpret_cast<unsigned *>(base + kOffMask); }      // [kRecCap][2]
+    __device__ _Float16 *rec_x() const { return reinterpret_cast<_Float16 *>(base); }                    // [kCap][DK]
+    __device__ unsigned *rec_mask() const { return reinterpret_cast<unsigned *>(base + kOffMask); }      // [kCap][2]
     __device__ unsigned short *rec_pid() const { return reinterpret_cast<unsigned short *>(base + kOffPid); }
     __device__ double *few() const { return reinterpret_cast<double *>(base + kOffFew); }                 // [4][32] squares of one (row, centroid)
     __device__ unsigned char *lab() const { return base + kOffLab; }                                      // [kRows] current labels (0xFF: none)
@@ -175,8 +179,8 @@ struct WaveQueue {
 // centroid of its row and evaluates the exact double distance (knobs ascending, no fused
 // multiply-add); the four lanes then agree on the smallest distance, lowest index on ties.  The
 // result goes to the row's entry of the labels of the pass under way.
-template <int DK>
-__device__ __forceinline__ void resolve_rows(const WaveQueue<DK> &Q, int nrec, const double *mu64T,
+template <int DK, typename Queue>
+__device__ __forceinline__ void resolve_rows(const Queue &Q, int nrec, const double *mu64T,
                                              const float *ojf, int KP, int k, int d)
 {
     const int lane = threadIdx.x & 63;
@@ -264,8 +268,8 @@ __device__ __forceinline__ void resolve_rows(const WaveQueue<DK> &Q, int nrec, c
 // sixteen lanes per (row, centroid): every lane squares the differences of its one or two knobs,
 // then one lane adds the d squares up in knob order (the only part that has to be serial) and the
 // lanes of a row agree on the smallest distance, lowest index on ties.
-template <int DK>
-__device__ __forceinline__ void resolve_few(const WaveQueue<DK> &Q, int nrec, const double *mu64T,
+template <int DK, typename Queue>
+__device__ __forceinline__ void resolve_few(const Queue &Q, int nrec, const double *mu64T,
                                             const float *ojf, int KP, int k, int d)
 {
     const int lane = threadIdx.x & 63;
@@ -341,8 +345,8 @@ __device__ __forceinline__ void resolve_few(const WaveQueue<DK> &Q, int nrec, co
     __builtin_amdgcn_wave_barrier();
 }
 
-template <int DK>
-__device__ __forceinline__ void resolve_queue(const WaveQueue<DK> &Q, int nrec, const double *mu64T,
+template <int DK, typename Queue>
+__device__ __forceinline__ void resolve_queue(const Queue &Q, int nrec, const double *mu64T,
                                               const float *ojf, int KP, int k, int d)
 {
     if constexpr (DK <= 32) {
@@ -383,8 +387,8 @@ __global__ void pack_rows_kernel(const XT *__restrict__ X, int64_t ld, int d, in
 // Apply queued label changes of this wave to the integer sums and counts: 256 / DK queued rows
 // per step, one lane per (row, group of 4 knobs).  Entry word: cur | prev << 8, prev = 0xFF for a
 // row that had no label yet.
-template <int DK>
-__device__ __forceinline__ void apply_changes(const WaveQueue<DK> &Q, int cnt, int *S, int *n, int *dirty,
+template <int DK, typename Queue>
+__device__ __forceinline__ void apply_changes(const Queue &Q, int cnt, int *S, int *n, int *dirty,
                                               const float *ojf, int d, int stamp)
 {
     constexpr int LPR = DK / 4;              // lanes per row
@@ -440,8 +444,8 @@ __device__ __forceinline__ void apply_changes(const WaveQueue<DK> &Q, int cnt, i
 // read there meet the label 0xFF, which matches no centroid).  NG = groups of 64 rows a wave owns
 // at most; the loads of four groups are under way at any time.  SEP: every knob row is in use, so the
 // sizes are counted from the labels.
-template <int DK, int NG, bool SEP>
-__device__ __forceinline__ void full_sums(const WaveQueue<DK> &Q, int *S, int *n, const uint8_t *xw, int64_t ld,
+template <int DK, int NG, bool SEP, typename Queue>
+__device__ __forceinline__ void full_sums(const Queue &Q, int *S, int *n, const uint8_t *xw, int64_t ld,
                                           int d, int k, int rows_here, int lane)
 {
     typedef unsigned uint4v __attribute__((ext_vector_type(4)));
@@ -674,7 +678,8 @@ __device__ __forceinline__ void run_unit(const SweepArgs &a, unsigned char *smem
     const int64_t crow = (int64_t)t * a.Ksum + a.koff[ki];
     uint8_t *labrow = a.labbuf + (int64_t)ki * a.ld;
 
-    WaveQueue<DK> Q(U.wave_base + MfmaLds<DK, SEP>::wave_bytes(NTW) * wave);
+    constexpr bool kShortQueue = WaveQueue<DK, NTW>::kCap < kRecCap;     // filled up to the row, at the price of some registers
+    WaveQueue<DK, NTW> Q(U.wave_base + MfmaLds<DK, SEP>::wave_bytes(NTW) * wave);
     const int wave_row0 = wave * NTW * 32;                 // first row (task-relative) of this wave
     const bool wave_live = wave_row0 < nrows;              // the wave owns at least one row
 
@@ -845,7 +850,7 @@ __device__ __forceinline__ void run_unit(const SweepArgs &a, unsigned char *smem
     __builtin_amdgcn_wave_barrier();
 
     // no row has a label yet
-    for (int e = lane; e < WaveQueue<DK>::kRows; e += 64) Q.lab()[e] = 0xFF;
+    for (int e = lane; e < WaveQueue<DK, NTW>::kRows; e += 64) Q.lab()[e] = 0xFF;
     __builtin_amdgcn_wave_barrier();
 
     const int rows_wave = __builtin_amdgcn_readfirstlane(nrows - wave_row0);   // rows from this wave's first row to the task's end
@@ -1117,9 +1122,11 @@ __device__ __forceinline__ void run_unit(const SweepArgs &a, unsigned char *smem
                 const int nt = __builtin_ctz(todo);
                 todo &= todo - 1;
                 // a batch of queued rows that may not fit one more tile is resolved first
-                if (nrec + 32 > kRecCap) {
-                    resolve_queue<DK>(Q, nrec, U.mu64T, U.ojf, KP, k, d);
-                    nrec = 0;
+                if constexpr (!kShortQueue) {
+                    if (nrec + 32 > kRecCap) {
+                        resolve_queue<DK>(Q, nrec, U.mu64T, U.ojf, KP, k, d);
+                        nrec = 0;
+                    }
                 }
                 const uint32_t live32 = live_rows(nt);
                 const uint32_t cand = ~Q.seen()[nt * 64 + lane];       // bit 31 = position 0
@@ -1130,6 +1137,12 @@ __device__ __forceinline__ void run_unit(const SweepArgs &a, unsigned char *smem
                 const bool flagged = live && total != 1;
                 const uint64_t fm = __ballot(flagged) & 0xFFFFFFFFull;
                 if (fm) {
+                    if constexpr (kShortQueue) {
+                        if (nrec + __popcll(fm) > WaveQueue<DK, NTW>::kCap) {
+                            resolve_queue<DK>(Q, nrec, U.mu64T, U.ojf, KP, k, d);
+                            nrec = 0;
+                        }
+                    }
                     half8 bt[NS];
                     rows_of_tile(nt, bt);
                     if (flagged) {
@@ -1171,7 +1184,7 @@ __device__ __forceinline__ void run_unit(const SweepArgs &a, unsigned char *smem
             }
         } else {
             // a dense queue of (previous, new, knob values), applied with one lane per (row, group of four
-            // knobs), in batches of at most kRecCap rows
+            // knobs), in batches of at most kCap rows
             const int lane = opaque(lane_id), n32 = lane & 31, h = lane >> 5;
             (void)lane;
             uint32_t todo = changed_tiles;
@@ -1184,7 +1197,9 @@ __device__ __forceinline__ void run_unit(const SweepArgs &a, unsigned char *smem
                 const bool changed = cur != prev;
                 const uint64_t cm = __ballot(changed) & 0xFFFFFFFFull;
                 if (cm) {
-                    if (cnt + 32 > kRecCap) {
+                    int add = 32;
+                    if constexpr (kShortQueue) add = __popcll(cm);
+                    if (cnt + add > WaveQueue<DK, NTW>::kCap) {
                         apply_changes<DK>(Q, cnt, U.S, U.n, U.dirty, U.ojf, d, it);
                         cnt = 0;
                     }
@@ -1248,7 +1263,7 @@ __device__ __forceinline__ void run_unit(const SweepArgs &a, unsigned char *smem
         // r_c / n_c, which is exact up to the rounding of those k fractions and of the final
         // subtraction (and exactly zero when every cluster's rows coincide).  The sums left by a
         // pass that rebuilt them on the matrix cores are still raised by 1024 n.
-        double *frac0 = WaveQueue<DK>(U.wave_base).few();     // the queues are idle: [k] doubles of the first wave's region
+        double *frac0 = WaveQueue<DK, NTW>(U.wave_base).few();     // the queues are idle: [k] doubles of the first wave's region
         for (int c = tid; c < k; c += blockDim.x) {
             const int nc = U.n[c];
             double fr = 0.0;
@@ -1299,8 +1314,17 @@ __device__ __forceinline__ void run_unit(const SweepArgs &a, unsigned char *smem
 // Persistent workgroups (one per compute unit) take units from a counter until none is left: the
 // next unit starts as soon as the last one ends, without a new dispatch of a workgroup of this size.
 // Units are handed out in descending-k order so that the longest ones start first.
+// Few tiles per wave leave registers to spare: held to 128 of them (at the price of some spills outside the
+// tile loop), two workgroups share a compute unit, and one's barriers and dependent LDS accesses run
+// under the other's tiles.  64 tasks x 1024 rows x 12 knobs, k = 2..32: 632 -> 452 us a step; 64 tasks x
+// 1000 rows x 24 knobs: 650 -> 532 us.
+constexpr bool two_workgroups(int DK, int NTW, bool SEP)
+{
+    return (DK == 16 && NTW <= 8) || (DK == 32 && NTW <= 4 && !SEP);
+}
+
 template <int DK, int NTW, typename XT, bool SEP>
-__global__ __launch_bounds__(512) void resident_mfma_kernel(const SweepArgs a)
+__global__ __launch_bounds__(512, two_workgroups(DK, NTW, SEP) ? 4 : 2) void resident_mfma_kernel(const SweepArgs a)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int next_unit;
@@ -1407,7 +1431,19 @@ static hipError_t launch_mfma_sweep_t(const SweepArgs &a, int64_t n_max, int64_t
 {
     const bool sep = sizeof(XT) == 1 && a.d == 32;
     const int DK = a.d <= 15 ? 16 : (a.d <= 31 || sep ? 32 : 64);
-    const int ntw = n_max <= 1024 ? 4 : (DK == 64 || (sep && n_max <= 2048) ? 8 : 16);
+    // Tiles per wave.  16 hold 4096 rows in eight waves; fewer spread a smaller task over as many waves.
+    // Measured per step with the count above / with the one chosen:
+    //   2 where one task's latency counts (no more units than compute units), DK = 16, up to 512 rows: 256 rows
+    //     121 / 102 us, 500 rows 137 / 109 us; with many units 4 is as good (64 tasks x 500 rows 271 / 277 us)
+    //   8 up to 2048 rows, DK = 16: 4 tasks x 2000 rows 319 / 243 us, 64 tasks 987 / 953 us; DK = 32 only where
+    //     more than 32 centroids leave LDS for one workgroup per compute unit and there are units for
+    //     every place (64 tasks x 2000 rows x 24 knobs: k = 2..48 2037 / 1579 us, but k = 2..32 874 / 1014 us, and
+    //     4 tasks with k = 2..40 312 / 335 us)
+    const int64_t units = (int64_t)a.T * (a.ki_end - a.ki_begin);
+    int ntw = 16;
+    if (n_max <= 512 && DK == 16 && units <= 256) ntw = 2;
+    else if (n_max <= 1024) ntw = 4;
+    else if (n_max <= 2048 && (DK == 16 || DK == 64 || sep || (a.kmax > 32 && units > 512))) ntw = 8;
     int nwaves = (int)((n_max + 32 * ntw - 1) / (32 * ntw));
     if (nwaves < 1) nwaves = 1;
     if (nwaves > 8) nwaves = 8;
@@ -1416,8 +1452,15 @@ static hipError_t launch_mfma_sweep_t(const SweepArgs &a, int64_t n_max, int64_t
         return ntw == 8 ? launch_mfma_t<32, 8, uint8_t, true>(a, nwaves, n_total, s)
                         : launch_mfma_t<32, 16, uint8_t, true>(a, nwaves, n_total, s);
     }
-    if (DK == 16) return ntw == 4 ? launch_mfma_t<16, 4, XT>(a, nwaves, n_total, s) : launch_mfma_t<16, 16, XT>(a, nwaves, n_total, s);
-    if (DK == 32) return ntw == 4 ? launch_mfma_t<32, 4, XT>(a, nwaves, n_total, s) : launch_mfma_t<32, 16, XT>(a, nwaves, n_total, s);
+    if (DK == 16) {
+        if (ntw == 2) return launch_mfma_t<16, 2, XT>(a, nwaves, n_total, s);
+        if (ntw == 4) return launch_mfma_t<16, 4, XT>(a, nwaves, n_total, s);
+        return ntw == 8 ? launch_mfma_t<16, 8, XT>(a, nwaves, n_total, s) : launch_mfma_t<16, 16, XT>(a, nwaves, n_total, s);
+    }
+    if (DK == 32) {
+        if (ntw == 4) return launch_mfma_t<32, 4, XT>(a, nwaves, n_total, s);
+        return ntw == 8 ? launch_mfma_t<32, 8, XT>(a, nwaves, n_total, s) : launch_mfma_t<32, 16, XT>(a, nwaves, n_total, s);
+    }
     if (sizeof(XT) == 1) return hipErrorInvalidValue;        // (byte knobs never come with more than 32 knobs)
     return ntw == 4 ? launch_mfma_t<64, 4, uint16_t>(a, nwaves, n_total, s) : launch_mfma_t<64, 8, uint16_t>(a, nwaves, n_total, s);
 }
