@@ -99,7 +99,7 @@ __device__ __forceinline__ int frag_row(int c)
 // 32-wide rows and 64 centroids share a compute unit (32 tasks x 1000 rows x 24 knobs, k = 2..48: 551 -> 458 us).
 __host__ __device__ constexpr int rec_cap(int DK, int ntw) { return DK == 32 && ntw <= 4 ? 40 : kRecCap; }
 
-// LDS carve-up.  DK = padded knob count (16, 32 or 64), KP = padded centroid count (32 or 64); SEP: the
+// LDS carve-up.  DK = padded knob count (16, 32, 48 or 64), KP = padded centroid count (32 or 64); SEP: the
 // bias has fragments of its own.
 template <int DK, bool SEP = false>
 struct MfmaLds {
@@ -397,10 +397,11 @@ __device__ __forceinline__ void apply_changes(const Queue &Q, int cnt, int *S, i
     const int j0 = 4 * (lane % LPR);
     const float4 o4 = *reinterpret_cast<const float4 *>(ojf + j0);
     const float of[4] = {o4.x, o4.y, o4.z, o4.w};
+    const bool on = j0 < d && lane < LPR * EPI;      // (twelve lanes per row leave four idle)
 #pragma unroll 2
     for (int e0 = 0; e0 < cnt; e0 += EPI) {
         const int e = e0 + lane / LPR;
-        if (e < cnt && j0 < d) {
+        if (e < cnt && on) {
             const unsigned w = Q.rec_mask()[e];
             typedef _Float16 half4 __attribute__((ext_vector_type(4)));
             const half4 xq = *reinterpret_cast<const half4 *>(Q.rec_x() + (size_t)e * DK + j0);
@@ -552,12 +553,13 @@ __device__ __forceinline__ void update_centroids(const MfmaLds<DK, SEP> &U, int 
                                                  bool raw = false, bool zero_after = false)
 {
     constexpr int NS = DK / 16, NS2 = 2 * NS, QN = DK / 4;
+    constexpr int LQ = QN == 12 ? 16 : QN;              // lanes per centroid: a power of two for the exchanges
     typedef _Float16 half4 __attribute__((ext_vector_type(4)));
-    const int items = k * QN;
+    const int items = k * LQ;
     for (int base = 0; base < items; base += blockDim.x) {      // uniform trip count: every lane shuffles
         const int item = base + (int)threadIdx.x;
-        const int c = item / QN, q = item % QN;
-        bool act = item < items;
+        const int c = item / LQ, q = item % LQ;
+        bool act = item < items && q < QN;
         int cnt = 0;
         if (act) {
             cnt = U.n[c];
@@ -604,8 +606,8 @@ __device__ __forceinline__ void update_centroids(const MfmaLds<DK, SEP> &U, int 
         }
         b = b + dpp_xor_f64<1>(b);
         b = b + dpp_xor_f64<2>(b);
-        if (QN >= 8) b = b + dpp_xor_f64<4>(b);
-        if (QN == 16) b = b + dpp_xor_f64<8>(b);
+        if (LQ >= 8) b = b + dpp_xor_f64<4>(b);
+        if (LQ == 16) b = b + dpp_xor_f64<8>(b);
         if (act && (4 * q < d || q == QN - 1)) {
             if (q == QN - 1) {
                 const float bs = (float)b * (1.0f / kBiasScale);
@@ -652,7 +654,7 @@ __device__ __forceinline__ void run_unit(const SweepArgs &a, unsigned char *smem
     constexpr int NS = DK / 16;          // distinct B fragments per row
     constexpr int NS2 = 2 * NS;          // chained instructions per 32x32 tile, without the bias step
     constexpr int NSA = NS2 + (SEP ? 1 : 0);   // ... with it
-    constexpr int CH = 16 / NS2;         // scores handled between two matrix instructions
+    constexpr int CH = NS2 == 6 ? 4 : 16 / NS2;   // scores handled between two matrix instructions
     const int KP = a.kmax > 32 ? 64 : 32;
     MfmaLds<DK, SEP> U(smem, KP);
 
@@ -981,7 +983,7 @@ __device__ __forceinline__ void run_unit(const SweepArgs &a, unsigned char *smem
             auto mark = [&](uint32_t &far, const float16v &acc, float thr, int i0) {
 #pragma unroll
                 for (int i = 0; i < CH; ++i)
-                    far = __builtin_amdgcn_alignbit(far, __float_as_uint(thr - acc[i0 + i]), 31);
+                    if (i0 + i < 16) far = __builtin_amdgcn_alignbit(far, __float_as_uint(thr - acc[i0 + i]), 31);
             };
             // minimum over the first nreg registers (nreg = 4, 8, 12 or 16)
             auto min_live = [&](const float16v &acc, auto nreg_tag) {
@@ -1430,7 +1432,9 @@ template <typename XT>
 static hipError_t launch_mfma_sweep_t(const SweepArgs &a, int64_t n_max, int64_t n_total, hipStream_t s)
 {
     const bool sep = sizeof(XT) == 1 && a.d == 32;
-    const int DK = a.d <= 15 ? 16 : (a.d <= 31 || sep ? 32 : 64);
+    // Row width: the next multiple of 16 with a slot to spare.  48 against 64 (64 tasks x 2048 rows x 40 knobs, k = 2..32):
+    // six instructions per tile instead of eight and rows that fit the registers (8 spilled, not 112): 1815 -> 1530 us a step.
+    const int DK = a.d <= 15 ? 16 : (a.d <= 31 || sep ? 32 : (a.d <= 47 ? 48 : 64));
     // Tiles per wave.  16 hold 4096 rows in eight waves; fewer spread a smaller task over as many waves.
     // Measured per step with the count above / with the one chosen:
     //   2 where one task's latency counts (no more units than compute units), DK = 16, up to 512 rows: 256 rows
@@ -1443,7 +1447,7 @@ static hipError_t launch_mfma_sweep_t(const SweepArgs &a, int64_t n_max, int64_t
     int ntw = 16;
     if (n_max <= 512 && DK == 16 && units <= 256) ntw = 2;
     else if (n_max <= 1024) ntw = 4;
-    else if (n_max <= 2048 && (DK == 16 || DK == 64 || sep || (a.kmax > 32 && units > 512))) ntw = 8;
+    else if (n_max <= 2048 && (DK == 16 || DK >= 48 || sep || (a.kmax > 32 && units > 512))) ntw = 8;
     int nwaves = (int)((n_max + 32 * ntw - 1) / (32 * ntw));
     if (nwaves < 1) nwaves = 1;
     if (nwaves > 8) nwaves = 8;
@@ -1462,6 +1466,7 @@ static hipError_t launch_mfma_sweep_t(const SweepArgs &a, int64_t n_max, int64_t
         return ntw == 8 ? launch_mfma_t<32, 8, XT>(a, nwaves, n_total, s) : launch_mfma_t<32, 16, XT>(a, nwaves, n_total, s);
     }
     if (sizeof(XT) == 1) return hipErrorInvalidValue;        // (byte knobs never come with more than 32 knobs)
+    if (DK == 48) return ntw == 4 ? launch_mfma_t<48, 4, uint16_t>(a, nwaves, n_total, s) : launch_mfma_t<48, 8, uint16_t>(a, nwaves, n_total, s);
     return ntw == 4 ? launch_mfma_t<64, 4, uint16_t>(a, nwaves, n_total, s) : launch_mfma_t<64, 8, uint16_t>(a, nwaves, n_total, s);
 }
 
