@@ -72,28 +72,44 @@ private:
 
 // Small host arrays travel to the device inside kernel arguments (copied at launch time), so
 // no host buffer has to outlive the call and no device memory is allocated.
-constexpr int kPokeWords = 496;           // with the two fields below just under the 4 KiB of kernel arguments
+// The same launch presets up to three arrays of words (a launch of its own costs about 2 us each: two
+// of the eleven launches of a step on one task of 256 rows).
+constexpr int kPokeWords = 496;           // with the fields below just under the 4 KiB of kernel arguments
 constexpr int kPokeThreads = 512;
+struct Fill {
+    int *dst;
+    int64_t n;
+    int value;
+};
 struct PokeArgs {
     uint64_t v[kPokeWords];
     uint64_t *dst;
+    Fill fill[3];
     int n;
 };
 static_assert(sizeof(PokeArgs) <= 4096 && kPokeWords <= kPokeThreads, "one thread per word, arguments within 4 KiB");
 __global__ void poke_kernel(const PokeArgs p)
 {
-    const int i = threadIdx.x;
+    const int64_t i = (int64_t)blockIdx.x * kPokeThreads + threadIdx.x;
     if (i < p.n) p.dst[i] = p.v[i];
+#pragma unroll
+    for (int f = 0; f < 3; ++f)
+        if (i < p.fill[f].n) p.fill[f].dst[i] = p.fill[f].value;
 }
 
-hipError_t stage_words(const Words &blob, uint64_t *dst, hipStream_t s)
+hipError_t stage_words(const Words &blob, uint64_t *dst, hipStream_t s, const Fill *fills = nullptr, int n_fills = 0)
 {
     for (size_t o = 0; o < blob.size(); o += kPokeWords) {
         PokeArgs p;
         p.n = (int)((blob.size() - o) < (size_t)kPokeWords ? (blob.size() - o) : (size_t)kPokeWords);
         for (int i = 0; i < p.n; ++i) p.v[i] = blob[o + i];
         p.dst = dst + o;
-        hipLaunchKernelGGL(poke_kernel, dim3(1), dim3(kPokeThreads), 0, s, p);
+        int64_t most = p.n;
+        for (int f = 0; f < 3; ++f) {
+            p.fill[f] = o == 0 && f < n_fills ? fills[f] : Fill{nullptr, 0, 0};
+            if (p.fill[f].n > most) most = p.fill[f].n;
+        }
+        hipLaunchKernelGGL(poke_kernel, dim3((unsigned)((most + kPokeThreads - 1) / kPokeThreads)), dim3(kPokeThreads), 0, s, p);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -360,7 +376,14 @@ static int32_t sweep_impl(const void *Xv, int xbytes, int64_t ld, int32_t d, con
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     unsigned char *ws = static_cast<unsigned char *>(workspace);
 
-    hipError_t e = stage_words(pl.blob, reinterpret_cast<uint64_t *>(ws + w.blob), s);
+    // Beside the tables: labelling passes per (task, k), n_iter + 1 unless the kernel records that it stopped
+    // earlier; the work counters of the launches (the matrix-core resident kernel hands out its units
+    // through one); the marks of tasks whose sweep has stopped.
+    int *done = chunked ? reinterpret_cast<int *>(ws + w.total) : nullptr;
+    const Fill fills[3] = {{reinterpret_cast<int *>(ws + w.passes), (int64_t)T * n_k, n_iter + 1},
+                           {reinterpret_cast<int *>(ws + w.counters), n_k + 1, 0},
+                           {done, chunked ? T : 0, 0}};
+    hipError_t e = stage_words(pl.blob, reinterpret_cast<uint64_t *>(ws + w.blob), s, fills, 3);
     if (e != hipSuccess) return hip_fail(e);
 
     SweepArgs a;
@@ -394,18 +417,6 @@ static int32_t sweep_impl(const void *Xv, int xbytes, int64_t ld, int32_t d, con
     a.ki_begin = 0;
     a.ki_end = n_k;
     a.done = nullptr;
-    int *done = chunked ? reinterpret_cast<int *>(ws + w.total) : nullptr;
-    if (chunked) {
-        e = launch_fill_i32(done, T, 0, s);
-        if (e != hipSuccess) return hip_fail(e);
-    }
-
-    // labelling passes per (task, k): n_iter + 1 unless the kernel records that it stopped earlier
-    e = launch_fill_i32(a.passes, (int64_t)T * n_k, n_iter + 1, s);
-    if (e != hipSuccess) return hip_fail(e);
-    // work counters of the launches (the matrix-core resident kernel hands out its units through one)
-    e = launch_fill_i32(reinterpret_cast<int *>(ws + w.counters), n_k + 1, 0, s);
-    if (e != hipSuccess) return hip_fail(e);
     if (init_mode == 0) {
         e = launch_first_distinct(a, reinterpret_cast<int *>(ws + w.init_rows),
                                   reinterpret_cast<int *>(ws + w.ndist), s);

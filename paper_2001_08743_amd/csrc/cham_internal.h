@@ -170,7 +170,6 @@ int64_t stream_lds_bytes(int d, int kpm);
 hipError_t launch_stream_sweep(const StreamArgs &a, int64_t n_total, int total_wgs, hipStream_t s);
 hipError_t launch_knee_update(const double *inertia, const int *status, int T, int n_k, int ki_end, double thr,
                               int *done, hipStream_t s);
-hipError_t launch_fill_i32(int *dst, int64_t n, int value, hipStream_t s);
 hipError_t launch_select_k(const double *inertia, const int *status, int T, int n_k, double thr,
                            int *chosen, hipStream_t s);
 hipError_t launch_snap(const SnapArgs &a, int nt, hipStream_t s);

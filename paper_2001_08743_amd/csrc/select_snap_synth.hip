@@ -56,12 +56,6 @@ __global__ void knee_update_kernel(const double *inertia, const int *status, int
     }
 }
 
-__global__ void fill_i32_kernel(int *dst, int64_t n, int value)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) dst[i] = value;
-}
-
 // ---------------------------------------------------------------------------------------------
 // Snap: one workgroup per task.  Labels under the chosen centroids (same two-stage exact
 // assignment as the sweep), then per cluster the member with the smallest exact distance,
@@ -1006,12 +1000,6 @@ hipError_t launch_knee_update(const double *inertia, const int *status, int T, i
 {
     hipLaunchKernelGGL(knee_update_kernel, dim3((T + 127) / 128), dim3(128), 0, s, inertia, status, T, n_k, ki_end, thr,
                        done);
-    return hipGetLastError();
-}
-
-hipError_t launch_fill_i32(int *dst, int64_t n, int value, hipStream_t s)
-{
-    if (n > 0) hipLaunchKernelGGL(fill_i32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, dst, n, value);
     return hipGetLastError();
 }
 
