@@ -499,7 +499,9 @@ static int32_t sweep_impl(const void *Xv, int xbytes, int64_t ld, int32_t d, con
         }
         if (e != hipSuccess) return hip_fail(e);
         if (chunked && ki_end < n_k) {
-            e = launch_knee_update(inertia, status, T, n_k, ki_end, threshold, done, s);
+            a.ki_begin = ki_end;
+            a.ki_end = ki_end + step < n_k ? ki_end + step : n_k;
+            e = launch_knee_update(a, ki_end, threshold, done, s);
             if (e != hipSuccess) return hip_fail(e);
         }
     }

@@ -1333,6 +1333,12 @@ __global__ __launch_bounds__(512, two_workgroups(DK, NTW, SEP) ? 4 : 2) void res
     const int tid = threadIdx.x;
     const int n_units = a.T * (a.ki_end - a.ki_begin);
 
+    if (a.done && a.T <= 4096) {
+        // a chunk in which every task has stopped: nothing to do (with very many tasks the look itself costs)
+        int live = 0;
+        for (int t = tid; t < a.T; t += blockDim.x) live |= a.done[t] == 0 ? 1 : 0;
+        if (!__syncthreads_or(live)) return;
+    }
     if (tid == 0) next_unit = atomicAdd(a.unit_counter, 1);
     for (;;) {
         __syncthreads();
@@ -1348,8 +1354,10 @@ __global__ __launch_bounds__(512, two_workgroups(DK, NTW, SEP) ? 4 : 2) void res
         const bool skipped = a.done && a.done[t];     // the task's sweep stopped at a smaller k
         const bool too_large = a.too_large && *a.too_large != 0;     // a two-byte value the f16 rows cannot hold
 
-        if (skipped || too_large || (a.init_mode == 0 && a.ndist[t] < k)) {
-            // fewer than k distinct rows, not needed any more, or unusable input: all outputs zero, status says which
+        if (skipped) {
+            // (its outputs were written when the task was marked)
+        } else if (too_large || (a.init_mode == 0 && a.ndist[t] < k)) {
+            // fewer than k distinct rows or unusable input: all outputs zero, status says which
             const int d = a.d;
             const int64_t r0 = a.task_off[t], r1 = a.task_off[t + 1];
             const int64_t slot = (int64_t)t * a.n_k + ki;
@@ -1359,7 +1367,7 @@ __global__ __launch_bounds__(512, two_workgroups(DK, NTW, SEP) ? 4 : 2) void res
             for (int c = tid; c < k; c += blockDim.x) a.counts[crow + c] = 0;
             for (int64_t r = r0 + tid; r < r1; r += blockDim.x) labrow[r] = 0;
             if (tid == 0) {
-                a.status[slot] = too_large ? 4 : (skipped ? 3 : 1);
+                a.status[slot] = too_large ? 4 : 1;
                 a.passes[slot] = 0;
                 a.inertia[slot] = 0.0;
             }
