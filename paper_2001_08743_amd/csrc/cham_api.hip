@@ -188,18 +188,20 @@ constexpr int kStreamRowsPerWg = 4096;      // rows per workgroup of the streami
 // of its four waves holds) while the launch has fewer workgroups than the chip has places for them (two
 // per compute unit).  Measured per sampling step, 4096 / 2048 / 1024 / 512 rows: 48 units of 900 to 2500 rows
 // 1064 / 1023 / 801 / 676 us; 42 units of 21 000 to 60 000 rows (385 / 770 / 1540 / 3080 workgroups)
-// 1749 / 1418 / 1476 / 1777 us; 5 units of 2^20 rows (1280 / 2560 workgroups) 2890 / 3052 us.  Below 4096 rows
-// the loss partials of the final pass stand in the unit's sums, which hold 512 of them at least.  A
-// traced sweep has partials in every pass and keeps 4096.
+// 1749 / 1418 / 1476 / 1777 us; 5 units of 2^20 rows (1280 / 2560 workgroups) 2890 / 3052 us.  Not below what
+// gives a task 512 workgroups: one unit of 300 000 x 16 with k = 64, 1024 / 512 rows (293 / 586 workgroups) 520 / 789 us
+// (its steps hold 1024 rows).  The order of the loss does not depend on it; below 4096 rows its partials, one
+// per 4096 rows, stand in the unit's sums, which hold 512 of them at least.  A traced sweep has them in every
+// pass and keeps 4096.
 int stream_rows_per_wg(const Plan &pl, const int64_t *task_off, int n_ks, bool traced)
 {
-    constexpr int kPlaces = 512, kMinRows = 512, kMaxPartials = 512;
+    constexpr int kPlaces = 512, kMinRows = 512, kMaxPerTask = 512;
     int rows = kStreamRowsPerWg;
     if (traced) return rows;
     while (rows > kMinRows) {
         int64_t wgs = 0;
         for (int t = 0; t < pl.T; ++t) wgs += (task_off[t + 1] - task_off[t] + rows - 1) / rows;
-        if (wgs * n_ks >= kPlaces || (pl.n_max + rows / 2 - 1) / (rows / 2) > kMaxPartials) break;
+        if (wgs * n_ks >= kPlaces || (pl.n_max + rows / 2 - 1) / (rows / 2) > kMaxPerTask) break;
         rows /= 2;
     }
     return rows;
@@ -464,7 +466,6 @@ static int32_t sweep_impl(const void *Xv, int xbytes, int64_t ld, int32_t d, con
             sa.it = 0;
             sa.final_pass = 0;
             sa.rows_per_wg = rpw;
-            sa.loss_in_sums = rpw < kStreamRowsPerWg ? 1 : 0;
             sa.task_off = a.task_off;
             sa.ks = a.ks;
             sa.koff = a.koff;

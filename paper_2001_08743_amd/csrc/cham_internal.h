@@ -71,8 +71,7 @@ struct StreamArgs {
     const int *done;               // [T] or null: tasks whose sweep has already stopped (their units report status 3)
     int it;                        // pass being run
     int final_pass;
-    int rows_per_wg;               // rows a workgroup of the assignment kernel walks
-    int loss_in_sums;              // 1: the loss partials of the final pass go to the unit's sums (rows_per_wg < 4096)
+    int rows_per_wg;               // rows a workgroup of the assignment kernel walks: 4096, or (not in a traced sweep) a smaller power of two
     const int64_t *task_off;
     const int *ks;
     const int *koff;
@@ -95,7 +94,7 @@ struct StreamArgs {
     void *afrag;                   // [n_units][kpm/32][4][64] 16-byte A fragments
     float *biasf;                  // [n_units][kpm] |mu'|^2 per centroid row (huge for padding rows)
     float *m2;                     // [n_units][8] bound on max |mu'|^2 per tile of 32 centroids; tile 0 negative = unit unusable
-    double *loss_part;             // [total workgroups] loss partials of the last pass
+    double *loss_part;             // [total workgroups] loss partials of the last pass (rows_per_wg = 4096)
     int *passes;                   // [T][n_k] during the sweep: 1 + the last pass that moved a row; n_iter + 1 at the end
 };
 

@@ -26,7 +26,12 @@ constexpr int kStepRows = kMaxTiles * 32;
 constexpr int kStreamRec = 32;       // queued rows whose knob values are kept in LDS
 constexpr int kWavesPerWg = 4;
 constexpr int kPairCap = 128;        // (queued row, candidate centroid) pairs evaluated per step and wave
+constexpr int kLossRows = 4096;      // rows of a partial sum of the loss, whatever an assigning workgroup walks
 constexpr float kPadScore = 1.0e30f; // score of a padding centroid row (real scores stay below 4 * 32 * 255^2)
+
+// Tiles of 32 rows a wave of the assignment takes per step for a unit of k centroids.
+template <int DK>
+__host__ __device__ constexpr int tiles_per_step(int k) { return k <= 64 && DK == 16 ? 8 : 4; }
 
 // Per-unit state in global memory.  KPM = kmax rounded up to 32.
 struct UnitState {
@@ -156,13 +161,13 @@ __global__ __launch_bounds__(32 * (DK / 8)) void stream_update_kernel(const Stre
         return;
     }
 
-    // loss of the pass that just ran: workgroup partials in workgroup order
+    // loss of the pass that just ran: partials in row order
     if (mt == 0 && mode != 0 && tid == 0 && (mode == 2 || a.trace)) {
-        const int nwg = a.wg_off[ul + 1] - a.wg_off[ul];
+        const int np = (int)((r1 - r0 + kLossRows - 1) / kLossRows);
         double s = 0.0;
-        const double *part = a.loss_in_sums ? reinterpret_cast<const double *>(st.S) : a.loss_part + a.wg_off[ul];
+        const double *part = a.rows_per_wg < kLossRows ? reinterpret_cast<const double *>(st.S) : a.loss_part + a.wg_off[ul];
 #pragma unroll 8
-        for (int w = 0; w < nwg; ++w) s = s + part[w];
+        for (int b = 0; b < np; ++b) s = s + part[b];
         if (a.trace) a.trace[slot * (a.n_iter + 1) + a.it] = s;
         if (mode == 2) {
             a.inertia[slot] = s;
@@ -253,17 +258,16 @@ struct StreamLds {
     int *n;              // [KPM]
     float *ojf;          // [DK]
     float *bias;         // [KPM]
-    double *red;         // [8]
     unsigned char *wave_base;
-    // per wave: knob values of queued rows, their row slots, resolved labels, labels of the step
+    // per wave: knob values of queued rows, their row slots, resolved labels, label changes
     // ... and for the exact evaluation of queued rows: (record, centroid) pairs, per record the
     // smallest distance (bits) and the lowest centroid attaining it, the pair counter
-    static constexpr size_t kWaveBytes = (size_t)kStreamRec * DK * 2 + kStepRows * 2 + kStepRows + kStepRows +
+    static constexpr size_t kWaveBytes = (size_t)kStreamRec * DK * 2 + kStepRows * 2 + kStepRows +
                                          kStreamRec * 4 + kPairCap * 2 + kStepRows * 8 + kStepRows * 4 + 16;
     __host__ __device__ static size_t bytes(int kpm)
     {
         size_t b = 16 * (size_t)(kpm / 32) * 4 * 64 + sizeof(int) * (size_t)kpm * DK + sizeof(int) * kpm +
-                   sizeof(float) * DK + sizeof(float) * kpm + sizeof(double) * 8 + 16;
+                   sizeof(float) * DK + sizeof(float) * kpm + 16;
         b = (b + 15) & ~(size_t)15;
         return b + ((kWaveBytes + 15) & ~(size_t)15) * kWavesPerWg;
     }
@@ -271,7 +275,6 @@ struct StreamLds {
     {
         size_t o = 0;
         afrag = reinterpret_cast<half8 *>(base + o);  o += 16 * (size_t)(kpm / 32) * 4 * 64;
-        red = reinterpret_cast<double *>(base + o);   o += sizeof(double) * 8;
         S = reinterpret_cast<int *>(base + o);        o += sizeof(int) * (size_t)kpm * DK;
         n = reinterpret_cast<int *>(base + o);        o += sizeof(int) * kpm;
         ojf = reinterpret_cast<float *>(base + o);    o += sizeof(float) * DK;
@@ -308,10 +311,10 @@ __device__ __forceinline__ void assign_unit(const StreamArgs &a, int unit_idx)
     if (m2 < 0.0f) return;                     // unusable unit (fewer than k distinct rows)
     // The pass before moved no row: sums and centroids are what that pass used, so this one would move
     // none either.  (passes holds 1 + the last pass that moved a row; a workgroup of this pass may
-    // raise it to it + 1 meanwhile, but only in a unit that none of them skips.)  The final pass runs
-    // for the loss, a traced sweep runs every pass.
+    // raise it to it + 1 meanwhile, but only in a unit that none of them skips.)  A traced sweep runs
+    // every pass.
     int *moved_at = a.passes + (int64_t)t * a.n_k + ki;
-    if (a.it > 0 && !a.final_pass && !a.trace && *moved_at < a.it) return;
+    if (a.it > 0 && !a.trace && *moved_at < a.it) return;
     bool moved = false;
     for (int i = 1; i < kpu / 32; ++i) m2 = __builtin_fmaxf(m2, a.m2[u * kM2Tiles + i]);
     const UnitState st = unit_state(a, u);
@@ -323,13 +326,11 @@ __device__ __forceinline__ void assign_unit(const StreamArgs &a, int unit_idx)
     const int64_t r1 = (r0 + rpw < t1) ? r0 + rpw : t1;
     uint8_t *labrow = a.labbuf + (int64_t)ki * a.ld;
     const bool first = a.it == 0;
-    const bool want_dist = a.final_pass || (a.trace != nullptr);
     unsigned char *wb = L.wave_base + ((StreamLds<DK>::kWaveBytes + 15) & ~(size_t)15) * wave;
     _Float16 *rec_x = reinterpret_cast<_Float16 *>(wb);                                          // [kStreamRec][DK]
     unsigned short *rec_slot = reinterpret_cast<unsigned short *>(wb + (size_t)kStreamRec * DK * 2);   // [kStepRows]
     unsigned char *lab_res = wb + (size_t)kStreamRec * DK * 2 + kStepRows * 2;                    // [kStepRows]
-    unsigned char *lab_new = lab_res + kStepRows;                                                  // [kStepRows]
-    unsigned *chg = reinterpret_cast<unsigned *>(lab_new + kStepRows);                             // [kStreamRec] cur | prev << 8 | first << 16
+    unsigned *chg = reinterpret_cast<unsigned *>(lab_res + kStepRows);                             // [kStreamRec] cur | prev << 8 | first << 16
     unsigned short *pairs = reinterpret_cast<unsigned short *>(chg + kStreamRec);                  // [kPairCap] record << 8 | centroid
     unsigned long long *best_bits = reinterpret_cast<unsigned long long *>(pairs + kPairCap);      // [kStepRows]
     int *best_c = reinterpret_cast<int *>(best_bits + kStepRows);                                  // [kStepRows]
@@ -337,7 +338,6 @@ __device__ __forceinline__ void assign_unit(const StreamArgs &a, int unit_idx)
 
     const _Float16 *xh = reinterpret_cast<const _Float16 *>(a.xh);
     const int nch = (k + 63) >> 6;
-    double part = 0.0;
 
     const int64_t step_rows = (int64_t)kWavesPerWg * TILES * 32;
 
@@ -710,7 +710,6 @@ __device__ __forceinline__ void assign_unit(const StreamArgs &a, int unit_idx)
             if ((flagged_mask >> tt) & 1u) cl = lab_res[tt * 32 + n32];
             const int prev = cur.prev[tt];
             const bool changed = live[tt] && (first || cl != prev);
-            if (want_dist && h == 0) lab_new[tt * 32 + n32] = (unsigned char)(live[tt] ? cl : 0);
             const uint64_t cm = __ballot(changed) & 0xFFFFFFFFull;
             if (cm) {
                 const int c = __popcll(cm);
@@ -735,41 +734,8 @@ __device__ __forceinline__ void assign_unit(const StreamArgs &a, int unit_idx)
             apply_changes(nchg);
             moved = true;
         }
-        if (want_dist) {
-            // exact loss terms of the rows of this step: one row per lane, knobs ascending
-            __builtin_amdgcn_wave_barrier();
-            for (int s0 = 0; s0 < TILES * 32; s0 += 64) {
-                const int sl = s0 + lane;
-                const int64_t row = wrow0 + sl;
-                if (row < r1) {
-                    const int c = lab_new[sl];
-                    // all loads of the row first (they are independent), then the sum in knob order
-                    double mu[DK];
-                    uint8_t xv[DK];
-#pragma unroll
-                    for (int j = 0; j < DK; ++j) {
-                        const int jj = j < d ? j : 0;
-                        xv[j] = a.X[(int64_t)jj * a.ld + row];
-                        mu[j] = st.mu[(size_t)jj * kpm + c];
-                    }
-                    double s = 0.0;
-#pragma unroll
-                    for (int j = 0; j < DK; ++j) {
-                        if (j < d) {
-                            const double tq = (double)xv[j] - mu[j];
-                            s = s + tq * tq;
-                        }
-                    }
-                    part = part + s;
-                }
-            }
-        }
     }
 
-    if (want_dist) {
-        const double ws = wave_sum(part);
-        if (lane == 0) L.red[wave] = ws;
-    }
     const bool any_moved = __syncthreads_or(moved ? 1 : 0) != 0;
     // changes of this workgroup -> the unit's sums (which nothing reads after the final pass)
     if (any_moved && !a.final_pass) {
@@ -783,23 +749,14 @@ __device__ __forceinline__ void assign_unit(const StreamArgs &a, int unit_idx)
         const int v = L.n[c];
         if (v != 0) atomicAdd(&st.n[c], v);
     }
-    if (want_dist && tid == 0) {
-        double s = 0.0;
-        for (int w = 0; w < kWavesPerWg; ++w) s = s + (w < (int)(blockDim.x >> 6) ? L.red[w] : 0.0);
-        // (a final pass leaves the sums alone: with many workgroups its partials stand there)
-        if (a.loss_in_sums) reinterpret_cast<double *>(st.S)[wgi] = s;
-        else a.loss_part[blockIdx.x] = s;
-    }
 }
 
-template <int DK>
-__global__ __launch_bounds__(kWavesPerWg * 64, 2) void stream_assign_kernel(const StreamArgs a)
+// Unit of this workgroup: the last one with wg_off[unit] <= blockIdx.x, by a 64-way search of the first
+// wave (one or two rounds of independent loads instead of a chain of dependent ones).
+__device__ __forceinline__ int unit_of_block(const StreamArgs &a, int *unit_sh)
 {
-    __shared__ int unit_sh;
     const int tid = threadIdx.x;
     if (tid < 64) {
-        // last unit with wg_off[unit] <= blockIdx.x: a 64-way search by the first wave (one or two
-        // rounds of independent loads instead of a chain of dependent ones)
         int lo = 0, hi = a.n_units;
         while (hi - lo > 1) {
             const int span = hi - lo;
@@ -812,10 +769,17 @@ __global__ __launch_bounds__(kWavesPerWg * 64, 2) void stream_assign_kernel(cons
             lo = nlo;
             hi = nhi;
         }
-        if (tid == 0) unit_sh = lo;
+        if (tid == 0) *unit_sh = lo;
     }
     __syncthreads();
-    const int unit_idx = __builtin_amdgcn_readfirstlane(unit_sh);
+    return __builtin_amdgcn_readfirstlane(*unit_sh);
+}
+
+template <int DK>
+__global__ __launch_bounds__(kWavesPerWg * 64, 2) void stream_assign_kernel(const StreamArgs a)
+{
+    __shared__ int unit_sh;
+    const int unit_idx = unit_of_block(a, &unit_sh);
     const int u = a.u_begin + unit_idx;
     const int k = a.ks[a.n_k - 1 - u / a.T];
     // the unit index goes through an opaque copy per variant: what a variant derives from it stays inside
@@ -823,13 +787,84 @@ __global__ __launch_bounds__(kWavesPerWg * 64, 2) void stream_assign_kernel(cons
     int ui = unit_idx;
     if (k <= 64) {
         asm volatile("" : "+s"(ui));
-        assign_unit<DK, 1, (DK == 16 ? 8 : 4)>(a, ui);
+        assign_unit<DK, 1, tiles_per_step<DK>(64)>(a, ui);
     } else if (k <= 128) {
         asm volatile("" : "+s"(ui));
-        assign_unit<DK, 2, 4>(a, ui);
+        assign_unit<DK, 2, tiles_per_step<DK>(128)>(a, ui);
     } else {
         asm volatile("" : "+s"(ui));
-        assign_unit<DK, 4, 4>(a, ui);
+        assign_unit<DK, 4, tiles_per_step<DK>(256)>(a, ui);
+    }
+}
+
+// Loss of the labels of the pass that just ran (the final one, or every one of a traced sweep): one
+// workgroup per kLossRows rows of a unit, whatever the assigning workgroups walk.  How the rows are split
+// among those depends on the batch and on the chunk of the list of k, and the knee rule compares the losses,
+// so the order of the sum must not: the terms of all rows go to LDS, then lane l of four waves adds up rows l,
+// l + 64, ... of its wave's runs of consecutive rows (the runs a wave of the assignment takes per step), then
+// the lanes, the waves and, in the update kernel, the blocks of kLossRows.  Bound by the latency of the
+// centroids' gathers, hence from LDS: a step of 171 256 x 14, k = 64 and 128 (84 workgroups), takes 529 us, 545 us
+// with gathers from memory and 536 us with the loss inside the assignment, where it cost registers.
+template <int DK>
+__global__ __launch_bounds__(1024) void stream_loss_kernel(const StreamArgs a)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    double *term = reinterpret_cast<double *>(smem);               // [kLossRows]
+    double *mu_sh = term + kLossRows;                              // [d][KPM] centroids
+    __shared__ double red[kWavesPerWg];
+    __shared__ int unit_sh;
+    const int tid = threadIdx.x;
+    const int unit_idx = unit_of_block(a, &unit_sh);
+    const int first = ((int)blockIdx.x - a.wg_off[unit_idx]) * a.rows_per_wg;     // of the assigning workgroup of this index
+    const int u = a.u_begin + unit_idx;
+    if (first % kLossRows != 0 || a.m2[u * kM2Tiles] < 0.0f) return;              // inside another block, or an unusable unit
+    const int ki = a.n_k - 1 - u / a.T;
+    const int t = u % a.T;
+    const int64_t r0 = a.task_off[t] + first, t1 = a.task_off[t + 1];
+    const int n = (int)(t1 - r0 < kLossRows ? t1 - r0 : kLossRows);
+    const int k = a.ks[ki], d = a.d, kpm = a.kpm;
+    const UnitState st = unit_state(a, u);
+    const uint8_t *lab = a.labbuf + (int64_t)ki * a.ld + r0;
+    for (int e = tid; e < d * kpm; e += blockDim.x) mu_sh[e] = st.mu[e];
+    __syncthreads();
+    for (int r = tid; r < n; r += blockDim.x) {
+        const int c = lab[r];
+        // all loads of the row first (they are independent), then the sum in knob order
+        double mu[DK];
+        uint8_t xv[DK];
+#pragma unroll
+        for (int j = 0; j < DK; ++j) {
+            const int jj = j < d ? j : 0;
+            xv[j] = a.X[(int64_t)jj * a.ld + r0 + r];
+            mu[j] = mu_sh[jj * kpm + c];
+        }
+        double s = 0.0;
+#pragma unroll
+        for (int j = 0; j < DK; ++j) {
+            if (j < d) {
+                const double tq = (double)xv[j] - mu[j];
+                s = s + tq * tq;
+            }
+        }
+        term[r] = s;
+    }
+    __syncthreads();
+    if (tid < kWavesPerWg * 64) {
+        const int run = 32 * tiles_per_step<DK>(k);
+        double part = 0.0;
+        for (int base = (tid >> 6) * run; base < n; base += kWavesPerWg * run)
+            for (int r = base + (tid & 63); r < base + run; r += 64)
+                if (r < n) part = part + term[r];
+        const double ws = wave_sum(part);
+        if ((tid & 63) == 0) red[tid >> 6] = ws;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        double s = 0.0;
+        for (int w = 0; w < kWavesPerWg; ++w) s = s + red[w];
+        // with fewer rows per workgroup the partials stand in the unit's sums, which nothing reads any more
+        if (a.rows_per_wg < kLossRows) reinterpret_cast<double *>(st.S)[first / kLossRows] = s;
+        else a.loss_part[blockIdx.x] = s;
     }
 }
 
@@ -839,6 +874,10 @@ hipError_t run_stream(StreamArgs a, int64_t n_total, int total_wgs, hipStream_t 
     const size_t lds = StreamLds<DK>::bytes(a.kpm);
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(stream_assign_kernel<DK>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    const size_t lds_loss = sizeof(double) * ((size_t)kLossRows + (size_t)a.d * a.kpm);      // at most 96 KiB
+    e = hipFuncSetAttribute(reinterpret_cast<const void *>(stream_loss_kernel<DK>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_loss);
     if (e != hipSuccess) return e;
     if (a.prepare) {
         hipLaunchKernelGGL(stream_offsets_kernel, dim3(a.T), dim3(256), 0, s, a);
@@ -853,6 +892,7 @@ hipError_t run_stream(StreamArgs a, int64_t n_total, int total_wgs, hipStream_t 
         a.it = it;
         a.final_pass = it == a.n_iter ? 1 : 0;
         hipLaunchKernelGGL(stream_assign_kernel<DK>, dim3(total_wgs), dim3(kWavesPerWg * 64), lds, s, a);
+        if (a.final_pass || a.trace) hipLaunchKernelGGL(stream_loss_kernel<DK>, dim3(total_wgs), dim3(1024), lds_loss, s, a);
         hipLaunchKernelGGL(stream_update_kernel<DK>, ugrid, ublock, 0, s, a, a.final_pass ? 2 : 1);
     }
     return hipGetLastError();

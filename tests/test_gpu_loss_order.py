@@ -1,0 +1,96 @@
+"""The order in which a loss is summed belongs to the task, its k and the largest task of the batch: it is the same in a whole
+sweep, in any chunking of it, with or without a trace, and (streaming path) whatever else is in the batch.  The knee rule compares
+these sums, so they are compared bit for bit here."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2001_08743_amd import binding, workloads
+
+pytestmark = pytest.mark.gpu
+
+
+def _wave_sum(v):
+    """64 lanes, partner lane ^ 32, 16, ..., 1."""
+    lanes = np.arange(64)
+    for off in (32, 16, 8, 4, 2, 1):
+        v = v + v[lanes ^ off]
+    return v[0]
+
+
+def _streaming_loss(rows, labels, mu, k):
+    """Blocks of 4096 rows; in a block four waves take runs of 128 rows in turn (256 with at most 16 knobs and k <= 64), 64 rows
+    at a time; waves, then blocks, in order."""
+    d = rows.shape[1]
+    term = np.zeros(len(rows))
+    for j in range(d):
+        t = rows[:, j].astype(np.float64) - mu[labels, j]
+        term = term + t * t
+    run = 256 if d <= 16 and k <= 64 else 128
+    total = 0.0
+    for b in range(0, len(rows), 4096):
+        block = np.zeros(4096)
+        n = min(4096, len(rows) - b)
+        block[:n] = term[b:b + n]
+        steps = block.reshape(4096 // (4 * run), 4, run // 64, 64)
+        s = 0.0
+        for w in range(4):
+            part = np.zeros(64)
+            for i in range(steps.shape[0]):
+                for q in range(run // 64):
+                    part = part + steps[i, w, q]
+            s = s + _wave_sum(part)
+        total = total + s
+    return total
+
+
+def _streaming(dw, off, wl, **kw):
+    return binding.cham_kmeans_sweep(dw.X, dw.ld, dw.d, off, wl.ks, wl.n_iter, flags=binding.F_STREAMING, **kw)
+
+
+@pytest.mark.parametrize("n,d,ks", [(1, 5, (1,)), (513, 16, (3, 64, 65)), (4095, 17, (2, 40)), (4096, 9, (7, 100)), (4097, 24, (5, 33, 256)),
+                                    (12289, 16, (16, 80)), (30001, 31, (2, 64))])
+def test_streaming_loss_is_the_documented_sum(n, d, ks):
+    wl = workloads.random_task(n + d, n, d, card_hi=30, n_blobs=7, sigma=1.1, ks=ks, n_iter=4, n_tasks=2, ragged=n > 1)
+    dw = binding.DeviceWorkload(wl)
+    out = _streaming(dw, wl.task_off, wl, want_labels=True)
+    traced = _streaming(dw, wl.task_off, wl, want_trace=True)
+    ref = oracle.sweep(wl.rows, wl.task_off, wl.ks, wl.n_iter, want_labels=True)
+    got = out["inertia"].cpu().numpy()
+    np.testing.assert_array_equal(traced["inertia"].cpu().numpy(), got)
+    np.testing.assert_array_equal(traced["trace"].cpu().numpy()[:, :, -1], got)
+    for t in range(2):
+        rows = slice(wl.task_off[t], wl.task_off[t + 1])
+        for i, k in enumerate(ks):
+            if ref["status"][t, i] == 0:
+                mu = ref["centroids"][t, ref["koff"][i]:ref["koff"][i + 1]]
+                assert got[t, i] == _streaming_loss(wl.rows[rows], ref["labels"][i, rows], mu, k), (t, k)
+            else:
+                assert got[t, i] == 0.0
+
+
+@pytest.mark.parametrize("n,d", [(700, 9), (5000, 14), (9000, 24)])
+def test_streaming_loss_does_not_depend_on_the_batch(n, d):
+    # alone a task's rows are split over the chip, among 60 others a workgroup takes them all
+    wl = workloads.random_task(n, n, d, card_hi=20, n_blobs=6, sigma=0.9, ks=(2, 9, 40, 70), n_iter=5, n_tasks=60, ragged=True)
+    dw = binding.DeviceWorkload(wl)
+    whole = _streaming(dw, wl.task_off, wl)["inertia"].cpu().numpy()
+    for t in (0, 17, 59):
+        alone = _streaming(dw, wl.task_off[t:t + 2], wl)["inertia"].cpu().numpy()
+        np.testing.assert_array_equal(alone[0], whole[t])
+
+
+def _chunked_equals_whole(wl, chunk, flags, sfx="", path=None):
+    dw = binding.DeviceWorkload(wl)
+    assert binding.cham_sweep_path(dw.ld, dw.d, wl.task_off, wl.ks, flags=flags, _sfx=sfx) == path
+    whole = binding.cham_kmeans_sweep(dw.X, dw.ld, dw.d, wl.task_off, wl.ks, wl.n_iter, flags=flags, _sfx=sfx)
+    part = binding.cham_kmeans_sweep_knee(dw.X, dw.ld, dw.d, wl.task_off, wl.ks, wl.n_iter, threshold=0.0, chunk=chunk, flags=flags, _sfx=sfx)
+    for key in ("status", "counts", "centroids", "inertia"):
+        np.testing.assert_array_equal(part[key].cpu().numpy(), whole[key].cpu().numpy(), err_msg=key)
+
+
+@pytest.mark.parametrize("n,d,tasks", [(5000, 14, 40), (6000, 24, 60), (9000, 9, 30), (120000, 12, 3)])
+@pytest.mark.parametrize("chunk", [1, 3])
+def test_chunked_streaming_sweep(n, d, tasks, chunk):
+    wl = workloads.random_task(n + d, n, d, card_hi=18, n_blobs=6, sigma=0.9, ks=(2, 4, 8, 16, 32, 64, 128), n_iter=4, n_tasks=tasks, ragged=True)
+    _chunked_equals_whole(wl, chunk, binding.F_STREAMING, path=1)
