@@ -148,8 +148,9 @@ const char *cham_sweep_path_kernel(int32_t path);
  * [T][n_k] int32 DEVICE.  Algorithm 1's K-means.run is n_iter update steps plus the final
  * labelling, n_iter + 1 passes; a pass that changes no label leaves sums, centroids and every
  * later pass unchanged, so a kernel may stop there with the results of the full iteration
- * (the matrix-core resident kernel does; the figure is what a throughput in executed distance
- * evaluations is computed from).  0 for a (task, k) that was skipped (status 1 or 3).  The
+ * (all of them do, at the latest a pass later, unless a loss trace asks the streaming path for every pass;
+ * the figure is what a throughput in executed distance evaluations is computed from).  0 for a
+ * (task, k) that was skipped (status 1 or 3).  The
  * arguments other than passes are those of the sweep call; works for both knob widths.
  */
 int32_t cham_sweep_passes(const void *workspace, int64_t workspace_bytes, int64_t ld, int32_t d,

@@ -95,7 +95,7 @@ struct StreamArgs {
     float *biasf;                  // [n_units][kpm] |mu'|^2 per centroid row (huge for padding rows)
     float *m2;                     // [n_units][8] bound on max |mu'|^2 per tile of 32 centroids; tile 0 negative = unit unusable
     double *loss_part;             // [total workgroups] loss partials of the last pass (rows_per_wg = 4096)
-    int *passes;                   // [T][n_k] during the sweep: 1 + the last pass that moved a row; n_iter + 1 at the end
+    int *passes;                   // [T][n_k] during the sweep: 1 + the last pass that moved a row; at the end: passes run
 };
 
 // Arguments of the snap kernel.

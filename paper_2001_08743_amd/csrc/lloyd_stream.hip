@@ -172,7 +172,8 @@ __global__ __launch_bounds__(32 * (DK / 8)) void stream_update_kernel(const Stre
         if (mode == 2) {
             a.inertia[slot] = s;
             a.status[slot] = 0;
-            a.passes[slot] = a.n_iter + 1;         // nominal: a pass of a settled unit is still launched
+            // up to and including the first pass that moved no row (a pass launched after it returns at once)
+            a.passes[slot] = a.trace ? a.n_iter + 1 : a.passes[slot] + 1;
         }
     }
     if (mode == 0 && mt == 0 && tid == 0) a.passes[slot] = 0;

@@ -60,3 +60,19 @@ def test_chunked_sweep_equals_the_whole():
     torch.cuda.synchronize()
     for key in ("status", "counts", "centroids", "labels", "inertia"):
         assert torch.equal(part[key], whole[key]), key
+
+
+@pytest.mark.parametrize("n_iter", [0, 1, 2, 3, 25])
+def test_passes_of_settled_units(n_iter):
+    # as the resident kernel: up to and including the pass that moves no row
+    wl = workloads.random_task(81, 3000, 12, card_hi=12, n_blobs=4, sigma=0.5, ks=(1, 2, 4, 20, 64), n_iter=n_iter, n_tasks=3, ragged=True)
+    dw, out = _sweep(wl)
+    ran = binding.cham_sweep_passes(out["workspace"], dw.ld, dw.d, wl.task_off, wl.ks, flags=binding.F_STREAMING).cpu().numpy()
+    res = binding.cham_kmeans_sweep(dw.X, dw.ld, dw.d, wl.task_off, wl.ks, n_iter)
+    stops = binding.cham_sweep_passes(res["workspace"], dw.ld, dw.d, wl.task_off, wl.ks).cpu().numpy()
+    np.testing.assert_array_equal(ran, stops)
+    if n_iter == 25:
+        assert ran.min() < n_iter + 1
+    _, traced = _sweep(wl, want_trace=True)
+    ran = binding.cham_sweep_passes(traced["workspace"], dw.ld, dw.d, wl.task_off, wl.ks, flags=binding.F_STREAMING).cpu().numpy()
+    assert (ran == n_iter + 1).all()
