@@ -99,6 +99,10 @@ __device__ __forceinline__ int frag_row(int c)
 // 32-wide rows and 64 centroids share a compute unit (32 tasks x 1000 rows x 24 knobs, k = 2..48: 551 -> 458 us).
 __host__ __device__ constexpr int rec_cap(int DK, int ntw) { return DK == 32 && ntw <= 4 ? 40 : kRecCap; }
 
+// Variants that launch_mfma_sweep_t prefers to the one with twice the tiles per wave by the number of units alone: they
+// sum the loss in its order.
+constexpr bool paired_loss(int DK, int ntw, bool SEP) { return (DK == 16 && ntw == 2) || (DK == 32 && ntw == 8 && !SEP); }
+
 // LDS carve-up.  DK = padded knob count (16, 32, 48 or 64), KP = padded centroid count (32 or 64); SEP: the
 // bias has fragments of its own.
 template <int DK, bool SEP = false>
@@ -892,9 +896,16 @@ __device__ __forceinline__ void run_unit(const SweepArgs &a, unsigned char *smem
 
     // Exact loss of the current labels from the rows in registers: (x - mu)^2 in double over the knobs
     // a lane holds (x = centred value + offset, exact), the two lanes of a row and all rows added up
-    // afterwards; the per-wave sums land in U.red[slot8 .. slot8 + nwaves).
+    // afterwards; the sums of the waves land in U.red[slot8 .. slot8 + n_parts).
+    // kPaired: the number of units chose this number of tiles per wave over twice it.  A loss is the same in
+    // a whole sweep and in a chunk of it, which have different numbers of units: the terms of an odd wave go
+    // through its idle queue to the wave before it, whose lanes add up what they would with twice the tiles.
+    constexpr bool kPaired = paired_loss(DK, NTW, SEP);
+    static_assert(!kPaired || (size_t)NTW * 64 * sizeof(double) <= WaveQueue<DK, NTW>::kOffMask, "the terms fit the queue's rows");
+    const int n_parts = kPaired ? (nwaves + 1) / 2 : nwaves;
     auto wave_loss = [&](int slot8) {
         double part = 0.0;
+        const bool handed_over = kPaired && (wave & 1) != 0;
         const int lane = opaque(lane_id), n32 = lane & 31, h = lane >> 5;
         if (wave_live) {
             float of[NS][8];
@@ -925,7 +936,16 @@ __device__ __forceinline__ void run_unit(const SweepArgs &a, unsigned char *smem
                         const double tq = (double)xf - mu[f][i];
                         s = s + tq * tq;
                     }
-                part = part + (live ? s : 0.0);
+                if (handed_over) reinterpret_cast<double *>(Q.rec_x())[nt * 64 + lane] = live ? s : 0.0;
+                else part = part + (live ? s : 0.0);
+            }
+        }
+        if constexpr (kPaired) {
+            __syncthreads();
+            if (!handed_over && wave_row0 + NTW * 32 < nrows) {          // the next wave owns rows
+                const double *terms = reinterpret_cast<const double *>(U.wave_base + MfmaLds<DK, SEP>::wave_bytes(NTW) * (wave + 1));
+#pragma unroll
+                for (int nt = 0; nt < NTW; ++nt) part = part + terms[nt * 64 + lane];
             }
         }
         // the wave's total in the fixed order lane ^ 32, 16, ..., 1 (partner indices from the local lane index)
@@ -937,7 +957,7 @@ __device__ __forceinline__ void run_unit(const SweepArgs &a, unsigned char *smem
             const int phi = __builtin_amdgcn_ds_bpermute((lane ^ off) << 2, (int)(b >> 32));
             ws = ws + __longlong_as_double(((long long)phi << 32) | (unsigned int)plo);
         }
-        if (lane == 0) U.red[slot8 + wave] = ws;
+        if (lane == 0 && !handed_over) U.red[slot8 + (kPaired ? wave >> 1 : wave)] = ws;
     };
 
     for (int it = 0; it <= a.n_iter; ++it) {
@@ -1232,7 +1252,7 @@ __device__ __forceinline__ void run_unit(const SweepArgs &a, unsigned char *smem
         __syncthreads();
         if (a.trace && tid == 0) {
             double s = 0.0;
-            for (int w = 0; w < nwaves; ++w) s = s + U.red[(it & 1) * 8 + w];
+            for (int w = 0; w < n_parts; ++w) s = s + U.red[(it & 1) * 8 + w];
             a.trace[slot * (a.n_iter + 1) + it] = s;
         }
         // A pass that moved no row leaves every sum, hence every centroid, as it was: the labels are
@@ -1295,7 +1315,7 @@ __device__ __forceinline__ void run_unit(const SweepArgs &a, unsigned char *smem
             __syncthreads();
         }
         if (tid == 0)
-            for (int w = 0; w < nwaves; ++w) loss = loss + U.red[loss_slot + w];
+            for (int w = 0; w < n_parts; ++w) loss = loss + U.red[loss_slot + w];
     }
     if (a.trace && tid == 0) {
         // the passes that were not run would have seen the same labels and centroids

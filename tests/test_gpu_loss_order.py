@@ -94,3 +94,26 @@ def _chunked_equals_whole(wl, chunk, flags, sfx="", path=None):
 def test_chunked_streaming_sweep(n, d, tasks, chunk):
     wl = workloads.random_task(n + d, n, d, card_hi=18, n_blobs=6, sigma=0.9, ks=(2, 4, 8, 16, 32, 64, 128), n_iter=4, n_tasks=tasks, ragged=True)
     _chunked_equals_whole(wl, chunk, binding.F_STREAMING, path=1)
+
+
+@pytest.mark.parametrize("n_iter", [3, 40])
+@pytest.mark.parametrize("n,d,tasks,ks,chunk", [(500, 12, 40, range(2, 12), 3), (1800, 24, 20, range(8, 41), 5)])
+def test_chunked_resident_sweep(n, d, tasks, ks, chunk, n_iter):
+    # the whole list has units for more than every place of the chip, a chunk of it has not: the rows of a task are split over the
+    # waves in another way.  n_iter = 3: units that have not reached their fixed point.
+    wl = workloads.random_task(n, n, d, card_hi=24, n_blobs=9, sigma=1.2, ks=tuple(ks), n_iter=n_iter, n_tasks=tasks, ragged=True)
+    _chunked_equals_whole(wl, chunk, 0, path=0)
+    wl = workloads.wide_space(n, n_tasks=tasks, n=n, d=d, ks=tuple(ks), n_iter=n_iter, ragged=True)
+    _chunked_equals_whole(wl, chunk, binding.F_VALUES_BELOW_2048, sfx="_u16", path=0)
+
+
+@pytest.mark.parametrize("n,d,ks", [(500, 12, (2, 9, 33)), (2000, 24, tuple(range(2, 42)))])
+def test_resident_loss_does_not_depend_on_the_batch(n, d, ks):
+    # (the largest task of a batch sets the number of waves: tasks of one size)
+    wl = workloads.random_task(n, n, d, card_hi=24, n_blobs=9, sigma=1.2, ks=ks, n_iter=4, n_tasks=100)
+    dw = binding.DeviceWorkload(wl)
+    whole = binding.cham_kmeans_sweep(dw.X, dw.ld, d, wl.task_off, ks, wl.n_iter, want_trace=True)
+    for t in (0, 99):
+        alone = binding.cham_kmeans_sweep(dw.X, dw.ld, d, wl.task_off[t:t + 2], ks, wl.n_iter, want_trace=True)
+        for key in ("inertia", "trace"):
+            np.testing.assert_array_equal(alone[key][0].cpu().numpy(), whole[key][t].cpu().numpy())
