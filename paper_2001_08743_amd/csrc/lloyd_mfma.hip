@@ -5,7 +5,7 @@
 // Screen:  score(c, i) = |mu'_c|^2 - 2 x'_i . mu'_c   (x', mu' centred by an integer offset)
 //   A (32 centroids x K) = [ hi(w) | lo(w) ],  w = fl32(-2 mu'),  hi = f16(w), lo = f16(w - hi)
 //   B (K x 32 rows)      = [ x' ; x' ]        (x' is a small integer: exact in f16)
-//   the last knob slot (unused when d < DK) carries the bias: B = 256, A = hi/lo of |mu'_c|^2 / 256;
+//   the last knob slot (unused when d < DK) carries the bias: B = 256 (16384 for two-byte knobs), A = hi/lo of |mu'_c|^2 / B;
 //   with d = DK = 32 (SEP) the bias is a step of its own at the head of the chain, slots 0 and 1 of
 //   sixteen: one instruction in five more, against twice the row registers and steps of 64-wide rows
 // so every product is exact and only the fp32 accumulation and the 22-bit splits round.
@@ -548,7 +548,8 @@ __device__ __forceinline__ void full_sums(const Queue &Q, int *S, int *n, const 
 // w = -2 (mu - o) (one 8-byte store each).  The DK/4 items of a centroid sit in adjacent lanes and
 // add up |mu - o|^2 among themselves; the last of them owns the bias slot (knob slot DK - 1, or with
 // SEP slots 0 and 1 of the bias step) and stores the sum / 256 there as hi/lo, and its rounded-up value for the error bound.
-// all: fragments from the centroids as they are (no sums yet).  raw: the sums were rebuilt by
+// all: fragments from the centroids as they are (no sums yet); starts from the caller may lie anywhere, so the
+// operands are clamped (a mean of rows is always in range).  raw: the sums were rebuilt by
 // full_sums for every cluster (each still raised by 1024 n): every cluster is updated, and the sums
 // are left either corrected (the next pass applies label changes to them) or, with zero_after,
 // cleared together with the sizes (the next pass rebuilds them).
@@ -557,6 +558,7 @@ __device__ __forceinline__ void update_centroids(const MfmaLds<DK, SEP> &U, int 
                                                  bool raw = false, bool zero_after = false)
 {
     constexpr int NS = DK / 16, NS2 = 2 * NS, QN = DK / 4;
+    constexpr float kBiasScale = bias_scale(BYTE_KNOBS);
     constexpr int LQ = QN == 12 ? 16 : QN;              // lanes per centroid: a power of two for the exchanges
     typedef _Float16 half4 __attribute__((ext_vector_type(4)));
     const int items = k * LQ;
@@ -602,7 +604,8 @@ __device__ __forceinline__ void update_centroids(const MfmaLds<DK, SEP> &U, int 
                 }
                 const double m = j < d ? mu - (double)U.ojf[j] : 0.0;
                 b = __builtin_fma(m, m, b);
-                const float w = (float)(-2.0 * m);
+                float w = (float)(-2.0 * m);
+                if (all) w = __builtin_amdgcn_fmed3f(w, -kHalfMax, kHalfMax);
                 const _Float16 hi = (_Float16)w;
                 hi4[i] = hi;
                 lo4[i] = (_Float16)(w - (float)hi);
@@ -614,7 +617,8 @@ __device__ __forceinline__ void update_centroids(const MfmaLds<DK, SEP> &U, int 
         if (LQ == 16) b = b + dpp_xor_f64<8>(b);
         if (act && (4 * q < d || q == QN - 1)) {
             if (q == QN - 1) {
-                const float bs = (float)b * (1.0f / kBiasScale);
+                float bs = (float)b * (1.0f / kBiasScale);
+                if (all) bs = __builtin_fminf(bs, kHalfMax);
                 const _Float16 bhi = (_Float16)bs;
                 const _Float16 blo = (_Float16)(bs - (float)bhi);
                 if constexpr (SEP) {
@@ -651,6 +655,7 @@ __device__ __forceinline__ void run_unit(const SweepArgs &a, unsigned char *smem
 {
     constexpr bool kByteKnobs = sizeof(XT) == 1;
     constexpr double kMaxValue = kByteKnobs ? 255.0 : 2047.0;
+    constexpr float kBiasScale = bias_scale(kByteKnobs);
     // 64-wide rows leave no registers for a second m-tile, nor do 16 tiles of rows beside the bias step: k <= 32 there
     constexpr bool kAllowTwo = DK <= 32 && !(SEP && NTW > 8);
     const XT *X = reinterpret_cast<const XT *>(a.X);
@@ -737,7 +742,7 @@ __device__ __forceinline__ void run_unit(const SweepArgs &a, unsigned char *smem
     for (int c = k + tid; c < KP; c += blockDim.x) {
         _Float16 *bslot = SEP ? reinterpret_cast<_Float16 *>(U.abias + (c >> 5) * 64 + frag_row(c))
                               : reinterpret_cast<_Float16 *>(U.afrag + ((c >> 5) * NS2 + bstep) * 64 + 32 * bhalf + frag_row(c)) + belem;
-        bslot[0] = (_Float16)kPadBiasHi;
+        bslot[0] = (_Float16)kHalfMax;
     }
     if (tid == 0) {
         U.stamp[0] = 0;           // (unused)
@@ -849,9 +854,11 @@ __device__ __forceinline__ void run_unit(const SweepArgs &a, unsigned char *smem
         // is a mean of rows (inside their convex hull) or stays where it started.
         float m2 = wave_max_nonneg(lane < k ? U.bias[lane] : 0.0f);
         m2 = __builtin_fmaxf(m2, __int_as_float(U.stamp[1])) * 1.000001f;
+        // starts beyond the range of the screen (their operands are clamped): every centroid is a candidate of every row
+        if (!(m2 <= max_screened(kByteKnobs))) m2 = 1.0e30f;
 #pragma unroll
         for (int nt = 0; nt < NTW; ++nt)
-            if (h == 0) Q.eb()[nt * 32 + n32] = mfma_bound<NSA>(x2row[nt], m2);
+            if (h == 0) Q.eb()[nt * 32 + n32] = mfma_bound<NSA, kByteKnobs>(x2row[nt], m2);
     }
     __builtin_amdgcn_wave_barrier();
 

@@ -226,7 +226,7 @@ __global__ __launch_bounds__(32 * (DK / 8)) void stream_update_kernel(const Stre
             st.mu[(size_t)j * kpm + c] = 0.0;
         }
         b = __builtin_fma(m, m, b);
-        const float w = (float)(-2.0 * m);
+        const float w = __builtin_amdgcn_fmed3f((float)(-2.0 * m), -kHalfMax, kHalfMax);
         const _Float16 hi = (_Float16)w;
         hi8[i] = hi;
         lo8[i] = (_Float16)(w - (float)hi);
@@ -241,6 +241,9 @@ __global__ __launch_bounds__(32 * (DK / 8)) void stream_update_kernel(const Stre
     st.afrag[(mt * 4 + NS + fstep) * 64 + 32 * hh + m32] = lo8;
 
     float bmax = c < k ? __double2float_ru(b) * 1.0000005f : 0.0f;
+    // a start (or an empty cluster still there) so far off that an operand may have been clamped: every centroid
+    // is a candidate of every row
+    if (!(bmax <= kHalfMax * kHalfMax / 4.0f)) bmax = 1.0e30f;
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) bmax = __builtin_fmaxf(bmax, __shfl_xor(bmax, off, 64));
     if ((tid & 63) == 0) red[tid >> 6] = bmax;
