@@ -122,13 +122,14 @@ __global__ __launch_bounds__(MAXNT) void resident_sweep_kernel(const SweepArgs a
     const int tile_rows = blockDim.x * R;
     const bool force_exact = (a.flags & 1) != 0;
 
-    if (skipped || (a.init_mode == 0 && a.ndist[t] < k)) {
-        // fewer than k distinct rows, or not needed any more: all outputs zero, status says which
+    if (skipped) return;                          // (its outputs were written when the task was marked)
+    if (a.init_mode == 0 && a.ndist[t] < k) {
+        // fewer than k distinct rows: all outputs zero
         for (int e = tid; e < k * d; e += blockDim.x) a.centroids[crow * d + e] = 0.0;
         for (int c = tid; c < k; c += blockDim.x) a.counts[crow + c] = 0;
         for (int64_t r = r0 + tid; r < r1; r += blockDim.x) labrow[r] = 0;
         if (tid == 0) {
-            a.status[slot] = skipped ? 3 : 1;
+            a.status[slot] = 1;
             a.passes[slot] = 0;
             a.inertia[slot] = 0.0;
         }

@@ -145,13 +145,13 @@ __global__ __launch_bounds__(32 * (DK / 8)) void stream_update_kernel(const Stre
     if (unusable) {
         if (mt != 0) return;
         if (mode == 0 && tid == 0) a.m2[u * kM2Tiles] = -1.0f;
-        if (mode == 2) {
+        if (mode == 2 && !skipped) {           // (the outputs of a skipped unit were written when its task was marked)
             for (int e = tid; e < k * d; e += blockDim.x) a.centroids[crow * d + e] = 0.0;
             for (int c = tid; c < k; c += blockDim.x) a.counts[crow + c] = 0;
             uint8_t *labrow = a.labbuf + (int64_t)ki * a.ld;
             for (int64_t r = r0 + tid; r < r1; r += blockDim.x) labrow[r] = 0;
             if (tid == 0) {
-                a.status[slot] = skipped ? 3 : 1;
+                a.status[slot] = 1;
                 a.passes[slot] = 0;
                 a.inertia[slot] = 0.0;
             }
