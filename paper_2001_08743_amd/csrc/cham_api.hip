@@ -425,6 +425,7 @@ static int32_t sweep_impl(const void *Xv, int xbytes, int64_t ld, int32_t d, con
         if (e != hipSuccess) return hip_fail(e);
     }
     const int step = chunked ? chunk : n_k;
+    int staged_rpw = 0, staged_units = 0;             // what the streaming path's table of workgroups was last made for
     for (int ki_begin = 0; ki_begin < n_k; ki_begin += step) {
         const int ki_end = ki_begin + step < n_k ? ki_begin + step : n_k;
         a.ki_begin = ki_begin;
@@ -434,20 +435,28 @@ static int32_t sweep_impl(const void *Xv, int xbytes, int64_t ld, int32_t d, con
         if (path == SweepPath::kStream) {
             // first workgroup of every unit, in launch order (largest k first)
             const int n_units = (ki_end - ki_begin) * T;        // units of this chunk, largest k first
-            Words wo;
-            if (no_heap) wo.forbid_heap();
-            if (!wo.assign(((size_t)n_units + 2) / 2)) return CHAM_E_NOMEM;
-            int32_t *po = reinterpret_cast<int32_t *>(wo.data());
-            int acc = 0;
             const int rpw = stream_rows_per_wg(pl, task_off, ki_end - ki_begin, inertia_trace != nullptr);
-            for (int u = 0; u < n_units; ++u) {
-                const int t = u % T;
-                po[u] = acc;
-                acc += (int)((task_off[t + 1] - task_off[t] + rpw - 1) / rpw);
+            int per_k = 0;
+            for (int t = 0; t < T; ++t) per_k += (int)((task_off[t + 1] - task_off[t] + rpw - 1) / rpw);
+            const int acc = per_k * (ki_end - ki_begin);
+            // the table depends on the rows per workgroup only; that of a chunk with fewer values of k is its beginning
+            if (rpw != staged_rpw || n_units > staged_units) {
+                Words wo;
+                if (no_heap) wo.forbid_heap();
+                if (!wo.assign(((size_t)n_units + 2) / 2)) return CHAM_E_NOMEM;
+                int32_t *po = reinterpret_cast<int32_t *>(wo.data());
+                int at = 0;
+                for (int u = 0; u < n_units; ++u) {
+                    const int t = u % T;
+                    po[u] = at;
+                    at += (int)((task_off[t + 1] - task_off[t] + rpw - 1) / rpw);
+                }
+                po[n_units] = at;
+                e = stage_words(wo, reinterpret_cast<uint64_t *>(ws + w.wg_off), s);
+                if (e != hipSuccess) return hip_fail(e);
+                staged_rpw = rpw;
+                staged_units = n_units;
             }
-            po[n_units] = acc;
-            e = stage_words(wo, reinterpret_cast<uint64_t *>(ws + w.wg_off), s);
-            if (e != hipSuccess) return hip_fail(e);
             StreamArgs sa;
             sa.X = X;
             sa.ld = ld;
