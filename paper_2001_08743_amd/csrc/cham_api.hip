@@ -185,23 +185,23 @@ int32_t check_common(const void *X, int64_t ld, int32_t d, const int64_t *task_o
 constexpr int kStreamRowsPerWg = 4096;      // rows per workgroup of the streaming assignment, at most
 
 // Rows one workgroup of the streaming assignment walks: 4096, halved (down to the 512 rows that one step
-// of its four waves holds) while the launch has fewer workgroups than the chip has places for them (two
-// per compute unit).  Measured per sampling step, 4096 / 2048 / 1024 / 512 rows: 48 units of 900 to 2500 rows
-// 1064 / 1023 / 801 / 676 us; 42 units of 21 000 to 60 000 rows (385 / 770 / 1540 / 3080 workgroups)
-// 1749 / 1418 / 1476 / 1777 us; 5 units of 2^20 rows (1280 / 2560 workgroups) 2890 / 3052 us.  Not below what
+// of its four waves holds) while the launch has fewer than two workgroups per compute unit.  Measured per
+// sampling step on 256 of them, 4096 / 2048 / 1024 / 512 rows: 48 units of 900 to 2500 rows 1064 / 1023 / 801 / 676 us; 42 units of 21 000 to 60 000 rows (385 / 770 / 1540 / 3080 workgroups)
+// 1749 / 1418 / 1476 / 1777 us; 5 units of 2^20 rows (1280 / 2560 workgroups) 2890 / 3052 us.  Two also where LDS holds
+// one at a time: 111 760 x 18, k = 16..256, 2048 / 1024 rows (275 / 550 workgroups) 1137 / 993 us.  Not below what
 // gives a task 512 workgroups: one unit of 300 000 x 16 with k = 64, 1024 / 512 rows (293 / 586 workgroups) 520 / 789 us
 // (its steps hold 1024 rows).  The order of the loss does not depend on it; below 4096 rows its partials, one
 // per 4096 rows, stand in the unit's sums, which hold 512 of them at least.  A traced sweep has them in every
 // pass and keeps 4096.
-int stream_rows_per_wg(const Plan &pl, const int64_t *task_off, int n_ks, bool traced)
+int stream_rows_per_wg(const Plan &pl, const int64_t *task_off, int n_ks, bool traced, int cus)
 {
-    constexpr int kPlaces = 512, kMinRows = 512, kMaxPerTask = 512;
+    constexpr int kMinRows = 512, kMaxPerTask = 512;
     int rows = kStreamRowsPerWg;
     if (traced) return rows;
     while (rows > kMinRows) {
         int64_t wgs = 0;
         for (int t = 0; t < pl.T; ++t) wgs += (task_off[t + 1] - task_off[t] + rows - 1) / rows;
-        if (wgs * n_ks >= kPlaces || (pl.n_max + rows / 2 - 1) / (rows / 2) > kMaxPerTask) break;
+        if (wgs * n_ks >= 2 * cus || (pl.n_max + rows / 2 - 1) / (rows / 2) > kMaxPerTask) break;
         rows /= 2;
     }
     return rows;
@@ -424,6 +424,12 @@ static int32_t sweep_impl(const void *Xv, int xbytes, int64_t ld, int32_t d, con
                                   reinterpret_cast<int *>(ws + w.ndist), s);
         if (e != hipSuccess) return hip_fail(e);
     }
+    int cus = 0;
+    if (path == SweepPath::kStream) {
+        if (stream_lds_bytes(d, w.kpm) > 160 * 1024) return CHAM_E_BAD_K;
+        e = compute_units(cus);
+        if (e != hipSuccess) return hip_fail(e);
+    }
     const int step = chunked ? chunk : n_k;
     int staged_rpw = 0, staged_units = 0;             // what the streaming path's table of workgroups was last made for
     for (int ki_begin = 0; ki_begin < n_k; ki_begin += step) {
@@ -435,7 +441,7 @@ static int32_t sweep_impl(const void *Xv, int xbytes, int64_t ld, int32_t d, con
         if (path == SweepPath::kStream) {
             // first workgroup of every unit, in launch order (largest k first)
             const int n_units = (ki_end - ki_begin) * T;        // units of this chunk, largest k first
-            const int rpw = stream_rows_per_wg(pl, task_off, ki_end - ki_begin, inertia_trace != nullptr);
+            const int rpw = stream_rows_per_wg(pl, task_off, ki_end - ki_begin, inertia_trace != nullptr, cus);
             int per_k = 0;
             for (int t = 0; t < T; ++t) per_k += (int)((task_off[t + 1] - task_off[t] + rpw - 1) / rpw);
             const int acc = per_k * (ki_end - ki_begin);
@@ -499,7 +505,6 @@ static int32_t sweep_impl(const void *Xv, int xbytes, int64_t ld, int32_t d, con
             sa.m2 = reinterpret_cast<float *>(ws + w.m2);
             sa.loss_part = reinterpret_cast<double *>(ws + w.loss);
             sa.passes = a.passes;
-            if (stream_lds_bytes(d, w.kpm) > 160 * 1024) return CHAM_E_BAD_K;
             e = acc > 0 ? launch_stream_sweep(sa, pl.n_total, acc, s) : hipSuccess;
             if (acc == 0) e = launch_resident_sweep(a, pl.nt, s);   // all tasks empty: trivial path
         } else if (path == SweepPath::kMfmaResident) {

@@ -166,6 +166,7 @@ bool mfma_path_fits_d32(int d, int kmax, int64_t n_max);
 bool mfma_path_fits_u16(int d, int kmax, int64_t n_max);
 hipError_t launch_mfma_sweep(const SweepArgs &a, int64_t n_max, int64_t n_total, hipStream_t s);
 int64_t stream_lds_bytes(int d, int kpm);
+hipError_t compute_units(int &cus);                       // of the current device
 hipError_t launch_stream_sweep(const StreamArgs &a, int64_t n_total, int total_wgs, hipStream_t s);
 // ki_end0: values of k computed so far; a.ki_begin .. a.ki_end: the coming chunk.
 hipError_t launch_knee_update(const SweepArgs &a, int ki_end0, double thr, int *done, hipStream_t s);

@@ -1411,7 +1411,7 @@ __global__ __launch_bounds__(512, two_workgroups(DK, NTW, SEP) ? 4 : 2) void res
 }
 
 template <int DK, int NTW, typename XT, bool SEP = false>
-hipError_t launch_mfma_t(const SweepArgs &a, int nwaves, int64_t n_total, hipStream_t s)
+hipError_t launch_mfma_t(const SweepArgs &a, int nwaves, int64_t n_total, int cus, hipStream_t s)
 {
     const unsigned pb = (unsigned)((n_total + 255) / 256);
     if (pb && a.ki_begin == 0)
@@ -1424,11 +1424,7 @@ hipError_t launch_mfma_t(const SweepArgs &a, int nwaves, int64_t n_total, hipStr
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     // as many workgroups as can be resident at once
-    int dev = 0, cus = 0, per_cu = 0;
-    e = hipGetDevice(&dev);
-    if (e != hipSuccess) return e;
-    e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (e != hipSuccess) return e;
+    int per_cu = 0;
     e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, nwaves * 64, lds);
     if (e != hipSuccess) return e;
     if (per_cu < 1) per_cu = 1;
@@ -1463,6 +1459,13 @@ bool mfma_path_fits_u16(int d, int kmax, int64_t n_max)
     return d >= 1 && d <= 63 && kmax <= 32 && n_max <= 2048;
 }
 
+hipError_t compute_units(int &cus)
+{
+    int dev = 0;
+    const hipError_t e = hipGetDevice(&dev);
+    return e != hipSuccess ? e : hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+}
+
 template <typename XT>
 static hipError_t launch_mfma_sweep_t(const SweepArgs &a, int64_t n_max, int64_t n_total, hipStream_t s)
 {
@@ -1478,31 +1481,34 @@ static hipError_t launch_mfma_sweep_t(const SweepArgs &a, int64_t n_max, int64_t
     //     more than 32 centroids leave LDS for one workgroup per compute unit and there are units for
     //     every place (64 tasks x 2000 rows x 24 knobs: k = 2..48 2037 / 1579 us, but k = 2..32 874 / 1014 us, and
     //     4 tasks with k = 2..40 312 / 335 us)
+    int cus = 0;
+    const hipError_t e = compute_units(cus);
+    if (e != hipSuccess) return e;
     const int64_t units = (int64_t)a.T * (a.ki_end - a.ki_begin);
     int ntw = 16;
-    if (n_max <= 512 && DK == 16 && units <= 256) ntw = 2;
+    if (n_max <= 512 && DK == 16 && units <= cus) ntw = 2;
     else if (n_max <= 1024) ntw = 4;
-    else if (n_max <= 2048 && (DK == 16 || DK >= 48 || sep || (a.kmax > 32 && units > 512))) ntw = 8;
+    else if (n_max <= 2048 && (DK == 16 || DK >= 48 || sep || (a.kmax > 32 && units > 2 * cus))) ntw = 8;
     int nwaves = (int)((n_max + 32 * ntw - 1) / (32 * ntw));
     if (nwaves < 1) nwaves = 1;
     if (nwaves > 8) nwaves = 8;
     if (sep) {
-        if (ntw == 4) return launch_mfma_t<32, 4, uint8_t, true>(a, nwaves, n_total, s);
-        return ntw == 8 ? launch_mfma_t<32, 8, uint8_t, true>(a, nwaves, n_total, s)
-                        : launch_mfma_t<32, 16, uint8_t, true>(a, nwaves, n_total, s);
+        if (ntw == 4) return launch_mfma_t<32, 4, uint8_t, true>(a, nwaves, n_total, cus, s);
+        return ntw == 8 ? launch_mfma_t<32, 8, uint8_t, true>(a, nwaves, n_total, cus, s)
+                        : launch_mfma_t<32, 16, uint8_t, true>(a, nwaves, n_total, cus, s);
     }
     if (DK == 16) {
-        if (ntw == 2) return launch_mfma_t<16, 2, XT>(a, nwaves, n_total, s);
-        if (ntw == 4) return launch_mfma_t<16, 4, XT>(a, nwaves, n_total, s);
-        return ntw == 8 ? launch_mfma_t<16, 8, XT>(a, nwaves, n_total, s) : launch_mfma_t<16, 16, XT>(a, nwaves, n_total, s);
+        if (ntw == 2) return launch_mfma_t<16, 2, XT>(a, nwaves, n_total, cus, s);
+        if (ntw == 4) return launch_mfma_t<16, 4, XT>(a, nwaves, n_total, cus, s);
+        return ntw == 8 ? launch_mfma_t<16, 8, XT>(a, nwaves, n_total, cus, s) : launch_mfma_t<16, 16, XT>(a, nwaves, n_total, cus, s);
     }
     if (DK == 32) {
-        if (ntw == 4) return launch_mfma_t<32, 4, XT>(a, nwaves, n_total, s);
-        return ntw == 8 ? launch_mfma_t<32, 8, XT>(a, nwaves, n_total, s) : launch_mfma_t<32, 16, XT>(a, nwaves, n_total, s);
+        if (ntw == 4) return launch_mfma_t<32, 4, XT>(a, nwaves, n_total, cus, s);
+        return ntw == 8 ? launch_mfma_t<32, 8, XT>(a, nwaves, n_total, cus, s) : launch_mfma_t<32, 16, XT>(a, nwaves, n_total, cus, s);
     }
     if (sizeof(XT) == 1) return hipErrorInvalidValue;        // (byte knobs never come with more than 32 knobs)
-    if (DK == 48) return ntw == 4 ? launch_mfma_t<48, 4, uint16_t>(a, nwaves, n_total, s) : launch_mfma_t<48, 8, uint16_t>(a, nwaves, n_total, s);
-    return ntw == 4 ? launch_mfma_t<64, 4, uint16_t>(a, nwaves, n_total, s) : launch_mfma_t<64, 8, uint16_t>(a, nwaves, n_total, s);
+    if (DK == 48) return ntw == 4 ? launch_mfma_t<48, 4, uint16_t>(a, nwaves, n_total, cus, s) : launch_mfma_t<48, 8, uint16_t>(a, nwaves, n_total, cus, s);
+    return ntw == 4 ? launch_mfma_t<64, 4, uint16_t>(a, nwaves, n_total, cus, s) : launch_mfma_t<64, 8, uint16_t>(a, nwaves, n_total, cus, s);
 }
 
 hipError_t launch_mfma_sweep(const SweepArgs &a, int64_t n_max, int64_t n_total, hipStream_t s)
