@@ -107,6 +107,19 @@ def test_chunked_resident_sweep(n, d, tasks, ks, chunk, n_iter):
     _chunked_equals_whole(wl, chunk, binding.F_VALUES_BELOW_2048, sfx="_u16", path=0)
 
 
+@pytest.mark.parametrize("n,d,flags,path", [(1000, 32, 0, 0), (2000, 32, 0, 0), (2000, 32, binding.F_NO_MFMA, 2)])
+def test_chunked_sweep_of_all_byte_knobs(n, d, flags, path):
+    wl = workloads.random_task(n, n, d, card_hi=24, n_blobs=9, sigma=1.2, ks=tuple(range(2, 34, 3)), n_iter=3, n_tasks=30, ragged=True)
+    _chunked_equals_whole(wl, 2, flags, path=path)
+
+
+@pytest.mark.parametrize("n,d", [(900, 40), (2048, 47), (1500, 60)])
+def test_chunked_sweep_of_two_byte_knobs(n, d):
+    # rows of 48 and of 64 slots
+    wl = workloads.wide_space(n, n_tasks=20, n=n, d=d, ks=tuple(range(2, 32)), n_iter=3, ragged=True)
+    _chunked_equals_whole(wl, 4, binding.F_VALUES_BELOW_2048, sfx="_u16", path=0)
+
+
 @pytest.mark.parametrize("n,d,ks", [(500, 12, (2, 9, 33)), (2000, 24, tuple(range(2, 42)))])
 def test_resident_loss_does_not_depend_on_the_batch(n, d, ks):
     # (the largest task of a batch sets the number of waves: tasks of one size)
