@@ -1340,13 +1340,13 @@ __device__ __forceinline__ void run_unit(const SweepArgs &a, unsigned char *smem
     }
 }
 
-// Persistent workgroups (one per compute unit) take units from a counter until none is left: the
+// Persistent workgroups (one or two per compute unit) take units from a counter until none is left: the
 // next unit starts as soon as the last one ends, without a new dispatch of a workgroup of this size.
 // Units are handed out in descending-k order so that the longest ones start first.
-// Few tiles per wave leave registers to spare: held to 128 of them (at the price of some spills outside the
-// tile loop), two workgroups share a compute unit, and one's barriers and dependent LDS accesses run
+// Few tiles per wave leave registers to spare: held to 128 of them, two workgroups share a compute unit, and one's barriers and dependent LDS accesses run
 // under the other's tiles.  64 tasks x 1024 rows x 12 knobs, k = 2..32: 632 -> 452 us a step; 64 tasks x
-// 1000 rows x 24 knobs: 650 -> 532 us.
+// 1000 rows x 24 knobs: 650 -> 532 us.  The price is scratch memory, in the tile loop too: with eight tiles of 16-wide
+// rows four of the row fragments are fetched from there in every pass, with four of 32-wide ones some single words.
 constexpr bool two_workgroups(int DK, int NTW, bool SEP)
 {
     return (DK == 16 && NTW <= 8) || (DK == 32 && NTW <= 4 && !SEP);
