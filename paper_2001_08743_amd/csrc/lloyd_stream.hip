@@ -809,6 +809,8 @@ __global__ __launch_bounds__(kWavesPerWg * 64, 2) void stream_assign_kernel(cons
 // the lanes, the waves and, in the update kernel, the blocks of kLossRows.  Bound by the latency of the
 // centroids' gathers, hence from LDS: a step of 171 256 x 14, k = 64 and 128 (84 workgroups), takes 529 us, 545 us
 // with gathers from memory and 536 us with the loss inside the assignment, where it cost registers.
+// Not unrolled over all knobs: the addresses of 32 loads in scalar registers cost more than their overlap gains
+// (pools of 21 000 to 60 000 x 23 1356 / 1343 us a step); 512 or 256 threads and more rows under way are slower.
 template <int DK>
 __global__ __launch_bounds__(1024) void stream_loss_kernel(const StreamArgs a)
 {
@@ -833,21 +835,17 @@ __global__ __launch_bounds__(1024) void stream_loss_kernel(const StreamArgs a)
     __syncthreads();
     for (int r = tid; r < n; r += blockDim.x) {
         const int c = lab[r];
-        // all loads of the row first (they are independent), then the sum in knob order
-        double mu[DK];
-        uint8_t xv[DK];
-#pragma unroll
-        for (int j = 0; j < DK; ++j) {
-            const int jj = j < d ? j : 0;
-            xv[j] = a.X[(int64_t)jj * a.ld + r0 + r];
-            mu[j] = mu_sh[jj * kpm + c];
-        }
         double s = 0.0;
+        for (int j0 = 0; j0 < d; j0 += 8) {                        // eight knob values under way at a time
+            uint8_t xv[8];
 #pragma unroll
-        for (int j = 0; j < DK; ++j) {
-            if (j < d) {
-                const double tq = (double)xv[j] - mu[j];
-                s = s + tq * tq;
+            for (int i = 0; i < 8; ++i) xv[i] = a.X[(int64_t)(j0 + i < d ? j0 + i : 0) * a.ld + r0 + r];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                if (j0 + i < d) {
+                    const double tq = (double)xv[i] - mu_sh[(j0 + i) * kpm + c];
+                    s = s + tq * tq;
+                }
             }
         }
         term[r] = s;
