@@ -238,15 +238,17 @@ SweepPath choose_path(const Plan &pl, int d, int flags, int xbytes = 1)
 }
 
 struct SweepWs {
-    int64_t blob = 0, init_rows = 0, ndist = 0, passes = 0, counters = 0, xh = 0, labbuf = 0, total = 0;
+    int64_t blob = 0, init_rows = 0, ndist = 0, passes = 0, counters = 0, xh = 0, task_ojf = 0, norms = 0, labbuf = 0, total = 0;
+    int64_t fetched = 0;           // of the total: what the matrix-core kernel that fetches its rows needs beside them
     // streaming path
     int64_t x2 = 0, ojf = 0, Sg = 0, ng = 0, mu = 0, afrag = 0, biasf = 0, m2 = 0, wg_off = 0, loss = 0;
     int kpm = 0, n_units = 0, total_wgs = 0;
 };
 
-// xh_halfs: f16 values per row of the packed copy of the rows (0: the path needs none).
+// xh_halfs: f16 values per row of the packed copy of the rows (0: the path needs none).  fetched: the matrix-core kernel that
+// fetches its rows in every pass runs (or, two-byte knobs, would run if the caller promised values below 2048).
 SweepWs sweep_ws(const Plan &pl, int64_t ld, bool own_labels, bool stream, const int64_t *task_off,
-                 int xh_halfs = 32)
+                 int xh_halfs, bool fetched, int tile_halfs)
 {
     SweepWs w;
     int64_t o = 0;
@@ -258,10 +260,21 @@ SweepWs sweep_ws(const Plan &pl, int64_t ld, bool own_labels, bool stream, const
     o += up((int64_t)pl.T * 4);
     w.passes = o;
     o += up((int64_t)pl.T * pl.n_k * 4);
-    w.counters = o;                                   // one work counter per launch of a chunked sweep
-    o += up(((int64_t)pl.n_k + 1) * 4);               // (+ the flag of a two-byte value too large for the f16 rows)
+    w.counters = o;                                   // work counters, kUnitQueues per launch of a chunked sweep
+    o += up(((int64_t)pl.n_k * kUnitQueues + 1) * 4); // (+ the flag of a two-byte value too large for the f16 rows)
     w.xh = o;
     o += up(ld * xh_halfs * 2);
+    if (fetched) {
+        // packed in tiles of 32 rows every task may need one more than its rows fill; behind them the offsets and norms of the
+        // tasks' centred rows, and room to read on for (four tiles of 2 KiB, or two of 4 KiB, are fetched ahead)
+        const int64_t rows_end = o;
+        o += up((int64_t)(pl.T + 1) * 32 * tile_halfs * 2);
+        w.task_ojf = o;
+        o += up((int64_t)pl.T * 64 * 4);
+        w.norms = o;
+        o += up((int64_t)pl.T * 32 * 4) + 16 * 1024;
+        w.fetched = o - rows_end;
+    }
     w.labbuf = o;
     if (own_labels) o += up((int64_t)pl.n_k * ld);
     if (stream) {
@@ -320,19 +333,30 @@ const char *cham_strerror(int32_t code)
 // Two-byte knobs always run the vector resident kernel; its LDS need bounds k * padded knob count.
 static bool u16_fits(const Plan &pl) { return resident_lds_bytes(pl.DP, pl.kmax, 8) <= 160 * 1024; }
 
+static int xh_halfs_of(SweepPath path, int xbytes, int d)
+{
+    return xbytes == 1 ? 32 : (path == SweepPath::kMfmaResident ? (d <= 31 ? 32 : 64) : 0);
+}
+
+// Two-byte knobs: whatever the promise, which adds the packed rows alone to the workspace.
+static bool fetched_rows(const Plan &pl, SweepPath path, int xbytes, int d)
+{
+    return (xbytes == 2 ? mfma_path_fits_u16(d, pl.kmax, pl.n_max) : path == SweepPath::kMfmaResident) && mfma_fetches_rows(d, pl.n_max);
+}
+
+// fetched: set to what of it SweepWs::fetched names.
 static int64_t sweep_ws_bytes(int xbytes, int64_t ld, int32_t d, const int64_t *task_off, int32_t T,
-                              const int32_t *ks, int32_t n_k, int32_t flags, bool no_heap = false)
+                              const int32_t *ks, int32_t n_k, int32_t flags, bool no_heap = false, int64_t *fetched = nullptr)
 {
     Plan pl;
     if (no_heap) pl.blob.forbid_heap();
     const int32_t rc = check_common(nullptr, ld, d, task_off, T, ks, n_k, false, pl, xbytes);
     if (rc != CHAM_OK) return rc;
-    if (xbytes == 2) {
-        if (choose_path(pl, d, flags, 2) == SweepPath::kMfmaResident)
-            return sweep_ws(pl, ld, true, false, task_off, d <= 31 ? 32 : 64).total;
-        return u16_fits(pl) ? sweep_ws(pl, ld, true, false, task_off, 0).total : CHAM_E_BAD_K;
-    }
-    return sweep_ws(pl, ld, true, choose_path(pl, d, flags) == SweepPath::kStream, task_off).total;
+    const SweepPath path = choose_path(pl, d, flags, xbytes);
+    if (xbytes == 2 && path == SweepPath::kVectorResident && !u16_fits(pl)) return CHAM_E_BAD_K;
+    const SweepWs w = sweep_ws(pl, ld, true, path == SweepPath::kStream, task_off, xh_halfs_of(path, xbytes, d), fetched_rows(pl, path, xbytes, d), d <= 32 ? 32 : 64);
+    if (fetched) *fetched = w.fetched;
+    return w.total;
 }
 
 int64_t cham_sweep_workspace_bytes(int64_t ld, int32_t d, const int64_t *task_off, int32_t T,
@@ -371,8 +395,7 @@ static int32_t sweep_impl(const void *Xv, int xbytes, int64_t ld, int32_t d, con
     if (xbytes == 2 && (flags & CHAM_F_STREAMING)) return CHAM_E_BAD_FLAG;
     const SweepPath path = choose_path(pl, d, flags, xbytes);
     if (xbytes == 2 && path == SweepPath::kVectorResident && !u16_fits(pl)) return CHAM_E_BAD_K;
-    const int xh_halfs = xbytes == 1 ? 32 : (path == SweepPath::kMfmaResident ? (d <= 31 ? 32 : 64) : 0);
-    const SweepWs w = sweep_ws(pl, ld, labels == nullptr, path == SweepPath::kStream, task_off, xh_halfs);
+    const SweepWs w = sweep_ws(pl, ld, labels == nullptr, path == SweepPath::kStream, task_off, xh_halfs_of(path, xbytes, d), fetched_rows(pl, path, xbytes, d), d <= 32 ? 32 : 64);
     const bool chunked = chunk > 0;
     const int64_t done_bytes = chunked ? up((int64_t)T * 4) : 0;
     if (!workspace || workspace_bytes < w.total + done_bytes) return CHAM_E_WORKSPACE;
@@ -385,7 +408,7 @@ static int32_t sweep_impl(const void *Xv, int xbytes, int64_t ld, int32_t d, con
     // through one); the marks of tasks whose sweep has stopped.
     int *done = chunked ? reinterpret_cast<int *>(ws + w.total) : nullptr;
     const Fill fills[3] = {{reinterpret_cast<int *>(ws + w.passes), (int64_t)T * n_k, n_iter + 1},
-                           {reinterpret_cast<int *>(ws + w.counters), n_k + 1, 0},
+                           {reinterpret_cast<int *>(ws + w.counters), (int64_t)n_k * kUnitQueues + 1, 0},
                            {done, chunked ? T : 0, 0}};
     hipError_t e = stage_words(pl.blob, reinterpret_cast<uint64_t *>(ws + w.blob), s, fills, 3);
     if (e != hipSuccess) return hip_fail(e);
@@ -415,9 +438,13 @@ static int32_t sweep_impl(const void *Xv, int xbytes, int64_t ld, int32_t d, con
     a.labbuf = labels ? labels : ws + w.labbuf;
     a.trace = inertia_trace;
     a.xh = reinterpret_cast<uint16_t *>(ws + w.xh);
+    a.ojf = reinterpret_cast<float *>(ws + w.task_ojf);
+    a.norms = reinterpret_cast<int *>(ws + w.norms);
     a.passes = reinterpret_cast<int *>(ws + w.passes);
     a.queue_lds_off = 0;
-    a.too_large = (xbytes == 2 && path == SweepPath::kMfmaResident) ? reinterpret_cast<int *>(ws + w.counters) + n_k : nullptr;
+    a.too_large = (xbytes == 2 && path == SweepPath::kMfmaResident) ? reinterpret_cast<int *>(ws + w.counters) + (int64_t)n_k * kUnitQueues : nullptr;
+    a.n_queues = 1;
+    a.queue_group = T;
     a.ki_begin = 0;
     a.ki_end = n_k;
     a.done = nullptr;
@@ -438,7 +465,7 @@ static int32_t sweep_impl(const void *Xv, int xbytes, int64_t ld, int32_t d, con
         const int ki_end = ki_begin + step < n_k ? ki_begin + step : n_k;
         a.ki_begin = ki_begin;
         a.ki_end = ki_end;
-        a.unit_counter = reinterpret_cast<int *>(ws + w.counters) + ki_begin;
+        a.unit_counter = reinterpret_cast<int *>(ws + w.counters) + (int64_t)ki_begin * kUnitQueues;
         a.done = ki_begin > 0 ? done : nullptr;
         if (path == SweepPath::kStream) {
             // first workgroup of every unit, in launch order (largest k first)
@@ -543,7 +570,9 @@ int32_t cham_kmeans_sweep(const uint8_t *X, int64_t ld, int32_t d, const int64_t
 // one array per GPU, inside the loaded code object, kept until the process ends.  The name below
 // is only a host-side handle of the symbol; the array's device address is looked up once per
 // device and every use in host code goes through that address.
-constexpr int64_t kStaticScratchBytes = (int64_t)CHAM_STATIC_SCRATCH_BYTES;
+// CHAM_STATIC_SCRATCH_BYTES bounds what the paths need without SweepWs::fetched; that part (byte knobs, fewer than 1024 tasks: 2.5 KiB
+// each and 16 KiB) has the place behind it.
+constexpr int64_t kStaticScratchBytes = (int64_t)CHAM_STATIC_SCRATCH_BYTES + 3 * 1024 * 1024;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 constexpr int kMaxDevices = 64;
 static void *g_scratch_addr[kMaxDevices];       // device address of `scratch` on each GPU, null until looked up
@@ -578,11 +607,12 @@ int32_t cham_kmeans_sweep_static(const uint8_t *X, int64_t ld, int32_t d, const 
                                  int32_t flags, void *stream)
 {
     // argument errors come out of the size query exactly as they would out of the sweep
-    const int64_t need = sweep_ws_bytes(1, ld, d, task_off, T, ks, n_k, flags, true);
+    int64_t fetched = 0;
+    const int64_t need = sweep_ws_bytes(1, ld, d, task_off, T, ks, n_k, flags, true, &fetched);
     if (need == CHAM_E_NOMEM) return CHAM_E_TOO_LARGE;      // tables beyond the part kept on the stack
     if (need < 0) return (int32_t)need;
     if (flags & ~kSweepFlags) return CHAM_E_BAD_FLAG;
-    if (need > kStaticScratchBytes) return CHAM_E_TOO_LARGE;
+    if (need - fetched > (int64_t)CHAM_STATIC_SCRATCH_BYTES || need > kStaticScratchBytes) return CHAM_E_TOO_LARGE;
     void *ws = nullptr;
     int32_t rc = static_scratch_address(&ws);
     if (rc != CHAM_OK) return rc;
@@ -648,7 +678,7 @@ int32_t cham_sweep_passes(const void *workspace, int64_t workspace_bytes, int64_
     if (rc != CHAM_OK) return rc;
     if (!passes) return CHAM_E_NULL;
     // the region sits before every part of the workspace whose size depends on the path or the knob width
-    const SweepWs w = sweep_ws(pl, ld, false, false, task_off, 0);
+    const SweepWs w = sweep_ws(pl, ld, false, false, task_off, 0, false, 0);
     if (!workspace || workspace_bytes < w.passes + (int64_t)T * n_k * 4) return CHAM_E_WORKSPACE;
     (void)flags;
     hipError_t e = hipMemcpyAsync(passes, static_cast<const unsigned char *>(workspace) + w.passes,

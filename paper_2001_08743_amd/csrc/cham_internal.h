@@ -5,6 +5,8 @@
 
 namespace cham {
 
+constexpr int kUnitQueues = 8;         // one per XCD
+
 // Arguments of the sweep kernels.  Pointers are device pointers.
 struct SweepArgs {
     const uint8_t *X;              // knob values, [d][ld] items of xbytes bytes each
@@ -34,7 +36,11 @@ struct SweepArgs {
     int *passes;                   // [T][n_k] labelling passes actually run (preset to n_iter + 1 by the host code)
     int *too_large;                // matrix-core kernels, two-byte knobs: set by the packing kernel when a value is 2048 or more (null: byte knobs)
     int queue_lds_off;             // vector kernel: LDS offset of the per-wave queues of moved rows, 0 = no room for them
-    int *unit_counter;             // zeroed before the launch: next unit to hand out (matrix-core resident kernel)
+    float *ojf;                    // [T][64] centring offsets of the rows in xh (matrix-core kernel that fetches its rows in every pass)
+    int *norms;                    // [T][32] per 256 rows of a task: [0..15] float bits of the largest squared norm of a centred row, [16..31] sum of the raw squared norms
+    int *unit_counter;             // [kUnitQueues] zeroed before the launch: next unit of every queue (matrix-core resident kernel)
+    int n_queues;                  // 1, or kUnitQueues: task t belongs to queue t % n_queues
+    int queue_group;               // tasks of a queue whose units are handed out together, largest k first
     int ki_begin, ki_end;          // this launch runs ks[ki_begin .. ki_end) (the whole list by default)
     const int *done;               // [T] or null: tasks whose sweep has already stopped; their units are skipped (status 3)
 };
@@ -164,6 +170,8 @@ int resident_dp16(int d);      // padded knob count the two-byte kernels use for
 bool mfma_path_fits(int d, int kmax, int64_t n_max);
 bool mfma_path_fits_d32(int d, int kmax, int64_t n_max);
 bool mfma_path_fits_u16(int d, int kmax, int64_t n_max);
+// Whether that kernel fetches its rows in every pass (from tiles of packed rows, with tables per task) or keeps them in registers.
+bool mfma_fetches_rows(int d, int64_t n_max);
 hipError_t launch_mfma_sweep(const SweepArgs &a, int64_t n_max, int64_t n_total, hipStream_t s);
 int64_t stream_lds_bytes(int d, int kpm);
 hipError_t compute_units(int &cus);                       // of the current device

@@ -99,16 +99,16 @@ __device__ __forceinline__ int frag_row(int c)
 // 32-wide rows and 64 centroids share a compute unit (32 tasks x 1000 rows x 24 knobs, k = 2..48: 551 -> 458 us).
 __host__ __device__ constexpr int rec_cap(int DK, int ntw) { return DK == 32 && ntw <= 4 ? 40 : kRecCap; }
 
-// Variants that launch_mfma_sweep_t prefers to the one with twice the tiles per wave by the number of units alone: they
-// sum the loss in its order.
-constexpr bool paired_loss(int DK, int ntw, bool SEP) { return (DK == 16 && ntw == 2) || (DK == 32 && ntw == 8 && !SEP); }
+// The variant that launch_mfma_sweep_t prefers to the one with twice the tiles per wave by the number of units alone: it
+// sums the loss in its order.
+constexpr bool paired_loss(int DK, int ntw) { return DK == 16 && ntw == 2; }
 
 // LDS carve-up.  DK = padded knob count (16, 32, 48 or 64), KP = padded centroid count (32 or 64); SEP: the
 // bias has fragments of its own.
 template <int DK, bool SEP = false>
 struct MfmaLds {
     double *mu64T;      // [DK][KP]   exact centroids, transposed
-    double *red;        // [16]       per-wave partial sums of the loss
+    double *red;        // [32]       partial sums of the loss
     float *bias;        // [KP]       upper bound of |mu - o|^2 per centroid (0 for padding rows)
     half8 *afrag;       // [KP/32][2*DK/16][64]  A fragments: hi parts then lo parts
     half8 *abias;       // [KP/32][64] A fragments of the bias step (SEP only; directly behind afrag)
@@ -123,20 +123,21 @@ struct MfmaLds {
     {
         return ((size_t)rec_cap(DK, ntw) * (DK * 2 + 8 + 2) + 4 * 32 * 8 + (size_t)ntw * 32 * 6 + (size_t)ntw * 64 * 4 + 15) / 16 * 16;
     }
-    __host__ __device__ static size_t bytes(int KP, int nwaves, int ntw)
+    // without the per-wave regions
+    __host__ __device__ static size_t base_bytes(int KP)
     {
-        size_t b = sizeof(double) * DK * KP + sizeof(double) * 16 + sizeof(float) * KP;
+        size_t b = sizeof(double) * DK * KP + sizeof(double) * 32 + sizeof(float) * KP;
         b += 16 * (size_t)(KP / 32) * (2 * DK / 16 + (SEP ? 1 : 0)) * 64;
         b += sizeof(int) * (size_t)KP * (DK + 1) + sizeof(int) * KP * 2 + sizeof(float) * DK + 32;
-        b = (b + 15) & ~(size_t)15;
-        return b + wave_bytes(ntw) * nwaves;
+        return (b + 15) & ~(size_t)15;
     }
+    __host__ __device__ static size_t bytes(int KP, int nwaves, int ntw) { return base_bytes(KP) + wave_bytes(ntw) * nwaves; }
     __device__ MfmaLds(unsigned char *base, int KP)
     {
         // plain offset arithmetic from the LDS base keeps every pointer provably in LDS
         size_t o = 0;
         mu64T = reinterpret_cast<double *>(base + o);  o += sizeof(double) * DK * KP;
-        red = reinterpret_cast<double *>(base + o);    o += sizeof(double) * 16;
+        red = reinterpret_cast<double *>(base + o);    o += sizeof(double) * 32;
         bias = reinterpret_cast<float *>(base + o);    o += sizeof(float) * KP;
         afrag = reinterpret_cast<half8 *>(base + o);   o += 16 * (size_t)(KP / 32) * (2 * DK / 16) * 64;
         abias = reinterpret_cast<half8 *>(base + o);   o += SEP ? 16 * (size_t)(KP / 32) * 64 : 0;
@@ -175,6 +176,8 @@ struct WaveQueue {
     __device__ double *few() const { return reinterpret_cast<double *>(base + kOffFew); }                 // [4][32] squares of one (row, centroid)
     __device__ unsigned char *lab() const { return base + kOffLab; }                                      // [kRows] current labels (0xFF: none)
     __device__ unsigned char *lab_new() const { return base + kOffNew; }                                  // [kRows] labels of the pass under way
+    static __device__ __forceinline__ unsigned stored(unsigned c) { return c; }                           // centroid -> entry of the label tables
+    static __device__ __forceinline__ unsigned centroid(unsigned v) { return v; }
     __device__ float *eb() const { return reinterpret_cast<float *>(base + kOffEb); }                     // [kRows] screen bound of the row
     __device__ unsigned *seen() const { return reinterpret_cast<unsigned *>(base + kOffSeen); }           // [tiles][64] mask at the last decision
 };
@@ -263,7 +266,7 @@ __device__ __forceinline__ void resolve_rows(const Queue &Q, int nrec, const dou
                 bc = oc;
             }
         }
-        if (have && q == 0) Q.lab_new()[pid] = (unsigned char)(bc < k ? bc : 0);
+        if (have && q == 0) Q.lab_new()[pid] = (unsigned char)Queue::stored(bc < k ? bc : 0);
     }
     __builtin_amdgcn_wave_barrier();
 }
@@ -344,7 +347,7 @@ __device__ __forceinline__ void resolve_few(const Queue &Q, int nrec, const doub
             bs = os;
             bc = oc;
         }
-        if (have && (lane & 31) == 0) Q.lab_new()[pid] = (unsigned char)(bc < k ? bc : 0);
+        if (have && (lane & 31) == 0) Q.lab_new()[pid] = (unsigned char)Queue::stored(bc < k ? bc : 0);
     }
     __builtin_amdgcn_wave_barrier();
 }
@@ -435,91 +438,76 @@ __device__ __forceinline__ void apply_changes(const Queue &Q, int cnt, int *S, i
 }
 
 // Sums and sizes of every cluster over this wave's rows, from the current labels, on the matrix
-// cores: S^T (knob x centroid) = X^T (knob x row) * onehot (row x centroid), sixteen rows per
-// instruction.  Lane (m, kh) of the A fragment holds knob m of eight consecutive rows, read straight
-// from the knob-major byte matrix (32 consecutive rows = 32 bytes per lane and group of 64 rows; the
-// same row order is used for the labels, so any order would do).  A byte b becomes the f16 value
-// 1024 + b by byte placement alone (0x6400 | b); the knob rows therefore sum to S + 1024 n, and the
-// rows of absent knobs (all bytes zero) to 1024 n, of which row 31 serves as the cluster size.  The
-// one-hot operand is clamp(1025 - (1024 + (label ^ centroid)), 0, 1).  Every product and partial sum
-// is an integer below 2^24, so the fp32 accumulation is exact.  The results are added to the sums
-// of the workgroup (still raised by 1024 n: the centroid update takes that off) and to the sizes.
-// Needs 16-byte aligned rows (xw, ld) and reads whole groups of 64 rows: the caller makes sure
-// that the last group of the task still lies inside the matrix (rows of other tasks or padding
-// read there meet the label 0xFF, which matches no centroid).  NG = groups of 64 rows a wave owns
-// at most; the loads of four groups are under way at any time.  SEP: every knob row is in use, so the
+// cores: S^T (knob x centroid) = X^T (knob x row) * onehot (row x centroid), 32 rows per instruction, all in bytes.
+// Lane (m, kh) of the A fragment holds knob m of sixteen consecutive rows, read straight
+// from the knob-major byte matrix (64 consecutive rows = 64 bytes per lane and group of 128 rows, so that a wave uses up the
+// lines it touches; the same row order is used for the labels, so any order would do).  A knob enters as the signed byte
+// x - 128 (x ^ 0x80), a row of the cluster as -128, any other as 0: with t = label ^ centroid (below 128), bit 7 of
+// t + 127 is clear where t is zero.  The sums come out as -128 (S - 128 n), |.| <= 2^26, and the knob rows of absent
+// knobs (all bytes zero) as 2^14 n, of which row 31 serves as the cluster size.  They are added to the sums
+// of the workgroup lowered by 128 n (kRawOffset: the centroid update takes that off) and to the sizes.  In bytes a
+// step of 32 rows takes 20 (k > 32: 32) vector instructions; in f16 (bytes widened by placement, one-hot by a clamped
+// difference) it was 44 (80), and the rebuild 30 000 cycles of the two workgroups of a compute unit for k = 1.
+// Needs 16-byte aligned rows (xw, ld) and reads whole runs of 64 rows: the caller makes sure
+// that the last run of the task still lies inside the matrix (rows of other tasks or padding
+// read there meet the label 0xFF, which matches no centroid).  NG = runs of 64 rows a wave owns
+// at most; the loads of 256 rows are under way at any time.  SEP: every knob row is in use, so the
 // sizes are counted from the labels.
+constexpr int kRawOffset = -128;
 template <int DK, int NG, bool SEP, typename Queue>
 __device__ __forceinline__ void full_sums(const Queue &Q, int *S, int *n, const uint8_t *xw, int64_t ld,
                                           int d, int k, int rows_here, int lane)
 {
-    typedef unsigned uint4v __attribute__((ext_vector_type(4)));
-    typedef _Float16 half2v __attribute__((ext_vector_type(2)));
-    constexpr int kDepth = NG < 4 ? NG : 4;
+    typedef int int4v __attribute__((ext_vector_type(4)));
+    typedef int int16v __attribute__((ext_vector_type(16)));
+    constexpr int W = NG % 2 == 0 ? 2 : 1;                  // a lane's 32-row pieces per group of 64 * W rows
+    constexpr int kGroups = NG / W;
+    constexpr int kDepth = kGroups < 4 / W ? kGroups : 4 / W;
     const int m32 = lane & 31, kh = lane >> 5;
     const bool two = k > 32;
     const bool knob = m32 < d;
-    const uint8_t *xp = xw + (int64_t)(knob ? m32 : 0) * ld + 32 * kh;
-    const unsigned char *lp = Q.lab() + 32 * kh;
-    const unsigned c4a = (unsigned)m32 * 0x01010101u, c4b = c4a + 0x20202020u;
-    const float16v zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    float16v acc0 = zero16, acc1 = zero16;
-    const int ngroups = (rows_here + 63) >> 6;
+    const uint8_t *xp = xw + (int64_t)(knob ? m32 : 0) * ld + 32 * W * kh;
+    const unsigned char *lp = Q.lab() + 32 * W * kh;
+    const int c4a = (int)(Queue::stored(m32) * 0x01010101u), c4b = (int)(Queue::stored(m32 + 32) * 0x01010101u);
+    int16v acc0, acc1;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        acc0[i] = 0;
+        acc1[i] = 0;
+    }
+    const int runs = (rows_here + 63) >> 6;
 
-    // this lane's 32 bytes of group g (zero where the knob or the group does not exist)
-    auto fetch = [&](int g, uint4v &w0, uint4v &w1) {
-        w0 = uint4v{0u, 0u, 0u, 0u};
-        w1 = w0;
-        if (knob && g < ngroups) {
-            w0 = *reinterpret_cast<const uint4v *>(xp + 64 * g);
-            w1 = *reinterpret_cast<const uint4v *>(xp + 64 * g + 16);
+    // this lane's bytes of group g (zero where the knob or the run of 64 rows does not exist)
+    auto fetch = [&](int g, int4v (&w)[2 * W]) {
+#pragma unroll
+        for (int i = 0; i < 2 * W; ++i) w[i] = int4v{0, 0, 0, 0};
+        if (knob && W * g + (W == 2 ? kh : 0) < runs) {
+#pragma unroll
+            for (int i = 0; i < 2 * W; ++i) w[i] = *reinterpret_cast<const int4v *>(xp + 64 * W * g + 16 * i);
         }
     };
-    // eight bytes -> eight f16 values 1024 + byte
-    auto widen = [](unsigned lo4, unsigned hi4) {
-        uint4v r;
-        r[0] = __builtin_amdgcn_perm(0x64646464u, lo4, 0x04010400u);
-        r[1] = __builtin_amdgcn_perm(0x64646464u, lo4, 0x04030402u);
-        r[2] = __builtin_amdgcn_perm(0x64646464u, hi4, 0x04010400u);
-        r[3] = __builtin_amdgcn_perm(0x64646464u, hi4, 0x04030402u);
-        return r;
-    };
-    // eight (label ^ centroid) bytes -> eight f16 values: 1 where the byte is zero, else 0
-    auto onehot = [&](unsigned lo4, unsigned hi4) {
-        const uint4v r = widen(lo4, hi4);
-        uint4v o;
+    // labels -> -128 for the rows of the centroid, 0 for others
+    auto members = [](const int4v &l, int c4) {
+        int4v o;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const unsigned re = r[e];           // (a scalar copy: a bit cast of the vector element itself reads element 0)
-            half2v v = __builtin_bit_cast(half2v, re);
-            v = half2v{(_Float16)1025.0f, (_Float16)1025.0f} - v;
-            v = __builtin_elementwise_min(__builtin_elementwise_max(v, half2v{(_Float16)0.0f, (_Float16)0.0f}),
-                                          half2v{(_Float16)1.0f, (_Float16)1.0f});
-            o[e] = __builtin_bit_cast(unsigned, v);
-        }
-        return __builtin_bit_cast(half8, o);
+        for (int e = 0; e < 4; ++e) o[e] = ~((l[e] ^ c4) + 0x7F7F7F7F) & (int)0x80808080;
+        return o;
     };
 
-    uint4v w0[kDepth], w1[kDepth];
+    int4v w[kDepth][2 * W];
 #pragma unroll
-    for (int g = 0; g < kDepth; ++g) fetch(g, w0[g], w1[g]);
+    for (int g = 0; g < kDepth; ++g) fetch(g, w[g]);
 #pragma unroll
-    for (int g = 0; g < NG; ++g) {
-        if (g < ngroups) {
-            const uint4v c0 = w0[g % kDepth], c1 = w1[g % kDepth];
-            const uint4v l0 = *reinterpret_cast<const uint4v *>(lp + 64 * g);
-            const uint4v l1 = *reinterpret_cast<const uint4v *>(lp + 64 * g + 16);
+    for (int g = 0; g < kGroups; ++g) {
+        if (W * g < runs) {
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const unsigned xa = t < 2 ? c0[(2 * t) & 3] : c1[(2 * t) & 3];
-                const unsigned xb = t < 2 ? c0[(2 * t + 1) & 3] : c1[(2 * t + 1) & 3];
-                const unsigned la = t < 2 ? l0[(2 * t) & 3] : l1[(2 * t) & 3];
-                const unsigned lb = t < 2 ? l0[(2 * t + 1) & 3] : l1[(2 * t + 1) & 3];
-                const half8 A = __builtin_bit_cast(half8, widen(xa, xb));
-                acc0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(A, onehot(la ^ c4a, lb ^ c4a), acc0, 0, 0, 0);
-                if (two) acc1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(A, onehot(la ^ c4b, lb ^ c4b), acc1, 0, 0, 0);
+            for (int i = 0; i < 2 * W; ++i) {
+                const int4v A = w[g % kDepth][i] ^ (int)0x80808080;
+                const int4v l = *reinterpret_cast<const int4v *>(lp + 64 * W * g + 16 * i) & 0x7F7F7F7F;
+                acc0 = __builtin_amdgcn_mfma_i32_32x32x32_i8(A, members(l, c4a), acc0, 0, 0, 0);
+                if (two) acc1 = __builtin_amdgcn_mfma_i32_32x32x32_i8(A, members(l, c4b), acc1, 0, 0, 0);
             }
-            if (g + kDepth < NG) fetch(g + kDepth, w0[g % kDepth], w1[g % kDepth]);
+            if (g + kDepth < kGroups) fetch(g + kDepth, w[g % kDepth]);
         }
     }
     // accumulator register i of lane (c, kh) = knob (i & 3) + 8 (i >> 2) + 4 kh of centroid c (or 32 + c)
@@ -527,18 +515,18 @@ __device__ __forceinline__ void full_sums(const Queue &Q, int *S, int *n, const 
     for (int i = 0; i < 16; ++i) {
         const int m = (i & 3) + 8 * (i >> 2) + 4 * kh;
         if (m < d) {
-            if (m32 < k) atomicAdd(&S[m32 * (DK + 1) + m], (int)acc0[i]);
-            if (two && m32 + 32 < k) atomicAdd(&S[(m32 + 32) * (DK + 1) + m], (int)acc1[i]);
+            if (m32 < k) atomicAdd(&S[m32 * (DK + 1) + m], -(acc0[i] >> 7));
+            if (two && m32 + 32 < k) atomicAdd(&S[(m32 + 32) * (DK + 1) + m], -(acc1[i] >> 7));
         }
-        if (!SEP && i == 15 && kh == 1) {                              // knob row 31: 1024 per row of the cluster
-            if (m32 < k) atomicAdd(&n[m32], (int)acc0[i] >> 10);
-            if (two && m32 + 32 < k) atomicAdd(&n[m32 + 32], (int)acc1[i] >> 10);
+        if (!SEP && i == 15 && kh == 1) {                              // knob row 31: 2^14 per row of the cluster
+            if (m32 < k) atomicAdd(&n[m32], acc0[i] >> 14);
+            if (two && m32 + 32 < k) atomicAdd(&n[m32 + 32], acc1[i] >> 14);
         }
     }
     if (SEP) {
         for (int e = lane; e < rows_here; e += 64) {
-            const int c = Q.lab()[e];
-            if (c < k) atomicAdd(&n[c], 1);
+            const unsigned v = Q.lab()[e];
+            if (v < 64u) atomicAdd(&n[Queue::centroid(v)], 1);
         }
     }
 }
@@ -550,7 +538,7 @@ __device__ __forceinline__ void full_sums(const Queue &Q, int *S, int *n, const 
 // SEP slots 0 and 1 of the bias step) and stores the sum / 256 there as hi/lo, and its rounded-up value for the error bound.
 // all: fragments from the centroids as they are (no sums yet); starts from the caller may lie anywhere, so the
 // operands are clamped (a mean of rows is always in range).  raw: the sums were rebuilt by
-// full_sums for every cluster (each still raised by 1024 n): every cluster is updated, and the sums
+// full_sums for every cluster (each still off by kRawOffset n): every cluster is updated, and the sums
 // are left either corrected (the next pass applies label changes to them) or, with zero_after,
 // cleared together with the sizes (the next pass rebuilds them).
 template <int DK, bool BYTE_KNOBS, bool SEP>
@@ -571,6 +559,7 @@ __device__ __forceinline__ void update_centroids(const MfmaLds<DK, SEP> &U, int 
             cnt = U.n[c];
             if (!all && ((!raw && U.dirty[c] != stamp) || cnt == 0)) act = false;   // an empty cluster keeps its centroid
         }
+        if (!zero_after && !__any(act)) continue;           // none of this wave's clusters was touched
         half4 hi4 = {(_Float16)0.0f, (_Float16)0.0f, (_Float16)0.0f, (_Float16)0.0f};
         half4 lo4 = hi4;
         double b = 0.0;
@@ -589,7 +578,7 @@ __device__ __forceinline__ void update_centroids(const MfmaLds<DK, SEP> &U, int 
                 if (!all && j < d) {
                     int sv = U.S[c * (DK + 1) + j];
                     if (raw) {
-                        sv -= 1024 * cnt;
+                        sv -= kRawOffset * cnt;
                         U.S[c * (DK + 1) + j] = sv;
                     }
                     const double sd = (double)sv;
@@ -907,7 +896,7 @@ __device__ __forceinline__ void run_unit(const SweepArgs &a, unsigned char *smem
     // kPaired: the number of units chose this number of tiles per wave over twice it.  A loss is the same in
     // a whole sweep and in a chunk of it, which have different numbers of units: the terms of an odd wave go
     // through its idle queue to the wave before it, whose lanes add up what they would with twice the tiles.
-    constexpr bool kPaired = paired_loss(DK, NTW, SEP);
+    constexpr bool kPaired = paired_loss(DK, NTW);
     static_assert(!kPaired || (size_t)NTW * 64 * sizeof(double) <= WaveQueue<DK, NTW>::kOffMask, "the terms fit the queue's rows");
     const int n_parts = kPaired ? (nwaves + 1) / 2 : nwaves;
     auto wave_loss = [&](int slot8) {
@@ -1291,7 +1280,7 @@ __device__ __forceinline__ void run_unit(const SweepArgs &a, unsigned char *smem
         // |S_c|^2 = q_c n_c + r_c it is the integer (sum |x|^2 - sum q_c) minus the sum of the fractions
         // r_c / n_c, which is exact up to the rounding of those k fractions and of the final
         // subtraction (and exactly zero when every cluster's rows coincide).  The sums left by a
-        // pass that rebuilt them on the matrix cores are still raised by 1024 n.
+        // pass that rebuilt them on the matrix cores are still off by kRawOffset n.
         double *frac0 = WaveQueue<DK, NTW>(U.wave_base).few();     // the queues are idle: [k] doubles of the first wave's region
         for (int c = tid; c < k; c += blockDim.x) {
             const int nc = U.n[c];
@@ -1299,7 +1288,7 @@ __device__ __forceinline__ void run_unit(const SweepArgs &a, unsigned char *smem
             if (nc > 0) {
                 unsigned long long ss = 0;
                 for (int j = 0; j < d; ++j) {
-                    const long long sv = (long long)U.S[c * (DK + 1) + j] - (full_mode ? 1024ll * nc : 0ll);
+                    const long long sv = (long long)U.S[c * (DK + 1) + j] - (full_mode ? (long long)kRawOffset * nc : 0ll);
                     ss += (unsigned long long)(sv * sv);
                 }
                 const unsigned long long qc = ss / (unsigned long long)nc;
@@ -1340,25 +1329,729 @@ __device__ __forceinline__ void run_unit(const SweepArgs &a, unsigned char *smem
     }
 }
 
+// ---- the variant that fetches its rows in every pass ----
+//
+// Rows of this many make up one workgroup of the packing kernel and one entry of the tasks' tables of norms.
+constexpr int kPackRows = 256;
+
+// The packed copy holds tiles of 32 rows in the order of B fragments: eight knobs (16 bytes) of row n, knob group g of a tile stand at
+// byte 1024 (g / 2) + 512 (g & 1) + 16 n, so that one load of a fragment reads 1024 bytes in a row.  (One row after the
+// other a load touched 16 lines of 128 bytes and half of each: 56 accesses to the vector cache per load instead of 16, which
+// kept it busy two thirds of the sweep.)  Task t starts at tile task_off[t] / 32 + t, which leaves every task room for its last tile.
+__device__ __forceinline__ size_t packed_at(int row, int g, int DK)
+{
+    return (size_t)(row >> 5) * (32 * DK * 2) + (g >> 1) * 1024 + (g & 1) * 512 + (row & 31) * 16;
+}
+__device__ __forceinline__ const unsigned char *packed_task(const SweepArgs &a, int t, int DK)
+{
+    return reinterpret_cast<const unsigned char *>(a.xh) + ((a.task_off[t] >> 5) + t) * (32 * DK * 2);
+}
+
+// Centred f16 copy of X: knob j less the task's offset, absent knobs zero, the bias slot
+// (last one, not with SEP) holding its constant, so that a lane's 16 bytes are a B fragment as they stand.  Offset of a
+// knob: the rounded mean over eight runs of eight rows spread over the task (any integer would do: it keeps the magnitudes
+// small).  Beside the rows, per workgroup: the largest squared norm of a centred row (for the error bound) and
+// the sum of the raw squared norms (for the loss at a fixed point; byte knobs).
+template <int DK, typename XT, bool SEP>
+__global__ __launch_bounds__(kPackRows) void pack_centred_kernel(const SweepArgs a, int per_task)
+{
+    constexpr bool kByteKnobs = sizeof(XT) == 1;
+    __shared__ int off[DK];
+    __shared__ unsigned top_sq, sum_sq;
+    const int t = (int)(blockIdx.x / (unsigned)per_task), b = (int)(blockIdx.x % (unsigned)per_task);
+    const int64_t r0 = a.task_off[t];
+    const int nrows = (int)(a.task_off[t + 1] - r0);
+    if (b * kPackRows >= nrows) return;
+    const XT *X = reinterpret_cast<const XT *>(a.X);
+    const int tid = threadIdx.x, d = a.d;
+    if (tid == 0) {
+        top_sq = 0u;
+        sum_sq = 0u;
+    }
+    for (int e = tid; e < DK * 8; e += kPackRows) {          // (uniform within a wave: every lane exchanges)
+        const int j = e >> 3, part = e & 7;
+        int sum = 0;
+        if (j < d) {
+            const int first = (int)((int64_t)nrows * part / 8);
+            for (int i = 0; i < 8; ++i) sum += (int)X[(int64_t)j * a.ld + r0 + (first + i < nrows ? first + i : nrows - 1)];
+        }
+        sum += dpp_xor_i32<1>(sum);
+        sum += dpp_xor_i32<2>(sum);
+        sum += dpp_xor_i32<4>(sum);
+        if (part == 0) {
+            const int o = (sum + 32) >> 6;
+            off[j] = o;
+            if (b == 0) a.ojf[t * 64 + j] = (float)o;
+        }
+    }
+    __syncthreads();
+    const int row = b * kPackRows + tid;
+    unsigned c2 = 0, raw2 = 0, top = 0;
+    if (row < nrows) {
+        unsigned char *out = const_cast<unsigned char *>(packed_task(a, t, DK));
+#pragma unroll
+        for (int g = 0; g < DK / 8; ++g) {
+            half8 v;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int j = 8 * g + i;
+                const int xv = j < d ? (int)X[(int64_t)j * a.ld + r0 + row] : 0;
+                const int cv = j < d ? xv - off[j] : 0;
+                top = (unsigned)xv > top ? (unsigned)xv : top;
+                raw2 += (unsigned)(xv * xv);
+                c2 += (unsigned)(cv * cv);
+                v[i] = (_Float16)(float)cv;
+            }
+            if (!SEP && g == DK / 8 - 1) v[7] = (_Float16)bias_scale(kByteKnobs);
+            *reinterpret_cast<half8 *>(out + packed_at(row, g, DK)) = v;
+        }
+        if (!kByteKnobs && top >= 2048u) *a.too_large = 1;
+    }
+    atomicMax(&top_sq, c2);
+    atomicAdd(&sum_sq, raw2);                                // (byte knobs: at most 256 * 32 * 255^2 < 2^32)
+    __syncthreads();
+    if (tid == 0) {
+        a.norms[t * 32 + b] = __float_as_int((float)top_sq * 1.000001f);
+        a.norms[t * 32 + 16 + b] = (int)sum_sq;
+    }
+}
+
+// Per-wave LDS region of this variant: the undecided rows of the tiles seen so far (candidate masks and row index), later the
+// label changes of the pass; the knobs of the rows being resolved, a batch at a time, from the packed copy; the labels.  A label is
+// stored as its position among the mask bits of a row (32 * lane half + position in that half's word), so that the mask of a
+// decided row is one shift away.
+template <int DK>
+struct FetchedQueue {
+    static constexpr int kRows = DK <= 32 ? 512 : 256;      // rows a wave owns at most
+    static constexpr int kCap = 96;                         // (a tile adds at most 32)
+    static constexpr int kBatch = 16;
+    static constexpr int kChanges = 64;
+    static constexpr size_t kOffFew = (size_t)8 * DK * 2;   // (behind the eight rows there are then at most; up to 32-wide rows)
+    static constexpr size_t kOffMask = DK <= 32 ? kOffFew + 4 * 32 * 8 : (size_t)kBatch * DK * 2;
+    static constexpr size_t kOffPid = kOffMask + (size_t)kCap * 8;
+    static constexpr size_t kOffLab = kOffPid + (size_t)kCap * 2;
+    static constexpr size_t kOffNew = kOffLab + (size_t)kRows;
+    static constexpr size_t kBytes = kOffNew + (size_t)kRows;
+    static_assert(kBytes % 16 == 0 && kOffLab % 16 == 0, "regions of a wave stay 16-byte aligned");
+    static_assert(kCap * 8 >= kChanges * 4 && kOffMask >= (size_t)kBatch * DK * 2 && kOffMask >= 64 * sizeof(double), "what shares a place fits it");
+    unsigned char *base;
+    int first;                                              // first row of the batch being resolved
+    __device__ explicit FetchedQueue(unsigned char *wb) : base(wb), first(0) {}
+    __device__ _Float16 *rec_x() const { return reinterpret_cast<_Float16 *>(base); }                    // [kBatch][DK]
+    __device__ unsigned *rec_mask() const { return reinterpret_cast<unsigned *>(base + kOffMask) + 2 * first; }      // [kCap][2]
+    __device__ unsigned short *rec_pid() const { return reinterpret_cast<unsigned short *>(base + kOffPid) + first; }
+    __device__ double *few() const { return reinterpret_cast<double *>(base + kOffFew); }                 // [4][32]
+    __device__ unsigned *changes() const { return reinterpret_cast<unsigned *>(base + kOffMask); }         // [kChanges] new label | previous << 8 | row << 16
+    __device__ unsigned char *lab() const { return base + kOffLab; }                                      // [kRows] current labels (0xFF: none)
+    __device__ unsigned char *lab_new() const { return base + kOffNew; }                                  // [kRows] labels of the pass under way
+    static __device__ __forceinline__ unsigned stored(unsigned c) { return (c >> 1) | ((c & 1u) << 5); }
+    static __device__ __forceinline__ unsigned centroid(unsigned v) { return ((v & 31u) << 1) | (v >> 5); }
+};
+
+// Listed label changes of this wave (centroids, not stored labels) -> integer sums and sizes: 256 / DK rows per step, one lane per
+// (row, four knobs), the knobs from the packed copy, those of four steps under way together.
+template <int DK, typename Queue>
+__device__ __forceinline__ void apply_listed(const Queue &Q, int cnt, const unsigned char *packed, int *S, int *n, int *dirty,
+                                             const float *ojf, int d, int stamp)
+{
+    typedef _Float16 half4 __attribute__((ext_vector_type(4)));
+    constexpr int LPR = DK / 4;              // lanes per row
+    constexpr int EPI = 64 / LPR;            // rows per step
+    constexpr int U = 4;
+    const int lane = threadIdx.x & 63;
+    const int j0 = 4 * (lane % LPR);
+    const float4 o4 = *reinterpret_cast<const float4 *>(ojf + j0);
+    const float of[4] = {o4.x, o4.y, o4.z, o4.w};
+    const bool on = j0 < d && lane < LPR * EPI;      // (twelve lanes per row leave four idle)
+    __builtin_amdgcn_wave_barrier();
+    for (int e0 = 0; e0 < cnt; e0 += U * EPI) {
+        unsigned w[U];
+        half4 xq[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int e = e0 + u * EPI + lane / LPR;
+            w[u] = Q.changes()[e < cnt ? e : 0];
+            xq[u] = *reinterpret_cast<const half4 *>(packed + packed_at(w[u] >> 16, j0 >> 3, DK) + 2 * (j0 & 4));
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int e = e0 + u * EPI + lane / LPR;
+            if (e < cnt && on) {
+                const int cur = w[u] & 0xFF, prev = (w[u] >> 8) & 0xFF;
+                const bool first = prev == 0xFF;
+                int *sc = S + cur * (DK + 1) + j0;
+                int *sp = S + (first ? cur : prev) * (DK + 1) + j0;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    if (j0 + i < d) {
+                        const int xi = (int)((float)xq[u][i] + of[i]);
+                        atomicAdd(sc + i, xi);
+                        if (!first) atomicSub(sp + i, xi);
+                    }
+                }
+                if (j0 == 0) {
+                    atomicAdd(&n[cur], 1);
+                    dirty[cur] = stamp;
+                    if (!first) {
+                        atomicSub(&n[prev], 1);
+                        dirty[prev] = stamp;
+                    }
+                }
+            }
+        }
+    }
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Tiles whose rows are fetched ahead (even: the accumulators alternate).
+constexpr int rows_ahead(int DK, bool two, bool SEP) { return DK == 16 || (DK == 32 && !two) ? 4 : 2; }
+
+constexpr int kParts = 16;
+
+// One unit, its rows fetched from the packed copy in every pass (L2 holds the rows of the tasks under way) instead of kept
+// in registers: 128 registers a wave and 80 KiB of LDS then let two workgroups share a compute unit whatever the size of the
+// task, and one's barriers and chains of dependent LDS accesses run under the other's tiles.
+template <int DK, typename XT, bool SEP>
+__device__ __forceinline__ void run_unit_fetched(const SweepArgs &a, unsigned char *smem, int ki, int t, int k)
+{
+    constexpr bool kByteKnobs = sizeof(XT) == 1;
+    constexpr float kBiasScale = bias_scale(kByteKnobs);
+    constexpr bool kAllowTwo = DK <= 32;      // (k <= 32 with wider rows)
+    typedef FetchedQueue<DK> Queue;
+    const XT *X = reinterpret_cast<const XT *>(a.X);
+    const bool two = kAllowTwo && k > 32;
+    constexpr int NS = DK / 16;          // distinct B fragments per row
+    constexpr int NS2 = 2 * NS;          // chained instructions per 32x32 tile, without the bias step
+    constexpr int NSA = NS2 + (SEP ? 1 : 0);   // ... with it
+    constexpr int CH = NS2 == 6 ? 4 : 16 / NS2;   // scores handled between two matrix instructions
+    const int KP = a.kmax > 32 ? 64 : 32;
+    MfmaLds<DK, SEP> U(smem, KP);
+
+    const int tid = threadIdx.x;
+    const int lane_id = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nwaves = blockDim.x >> 6;
+    // the phases of a pass take the lane index through this: values derived from it are then computed where they are used
+    auto opaque = [](int v) {
+        asm volatile("" : "+v"(v));
+        return v;
+    };
+
+    const int d = a.d;
+    const int64_t r0 = a.task_off[t], r1 = a.task_off[t + 1];
+    const int nrows = (int)(r1 - r0);
+    const int64_t slot = (int64_t)t * a.n_k + ki;
+    const int64_t crow = (int64_t)t * a.Ksum + a.koff[ki];
+    uint8_t *labrow = a.labbuf + (int64_t)ki * a.ld;
+
+    Queue Q(U.wave_base + Queue::kBytes * wave);
+    // Rows of the task in kParts equal parts of whole groups of 64; a wave has one, or two in a row.  The loss is summed part by
+    // part, so that its order does not depend on the number of waves.
+    const int part_rows = nrows > 64 * kParts ? (nrows + 64 * kParts - 1) / (64 * kParts) * 64 : 64;
+    const int run = part_rows * (kParts / nwaves);
+    const int wave_row0 = wave * run;
+    const int rows_wave = nrows - wave_row0 < run ? (nrows - wave_row0 > 0 ? nrows - wave_row0 : 0) : run;
+    const bool wave_live = rows_wave > 0;
+    const int ntiles = (rows_wave + 31) >> 5;
+    const unsigned char *packed = packed_task(a, t, DK) + (size_t)(wave_live ? wave_row0 : 0) * (DK * 2);      // (whole tiles)
+
+    const int kk_last = two ? k - 32 : k;                  // centroids in the last (or only) m-tile
+    const int lregs = ((kk_last + 1) / 2 + 3) & ~3;        // live accumulator registers, in groups of four
+    constexpr int bstep = NS - 1, bhalf = 1, belem = 7;
+    constexpr int kFullDivisor = 8;
+
+    // ---- set-up
+    for (int e = tid; e < DK * KP; e += blockDim.x) U.mu64T[e] = 0.0;
+    for (int e = tid; e < KP * (DK + 1); e += blockDim.x) U.S[e] = 0;
+    for (int c = tid; c < KP; c += blockDim.x) {
+        U.n[c] = 0;
+        U.dirty[c] = -1;
+        U.bias[c] = 0.0f;
+    }
+    if (tid < DK) U.ojf[tid] = a.ojf[t * 64 + tid];
+    {
+        half8 z;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) z[i] = (_Float16)0.0f;
+        for (int e = tid; e < (KP / 32) * NSA * 64; e += blockDim.x) U.afrag[e] = z;      // (abias included)
+    }
+    if (tid == 0) {
+        U.stamp[1] = 0;           // float bits of the largest squared norm of a centred row
+        U.stamp[2] = 0;           // rows that changed their label in an even pass
+        U.stamp[3] = 0;           // ... in an odd pass
+        U.acc64[0] = 0ull;
+        U.acc64[1] = 0ull;
+    }
+    for (int e = lane_id; e < 2 * Queue::kRows / 4; e += 64) reinterpret_cast<unsigned *>(Q.lab())[e] = 0xFFFFFFFFu;      // no row has a label yet
+    __syncthreads();
+    // padding centroid rows (beyond k) carry a huge bias so that they never win
+    for (int c = k + tid; c < KP; c += blockDim.x) {
+        _Float16 *bslot = SEP ? reinterpret_cast<_Float16 *>(U.abias + (c >> 5) * 64 + frag_row(c))
+                              : reinterpret_cast<_Float16 *>(U.afrag + ((c >> 5) * NS2 + bstep) * 64 + 32 * bhalf + frag_row(c)) + belem;
+        bslot[0] = (_Float16)kHalfMax;
+    }
+    if (tid < (nrows + kPackRows - 1) / kPackRows) {
+        atomicMax(&U.stamp[1], a.norms[t * 32 + tid]);           // non-negative floats order like integers
+        if (kByteKnobs) atomicAdd(&U.acc64[0], (unsigned long long)(unsigned)a.norms[t * 32 + 16 + tid]);
+    }
+    for (int e = tid; e < k * d; e += blockDim.x) {
+        const int c = e / d, j = e % d;
+        double v;
+        if (a.init_mode == 0) {
+            const int row = a.init_rows[(int64_t)t * a.kmax + c];
+            v = (double)X[(int64_t)j * a.ld + r0 + row];
+        } else {
+            v = a.init_centroids[(crow + c) * d + j];
+        }
+        U.mu64T[(size_t)j * KP + c] = v;
+    }
+    __syncthreads();
+    update_centroids<DK, kByteKnobs, SEP>(U, k, KP, d, 0, true);
+    __syncthreads();
+    // Screen bound of the unit: that of its farthest row.  Largest squared norm a centred centroid can take during the iteration: every
+    // later centroid is a mean of rows (inside their convex hull) or stays where it started.
+    float bound;
+    {
+        const float x2 = __int_as_float(U.stamp[1]);
+        float m2 = wave_max_nonneg(lane_id < k ? U.bias[lane_id] : 0.0f);
+        m2 = __builtin_fmaxf(m2, x2) * 1.000001f;
+        // starts beyond the range of the screen (their operands are clamped): every centroid is a candidate of every row
+        if (!(m2 <= max_screened(kByteKnobs))) m2 = 1.0e30f;
+        bound = mfma_bound<NSA, kByteKnobs>(x2, m2);
+    }
+
+    int passes_run = 0;
+    bool at_fixed_point = false;         // the last pass run moved no row: every centroid is the mean of its cluster
+    // A pass after one that moved many rows rebuilds the sums from the labels on the matrix cores
+    // instead of applying the changes one by one; the first pass (every row is new) always does.
+    const uint8_t *xw = a.X + r0 + (wave_live ? wave_row0 : 0);
+    const bool x_aligned = kByteKnobs &&                              // (the rebuild reads the byte matrix)
+                           ((reinterpret_cast<uintptr_t>(a.X) | (uintptr_t)a.ld | (uintptr_t)r0) & 15) == 0 &&
+                           r0 + ((nrows + 63) & ~63) <= a.ld;       // ... and its last group of 64 rows lies inside the matrix
+    bool full_mode = x_aligned;
+    const int full_above = nrows / kFullDivisor;      // changed rows of a pass above which the next one rebuilds
+    bool traced_last = false;
+
+    // lanes of tile nt (as a 32-bit mask over the row index within the tile) whose row belongs to the task
+    auto live_rows = [&](int nt) -> uint32_t {
+        const int left = rows_wave - 32 * nt;
+        return left >= 32 ? 0xFFFFFFFFu : (left <= 0 ? 0u : ((1u << left) - 1u));
+    };
+    // this lane's B fragments of a tile (rows behind the task's last are read, from inside the workspace, and ignored)
+    constexpr unsigned kTileBytes = 32 * DK * 2;
+    auto fetch = [&](half8 (&Bt)[NS], const unsigned char *p, unsigned lane_off) {
+        // a scalar base in global memory: a lane's part of the address is one 32-bit register
+        uint64_t at = reinterpret_cast<uint64_t>(p);
+        asm volatile("" : "+s"(at));
+        typedef const __attribute__((address_space(1))) unsigned char gbyte;
+        typedef const __attribute__((address_space(1))) half8 ghalf8;
+#pragma unroll
+        for (int f = 0; f < NS; ++f) Bt[f] = *reinterpret_cast<ghalf8 *>(reinterpret_cast<gbyte *>(at) + lane_off + 1024 * f);
+    };
+
+    // Exact loss of the current labels: (x - mu)^2 in double over the knobs a lane holds (x = centred value + offset, exact), the two
+    // lanes of a row and all rows of a part added up afterwards; the sums of the parts land in U.red[at .. at + kParts).
+    auto wave_loss = [&](int at) {
+        const int lane = opaque(lane_id), n32 = lane & 31, h = lane >> 5;
+        float of[NS][8];
+#pragma unroll
+        for (int f = 0; f < NS; ++f)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) of[f][i] = U.ojf[16 * f + 8 * h + i];
+        for (int first = 0; first < run; first += part_rows) {
+            double part = 0.0;
+            const int last = first + part_rows < rows_wave ? first + part_rows : rows_wave;
+            for (int nt = first >> 5; 32 * nt < last; ++nt) {
+                half8 bt[NS];
+                fetch(bt, packed + nt * kTileBytes, (unsigned)(16 * lane));
+                const uint32_t lab = Q.lab()[nt * 32 + n32];
+                const bool live = lab != 0xFFu;
+                const double *mc = U.mu64T + (live ? Queue::centroid(lab) : 0u) + (size_t)(8 * h) * KP;
+                double s = 0.0;
+#pragma unroll
+                for (int f = 0; f < NS; ++f) {
+                    // the centroid's knobs first, all loads under way together, then the sum in knob order
+                    double mu[8];
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) mu[i] = mc[(size_t)(16 * f + i) * KP];
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        float xf = (float)bt[f][i] + of[f][i];
+                        if (!SEP && f == bstep && i == belem) xf = h == bhalf ? 0.0f : xf;     // the bias slot is no knob
+                        const double tq = (double)xf - mu[i];
+                        s = s + tq * tq;
+                    }
+                }
+                part = part + (live ? s : 0.0);
+            }
+            // the part's total in the fixed order lane ^ 32, 16, ..., 1 (partner indices from the local lane index)
+            double ws = part;
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) {
+                const long long b = __double_as_longlong(ws);
+                const int plo = __builtin_amdgcn_ds_bpermute((lane ^ off) << 2, (int)(b & 0xFFFFFFFFll));
+                const int phi = __builtin_amdgcn_ds_bpermute((lane ^ off) << 2, (int)(b >> 32));
+                ws = ws + __longlong_as_double(((long long)phi << 32) | (unsigned int)plo);
+            }
+            if (lane == 0) U.red[at + (wave_row0 + first) / part_rows] = ws;
+        }
+    };
+
+    for (int it = 0; it <= a.n_iter; ++it) {
+        const bool last_pass = (it == a.n_iter);
+        passes_run = it + 1;
+        int nrec = 0;                    // queued rows that the screen could not decide
+        const uint64_t undecided = it == 0 ? ~0ull : 0ull;
+
+        // The tile loop from tile nt on, compiled once per number of live registers of the last m-tile (4, 8, 12 or 16), so that
+        // the epilogue has no branches.  Returns the tile to go on with: ntiles, or an earlier one when the queue has to be emptied.
+        auto tile_pass = [&](auto live_tag, auto two_tag, int nt) -> int {
+            constexpr int LREGS = decltype(live_tag)::value;
+            constexpr bool two = decltype(two_tag)::value;
+            constexpr int kAhead = rows_ahead(DK, two, SEP);
+            const int lane = opaque(lane_id), n32 = lane & 31;
+            const bool upper = lane >= 32;
+            const unsigned lane_off = (unsigned)(16 * lane);
+            half8 Bq[kAhead][NS];                // rows of tiles nt .. nt + kAhead - 1
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) fetch(Bq[u], packed + (nt + u) * kTileBytes, lane_off);
+            const unsigned char *ahead = packed + (nt + kAhead) * kTileBytes;
+            int end = ntiles;                    // where this call stops
+            const unsigned char *labs = Q.lab() + nt * 32 + n32;
+            // A fragments of this pass (the bias slot included)
+            half8 A0[NSA], A1[NSA];
+#pragma unroll
+            for (int s = 0; s < NS2; ++s) {
+                A0[s] = U.afrag[s * 64 + lane];
+                A1[s] = two ? U.afrag[(NS2 + s) * 64 + lane] : A0[s];
+            }
+            // the bias step: 256 against hi (slot 0) and lo (slot 1), the same for every row
+            half8 bias_b;
+            if constexpr (SEP) {
+                A0[NS2] = U.abias[lane];
+                A1[NS2] = two ? U.abias[64 + lane] : A0[NS2];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) bias_b[i] = (_Float16)(i < 2 && lane < 32 ? kBiasScale : 0.0f);
+            }
+
+            float16v accA, accB;
+            const float16v zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            // one matrix instruction of the chain of a 32x32 tile (the first one behind the bias step)
+            auto mma = [&](float16v &acc, const half8 (&Af)[NSA], const half8 (&Bt)[NS], int s) {
+                if constexpr (SEP) {
+                    if (s == 0) acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(Af[NS2], bias_b, zero16, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(Af[s], Bt[s % NS], acc, 0, 0, 0);
+                    return;
+                }
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(Af[s], Bt[s % NS], s == 0 ? zero16 : acc, 0, 0, 0);
+            };
+            // mark scores [i0, i0 + CH): bit set = below the threshold
+            auto mark = [&](uint32_t &near, const float16v &acc, float thr, int i0) {
+#pragma unroll
+                for (int i = 0; i < CH; ++i)
+                    if (i0 + i < 16) near = __builtin_amdgcn_alignbit(near, __float_as_uint(acc[i0 + i] - thr), 31);
+            };
+            // minimum over the first nreg registers (nreg = 4, 8, 12 or 16)
+            auto min_live = [&](const float16v &acc, auto nreg_tag) {
+                constexpr int nreg = decltype(nreg_tag)::value;
+                float b = vmin(vmin3(acc[0], acc[1], acc[2]), acc[3]);
+                if (nreg > 4) b = vmin3(vmin3(b, acc[4], acc[5]), acc[6], acc[7]);
+                if (nreg > 8) b = vmin3(vmin3(b, acc[8], acc[9]), acc[10], acc[11]);
+                if (nreg > 12) b = vmin3(vmin3(b, acc[12], acc[13]), acc[14], acc[15]);
+                return b;
+            };
+            // both lane halves' minima of a row -> the row's minimum
+            auto row_min = [&](float v) {
+                unsigned lo, hi;
+                both_halves(__float_as_uint(v), lo, hi);
+                return vmin(__uint_as_float(lo), __uint_as_float(hi));
+            };
+            // After the masks of tile nt: a tile whose rows all have exactly their current label marked is done (but in the first
+            // pass).  Otherwise the tile's rows are decided: a row with exactly one candidate takes it, any other row is queued
+            // for the exact evaluation after the tile loop (label 0xFE until then).  (The matrix instructions of the next tile are under way meanwhile.)
+            auto settle = [&](uint32_t cand, uint32_t prev, int nt) {       // cand: bit 31 = position 0
+                const uint64_t place = 0x8000000000000000ull >> (prev & 63u);
+                const uint32_t own = upper ? (uint32_t)place : (uint32_t)(place >> 32);
+                if ((__ballot(cand != own) | undecided) == 0) return;
+                const uint32_t live32 = live_rows(nt);
+                uint32_t cand_lo, cand_hi;
+                both_halves(cand, cand_lo, cand_hi);
+                const int total = __popc(cand_lo) + __popc(cand_hi);
+                const bool live = (live32 >> n32) & 1u;
+                const bool flagged = live && total != 1;
+                const uint32_t fm = (uint32_t)__ballot(flagged);
+                if (fm) {
+                    if (flagged) {
+                        const int rs = nrec + __popc(fm & ((1u << n32) - 1u));
+                        // no candidate at all cannot happen (the smallest score is always one); if it does, every centroid is one
+                        Q.rec_mask()[rs * 2 + (upper ? 1 : 0)] = total ? cand : 0xFFFFFFFFu;
+                        if (!upper) Q.rec_pid()[rs] = (unsigned short)(nt * 32 + n32);
+                    }
+                    nrec += __popc(fm);
+                    if (nrec > Queue::kCap - 32) end = nt + 1;      // the next tile might not fit
+                }
+                const uint32_t lab = cand_lo ? (uint32_t)__clz((int)cand_lo) : 32u + ((uint32_t)__clz((int)cand_hi) & 31u);
+                const uint32_t now = !live ? 0xFFu : (flagged ? 0xFEu : lab);
+                if (!upper) Q.lab_new()[nt * 32 + n32] = (unsigned char)now;
+            };
+
+            if constexpr (two) {
+                // accA = centroids 0..31 (all sixteen registers live), accB = centroids 32..k-1 of the current tile; Bn = rows of
+                // the next tile, Bf = free for those of the tile kAhead further on
+                auto step = [&](half8 (&Bn)[NS], half8 (&Bf)[NS]) {
+                    fetch(Bf, ahead, lane_off);
+                    ahead += kTileBytes;
+                    const uint32_t prev = *labs;
+                    labs += 32;
+                    const float best = row_min(vmin(min_live(accA, std::integral_constant<int, 16>{}), min_live(accB, live_tag)));
+                    const float thr = best + bound;
+                    uint32_t near = 0;
+#pragma unroll
+                    for (int s = 0; s < NS2; ++s) mark(near, accA, thr, s * CH);
+                    // accA is consumed: its next chain runs under the marking of accB
+#pragma unroll
+                    for (int s = 0; s < NS2; ++s) {
+                        __builtin_amdgcn_sched_barrier(0);
+                        mma(accA, A0, Bn, s);
+                        __builtin_amdgcn_sched_barrier(0);
+                        if (s * CH < LREGS) mark(near, accB, thr, s * CH);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int s = 0; s < NS2; ++s) mma(accB, A1, Bn, s);
+                    // (registers of accB that were not walked hold padding only)
+                    constexpr int live_marks = CH * ((LREGS + CH - 1) / CH);
+                    settle(near << (16 - live_marks), prev, nt);
+                    __builtin_amdgcn_sched_barrier(0);
+                    asm volatile("" : "+v"(accB));      // (as below)
+                };
+#pragma unroll
+                for (int s = 0; s < NS2; ++s) mma(accA, A0, Bq[0], s);
+#pragma unroll
+                for (int s = 0; s < NS2; ++s) mma(accB, A1, Bq[0], s);
+                for (;;) {
+#pragma unroll
+                    for (int u = 0; u < kAhead; ++u) {
+                        step(Bq[(u + 1) % kAhead], Bq[u]);
+                        if (++nt >= end) return nt;
+                    }
+                }
+            } else {
+                // one m-tile: the accumulators alternate, the next tile's chain runs under this epilogue
+                auto step = [&](float16v &cur, float16v &nxt, half8 (&Bn)[NS], half8 (&Bf)[NS]) {
+                    fetch(Bf, ahead, lane_off);
+                    ahead += kTileBytes;
+                    const uint32_t prev = *labs;
+                    labs += 32;
+                    const float best = row_min(min_live(cur, live_tag));
+                    const float thr = best + bound;
+                    uint32_t near = 0;
+#pragma unroll
+                    for (int s = 0; s < NS2; ++s) {
+                        __builtin_amdgcn_sched_barrier(0);
+                        mma(nxt, A0, Bn, s);
+                        __builtin_amdgcn_sched_barrier(0);
+                        if (s * CH < LREGS) mark(near, cur, thr, s * CH);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                    constexpr int live_marks = CH * ((LREGS + CH - 1) / CH);
+                    settle(near << (32 - live_marks), prev, nt);
+                    __builtin_amdgcn_sched_barrier(0);
+                    // registers of dead scores are not used for anything else meanwhile: that would wait for the chain's end
+                    asm volatile("" : "+v"(nxt));
+                };
+#pragma unroll
+                for (int s = 0; s < NS2; ++s) mma(accA, A0, Bq[0], s);
+                for (;;) {
+#pragma unroll
+                    for (int u = 0; u < kAhead; ++u) {
+                        step(u & 1 ? accB : accA, u & 1 ? accA : accB, Bq[(u + 1) % kAhead], Bq[u]);
+                        if (++nt >= end) return nt;
+                    }
+                }
+            }
+        };
+        if (wave_live) {
+            int nt = 0;
+            do {
+                auto live_pass = [&](auto two_tag) {
+                    switch (lregs) {
+                    case 4: nt = tile_pass(std::integral_constant<int, 4>{}, two_tag, nt); break;
+                    case 8: nt = tile_pass(std::integral_constant<int, 8>{}, two_tag, nt); break;
+                    case 12: nt = tile_pass(std::integral_constant<int, 12>{}, two_tag, nt); break;
+                    default: nt = tile_pass(std::integral_constant<int, 16>{}, two_tag, nt); break;
+                    }
+                };
+                if constexpr (kAllowTwo) {
+                    if (two) live_pass(std::true_type{});
+                    else live_pass(std::false_type{});
+                } else {
+                    live_pass(std::false_type{});
+                }
+                // the undecided rows: their knobs from the packed copy, then the exact evaluation
+                if (nrec) {
+                    constexpr int LPR = DK / 8;              // lanes per row, 16 bytes each
+                    const int lane = opaque(lane_id);
+                    Queue part = Q;
+                    for (part.first = 0; part.first < nrec; part.first += Queue::kBatch) {
+                        const int left = nrec - part.first, rows = left < Queue::kBatch ? left : Queue::kBatch;
+                        __builtin_amdgcn_wave_barrier();
+                        for (int e = lane; e < rows * LPR; e += 64)
+                            *reinterpret_cast<half8 *>(part.rec_x() + 8 * e) =
+                                *reinterpret_cast<const half8 *>(packed + packed_at(part.rec_pid()[e / LPR], e % LPR, DK));
+                        resolve_queue<DK>(part, rows, U.mu64T, U.ojf, KP, k, d);
+                    }
+                    nrec = 0;
+                }
+            } while (nt < ntiles);
+        }
+
+        // ---- label changes -> integer sums and sizes.  Both label tables agree but for this pass's changes (a row without a label
+        // yet has previous = 0xFF; rows outside the task keep 0xFF): a lane compares four rows at a time.
+        int wave_changed = 0;
+        {
+            const int lane = opaque(lane_id);
+            const uint64_t below = (1ull << lane) - 1ull;
+            int cnt = 0;
+            __builtin_amdgcn_wave_barrier();
+            for (int first = 0; first < rows_wave; first += 256) {
+                const unsigned at = first + 4 * lane;
+                unsigned *oldp = reinterpret_cast<unsigned *>(Q.lab() + at);
+                const unsigned cur4 = at < (unsigned)Queue::kRows ? *reinterpret_cast<const unsigned *>(Q.lab_new() + at) : 0u;
+                const unsigned prev4 = at < (unsigned)Queue::kRows ? *oldp : 0u;
+                const unsigned diff = cur4 ^ prev4;
+                if (!__ballot(diff != 0u)) continue;
+                if (diff) *oldp = cur4;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const bool changed = ((diff >> (8 * i)) & 0xFFu) != 0u;
+                    const uint64_t cm = __ballot(changed);
+                    if (!cm) continue;
+                    const int add = __popcll(cm);
+                    wave_changed += add;
+                    if (full_mode) continue;                     // (the sums are rebuilt from all labels)
+                    if (cnt + add > Queue::kChanges) {
+                        apply_listed<DK>(Q, cnt, packed, U.S, U.n, U.dirty, U.ojf, d, it);
+                        cnt = 0;
+                    }
+                    if (changed) {
+                        const unsigned cur = (cur4 >> (8 * i)) & 0xFFu, prev = (prev4 >> (8 * i)) & 0xFFu;
+                        Q.changes()[cnt + __popcll(cm & below)] =
+                            Queue::centroid(cur) | (prev == 0xFFu ? 0xFFu : Queue::centroid(prev)) << 8 | (at + i) << 16;
+                    }
+                    cnt += add;
+                }
+            }
+            if (full_mode) {
+                __builtin_amdgcn_wave_barrier();
+                if (wave_live) full_sums<DK, Queue::kRows / 64, SEP>(Q, U.S, U.n, xw, a.ld, d, k, rows_wave, lane_id);
+            } else if (cnt) {
+                apply_listed<DK>(Q, cnt, packed, U.S, U.n, U.dirty, U.ojf, d, it);
+            }
+        }
+        if (wave_changed && lane_id == 0) atomicAdd(&U.stamp[2 + (it & 1)], wave_changed);
+        traced_last = false;
+        if (a.trace) {
+            wave_loss((it & 1) * kParts);
+            traced_last = true;
+        }
+        __syncthreads();
+        if (a.trace && tid == 0) {
+            double s = 0.0;
+            for (int p = 0; p < kParts; ++p) s = s + U.red[(it & 1) * kParts + p];
+            a.trace[slot * (a.n_iter + 1) + it] = s;
+        }
+        // A pass that moved no row leaves every sum, hence every centroid, as it was: the labels are
+        // final.  (The count is read between this pass's two barriers, or after its only one when the
+        // loop ends here; no wave adds to it in between.)
+        const int rows_changed = __builtin_amdgcn_readfirstlane(U.stamp[2 + (it & 1)]);
+        at_fixed_point = rows_changed == 0;
+        if (last_pass || rows_changed == 0) break;
+        if (tid == 0) U.stamp[2 + ((it + 1) & 1)] = 0;      // the next pass counts from zero (nobody adds before the barrier below)
+        const bool full_next = x_aligned && rows_changed > full_above;
+        update_centroids<DK, kByteKnobs, SEP>(U, k, KP, d, it, false, full_mode, full_next);
+        full_mode = full_next;
+        __syncthreads();
+    }
+
+    // ---- results: labels, loss, centroids, counts
+    for (int e = lane_id; e < rows_wave; e += 64) labrow[r0 + wave_row0 + e] = (uint8_t)Queue::centroid(Q.lab()[e]);
+    // the loss of the final labels: the per-wave sums of the last traced pass are still in place
+    int loss_slot = ((passes_run - 1) & 1) * kParts;
+    double loss = 0.0;
+    if (kByteKnobs && !traced_last && at_fixed_point) {
+        // At a fixed point every non-empty centroid is the mean S / n of its cluster: the loss in integers, as in run_unit
+        double *frac0 = reinterpret_cast<double *>(U.wave_base);     // the queues are idle: [k] doubles of the first wave's region
+        for (int c = tid; c < k; c += blockDim.x) {
+            const int nc = U.n[c];
+            double fr = 0.0;
+            if (nc > 0) {
+                unsigned long long ss = 0;
+                for (int j = 0; j < d; ++j) {
+                    const long long sv = (long long)U.S[c * (DK + 1) + j] - (full_mode ? (long long)kRawOffset * nc : 0ll);
+                    ss += (unsigned long long)(sv * sv);
+                }
+                const unsigned long long qc = ss / (unsigned long long)nc;
+                const unsigned long long rc = ss - qc * (unsigned long long)nc;
+                atomicAdd(&U.acc64[1], qc);
+                fr = (double)rc / (double)nc;
+            }
+            frac0[c] = fr;
+        }
+        __syncthreads();
+        if (tid == 0) {
+            double fsum = 0.0;
+            for (int c = 0; c < k; ++c) fsum = fsum + frac0[c];
+            loss = (double)(U.acc64[0] - U.acc64[1]) - fsum;
+        }
+    } else {
+        if (!traced_last) {
+            loss_slot = 0;
+            wave_loss(0);
+            __syncthreads();
+        }
+        if (tid == 0)
+            for (int p = 0; p < kParts; ++p) loss = loss + U.red[loss_slot + p];
+    }
+    if (a.trace && tid == 0) {
+        // the passes that were not run would have seen the same labels and centroids
+        for (int it = passes_run; it <= a.n_iter; ++it) a.trace[slot * (a.n_iter + 1) + it] = loss;
+    }
+    for (int e = tid; e < k * d; e += blockDim.x) {
+        const int c = e / d, j = e % d;
+        a.centroids[(crow + c) * d + j] = U.mu64T[(size_t)j * KP + c];
+    }
+    for (int c = tid; c < k; c += blockDim.x) a.counts[crow + c] = U.n[c];
+    if (tid == 0) {
+        a.status[slot] = 0;
+        a.inertia[slot] = loss;
+        a.passes[slot] = passes_run;
+    }
+}
+
 // Persistent workgroups (one or two per compute unit) take units from a counter until none is left: the
 // next unit starts as soon as the last one ends, without a new dispatch of a workgroup of this size.
 // Units are handed out in descending-k order so that the longest ones start first.
 // Few tiles per wave leave registers to spare: held to 128 of them, two workgroups share a compute unit, and one's barriers and dependent LDS accesses run
 // under the other's tiles.  64 tasks x 1024 rows x 12 knobs, k = 2..32: 632 -> 452 us a step; 64 tasks x
-// 1000 rows x 24 knobs: 650 -> 532 us.  The price is scratch memory, in the tile loop too: with eight tiles of 16-wide
-// rows four of the row fragments are fetched from there in every pass, with four of 32-wide ones some single words.
-constexpr bool two_workgroups(int DK, int NTW, bool SEP)
-{
-    return (DK == 16 && NTW <= 8) || (DK == 32 && NTW <= 4 && !SEP);
-}
+// 1000 rows x 24 knobs: 650 -> 532 us.  The price is scratch memory, in the tile loop too: with four tiles of 32-wide rows
+// some single words.
+constexpr bool two_workgroups(int DK, int NTW, bool SEP) { return NTW == 0 || DK == 16 || (DK == 32 && !SEP); }
 
+// Rows that are fetched in every pass have to come from the L2 of the XCD that runs the unit (4 MiB; workgroups go to XCDs in turn),
+// so tasks belong to queues, one per XCD, once the packed rows of a call exceed 3 MiB, and the units of kQueueGroup tasks (1 MiB at
+// most for 32-wide rows) are handed out together.  256 tasks x 4096 x 24: one queue 17.5 ms a step, eight 14.3 ms.  A workgroup
+// whose queue is empty goes on with the next one.
+constexpr int kQueueGroup = 4;
+
+// NTW = 0: rows fetched per pass (run_unit_fetched), otherwise tiles of rows a wave keeps in registers (run_unit).
 template <int DK, int NTW, typename XT, bool SEP>
-__global__ __launch_bounds__(512, two_workgroups(DK, NTW, SEP) ? 4 : 2) void resident_mfma_kernel(const SweepArgs a)
+__global__ __launch_bounds__(NTW == 0 ? 1024 : 512, two_workgroups(DK, NTW, SEP) ? 4 : 2) void resident_mfma_kernel(const SweepArgs a)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int next_unit;
     const int tid = threadIdx.x;
-    const int n_units = a.T * (a.ki_end - a.ki_begin);
+    const int nk = a.ki_end - a.ki_begin;
 
     if (a.done && a.T <= 4096) {
         // a chunk in which every task has stopped: nothing to do (with very many tasks the look itself costs)
@@ -1366,16 +2059,32 @@ __global__ __launch_bounds__(512, two_workgroups(DK, NTW, SEP) ? 4 : 2) void res
         for (int t = tid; t < a.T; t += blockDim.x) live |= a.done[t] == 0 ? 1 : 0;
         if (!__syncthreads_or(live)) return;
     }
-    if (tid == 0) next_unit = atomicAdd(a.unit_counter, 1);
+    // (thread 0) place in a queue -> unit, moving on to the next queue when this one is empty; -1: all are
+    int q = (int)blockIdx.x % a.n_queues, hops = 0;
+    auto unit_of = [&](int v) -> int {
+        for (;;) {
+            const int tasks = (a.T - q + a.n_queues - 1) / a.n_queues;
+            if (v < tasks * nk) {
+                const int first = v / (a.queue_group * nk) * a.queue_group;
+                const int group = tasks - first < a.queue_group ? tasks - first : a.queue_group;
+                const int w = v - first * nk;
+                return (nk - 1 - w / group) * a.T + q + a.n_queues * (first + w % group);
+            }
+            if (++hops >= a.n_queues) return -1;
+            q = q + 1 < a.n_queues ? q + 1 : 0;
+            v = atomicAdd(a.unit_counter + q, 1);
+        }
+    };
+    if (tid == 0) next_unit = unit_of(atomicAdd(a.unit_counter + q, 1));
     for (;;) {
         __syncthreads();
         const int u = __builtin_amdgcn_readfirstlane(next_unit);     // uniform: what derives from it lives in scalar registers
         __syncthreads();                           // everyone has read it before it is written again
-        if (u >= n_units) break;
+        if (u < 0) break;
         // the unit after this one is asked for now; the answer is needed when this one is done
         int after = 0;
-        if (tid == 0) after = atomicAdd(a.unit_counter, 1);
-        const int ki = a.ki_end - 1 - u / a.T;
+        if (tid == 0) after = atomicAdd(a.unit_counter + q, 1);
+        const int ki = a.ki_begin + u / a.T;
         const int t = u % a.T;
         const int k = a.ks[ki];
         const bool skipped = a.done && a.done[t];     // the task's sweep stopped at a smaller k
@@ -1401,9 +2110,10 @@ __global__ __launch_bounds__(512, two_workgroups(DK, NTW, SEP) ? 4 : 2) void res
             if (a.trace)
                 for (int e = tid; e <= a.n_iter; e += blockDim.x) a.trace[slot * (a.n_iter + 1) + e] = 0.0;
         } else {
-            run_unit<DK, NTW, XT, SEP>(a, smem, ki, t, k);
+            if constexpr (NTW == 0) run_unit_fetched<DK, XT, SEP>(a, smem, ki, t, k);
+            else run_unit<DK, NTW, XT, SEP>(a, smem, ki, t, k);
         }
-        if (tid == 0) next_unit = after;            // (read by everyone after the barrier at the loop's head)
+        if (tid == 0) next_unit = unit_of(after);   // (read by everyone after the barrier at the loop's head)
         // The compiler leaves out the wait for this write across the loop's back edge: without it a wave may
         // pass the barrier and still read the unit before (LDS requests of different SIMDs are not ordered).
         __builtin_amdgcn_s_waitcnt(0xC07F);         // lgkmcnt(0)
@@ -1411,14 +2121,25 @@ __global__ __launch_bounds__(512, two_workgroups(DK, NTW, SEP) ? 4 : 2) void res
 }
 
 template <int DK, int NTW, typename XT, bool SEP = false>
-hipError_t launch_mfma_t(const SweepArgs &a, int nwaves, int64_t n_total, int cus, hipStream_t s)
+hipError_t launch_mfma_t(const SweepArgs &a, int nwaves, int64_t n_max, int64_t n_total, int cus, hipStream_t s)
 {
-    const unsigned pb = (unsigned)((n_total + 255) / 256);
-    if (pb && a.ki_begin == 0)
-        hipLaunchKernelGGL((pack_rows_kernel<DK, XT>), dim3(pb), dim3(256), 0, s, reinterpret_cast<const XT *>(a.X), a.ld, a.d,
-                           n_total, reinterpret_cast<_Float16 *>(a.xh), a.too_large);
     const int KP = a.kmax > 32 ? 64 : 32;
-    const size_t lds = MfmaLds<DK, SEP>::bytes(KP, nwaves, NTW);
+    size_t lds;
+    if constexpr (NTW == 0) {
+        const unsigned per_task = (unsigned)((n_max + kPackRows - 1) / kPackRows);
+        if (per_task && a.ki_begin == 0)
+            hipLaunchKernelGGL((pack_centred_kernel<DK, XT, SEP>), dim3(per_task * (unsigned)a.T), dim3(kPackRows), 0, s, a, (int)per_task);
+        lds = MfmaLds<DK, SEP>::base_bytes(KP) + FetchedQueue<DK>::kBytes * nwaves;
+    } else {
+        const unsigned pb = (unsigned)((n_total + 255) / 256);
+        if (pb && a.ki_begin == 0)
+            hipLaunchKernelGGL((pack_rows_kernel<DK, XT>), dim3(pb), dim3(256), 0, s, reinterpret_cast<const XT *>(a.X), a.ld, a.d,
+                               n_total, reinterpret_cast<_Float16 *>(a.xh), a.too_large);
+        lds = MfmaLds<DK, SEP>::bytes(KP, nwaves, NTW);
+    }
+    SweepArgs b = a;
+    b.n_queues = NTW == 0 && n_total * DK * 2 > 3 * 1024 * 1024 ? kUnitQueues : 1;
+    b.queue_group = b.n_queues == 1 ? a.T : kQueueGroup;
     auto kern = resident_mfma_kernel<DK, NTW, XT, SEP>;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -1432,7 +2153,7 @@ hipError_t launch_mfma_t(const SweepArgs &a, int nwaves, int64_t n_total, int cu
     unsigned grid = (unsigned)cus * (unsigned)per_cu;
     if (grid > units) grid = units;
     if (grid < 1) grid = 1;
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(nwaves * 64), lds, s, a);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(nwaves * 64), lds, s, b);
     return hipGetLastError();
 }
 
@@ -1466,6 +2187,8 @@ hipError_t compute_units(int &cus)
     return e != hipSuccess ? e : hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
 }
 
+bool mfma_fetches_rows(int d, int64_t n_max) { return n_max > (d > 32 ? 512 : 1024); }
+
 template <typename XT>
 static hipError_t launch_mfma_sweep_t(const SweepArgs &a, int64_t n_max, int64_t n_total, hipStream_t s)
 {
@@ -1473,42 +2196,38 @@ static hipError_t launch_mfma_sweep_t(const SweepArgs &a, int64_t n_max, int64_t
     // Row width: the next multiple of 16 with a slot to spare.  48 against 64 (64 tasks x 2048 rows x 40 knobs, k = 2..32):
     // six instructions per tile instead of eight and rows that fit the registers (8 spilled, not 112): 1815 -> 1530 us a step.
     const int DK = a.d <= 15 ? 16 : (a.d <= 31 || sep ? 32 : (a.d <= 47 ? 48 : 64));
-    // Tiles per wave.  16 hold 4096 rows in eight waves; fewer spread a smaller task over as many waves.
-    // Measured per step with the count above / with the one chosen:
-    //   2 where one task's latency counts (no more units than compute units), DK = 16, up to 512 rows: 256 rows
-    //     121 / 102 us, 500 rows 137 / 109 us; with many units 4 is as good (64 tasks x 500 rows 271 / 277 us)
-    //   8 up to 2048 rows, DK = 16: 4 tasks x 2000 rows 319 / 243 us, 64 tasks 987 / 953 us; DK = 32 only where
-    //     more than 32 centroids leave LDS for one workgroup per compute unit and there are units for
-    //     every place (64 tasks x 2000 rows x 24 knobs: k = 2..48 2037 / 1579 us, but k = 2..32 874 / 1014 us, and
-    //     4 tasks with k = 2..40 312 / 335 us)
     int cus = 0;
     const hipError_t e = compute_units(cus);
     if (e != hipSuccess) return e;
-    const int64_t units = (int64_t)a.T * (a.ki_end - a.ki_begin);
-    int ntw = 16;
-    if (n_max <= 512 && DK == 16 && units <= cus) ntw = 2;
-    else if (n_max <= 1024) ntw = 4;
-    else if (n_max <= 2048 && (DK == 16 || DK >= 48 || sep || (a.kmax > 32 && units > 2 * cus))) ntw = 8;
+    const int64_t units = (int64_t)a.T * a.n_k;            // of the whole list of k: a chunk of it is run the same way
+    if (mfma_fetches_rows(a.d, n_max)) {
+        // One workgroup per compute unit at most: sixteen waves hide what two workgroups of eight would (4096 x 12, k = 2..64, 63
+        // units: 8 / 16 waves 519 / 483 us a step).
+        const int nwaves = units <= cus ? 16 : 8;
+        if (sep) return launch_mfma_t<32, 0, uint8_t, true>(a, nwaves, n_max, n_total, cus, s);
+        if (DK == 16) return launch_mfma_t<16, 0, XT>(a, nwaves, n_max, n_total, cus, s);
+        if (DK == 32) return launch_mfma_t<32, 0, XT>(a, nwaves, n_max, n_total, cus, s);
+        if constexpr (sizeof(XT) == 2) {
+            if (DK == 48) return launch_mfma_t<48, 0, XT>(a, nwaves, n_max, n_total, cus, s);
+            return launch_mfma_t<64, 0, XT>(a, nwaves, n_max, n_total, cus, s);
+        }
+        return hipErrorInvalidValue;        // (byte knobs never come with more than 32 knobs)
+    }
+    // Rows in registers: four tiles per wave hold 1024 rows in eight waves.  Two where one task's latency counts (no more units than
+    // compute units), DK = 16, up to 512 rows: 256 rows 121 / 102 us a step, 500 rows 137 / 109 us; with many
+    // units four are as good (64 tasks x 500 rows 271 / 277 us).
+    const int ntw = n_max <= 512 && DK == 16 && (int64_t)a.T * (a.ki_end - a.ki_begin) <= cus ? 2 : 4;
     int nwaves = (int)((n_max + 32 * ntw - 1) / (32 * ntw));
     if (nwaves < 1) nwaves = 1;
-    if (nwaves > 8) nwaves = 8;
-    if (sep) {
-        if (ntw == 4) return launch_mfma_t<32, 4, uint8_t, true>(a, nwaves, n_total, cus, s);
-        return ntw == 8 ? launch_mfma_t<32, 8, uint8_t, true>(a, nwaves, n_total, cus, s)
-                        : launch_mfma_t<32, 16, uint8_t, true>(a, nwaves, n_total, cus, s);
+    if (sep) return launch_mfma_t<32, 4, uint8_t, true>(a, nwaves, n_max, n_total, cus, s);
+    if (DK == 16)
+        return ntw == 2 ? launch_mfma_t<16, 2, XT>(a, nwaves, n_max, n_total, cus, s) : launch_mfma_t<16, 4, XT>(a, nwaves, n_max, n_total, cus, s);
+    if (DK == 32) return launch_mfma_t<32, 4, XT>(a, nwaves, n_max, n_total, cus, s);
+    if constexpr (sizeof(XT) == 2) {
+        if (DK == 48) return launch_mfma_t<48, 4, XT>(a, nwaves, n_max, n_total, cus, s);
+        return launch_mfma_t<64, 4, XT>(a, nwaves, n_max, n_total, cus, s);
     }
-    if (DK == 16) {
-        if (ntw == 2) return launch_mfma_t<16, 2, XT>(a, nwaves, n_total, cus, s);
-        if (ntw == 4) return launch_mfma_t<16, 4, XT>(a, nwaves, n_total, cus, s);
-        return ntw == 8 ? launch_mfma_t<16, 8, XT>(a, nwaves, n_total, cus, s) : launch_mfma_t<16, 16, XT>(a, nwaves, n_total, cus, s);
-    }
-    if (DK == 32) {
-        if (ntw == 4) return launch_mfma_t<32, 4, XT>(a, nwaves, n_total, cus, s);
-        return ntw == 8 ? launch_mfma_t<32, 8, XT>(a, nwaves, n_total, cus, s) : launch_mfma_t<32, 16, XT>(a, nwaves, n_total, cus, s);
-    }
-    if (sizeof(XT) == 1) return hipErrorInvalidValue;        // (byte knobs never come with more than 32 knobs)
-    if (DK == 48) return ntw == 4 ? launch_mfma_t<48, 4, uint16_t>(a, nwaves, n_total, cus, s) : launch_mfma_t<48, 8, uint16_t>(a, nwaves, n_total, cus, s);
-    return ntw == 4 ? launch_mfma_t<64, 4, uint16_t>(a, nwaves, n_total, cus, s) : launch_mfma_t<64, 8, uint16_t>(a, nwaves, n_total, cus, s);
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_mfma_sweep(const SweepArgs &a, int64_t n_max, int64_t n_total, hipStream_t s)
