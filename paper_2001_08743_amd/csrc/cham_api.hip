@@ -237,6 +237,13 @@ SweepPath choose_path(const Plan &pl, int d, int flags, int xbytes = 1)
     return SweepPath::kStream;
 }
 
+// The streaming path's lists of k for tasks of at most 4096 rows (no flag asks for the streaming kernels): one launch of the
+// resident matrix-core kernel in its form for many centroids.
+bool many_centroids(const Plan &pl, SweepPath path, int d, int flags)
+{
+    return path == SweepPath::kStream && !(flags & CHAM_F_STREAMING) && mfma_many_fits(d, pl.kmax, pl.n_max);
+}
+
 struct SweepWs {
     int64_t blob = 0, init_rows = 0, ndist = 0, passes = 0, counters = 0, xh = 0, task_ojf = 0, norms = 0, labbuf = 0, total = 0;
     int64_t fetched = 0;           // of the total: what the matrix-core kernel that fetches its rows needs beside them
@@ -339,8 +346,9 @@ static int xh_halfs_of(SweepPath path, int xbytes, int d)
 }
 
 // Two-byte knobs: whatever the promise, which adds the packed rows alone to the workspace.
-static bool fetched_rows(const Plan &pl, SweepPath path, int xbytes, int d)
+static bool fetched_rows(const Plan &pl, SweepPath path, int xbytes, int d, int flags)
 {
+    if (many_centroids(pl, path, d, flags)) return true;
     return (xbytes == 2 ? mfma_path_fits_u16(d, pl.kmax, pl.n_max) : path == SweepPath::kMfmaResident) && mfma_fetches_rows(d, pl.n_max);
 }
 
@@ -354,7 +362,7 @@ static int64_t sweep_ws_bytes(int xbytes, int64_t ld, int32_t d, const int64_t *
     if (rc != CHAM_OK) return rc;
     const SweepPath path = choose_path(pl, d, flags, xbytes);
     if (xbytes == 2 && path == SweepPath::kVectorResident && !u16_fits(pl)) return CHAM_E_BAD_K;
-    const SweepWs w = sweep_ws(pl, ld, true, path == SweepPath::kStream, task_off, xh_halfs_of(path, xbytes, d), fetched_rows(pl, path, xbytes, d), d <= 32 ? 32 : 64);
+    const SweepWs w = sweep_ws(pl, ld, true, path == SweepPath::kStream && !many_centroids(pl, path, d, flags), task_off, xh_halfs_of(path, xbytes, d), fetched_rows(pl, path, xbytes, d, flags), d <= 32 ? 32 : 64);
     if (fetched) *fetched = w.fetched;
     return w.total;
 }
@@ -395,7 +403,7 @@ static int32_t sweep_impl(const void *Xv, int xbytes, int64_t ld, int32_t d, con
     if (xbytes == 2 && (flags & CHAM_F_STREAMING)) return CHAM_E_BAD_FLAG;
     const SweepPath path = choose_path(pl, d, flags, xbytes);
     if (xbytes == 2 && path == SweepPath::kVectorResident && !u16_fits(pl)) return CHAM_E_BAD_K;
-    const SweepWs w = sweep_ws(pl, ld, labels == nullptr, path == SweepPath::kStream, task_off, xh_halfs_of(path, xbytes, d), fetched_rows(pl, path, xbytes, d), d <= 32 ? 32 : 64);
+    const SweepWs w = sweep_ws(pl, ld, labels == nullptr, path == SweepPath::kStream && !many_centroids(pl, path, d, flags), task_off, xh_halfs_of(path, xbytes, d), fetched_rows(pl, path, xbytes, d, flags), d <= 32 ? 32 : 64);
     const bool chunked = chunk > 0;
     const int64_t done_bytes = chunked ? up((int64_t)T * 4) : 0;
     if (!workspace || workspace_bytes < w.total + done_bytes) return CHAM_E_WORKSPACE;
@@ -454,7 +462,8 @@ static int32_t sweep_impl(const void *Xv, int xbytes, int64_t ld, int32_t d, con
         if (e != hipSuccess) return hip_fail(e);
     }
     int cus = 0;
-    if (path == SweepPath::kStream) {
+    const bool many = many_centroids(pl, path, d, flags);
+    if (path == SweepPath::kStream && !many) {
         if (stream_lds_bytes(d, w.kpm) > 160 * 1024) return CHAM_E_BAD_K;
         e = compute_units(cus);
         if (e != hipSuccess) return hip_fail(e);
@@ -467,7 +476,9 @@ static int32_t sweep_impl(const void *Xv, int xbytes, int64_t ld, int32_t d, con
         a.ki_end = ki_end;
         a.unit_counter = reinterpret_cast<int *>(ws + w.counters) + (int64_t)ki_begin * kUnitQueues;
         a.done = ki_begin > 0 ? done : nullptr;
-        if (path == SweepPath::kStream) {
+        if (many) {
+            e = launch_mfma_many(a, pl.n_max, pl.n_total, s);
+        } else if (path == SweepPath::kStream) {
             // first workgroup of every unit, in launch order (largest k first)
             const int n_units = (ki_end - ki_begin) * T;        // units of this chunk, largest k first
             const int rpw = stream_rows_per_wg(pl, task_off, ki_end - ki_begin, inertia_trace != nullptr, cus);

@@ -454,9 +454,10 @@ __device__ __forceinline__ void apply_changes(const Queue &Q, int cnt, int *S, i
 // at most; the loads of 256 rows are under way at any time.  SEP: every knob row is in use, so the
 // sizes are counted from the labels.
 constexpr int kRawOffset = -128;
-template <int DK, int NG, bool SEP, typename Queue>
+// first: the 64 centroids [first, first + 64) are summed; MANY: there are more than those (labels up to 223).
+template <int DK, int NG, bool SEP, bool MANY = false, typename Queue>
 __device__ __forceinline__ void full_sums(const Queue &Q, int *S, int *n, const uint8_t *xw, int64_t ld,
-                                          int d, int k, int rows_here, int lane)
+                                          int d, int k_all, int rows_here, int lane, int first = 0)
 {
     typedef int int4v __attribute__((ext_vector_type(4)));
     typedef int int16v __attribute__((ext_vector_type(16)));
@@ -464,11 +465,14 @@ __device__ __forceinline__ void full_sums(const Queue &Q, int *S, int *n, const 
     constexpr int kGroups = NG / W;
     constexpr int kDepth = kGroups < 4 / W ? kGroups : 4 / W;
     const int m32 = lane & 31, kh = lane >> 5;
+    const int k = k_all - first;
+    S += first * (DK + 1);
+    n += first;
     const bool two = k > 32;
     const bool knob = m32 < d;
     const uint8_t *xp = xw + (int64_t)(knob ? m32 : 0) * ld + 32 * W * kh;
     const unsigned char *lp = Q.lab() + 32 * W * kh;
-    const int c4a = (int)(Queue::stored(m32) * 0x01010101u), c4b = (int)(Queue::stored(m32 + 32) * 0x01010101u);
+    const int c4a = (int)(Queue::stored(first + m32) * 0x01010101u), c4b = (int)(Queue::stored(first + m32 + 32) * 0x01010101u);
     int16v acc0, acc1;
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
@@ -490,7 +494,10 @@ __device__ __forceinline__ void full_sums(const Queue &Q, int *S, int *n, const 
     auto members = [](const int4v &l, int c4) {
         int4v o;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) o[e] = ~((l[e] ^ c4) + 0x7F7F7F7F) & (int)0x80808080;
+        for (int e = 0; e < 4; ++e) {
+            const int t = l[e] ^ c4;
+            o[e] = MANY ? ~(((t & 0x7F7F7F7F) + 0x7F7F7F7F) | t) & (int)0x80808080 : ~(t + 0x7F7F7F7F) & (int)0x80808080;
+        }
         return o;
     };
 
@@ -503,7 +510,8 @@ __device__ __forceinline__ void full_sums(const Queue &Q, int *S, int *n, const 
 #pragma unroll
             for (int i = 0; i < 2 * W; ++i) {
                 const int4v A = w[g % kDepth][i] ^ (int)0x80808080;
-                const int4v l = *reinterpret_cast<const int4v *>(lp + 64 * W * g + 16 * i) & 0x7F7F7F7F;
+                int4v l = *reinterpret_cast<const int4v *>(lp + 64 * W * g + 16 * i);
+                if (!MANY) l = l & 0x7F7F7F7F;
                 acc0 = __builtin_amdgcn_mfma_i32_32x32x32_i8(A, members(l, c4a), acc0, 0, 0, 0);
                 if (two) acc1 = __builtin_amdgcn_mfma_i32_32x32x32_i8(A, members(l, c4b), acc1, 0, 0, 0);
             }
@@ -526,7 +534,7 @@ __device__ __forceinline__ void full_sums(const Queue &Q, int *S, int *n, const 
     if (SEP) {
         for (int e = lane; e < rows_here; e += 64) {
             const unsigned v = Q.lab()[e];
-            if (v < 64u) atomicAdd(&n[Queue::centroid(v)], 1);
+            if (v < 64u) atomicAdd(&n[Queue::centroid(v)], 1);       // (k <= 64)
         }
     }
 }
@@ -1448,6 +1456,106 @@ struct FetchedQueue {
     static __device__ __forceinline__ unsigned centroid(unsigned v) { return ((v & 31u) << 1) | (v >> 5); }
 };
 
+// ... of the form for more than 64 centroids: undecided rows with (row, candidate) pairs instead of masks, and what the evaluation of
+// the pairs leaves per row.  Chunk c / 64 of a centroid is bits 6 and 7 of its stored label.
+constexpr int kManyCentroids = 224;                         // (labels 0xFE and 0xFF mean undecided and none; LDS)
+template <int DK>
+struct ManyQueue {
+    static constexpr int kRows = 512;
+    static constexpr int kCap = 96;                         // (a tile adds at most 32)
+    static constexpr int kPairs = 256;
+    static constexpr int kChanges = 64;
+    static constexpr size_t kOffBestC = (size_t)kCap * 8;
+    static constexpr size_t kOffPid = kOffBestC + (size_t)kCap * 4;
+    static constexpr size_t kOffPairs = kOffPid + (size_t)kCap * 2;
+    static constexpr size_t kOffCount = kOffPairs + (size_t)kPairs * 4;
+    static constexpr size_t kOffLab = kOffCount + 16;
+    static_assert(kPairs >= kChanges && kOffLab % 16 == 0, "the label changes fit the pairs' place");
+    static __host__ __device__ size_t bytes(int nwaves) { return kOffLab + 2 * (size_t)(nwaves == 16 ? kRows / 2 : kRows); }
+    unsigned char *base;
+    int rows;                                               // rows a wave owns at most
+    __device__ ManyQueue(unsigned char *wb, int nwaves) : base(wb), rows(nwaves == 16 ? kRows / 2 : kRows) {}
+    __device__ unsigned long long *best() const { return reinterpret_cast<unsigned long long *>(base); }            // [kCap] smallest distance (bits)
+    __device__ int *best_c() const { return reinterpret_cast<int *>(base + kOffBestC); }                            // [kCap] lowest centroid attaining it
+    __device__ unsigned short *rec_pid() const { return reinterpret_cast<unsigned short *>(base + kOffPid); }       // [kCap]
+    __device__ unsigned *pairs() const { return reinterpret_cast<unsigned *>(base + kOffPairs); }                   // [kPairs] queued row << 8 | centroid
+    __device__ unsigned *changes() const { return pairs(); }                                                         // [kChanges] new label | previous << 8 | row << 16
+    __device__ unsigned *n_pairs() const { return reinterpret_cast<unsigned *>(base + kOffCount); }
+    __device__ unsigned char *lab() const { return base + kOffLab; }
+    __device__ unsigned char *lab_new() const { return base + kOffLab + rows; }
+    static __device__ __forceinline__ unsigned stored(unsigned c) { return (c & 0xC0u) | ((c & 63u) >> 1) | ((c & 1u) << 5); }
+    static __device__ __forceinline__ unsigned centroid(unsigned v) { return (v & 0xC0u) | ((v & 31u) << 1) | ((v >> 5) & 1u); }
+};
+
+// Exact evaluation of the queued rows against their candidates, one lane per (row, centroid) pair: the distance as
+// sum_j ((double)x_j - mu_j)^2 with j ascending, no fused multiply-add; per row the smallest distance, then the lowest centroid
+// attaining it.  all: every centroid of every queued row instead of the listed pairs (they found no room).
+template <int DK>
+__device__ __forceinline__ void resolve_pairs(const ManyQueue<DK> &Q, int nrec, bool all, const unsigned char *packed, const double *mu64T,
+                                              const float *ojf, int KP, int k, int d, int lane)
+{
+    for (int r = lane; r < nrec; r += 64) {
+        Q.best()[r] = ~0ull;
+        Q.best_c()[r] = 0x7fffffff;
+    }
+    __builtin_amdgcn_wave_barrier();
+    const unsigned np = all ? (unsigned)(nrec * k) : *Q.n_pairs();
+    auto distance = [&](unsigned p, int &r, int &c) {
+        if (all) {
+            r = (int)(p / (unsigned)k);
+            c = (int)(p % (unsigned)k);
+        } else {
+            const unsigned w = Q.pairs()[p];
+            r = (int)(w >> 8);
+            c = (int)(w & 0xFFu);
+        }
+        const unsigned char *x = packed + packed_at(Q.rec_pid()[r], 0, DK);
+        double s = 0.0;
+        for (int j0 = 0; j0 < d; j0 += 8) {
+            const half8 xq = *reinterpret_cast<const half8 *>(x + packed_at(0, j0 >> 3, DK));
+            double mu[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) mu[i] = mu64T[(size_t)(j0 + i) * KP + c];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                if (j0 + i < d) {
+                    const double tq = (double)((float)xq[i] + ojf[j0 + i]) - mu[i];
+                    s = s + tq * tq;
+                }
+            }
+        }
+        return (unsigned long long)__double_as_longlong(s);
+    };
+    if (np <= 64u) {                 // the usual case: a distance is evaluated once
+        int r = 0, c = 0;
+        unsigned long long mine = ~0ull;
+        if ((unsigned)lane < np) {
+            mine = distance((unsigned)lane, r, c);
+            atomicMin(&Q.best()[r], mine);
+        }
+        __builtin_amdgcn_wave_barrier();
+        if ((unsigned)lane < np && Q.best()[r] == mine) atomicMin(&Q.best_c()[r], c);
+    } else {
+        for (unsigned p = lane; p < np; p += 64) {
+            int r, c;
+            const unsigned long long mine = distance(p, r, c);
+            atomicMin(&Q.best()[r], mine);
+        }
+        __builtin_amdgcn_wave_barrier();
+        for (unsigned p = lane; p < np; p += 64) {
+            int r, c;
+            const unsigned long long mine = distance(p, r, c);
+            if (Q.best()[r] == mine) atomicMin(&Q.best_c()[r], c);
+        }
+    }
+    __builtin_amdgcn_wave_barrier();
+    for (int r = lane; r < nrec; r += 64) {
+        const int c = Q.best_c()[r];
+        Q.lab_new()[Q.rec_pid()[r]] = (unsigned char)ManyQueue<DK>::stored(c < k ? c : 0);
+    }
+    __builtin_amdgcn_wave_barrier();
+}
+
 // Listed label changes of this wave (centroids, not stored labels) -> integer sums and sizes: 256 / DK rows per step, one lane per
 // (row, four knobs), the knobs from the packed copy, those of four steps under way together.
 template <int DK, typename Queue>
@@ -1508,23 +1616,32 @@ constexpr int rows_ahead(int DK, bool two, bool SEP) { return DK == 16 || (DK ==
 
 constexpr int kParts = 16;
 
+// Centroid rows LDS holds (KP).
+template <bool MANY>
+__host__ __device__ constexpr int centroid_rows(int kmax) { return MANY ? (kmax + 31) / 32 * 32 : (kmax > 32 ? 64 : 32); }
+
 // One unit, its rows fetched from the packed copy in every pass (L2 holds the rows of the tasks under way) instead of kept
 // in registers: 128 registers a wave and 80 KiB of LDS then let two workgroups share a compute unit whatever the size of the
 // task, and one's barriers and chains of dependent LDS accesses run under the other's tiles.
-template <int DK, typename XT, bool SEP>
+// MANY: k up to kManyCentroids, a tile against 64 centroids at a time.  A chunk of 64 leaves its minimum and the marks within the
+// bound of it; the marks of a chunk count iff its minimum is within the bound of the overall one (that keeps every centroid
+// within the bound of the overall minimum, and some up to two bounds away).  LDS holds one workgroup per compute unit, of
+// sixteen waves up to k = 192.  16 tasks of up to 2500 x 24, k = 72, 96, 128, 20 steps: the streaming kernels' 43
+// launches 645 us a step, one launch of this NEWFIG us.
+template <int DK, typename XT, bool SEP, bool MANY>
 __device__ __forceinline__ void run_unit_fetched(const SweepArgs &a, unsigned char *smem, int ki, int t, int k)
 {
     constexpr bool kByteKnobs = sizeof(XT) == 1;
     constexpr float kBiasScale = bias_scale(kByteKnobs);
     constexpr bool kAllowTwo = DK <= 32;      // (k <= 32 with wider rows)
-    typedef FetchedQueue<DK> Queue;
+    typedef typename std::conditional<MANY, ManyQueue<DK>, FetchedQueue<DK>>::type Queue;
     const XT *X = reinterpret_cast<const XT *>(a.X);
     const bool two = kAllowTwo && k > 32;
     constexpr int NS = DK / 16;          // distinct B fragments per row
     constexpr int NS2 = 2 * NS;          // chained instructions per 32x32 tile, without the bias step
     constexpr int NSA = NS2 + (SEP ? 1 : 0);   // ... with it
     constexpr int CH = NS2 == 6 ? 4 : 16 / NS2;   // scores handled between two matrix instructions
-    const int KP = a.kmax > 32 ? 64 : 32;
+    const int KP = centroid_rows<MANY>(a.kmax);
     MfmaLds<DK, SEP> U(smem, KP);
 
     const int tid = threadIdx.x;
@@ -1544,7 +1661,12 @@ __device__ __forceinline__ void run_unit_fetched(const SweepArgs &a, unsigned ch
     const int64_t crow = (int64_t)t * a.Ksum + a.koff[ki];
     uint8_t *labrow = a.labbuf + (int64_t)ki * a.ld;
 
-    Queue Q(U.wave_base + Queue::kBytes * wave);
+    auto region = [&]() {
+        if constexpr (MANY) return Queue(U.wave_base + Queue::bytes(nwaves) * wave, nwaves);
+        else return Queue(U.wave_base + Queue::kBytes * wave);
+    };
+    const Queue Q = region();
+    const int lab_rows = nwaves == 16 && MANY ? Queue::kRows / 2 : Queue::kRows;       // rows the label tables hold
     // Rows of the task in kParts equal parts of whole groups of 64; a wave has one, or two in a row.  The loss is summed part by
     // part, so that its order does not depend on the number of waves.
     const int part_rows = nrows > 64 * kParts ? (nrows + 64 * kParts - 1) / (64 * kParts) * 64 : 64;
@@ -1582,7 +1704,7 @@ __device__ __forceinline__ void run_unit_fetched(const SweepArgs &a, unsigned ch
         U.acc64[0] = 0ull;
         U.acc64[1] = 0ull;
     }
-    for (int e = lane_id; e < 2 * Queue::kRows / 4; e += 64) reinterpret_cast<unsigned *>(Q.lab())[e] = 0xFFFFFFFFu;      // no row has a label yet
+    for (int e = lane_id; e < 2 * lab_rows / 4; e += 64) reinterpret_cast<unsigned *>(Q.lab())[e] = 0xFFFFFFFFu;      // no row has a label yet
     __syncthreads();
     // padding centroid rows (beyond k) carry a huge bias so that they never win
     for (int c = k + tid; c < KP; c += blockDim.x) {
@@ -1613,7 +1735,10 @@ __device__ __forceinline__ void run_unit_fetched(const SweepArgs &a, unsigned ch
     float bound;
     {
         const float x2 = __int_as_float(U.stamp[1]);
-        float m2 = wave_max_nonneg(lane_id < k ? U.bias[lane_id] : 0.0f);
+        float m2 = lane_id < k ? U.bias[lane_id] : 0.0f;
+        if (MANY)
+            for (int c = lane_id + 64; c < k; c += 64) m2 = __builtin_fmaxf(m2, U.bias[c]);
+        m2 = wave_max_nonneg(m2);
         m2 = __builtin_fmaxf(m2, x2) * 1.000001f;
         // starts beyond the range of the screen (their operands are clamped): every centroid is a candidate of every row
         if (!(m2 <= max_screened(kByteKnobs))) m2 = 1.0e30f;
@@ -1701,8 +1826,128 @@ __device__ __forceinline__ void run_unit_fetched(const SweepArgs &a, unsigned ch
         const bool last_pass = (it == a.n_iter);
         passes_run = it + 1;
         int nrec = 0;                    // queued rows that the screen could not decide
+        bool all_pairs = false;          // MANY: the list of pairs is not complete
         const uint64_t undecided = it == 0 ? ~0ull : 0ull;
 
+        if constexpr (MANY) {
+            constexpr int kChunks = (kManyCentroids + 63) / 64;
+            const int lane = opaque(lane_id), n32 = lane & 31;
+            const bool upper = lane >= 32;
+            const unsigned lane_off = (unsigned)(16 * lane);
+            const int nch = (k + 63) >> 6, kpu = (k + 31) & ~31;
+            const float16v zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            half8 Bn[NS];
+            if (lane == 0) *Q.n_pairs() = 0u;
+            if (wave_live) fetch(Bn, packed, lane_off);
+            for (int nt = 0; nt < ntiles; ++nt) {
+                half8 Bt[NS];
+#pragma unroll
+                for (int f = 0; f < NS; ++f) Bt[f] = Bn[f];
+                fetch(Bn, packed + (nt + 1) * kTileBytes, lane_off);
+                const uint32_t prev = Q.lab()[nt * 32 + n32];
+                uint32_t near[kChunks];
+                float least[kChunks];
+                float best = __builtin_inff();
+#pragma unroll
+                for (int ch = 0; ch < kChunks; ++ch) {
+                    near[ch] = 0u;
+                    least[ch] = __builtin_inff();
+                    if (ch < nch) {
+                        const bool has1 = (2 * ch + 1) * 32 < kpu;
+                        float16v accA, accB;
+#pragma unroll
+                        for (int s = 0; s < NS2; ++s)
+                            accA = __builtin_amdgcn_mfma_f32_32x32x16_f16(U.afrag[((2 * ch) * NS2 + s) * 64 + lane], Bt[s % NS], s == 0 ? zero16 : accA, 0, 0, 0);
+                        if (has1) {
+#pragma unroll
+                            for (int s = 0; s < NS2; ++s)
+                                accB = __builtin_amdgcn_mfma_f32_32x32x16_f16(U.afrag[((2 * ch + 1) * NS2 + s) * 64 + lane], Bt[s % NS], s == 0 ? zero16 : accB, 0, 0, 0);
+                        }
+                        auto min16 = [](const float16v &acc) {
+                            float m = vmin3(acc[0], acc[1], acc[2]);
+#pragma unroll
+                            for (int i = 3; i < 15; i += 2) m = vmin3(m, acc[i], acc[i + 1]);
+                            return vmin(m, acc[15]);
+                        };
+                        float m = min16(accA);
+                        if (has1) m = vmin(m, min16(accB));
+                        unsigned lo, hi;
+                        both_halves(__float_as_uint(m), lo, hi);
+                        m = vmin(__uint_as_float(lo), __uint_as_float(hi));
+                        const float thr = m + bound;
+                        uint32_t bits = 0;
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) bits = __builtin_amdgcn_alignbit(bits, __float_as_uint(accA[i] - thr), 31);
+                        if (has1) {
+#pragma unroll
+                            for (int i = 0; i < 16; ++i) bits = __builtin_amdgcn_alignbit(bits, __float_as_uint(accB[i] - thr), 31);
+                        } else {
+                            bits <<= 16;
+                        }
+                        near[ch] = bits;
+                        least[ch] = m;
+                        best = vmin(best, m);
+                    }
+                }
+                // a tile whose rows all have exactly their current label marked is done (but in the first pass)
+                const float lim = best + bound;
+                const uint64_t place = 0x8000000000000000ull >> (prev & 63u);
+                const uint32_t own = upper ? (uint32_t)place : (uint32_t)(place >> 32);
+                uint32_t diff = 0u;
+#pragma unroll
+                for (int ch = 0; ch < kChunks; ++ch) {
+                    near[ch] = least[ch] <= lim ? near[ch] : 0u;
+                    diff |= near[ch] ^ ((prev >> 6) == (uint32_t)ch ? own : 0u);
+                }
+                if ((__ballot(diff != 0u) | undecided) == 0) continue;
+                const uint32_t live32 = live_rows(nt);
+                int cnt = 0, at = 0;                       // marks of this lane half, stored label of one of them
+#pragma unroll
+                for (int ch = 0; ch < kChunks; ++ch) {
+                    cnt += __popc(near[ch]);
+                    at = near[ch] ? 64 * ch + (upper ? 32 : 0) + __clz((int)near[ch]) : at;
+                }
+                unsigned c_lo, c_hi, at_lo, at_hi;
+                both_halves((unsigned)cnt, c_lo, c_hi);
+                both_halves((unsigned)at, at_lo, at_hi);
+                const bool live = (live32 >> n32) & 1u;
+                const bool flagged = live && c_lo + c_hi != 1u;
+                const uint32_t fm = (uint32_t)__ballot(flagged);
+                if (fm) {
+                    if (flagged) {
+                        const int rs = nrec + __popc(fm & ((1u << n32) - 1u));
+                        if (!upper) Q.rec_pid()[rs] = (unsigned short)(nt * 32 + n32);
+                        unsigned pos = atomicAdd(Q.n_pairs(), (unsigned)cnt);
+#pragma unroll
+                        for (int ch = 0; ch < kChunks; ++ch) {
+                            uint32_t m = near[ch];
+                            while (m) {
+                                const int q = __clz((int)m);
+                                m &= ~(0x80000000u >> q);
+                                const int c = 64 * ch + slot_centroid(q, upper ? 1 : 0);
+                                if (pos < (unsigned)Queue::kPairs) Q.pairs()[pos] = (unsigned)(rs << 8 | c);
+                                ++pos;
+                            }
+                        }
+                        if (pos > (unsigned)Queue::kPairs) all_pairs = true;
+                    }
+                    // no candidate at all cannot happen (the smallest score is always one); if it does, every centroid is one
+                    if (flagged && c_lo + c_hi == 0u) all_pairs = true;
+                    nrec += __popc(fm);
+                    if (nrec > Queue::kCap - 32) {         // the next tile might not fit
+                        resolve_pairs<DK>(Q, nrec, __any(all_pairs), packed, U.mu64T, U.ojf, KP, k, d, lane);
+                        nrec = 0;
+                        all_pairs = false;
+                        if (lane == 0) *Q.n_pairs() = 0u;
+                        __builtin_amdgcn_wave_barrier();
+                    }
+                }
+                const uint32_t now = !live ? 0xFFu : (flagged ? 0xFEu : (c_lo ? at_lo : at_hi));
+                // (a row resolved just now has its label already)
+                if (!upper && now != 0xFEu) Q.lab_new()[nt * 32 + n32] = (unsigned char)now;
+            }
+            if (nrec) resolve_pairs<DK>(Q, nrec, __any(all_pairs), packed, U.mu64T, U.ojf, KP, k, d, lane);
+        } else {
         // The tile loop from tile nt on, compiled once per number of live registers of the last m-tile (4, 8, 12 or 16), so that
         // the epilogue has no branches.  Returns the tile to go on with: ntiles, or an earlier one when the queue has to be emptied.
         auto tile_pass = [&](auto live_tag, auto two_tag, int nt) -> int {
@@ -1905,6 +2150,7 @@ __device__ __forceinline__ void run_unit_fetched(const SweepArgs &a, unsigned ch
                 }
             } while (nt < ntiles);
         }
+        }
 
         // ---- label changes -> integer sums and sizes.  Both label tables agree but for this pass's changes (a row without a label
         // yet has previous = 0xFF; rows outside the task keep 0xFF): a lane compares four rows at a time.
@@ -1917,8 +2163,8 @@ __device__ __forceinline__ void run_unit_fetched(const SweepArgs &a, unsigned ch
             for (int first = 0; first < rows_wave; first += 256) {
                 const unsigned at = first + 4 * lane;
                 unsigned *oldp = reinterpret_cast<unsigned *>(Q.lab() + at);
-                const unsigned cur4 = at < (unsigned)Queue::kRows ? *reinterpret_cast<const unsigned *>(Q.lab_new() + at) : 0u;
-                const unsigned prev4 = at < (unsigned)Queue::kRows ? *oldp : 0u;
+                const unsigned cur4 = at < (unsigned)lab_rows ? *reinterpret_cast<const unsigned *>(Q.lab_new() + at) : 0u;
+                const unsigned prev4 = at < (unsigned)lab_rows ? *oldp : 0u;
                 const unsigned diff = cur4 ^ prev4;
                 if (!__ballot(diff != 0u)) continue;
                 if (diff) *oldp = cur4;
@@ -1944,7 +2190,14 @@ __device__ __forceinline__ void run_unit_fetched(const SweepArgs &a, unsigned ch
             }
             if (full_mode) {
                 __builtin_amdgcn_wave_barrier();
-                if (wave_live) full_sums<DK, Queue::kRows / 64, SEP>(Q, U.S, U.n, xw, a.ld, d, k, rows_wave, lane_id);
+                if (wave_live) {
+                    if constexpr (MANY) {
+                        for (int first = 0; first < k; first += 64)
+                            full_sums<DK, Queue::kRows / 64, SEP, true>(Q, U.S, U.n, xw, a.ld, d, k, rows_wave, lane_id, first);
+                    } else {
+                        full_sums<DK, Queue::kRows / 64, SEP>(Q, U.S, U.n, xw, a.ld, d, k, rows_wave, lane_id);
+                    }
+                }
             } else if (cnt) {
                 apply_listed<DK>(Q, cnt, packed, U.S, U.n, U.dirty, U.ojf, d, it);
             }
@@ -2045,7 +2298,7 @@ constexpr bool two_workgroups(int DK, int NTW, bool SEP) { return NTW == 0 || DK
 constexpr int kQueueGroup = 4;
 
 // NTW = 0: rows fetched per pass (run_unit_fetched), otherwise tiles of rows a wave keeps in registers (run_unit).
-template <int DK, int NTW, typename XT, bool SEP>
+template <int DK, int NTW, typename XT, bool SEP, bool MANY>
 __global__ __launch_bounds__(NTW == 0 ? 1024 : 512, two_workgroups(DK, NTW, SEP) ? 4 : 2) void resident_mfma_kernel(const SweepArgs a)
 {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -2110,7 +2363,7 @@ __global__ __launch_bounds__(NTW == 0 ? 1024 : 512, two_workgroups(DK, NTW, SEP)
             if (a.trace)
                 for (int e = tid; e <= a.n_iter; e += blockDim.x) a.trace[slot * (a.n_iter + 1) + e] = 0.0;
         } else {
-            if constexpr (NTW == 0) run_unit_fetched<DK, XT, SEP>(a, smem, ki, t, k);
+            if constexpr (NTW == 0) run_unit_fetched<DK, XT, SEP, MANY>(a, smem, ki, t, k);
             else run_unit<DK, NTW, XT, SEP>(a, smem, ki, t, k);
         }
         if (tid == 0) next_unit = unit_of(after);   // (read by everyone after the barrier at the loop's head)
@@ -2120,16 +2373,16 @@ __global__ __launch_bounds__(NTW == 0 ? 1024 : 512, two_workgroups(DK, NTW, SEP)
     }
 }
 
-template <int DK, int NTW, typename XT, bool SEP = false>
+template <int DK, int NTW, typename XT, bool SEP = false, bool MANY = false>
 hipError_t launch_mfma_t(const SweepArgs &a, int nwaves, int64_t n_max, int64_t n_total, int cus, hipStream_t s)
 {
-    const int KP = a.kmax > 32 ? 64 : 32;
+    const int KP = centroid_rows<MANY>(a.kmax);
     size_t lds;
     if constexpr (NTW == 0) {
         const unsigned per_task = (unsigned)((n_max + kPackRows - 1) / kPackRows);
         if (per_task && a.ki_begin == 0)
             hipLaunchKernelGGL((pack_centred_kernel<DK, XT, SEP>), dim3(per_task * (unsigned)a.T), dim3(kPackRows), 0, s, a, (int)per_task);
-        lds = MfmaLds<DK, SEP>::base_bytes(KP) + FetchedQueue<DK>::kBytes * nwaves;
+        lds = MfmaLds<DK, SEP>::base_bytes(KP) + (MANY ? ManyQueue<DK>::bytes(nwaves) : FetchedQueue<DK>::kBytes) * nwaves;
     } else {
         const unsigned pb = (unsigned)((n_total + 255) / 256);
         if (pb && a.ki_begin == 0)
@@ -2140,7 +2393,7 @@ hipError_t launch_mfma_t(const SweepArgs &a, int nwaves, int64_t n_max, int64_t 
     SweepArgs b = a;
     b.n_queues = NTW == 0 && n_total * DK * 2 > 3 * 1024 * 1024 ? kUnitQueues : 1;
     b.queue_group = b.n_queues == 1 ? a.T : kQueueGroup;
-    auto kern = resident_mfma_kernel<DK, NTW, XT, SEP>;
+    auto kern = resident_mfma_kernel<DK, NTW, XT, SEP, MANY>;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
@@ -2228,6 +2481,22 @@ static hipError_t launch_mfma_sweep_t(const SweepArgs &a, int64_t n_max, int64_t
         return launch_mfma_t<64, 4, XT>(a, nwaves, n_max, n_total, cus, s);
     }
     return hipErrorInvalidValue;
+}
+
+// k beyond 64 (byte knobs, d <= 31): within what LDS holds beside a wave's labels.
+bool mfma_many_fits(int d, int kmax, int64_t n_max)
+{
+    return d >= 1 && d <= 31 && kmax > 64 && kmax <= kManyCentroids && n_max <= 4096;
+}
+
+hipError_t launch_mfma_many(const SweepArgs &a, int64_t n_max, int64_t n_total, hipStream_t s)
+{
+    int cus = 0;
+    const hipError_t e = compute_units(cus);
+    if (e != hipSuccess) return e;
+    const int nwaves = a.kmax <= 192 ? 16 : 8;             // 160 KiB of LDS hold sixteen waves' regions beside 192 centroids
+    if (a.d <= 15) return launch_mfma_t<16, 0, uint8_t, false, true>(a, nwaves, n_max, n_total, cus, s);
+    return launch_mfma_t<32, 0, uint8_t, false, true>(a, nwaves, n_max, n_total, cus, s);
 }
 
 hipError_t launch_mfma_sweep(const SweepArgs &a, int64_t n_max, int64_t n_total, hipStream_t s)

@@ -1,0 +1,58 @@
+"""Lists of k beyond 64 on tasks of at most 4096 rows, without a flag: the resident matrix-core kernel's form for many centroids, up to
+k = 224.  Sizes around the chunks of 64 centroids, the waves' rows and the LDS limits, against the oracle; losses of chunks of the
+list against the whole list's."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2001_08743_amd import binding, workloads
+from parity_util import check_sweep
+
+pytestmark = pytest.mark.gpu
+
+
+def _sweep(wl, want_trace=False, init=None):
+    import torch
+    dw = binding.DeviceWorkload(wl)
+    kw = {} if init is None else dict(init_centroids=torch.from_numpy(init).to(dw.X.device))
+    out = binding.cham_kmeans_sweep(dw.X, dw.ld, dw.d, wl.task_off, wl.ks, wl.n_iter, want_labels=True, want_trace=want_trace, **kw)
+    torch.cuda.synchronize()
+    ref = oracle.sweep(wl.rows, wl.task_off, wl.ks, wl.n_iter, init=init, want_labels=True, want_trace=want_trace)
+    check_sweep(wl, out, ref, dw.ld)
+    return dw, out
+
+
+@pytest.mark.parametrize("n", [66, 300, 1023, 1025, 2500, 4095, 4096])
+@pytest.mark.parametrize("d,ks", [(9, (5, 64, 65)), (15, (96, 97, 128)), (16, (33, 129, 160)), (24, (2, 191, 192)), (31, (193, 224))])
+def test_sizes(n, d, ks):
+    wl = workloads.random_task(3 * n + d, n, d, card_hi=20, n_blobs=9, sigma=0.8, ks=ks, n_iter=12, n_tasks=3, ragged=n % 2 == 1)
+    _sweep(wl, want_trace=n == 300)
+
+
+@pytest.mark.parametrize("k", [100, 200])
+def test_ties_on_every_row(k):
+    # few values per knob: many rows at the same distance from several centroids, more (row, candidate) pairs than a queue holds
+    wl = workloads.random_task(k, 1500, 8, card_hi=3, n_blobs=3, sigma=2.0, ks=(k,), n_iter=6, n_tasks=2)
+    _sweep(wl)
+
+
+def test_candidates_without_number():
+    # starts far outside the knobs' range: every centroid is a candidate of every row
+    wl = workloads.random_task(5, 700, 12, card_hi=12, n_blobs=5, sigma=1.0, ks=(70,), n_iter=3, n_tasks=2)
+    init = np.full((2, 70, 12), 1.0e9) + np.arange(70)[None, :, None]
+    init[:, :3] = wl.rows[:3].astype(np.float64)
+    _sweep(wl, init=init)
+
+
+def test_unaligned_tasks_and_more_units_than_places():
+    wl = workloads.random_task(6, 333, 10, card_hi=16, n_blobs=6, sigma=0.8, ks=tuple(range(60, 74)), n_iter=8, n_tasks=30, ragged=True)
+    _sweep(wl)
+
+
+@pytest.mark.parametrize("chunk", [1, 2])
+def test_chunked_sweep_equals_the_whole(chunk):
+    wl = workloads.random_task(7, 2000, 14, card_hi=18, n_blobs=6, sigma=0.9, ks=(8, 64, 65, 128, 130), n_iter=3, n_tasks=9, ragged=True)
+    dw, whole = _sweep(wl)
+    part = binding.cham_kmeans_sweep_knee(dw.X, dw.ld, dw.d, wl.task_off, wl.ks, wl.n_iter, threshold=0.0, chunk=chunk, want_labels=True)
+    for key in ("status", "counts", "centroids", "labels", "inertia"):
+        np.testing.assert_array_equal(part[key].cpu().numpy(), whole[key].cpu().numpy(), err_msg=key)
