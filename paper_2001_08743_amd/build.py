@@ -17,9 +17,9 @@ FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-ffp-contract=o
          "-Wall", "-Wno-unused-function"]
 
 
-# Per-file additions.  The matrix-core kernel takes minima of scores that are finite by construction;
+# Per-file additions.  The matrix-core kernels take minima of scores that are finite by construction;
 # without the NaN semantics each minimum is one instruction.
-FILE_FLAGS = {"lloyd_mfma.hip": ["-fno-honor-nans"]}
+FILE_FLAGS = {"lloyd_mfma.hip": ["-fno-honor-nans"], "lloyd_stream.hip": ["-fno-honor-nans"]}
 
 
 def build_lib(verbose: bool = False, extra=()) -> str:

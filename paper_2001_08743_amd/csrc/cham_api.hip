@@ -271,7 +271,7 @@ SweepWs sweep_ws(const Plan &pl, int64_t ld, bool own_labels, bool stream, const
     o += up(((int64_t)pl.n_k * kUnitQueues + 1) * 4); // (+ the flag of a two-byte value too large for the f16 rows)
     w.xh = o;
     o += up(ld * xh_halfs * 2);
-    if (fetched) {
+    if (fetched || stream) {
         // packed in tiles of 32 rows every task may need one more than its rows fill; behind them the offsets and norms of the
         // tasks' centred rows, and room to read on for (four tiles of 2 KiB, or two of 4 KiB, are fetched ahead)
         const int64_t rows_end = o;

@@ -34,66 +34,11 @@
 #include "cham_device.h"
 #include "cham_internal.h"
 #include "mfma_common.h"
+#include "fetched_tiles.h"
 
 namespace cham {
 
 namespace {
-
-// Cross-lane exchanges done in the vector ALU (DPP), no LDS round trip.
-// xor_lanes<1|2|4|8>: the value held by lane ^ 1, 2, 4 or 8.
-template <int XOR>
-__device__ __forceinline__ int dpp_xor_i32(int v)
-{
-    if (XOR == 8) return __builtin_amdgcn_update_dpp(0, v, 0x128, 0xF, 0xF, false);     // row_ror:8 = lane ^ 8 within a row of 16
-    if (XOR == 1) return __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, false);      // quad_perm [1,0,3,2]
-    if (XOR == 2) return __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, false);      // quad_perm [2,3,0,1]
-    // lane ^ 4 = mirror within each group of eight lanes, then reverse within each quad
-    const int m = __builtin_amdgcn_update_dpp(0, v, 0x141, 0xF, 0xF, false);            // row_half_mirror
-    return __builtin_amdgcn_update_dpp(0, m, 0x1B, 0xF, 0xF, false);                    // quad_perm [3,2,1,0]
-}
-template <int XOR>
-__device__ __forceinline__ double dpp_xor_f64(double v)
-{
-    const long long b = __double_as_longlong(v);
-    const int lo = dpp_xor_i32<XOR>((int)(b & 0xFFFFFFFFll));
-    const int hi = dpp_xor_i32<XOR>((int)(b >> 32));
-    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-// maximum of a non-negative float over the wave: rotations within the 16-lane rows, then the four
-// row results through scalar registers
-__device__ __forceinline__ float wave_max_nonneg(float v)
-{
-    int b = __float_as_int(v);          // non-negative floats order like integers
-    int o = __builtin_amdgcn_update_dpp(0, b, 0x128, 0xF, 0xF, false);    // row_ror:8
-    b = b > o ? b : o;
-    o = __builtin_amdgcn_update_dpp(0, b, 0x124, 0xF, 0xF, false);        // row_ror:4
-    b = b > o ? b : o;
-    o = __builtin_amdgcn_update_dpp(0, b, 0x122, 0xF, 0xF, false);        // row_ror:2
-    b = b > o ? b : o;
-    o = __builtin_amdgcn_update_dpp(0, b, 0x121, 0xF, 0xF, false);        // row_ror:1
-    b = b > o ? b : o;
-    const int r0 = __builtin_amdgcn_readlane(b, 0), r1 = __builtin_amdgcn_readlane(b, 16);
-    const int r2 = __builtin_amdgcn_readlane(b, 32), r3 = __builtin_amdgcn_readlane(b, 48);
-    const int m01 = r0 > r1 ? r0 : r1, m23 = r2 > r3 ? r2 : r3;
-    return __int_as_float(m01 > m23 ? m01 : m23);
-}
-
-// Minimum of two / three scores.  This file is compiled with -fno-honor-nans (every score is a finite
-// sum of finite products), which spares the instruction that would otherwise quiet a possible NaN in
-// each operand coming out of a matrix instruction.  (Not inline assembly: the compiler has to see
-// these reads to keep the wait states between a matrix instruction and the use of its result.)
-__device__ __forceinline__ float vmin(float a, float b) { return __builtin_fminf(a, b); }
-__device__ __forceinline__ float vmin3(float a, float b, float c) { return __builtin_fminf(__builtin_fminf(a, b), c); }
-
-// Score position -> centroid.  Position q = 16 * m-tile + accumulator register (the order in which
-// the mask bits are collected, most significant first), hh = lane half.
-__device__ __forceinline__ int slot_centroid(int q, int hh) { return 2 * q + hh; }
-// Row of the 32-row A fragment that holds centroid c of its m-tile.
-__device__ __forceinline__ int frag_row(int c)
-{
-    const int i = (c & 31) >> 1;
-    return 8 * (i >> 2) + 4 * (c & 1) + (i & 3);
-}
 
 // Rows a wave's queue holds (a tile fills at most 32): with few tiles per wave, 40 let two workgroups of
 // 32-wide rows and 64 centroids share a compute unit (32 tasks x 1000 rows x 24 knobs, k = 2..48: 551 -> 458 us).
@@ -182,189 +127,6 @@ struct WaveQueue {
     __device__ unsigned *seen() const { return reinterpret_cast<unsigned *>(base + kOffSeen); }           // [tiles][64] mask at the last decision
 };
 
-// Resolve the queued rows of this wave: four lanes per row, each lane takes every fourth marked
-// centroid of its row and evaluates the exact double distance (knobs ascending, no fused
-// multiply-add); the four lanes then agree on the smallest distance, lowest index on ties.  The
-// result goes to the row's entry of the labels of the pass under way.
-template <int DK, typename Queue>
-__device__ __forceinline__ void resolve_rows(const Queue &Q, int nrec, const double *mu64T,
-                                             const float *ojf, int KP, int k, int d)
-{
-    const int lane = threadIdx.x & 63;
-    const int q = lane & 3;
-    __builtin_amdgcn_wave_barrier();
-    for (int r0 = 0; r0 < nrec; r0 += 16) {
-        const int r = r0 + (lane >> 2);
-        const bool have = r < nrec;
-        const int rr = have ? r : 0;
-        unsigned rem0 = 0, rem1 = 0;
-        if (have) {
-            rem0 = Q.rec_mask()[r * 2 + 0];
-            rem1 = Q.rec_mask()[r * 2 + 1];
-        }
-        const int pid = Q.rec_pid()[rr];
-        // next marked centroid of the row, -1 when none is left
-        auto pop = [&]() -> int {
-            int c = -1;
-            if (rem0) {
-                const int b = __clz((int)rem0);
-                rem0 &= ~(0x80000000u >> b);
-                c = slot_centroid(b, 0);
-            } else if (rem1) {
-                const int b = __clz((int)rem1);
-                rem1 &= ~(0x80000000u >> b);
-                c = slot_centroid(b, 1);
-            }
-            return c;
-        };
-        for (int i = 0; i < q; ++i) pop();
-        double bs = __builtin_inf();
-        int bc = 0x7fffffff;
-        while (__ballot((rem0 | rem1) != 0u)) {
-            const int cc = pop();
-            const int ci = (cc < 0 || cc >= k) ? 0 : cc;
-            double ss = 0.0;
-            // knobs in groups of 8; the loads of a group are independent and overlap
-            for (int j0 = 0; j0 < d; j0 += 8) {
-                const half8 xq = *reinterpret_cast<const half8 *>(Q.rec_x() + (size_t)rr * DK + j0);
-                const float4 oa = *reinterpret_cast<const float4 *>(ojf + j0);
-                const float4 ob = *reinterpret_cast<const float4 *>(ojf + j0 + 4);
-                const float of[8] = {oa.x, oa.y, oa.z, oa.w, ob.x, ob.y, ob.z, ob.w};
-                double mu[8];
-#pragma unroll
-                for (int i = 0; i < 8; ++i) mu[i] = mu64T[(size_t)(j0 + i) * KP + ci];
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    // queued copies are centred; padded knobs are skipped (the last one carries the bias)
-                    float xf = (float)xq[i] + of[i];
-                    if (j0 + i >= d) xf = 0.0f;
-                    const double tq = (double)xf - mu[i];
-                    ss = ss + tq * tq;
-                }
-            }
-            if (cc >= 0 && cc < k && (ss < bs || (ss == bs && cc < bc))) {
-                bs = ss;
-                bc = cc;
-            }
-            pop();
-            pop();
-            pop();
-        }
-        {
-            const double os = dpp_xor_f64<1>(bs);
-            const int oc = dpp_xor_i32<1>(bc);
-            if (os < bs || (os == bs && oc < bc)) {
-                bs = os;
-                bc = oc;
-            }
-        }
-        {
-            const double os = dpp_xor_f64<2>(bs);
-            const int oc = dpp_xor_i32<2>(bc);
-            if (os < bs || (os == bs && oc < bc)) {
-                bs = os;
-                bc = oc;
-            }
-        }
-        if (have && q == 0) Q.lab_new()[pid] = (unsigned char)Queue::stored(bc < k ? bc : 0);
-    }
-    __builtin_amdgcn_wave_barrier();
-}
-
-// A few queued rows (the usual case): two rows at a time, two marked centroids per row at a time,
-// sixteen lanes per (row, centroid): every lane squares the differences of its one or two knobs,
-// then one lane adds the d squares up in knob order (the only part that has to be serial) and the
-// lanes of a row agree on the smallest distance, lowest index on ties.
-template <int DK, typename Queue>
-__device__ __forceinline__ void resolve_few(const Queue &Q, int nrec, const double *mu64T,
-                                            const float *ojf, int KP, int k, int d)
-{
-    const int lane = threadIdx.x & 63;
-    const int slot = lane >> 4, jl = lane & 15;
-    double *sc = Q.few() + slot * 32;      // squares of one (row, centroid)
-    __builtin_amdgcn_wave_barrier();
-    for (int r0 = 0; r0 < nrec; r0 += 2) {
-        const int r = r0 + (slot >> 1);
-        const bool have = r < nrec;
-        const int rr = have ? r : 0;
-        unsigned rem0 = 0, rem1 = 0;
-        if (have) {
-            rem0 = Q.rec_mask()[r * 2 + 0];
-            rem1 = Q.rec_mask()[r * 2 + 1];
-        }
-        const int pid = Q.rec_pid()[rr];
-        // this lane's knobs of the row (the queued copy is centred; the bias slot and padded slots count as zero)
-        float xa = 0.0f, xb = 0.0f;
-        if (jl < d) xa = (float)Q.rec_x()[(size_t)rr * DK + jl] + ojf[jl];
-        if (DK == 32 && jl + 16 < d) xb = (float)Q.rec_x()[(size_t)rr * DK + jl + 16] + ojf[jl + 16];
-        auto pop = [&]() -> int {
-            int c = -1;
-            if (rem0) {
-                const int b = __clz((int)rem0);
-                rem0 &= ~(0x80000000u >> b);
-                c = slot_centroid(b, 0);
-            } else if (rem1) {
-                const int b = __clz((int)rem1);
-                rem1 &= ~(0x80000000u >> b);
-                c = slot_centroid(b, 1);
-            }
-            return c;
-        };
-        if (slot & 1) pop();
-        double bs = __builtin_inf();
-        int bc = 0x7fffffff;
-        while (__ballot((rem0 | rem1) != 0u)) {
-            const int cc = pop();
-            const int ci = (cc < 0 || cc >= k) ? 0 : cc;
-            const double ta = (double)xa - mu64T[(size_t)jl * KP + ci];
-            sc[jl] = ta * ta;
-            if (DK == 32) {
-                const double tb = (double)xb - mu64T[(size_t)(jl + 16) * KP + ci];
-                sc[jl + 16] = tb * tb;
-            }
-            __builtin_amdgcn_wave_barrier();
-            if (jl == 0) {
-                // eight loads in flight at a time; slots from d on hold exact zeros
-                double ss = 0.0;
-                for (int j0 = 0; j0 < d; j0 += 8) {
-                    double v[8];
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) v[i] = sc[j0 + i];
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) ss = ss + v[i];
-                }
-                if (cc >= 0 && cc < k && (ss < bs || (ss == bs && cc < bc))) {
-                    bs = ss;
-                    bc = cc;
-                }
-            }
-            __builtin_amdgcn_wave_barrier();
-            pop();
-        }
-        const double os = __shfl_xor(bs, 16, 64);
-        const int oc = __shfl_xor(bc, 16, 64);
-        if (os < bs || (os == bs && oc < bc)) {
-            bs = os;
-            bc = oc;
-        }
-        if (have && (lane & 31) == 0) Q.lab_new()[pid] = (unsigned char)Queue::stored(bc < k ? bc : 0);
-    }
-    __builtin_amdgcn_wave_barrier();
-}
-
-template <int DK, typename Queue>
-__device__ __forceinline__ void resolve_queue(const Queue &Q, int nrec, const double *mu64T,
-                                              const float *ojf, int KP, int k, int d)
-{
-    if constexpr (DK <= 32) {
-        if (nrec <= 8) {
-            resolve_few<DK>(Q, nrec, mu64T, ojf, KP, k, d);
-            return;
-        }
-    }
-    resolve_rows<DK>(Q, nrec, mu64T, ojf, KP, k, d);
-}
-
 // Row-major f16 copy of X (one row = DK halfs, padded knobs zero): a lane fetches the eight knobs
 // of a B fragment with one 16-byte load.
 // Two-byte knobs take this path only when every value is below 2048 (integers up to 2048 are
@@ -435,108 +197,6 @@ __device__ __forceinline__ void apply_changes(const Queue &Q, int cnt, int *S, i
         }
     }
     __builtin_amdgcn_wave_barrier();
-}
-
-// Sums and sizes of every cluster over this wave's rows, from the current labels, on the matrix
-// cores: S^T (knob x centroid) = X^T (knob x row) * onehot (row x centroid), 32 rows per instruction, all in bytes.
-// Lane (m, kh) of the A fragment holds knob m of sixteen consecutive rows, read straight
-// from the knob-major byte matrix (64 consecutive rows = 64 bytes per lane and group of 128 rows, so that a wave uses up the
-// lines it touches; the same row order is used for the labels, so any order would do).  A knob enters as the signed byte
-// x - 128 (x ^ 0x80), a row of the cluster as -128, any other as 0: with t = label ^ centroid (below 128), bit 7 of
-// t + 127 is clear where t is zero.  The sums come out as -128 (S - 128 n), |.| <= 2^26, and the knob rows of absent
-// knobs (all bytes zero) as 2^14 n, of which row 31 serves as the cluster size.  They are added to the sums
-// of the workgroup lowered by 128 n (kRawOffset: the centroid update takes that off) and to the sizes.  In bytes a
-// step of 32 rows takes 20 (k > 32: 32) vector instructions; in f16 (bytes widened by placement, one-hot by a clamped
-// difference) it was 44 (80), and the rebuild 30 000 cycles of the two workgroups of a compute unit for k = 1.
-// Needs 16-byte aligned rows (xw, ld) and reads whole runs of 64 rows: the caller makes sure
-// that the last run of the task still lies inside the matrix (rows of other tasks or padding
-// read there meet the label 0xFF, which matches no centroid).  NG = runs of 64 rows a wave owns
-// at most; the loads of 256 rows are under way at any time.  SEP: every knob row is in use, so the
-// sizes are counted from the labels.
-constexpr int kRawOffset = -128;
-// first: the 64 centroids [first, first + 64) are summed; MANY: there are more than those (labels up to 223).
-template <int DK, int NG, bool SEP, bool MANY = false, typename Queue>
-__device__ __forceinline__ void full_sums(const Queue &Q, int *S, int *n, const uint8_t *xw, int64_t ld,
-                                          int d, int k_all, int rows_here, int lane, int first = 0)
-{
-    typedef int int4v __attribute__((ext_vector_type(4)));
-    typedef int int16v __attribute__((ext_vector_type(16)));
-    constexpr int W = NG % 2 == 0 ? 2 : 1;                  // a lane's 32-row pieces per group of 64 * W rows
-    constexpr int kGroups = NG / W;
-    constexpr int kDepth = kGroups < 4 / W ? kGroups : 4 / W;
-    const int m32 = lane & 31, kh = lane >> 5;
-    const int k = k_all - first;
-    S += first * (DK + 1);
-    n += first;
-    const bool two = k > 32;
-    const bool knob = m32 < d;
-    const uint8_t *xp = xw + (int64_t)(knob ? m32 : 0) * ld + 32 * W * kh;
-    const unsigned char *lp = Q.lab() + 32 * W * kh;
-    const int c4a = (int)(Queue::stored(first + m32) * 0x01010101u), c4b = (int)(Queue::stored(first + m32 + 32) * 0x01010101u);
-    int16v acc0, acc1;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        acc0[i] = 0;
-        acc1[i] = 0;
-    }
-    const int runs = (rows_here + 63) >> 6;
-
-    // this lane's bytes of group g (zero where the knob or the run of 64 rows does not exist)
-    auto fetch = [&](int g, int4v (&w)[2 * W]) {
-#pragma unroll
-        for (int i = 0; i < 2 * W; ++i) w[i] = int4v{0, 0, 0, 0};
-        if (knob && W * g + (W == 2 ? kh : 0) < runs) {
-#pragma unroll
-            for (int i = 0; i < 2 * W; ++i) w[i] = *reinterpret_cast<const int4v *>(xp + 64 * W * g + 16 * i);
-        }
-    };
-    // labels -> -128 for the rows of the centroid, 0 for others
-    auto members = [](const int4v &l, int c4) {
-        int4v o;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int t = l[e] ^ c4;
-            o[e] = MANY ? ~(((t & 0x7F7F7F7F) + 0x7F7F7F7F) | t) & (int)0x80808080 : ~(t + 0x7F7F7F7F) & (int)0x80808080;
-        }
-        return o;
-    };
-
-    int4v w[kDepth][2 * W];
-#pragma unroll
-    for (int g = 0; g < kDepth; ++g) fetch(g, w[g]);
-#pragma unroll
-    for (int g = 0; g < kGroups; ++g) {
-        if (W * g < runs) {
-#pragma unroll
-            for (int i = 0; i < 2 * W; ++i) {
-                const int4v A = w[g % kDepth][i] ^ (int)0x80808080;
-                int4v l = *reinterpret_cast<const int4v *>(lp + 64 * W * g + 16 * i);
-                if (!MANY) l = l & 0x7F7F7F7F;
-                acc0 = __builtin_amdgcn_mfma_i32_32x32x32_i8(A, members(l, c4a), acc0, 0, 0, 0);
-                if (two) acc1 = __builtin_amdgcn_mfma_i32_32x32x32_i8(A, members(l, c4b), acc1, 0, 0, 0);
-            }
-            if (g + kDepth < kGroups) fetch(g + kDepth, w[g % kDepth]);
-        }
-    }
-    // accumulator register i of lane (c, kh) = knob (i & 3) + 8 (i >> 2) + 4 kh of centroid c (or 32 + c)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const int m = (i & 3) + 8 * (i >> 2) + 4 * kh;
-        if (m < d) {
-            if (m32 < k) atomicAdd(&S[m32 * (DK + 1) + m], -(acc0[i] >> 7));
-            if (two && m32 + 32 < k) atomicAdd(&S[(m32 + 32) * (DK + 1) + m], -(acc1[i] >> 7));
-        }
-        if (!SEP && i == 15 && kh == 1) {                              // knob row 31: 2^14 per row of the cluster
-            if (m32 < k) atomicAdd(&n[m32], acc0[i] >> 14);
-            if (two && m32 + 32 < k) atomicAdd(&n[m32 + 32], acc1[i] >> 14);
-        }
-    }
-    if (SEP) {
-        for (int e = lane; e < rows_here; e += 64) {
-            const unsigned v = Q.lab()[e];
-            if (v < 64u) atomicAdd(&n[Queue::centroid(v)], 1);       // (k <= 64)
-        }
-    }
 }
 
 // Centroid update for the clusters touched in this pass, all threads: item (c, q) owns knobs
@@ -1342,14 +1002,6 @@ __device__ __forceinline__ void run_unit(const SweepArgs &a, unsigned char *smem
 // Rows of this many make up one workgroup of the packing kernel and one entry of the tasks' tables of norms.
 constexpr int kPackRows = 256;
 
-// The packed copy holds tiles of 32 rows in the order of B fragments: eight knobs (16 bytes) of row n, knob group g of a tile stand at
-// byte 1024 (g / 2) + 512 (g & 1) + 16 n, so that one load of a fragment reads 1024 bytes in a row.  (One row after the
-// other a load touched 16 lines of 128 bytes and half of each: 56 accesses to the vector cache per load instead of 16, which
-// kept it busy two thirds of the sweep.)  Task t starts at tile task_off[t] / 32 + t, which leaves every task room for its last tile.
-__device__ __forceinline__ size_t packed_at(int row, int g, int DK)
-{
-    return (size_t)(row >> 5) * (32 * DK * 2) + (g >> 1) * 1024 + (g & 1) * 512 + (row & 31) * 16;
-}
 __device__ __forceinline__ const unsigned char *packed_task(const SweepArgs &a, int t, int DK)
 {
     return reinterpret_cast<const unsigned char *>(a.xh) + ((a.task_off[t] >> 5) + t) * (32 * DK * 2);
@@ -1424,196 +1076,6 @@ __global__ __launch_bounds__(kPackRows) void pack_centred_kernel(const SweepArgs
     }
 }
 
-// Per-wave LDS region of this variant: the undecided rows of the tiles seen so far (candidate masks and row index), later the
-// label changes of the pass; the knobs of the rows being resolved, a batch at a time, from the packed copy; the labels.  A label is
-// stored as its position among the mask bits of a row (32 * lane half + position in that half's word), so that the mask of a
-// decided row is one shift away.
-template <int DK>
-struct FetchedQueue {
-    static constexpr int kRows = DK <= 32 ? 512 : 256;      // rows a wave owns at most
-    static constexpr int kCap = 96;                         // (a tile adds at most 32)
-    static constexpr int kBatch = 16;
-    static constexpr int kChanges = 64;
-    static constexpr size_t kOffFew = (size_t)8 * DK * 2;   // (behind the eight rows there are then at most; up to 32-wide rows)
-    static constexpr size_t kOffMask = DK <= 32 ? kOffFew + 4 * 32 * 8 : (size_t)kBatch * DK * 2;
-    static constexpr size_t kOffPid = kOffMask + (size_t)kCap * 8;
-    static constexpr size_t kOffLab = kOffPid + (size_t)kCap * 2;
-    static constexpr size_t kOffNew = kOffLab + (size_t)kRows;
-    static constexpr size_t kBytes = kOffNew + (size_t)kRows;
-    static_assert(kBytes % 16 == 0 && kOffLab % 16 == 0, "regions of a wave stay 16-byte aligned");
-    static_assert(kCap * 8 >= kChanges * 4 && kOffMask >= (size_t)kBatch * DK * 2 && kOffMask >= 64 * sizeof(double), "what shares a place fits it");
-    unsigned char *base;
-    int first;                                              // first row of the batch being resolved
-    __device__ explicit FetchedQueue(unsigned char *wb) : base(wb), first(0) {}
-    __device__ _Float16 *rec_x() const { return reinterpret_cast<_Float16 *>(base); }                    // [kBatch][DK]
-    __device__ unsigned *rec_mask() const { return reinterpret_cast<unsigned *>(base + kOffMask) + 2 * first; }      // [kCap][2]
-    __device__ unsigned short *rec_pid() const { return reinterpret_cast<unsigned short *>(base + kOffPid) + first; }
-    __device__ double *few() const { return reinterpret_cast<double *>(base + kOffFew); }                 // [4][32]
-    __device__ unsigned *changes() const { return reinterpret_cast<unsigned *>(base + kOffMask); }         // [kChanges] new label | previous << 8 | row << 16
-    __device__ unsigned char *lab() const { return base + kOffLab; }                                      // [kRows] current labels (0xFF: none)
-    __device__ unsigned char *lab_new() const { return base + kOffNew; }                                  // [kRows] labels of the pass under way
-    static __device__ __forceinline__ unsigned stored(unsigned c) { return (c >> 1) | ((c & 1u) << 5); }
-    static __device__ __forceinline__ unsigned centroid(unsigned v) { return ((v & 31u) << 1) | (v >> 5); }
-};
-
-// ... of the form for more than 64 centroids: undecided rows with (row, candidate) pairs instead of masks, and what the evaluation of
-// the pairs leaves per row.  Chunk c / 64 of a centroid is bits 6 and 7 of its stored label.
-constexpr int kManyCentroids = 224;                         // (labels 0xFE and 0xFF mean undecided and none; LDS)
-template <int DK>
-struct ManyQueue {
-    static constexpr int kRows = 512;
-    static constexpr int kCap = 96;                         // (a tile adds at most 32)
-    static constexpr int kPairs = 256;
-    static constexpr int kChanges = 64;
-    static constexpr size_t kOffBestC = (size_t)kCap * 8;
-    static constexpr size_t kOffPid = kOffBestC + (size_t)kCap * 4;
-    static constexpr size_t kOffPairs = kOffPid + (size_t)kCap * 2;
-    static constexpr size_t kOffCount = kOffPairs + (size_t)kPairs * 4;
-    static constexpr size_t kOffLab = kOffCount + 16;
-    static_assert(kPairs >= kChanges && kOffLab % 16 == 0, "the label changes fit the pairs' place");
-    static __host__ __device__ size_t bytes(int nwaves) { return kOffLab + 2 * (size_t)(nwaves == 16 ? kRows / 2 : kRows); }
-    unsigned char *base;
-    int rows;                                               // rows a wave owns at most
-    __device__ ManyQueue(unsigned char *wb, int nwaves) : base(wb), rows(nwaves == 16 ? kRows / 2 : kRows) {}
-    __device__ unsigned long long *best() const { return reinterpret_cast<unsigned long long *>(base); }            // [kCap] smallest distance (bits)
-    __device__ int *best_c() const { return reinterpret_cast<int *>(base + kOffBestC); }                            // [kCap] lowest centroid attaining it
-    __device__ unsigned short *rec_pid() const { return reinterpret_cast<unsigned short *>(base + kOffPid); }       // [kCap]
-    __device__ unsigned *pairs() const { return reinterpret_cast<unsigned *>(base + kOffPairs); }                   // [kPairs] queued row << 8 | centroid
-    __device__ unsigned *changes() const { return pairs(); }                                                         // [kChanges] new label | previous << 8 | row << 16
-    __device__ unsigned *n_pairs() const { return reinterpret_cast<unsigned *>(base + kOffCount); }
-    __device__ unsigned char *lab() const { return base + kOffLab; }
-    __device__ unsigned char *lab_new() const { return base + kOffLab + rows; }
-    static __device__ __forceinline__ unsigned stored(unsigned c) { return (c & 0xC0u) | ((c & 63u) >> 1) | ((c & 1u) << 5); }
-    static __device__ __forceinline__ unsigned centroid(unsigned v) { return (v & 0xC0u) | ((v & 31u) << 1) | ((v >> 5) & 1u); }
-};
-
-// Exact evaluation of the queued rows against their candidates, one lane per (row, centroid) pair: the distance as
-// sum_j ((double)x_j - mu_j)^2 with j ascending, no fused multiply-add; per row the smallest distance, then the lowest centroid
-// attaining it.  all: every centroid of every queued row instead of the listed pairs (they found no room).
-template <int DK>
-__device__ __forceinline__ void resolve_pairs(const ManyQueue<DK> &Q, int nrec, bool all, const unsigned char *packed, const double *mu64T,
-                                              const float *ojf, int KP, int k, int d, int lane)
-{
-    for (int r = lane; r < nrec; r += 64) {
-        Q.best()[r] = ~0ull;
-        Q.best_c()[r] = 0x7fffffff;
-    }
-    __builtin_amdgcn_wave_barrier();
-    const unsigned np = all ? (unsigned)(nrec * k) : *Q.n_pairs();
-    auto distance = [&](unsigned p, int &r, int &c) {
-        if (all) {
-            r = (int)(p / (unsigned)k);
-            c = (int)(p % (unsigned)k);
-        } else {
-            const unsigned w = Q.pairs()[p];
-            r = (int)(w >> 8);
-            c = (int)(w & 0xFFu);
-        }
-        const unsigned char *x = packed + packed_at(Q.rec_pid()[r], 0, DK);
-        double s = 0.0;
-        for (int j0 = 0; j0 < d; j0 += 8) {
-            const half8 xq = *reinterpret_cast<const half8 *>(x + packed_at(0, j0 >> 3, DK));
-            double mu[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) mu[i] = mu64T[(size_t)(j0 + i) * KP + c];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                if (j0 + i < d) {
-                    const double tq = (double)((float)xq[i] + ojf[j0 + i]) - mu[i];
-                    s = s + tq * tq;
-                }
-            }
-        }
-        return (unsigned long long)__double_as_longlong(s);
-    };
-    if (np <= 64u) {                 // the usual case: a distance is evaluated once
-        int r = 0, c = 0;
-        unsigned long long mine = ~0ull;
-        if ((unsigned)lane < np) {
-            mine = distance((unsigned)lane, r, c);
-            atomicMin(&Q.best()[r], mine);
-        }
-        __builtin_amdgcn_wave_barrier();
-        if ((unsigned)lane < np && Q.best()[r] == mine) atomicMin(&Q.best_c()[r], c);
-    } else {
-        for (unsigned p = lane; p < np; p += 64) {
-            int r, c;
-            const unsigned long long mine = distance(p, r, c);
-            atomicMin(&Q.best()[r], mine);
-        }
-        __builtin_amdgcn_wave_barrier();
-        for (unsigned p = lane; p < np; p += 64) {
-            int r, c;
-            const unsigned long long mine = distance(p, r, c);
-            if (Q.best()[r] == mine) atomicMin(&Q.best_c()[r], c);
-        }
-    }
-    __builtin_amdgcn_wave_barrier();
-    for (int r = lane; r < nrec; r += 64) {
-        const int c = Q.best_c()[r];
-        Q.lab_new()[Q.rec_pid()[r]] = (unsigned char)ManyQueue<DK>::stored(c < k ? c : 0);
-    }
-    __builtin_amdgcn_wave_barrier();
-}
-
-// Listed label changes of this wave (centroids, not stored labels) -> integer sums and sizes: 256 / DK rows per step, one lane per
-// (row, four knobs), the knobs from the packed copy, those of four steps under way together.
-template <int DK, typename Queue>
-__device__ __forceinline__ void apply_listed(const Queue &Q, int cnt, const unsigned char *packed, int *S, int *n, int *dirty,
-                                             const float *ojf, int d, int stamp)
-{
-    typedef _Float16 half4 __attribute__((ext_vector_type(4)));
-    constexpr int LPR = DK / 4;              // lanes per row
-    constexpr int EPI = 64 / LPR;            // rows per step
-    constexpr int U = 4;
-    const int lane = threadIdx.x & 63;
-    const int j0 = 4 * (lane % LPR);
-    const float4 o4 = *reinterpret_cast<const float4 *>(ojf + j0);
-    const float of[4] = {o4.x, o4.y, o4.z, o4.w};
-    const bool on = j0 < d && lane < LPR * EPI;      // (twelve lanes per row leave four idle)
-    __builtin_amdgcn_wave_barrier();
-    for (int e0 = 0; e0 < cnt; e0 += U * EPI) {
-        unsigned w[U];
-        half4 xq[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int e = e0 + u * EPI + lane / LPR;
-            w[u] = Q.changes()[e < cnt ? e : 0];
-            xq[u] = *reinterpret_cast<const half4 *>(packed + packed_at(w[u] >> 16, j0 >> 3, DK) + 2 * (j0 & 4));
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int e = e0 + u * EPI + lane / LPR;
-            if (e < cnt && on) {
-                const int cur = w[u] & 0xFF, prev = (w[u] >> 8) & 0xFF;
-                const bool first = prev == 0xFF;
-                int *sc = S + cur * (DK + 1) + j0;
-                int *sp = S + (first ? cur : prev) * (DK + 1) + j0;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    if (j0 + i < d) {
-                        const int xi = (int)((float)xq[u][i] + of[i]);
-                        atomicAdd(sc + i, xi);
-                        if (!first) atomicSub(sp + i, xi);
-                    }
-                }
-                if (j0 == 0) {
-                    atomicAdd(&n[cur], 1);
-                    dirty[cur] = stamp;
-                    if (!first) {
-                        atomicSub(&n[prev], 1);
-                        dirty[prev] = stamp;
-                    }
-                }
-            }
-        }
-    }
-    __builtin_amdgcn_wave_barrier();
-}
-
-// Tiles whose rows are fetched ahead (even: the accumulators alternate).
-constexpr int rows_ahead(int DK, bool two, bool SEP) { return DK == 16 || (DK == 32 && !two) ? 4 : 2; }
-
 constexpr int kParts = 16;
 
 // Centroid rows LDS holds (KP).
@@ -1640,7 +1102,6 @@ __device__ __forceinline__ void run_unit_fetched(const SweepArgs &a, unsigned ch
     constexpr int NS = DK / 16;          // distinct B fragments per row
     constexpr int NS2 = 2 * NS;          // chained instructions per 32x32 tile, without the bias step
     constexpr int NSA = NS2 + (SEP ? 1 : 0);   // ... with it
-    constexpr int CH = NS2 == 6 ? 4 : 16 / NS2;   // scores handled between two matrix instructions
     const int KP = centroid_rows<MANY>(a.kmax);
     MfmaLds<DK, SEP> U(smem, KP);
 
@@ -1757,23 +1218,6 @@ __device__ __forceinline__ void run_unit_fetched(const SweepArgs &a, unsigned ch
     const int full_above = nrows / kFullDivisor;      // changed rows of a pass above which the next one rebuilds
     bool traced_last = false;
 
-    // lanes of tile nt (as a 32-bit mask over the row index within the tile) whose row belongs to the task
-    auto live_rows = [&](int nt) -> uint32_t {
-        const int left = rows_wave - 32 * nt;
-        return left >= 32 ? 0xFFFFFFFFu : (left <= 0 ? 0u : ((1u << left) - 1u));
-    };
-    // this lane's B fragments of a tile (rows behind the task's last are read, from inside the workspace, and ignored)
-    constexpr unsigned kTileBytes = 32 * DK * 2;
-    auto fetch = [&](half8 (&Bt)[NS], const unsigned char *p, unsigned lane_off) {
-        // a scalar base in global memory: a lane's part of the address is one 32-bit register
-        uint64_t at = reinterpret_cast<uint64_t>(p);
-        asm volatile("" : "+s"(at));
-        typedef const __attribute__((address_space(1))) unsigned char gbyte;
-        typedef const __attribute__((address_space(1))) half8 ghalf8;
-#pragma unroll
-        for (int f = 0; f < NS; ++f) Bt[f] = *reinterpret_cast<ghalf8 *>(reinterpret_cast<gbyte *>(at) + lane_off + 1024 * f);
-    };
-
     // Exact loss of the current labels: (x - mu)^2 in double over the knobs a lane holds (x = centred value + offset, exact), the two
     // lanes of a row and all rows of a part added up afterwards; the sums of the parts land in U.red[at .. at + kParts).
     auto wave_loss = [&](int at) {
@@ -1788,7 +1232,7 @@ __device__ __forceinline__ void run_unit_fetched(const SweepArgs &a, unsigned ch
             const int last = first + part_rows < rows_wave ? first + part_rows : rows_wave;
             for (int nt = first >> 5; 32 * nt < last; ++nt) {
                 half8 bt[NS];
-                fetch(bt, packed + nt * kTileBytes, (unsigned)(16 * lane));
+                fetch_tile<DK>(bt, packed + nt * (32 * DK * 2), (unsigned)(16 * lane));
                 const uint32_t lab = Q.lab()[nt * 32 + n32];
                 const bool live = lab != 0xFFu;
                 const double *mc = U.mu64T + (live ? Queue::centroid(lab) : 0u) + (size_t)(8 * h) * KP;
@@ -1826,305 +1270,20 @@ __device__ __forceinline__ void run_unit_fetched(const SweepArgs &a, unsigned ch
         const bool last_pass = (it == a.n_iter);
         passes_run = it + 1;
         int nrec = 0;                    // queued rows that the screen could not decide
-        bool all_pairs = false;          // MANY: the list of pairs is not complete
-        const uint64_t undecided = it == 0 ? ~0ull : 0ull;
+        const Tiles tiles = {packed, U.afrag, U.abias, nullptr, nullptr, bound, 0.0f, kBiasScale, ntiles, rows_wave, it == 0 ? ~0ull : 0ull};
 
         if constexpr (MANY) {
-            constexpr int kChunks = (kManyCentroids + 63) / 64;
-            const int lane = opaque(lane_id), n32 = lane & 31;
-            const bool upper = lane >= 32;
-            const unsigned lane_off = (unsigned)(16 * lane);
-            const int nch = (k + 63) >> 6, kpu = (k + 31) & ~31;
-            const float16v zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-            half8 Bn[NS];
-            if (lane == 0) *Q.n_pairs() = 0u;
-            if (wave_live) fetch(Bn, packed, lane_off);
-            for (int nt = 0; nt < ntiles; ++nt) {
-                half8 Bt[NS];
-#pragma unroll
-                for (int f = 0; f < NS; ++f) Bt[f] = Bn[f];
-                fetch(Bn, packed + (nt + 1) * kTileBytes, lane_off);
-                const uint32_t prev = Q.lab()[nt * 32 + n32];
-                uint32_t near[kChunks];
-                float least[kChunks];
-                float best = __builtin_inff();
-#pragma unroll
-                for (int ch = 0; ch < kChunks; ++ch) {
-                    near[ch] = 0u;
-                    least[ch] = __builtin_inff();
-                    if (ch < nch) {
-                        const bool has1 = (2 * ch + 1) * 32 < kpu;
-                        float16v accA, accB;
-#pragma unroll
-                        for (int s = 0; s < NS2; ++s)
-                            accA = __builtin_amdgcn_mfma_f32_32x32x16_f16(U.afrag[((2 * ch) * NS2 + s) * 64 + lane], Bt[s % NS], s == 0 ? zero16 : accA, 0, 0, 0);
-                        if (has1) {
-#pragma unroll
-                            for (int s = 0; s < NS2; ++s)
-                                accB = __builtin_amdgcn_mfma_f32_32x32x16_f16(U.afrag[((2 * ch + 1) * NS2 + s) * 64 + lane], Bt[s % NS], s == 0 ? zero16 : accB, 0, 0, 0);
-                        }
-                        auto min16 = [](const float16v &acc) {
-                            float m = vmin3(acc[0], acc[1], acc[2]);
-#pragma unroll
-                            for (int i = 3; i < 15; i += 2) m = vmin3(m, acc[i], acc[i + 1]);
-                            return vmin(m, acc[15]);
-                        };
-                        float m = min16(accA);
-                        if (has1) m = vmin(m, min16(accB));
-                        unsigned lo, hi;
-                        both_halves(__float_as_uint(m), lo, hi);
-                        m = vmin(__uint_as_float(lo), __uint_as_float(hi));
-                        const float thr = m + bound;
-                        uint32_t bits = 0;
-#pragma unroll
-                        for (int i = 0; i < 16; ++i) bits = __builtin_amdgcn_alignbit(bits, __float_as_uint(accA[i] - thr), 31);
-                        if (has1) {
-#pragma unroll
-                            for (int i = 0; i < 16; ++i) bits = __builtin_amdgcn_alignbit(bits, __float_as_uint(accB[i] - thr), 31);
-                        } else {
-                            bits <<= 16;
-                        }
-                        near[ch] = bits;
-                        least[ch] = m;
-                        best = vmin(best, m);
-                    }
-                }
-                // a tile whose rows all have exactly their current label marked is done (but in the first pass)
-                const float lim = best + bound;
-                const uint64_t place = 0x8000000000000000ull >> (prev & 63u);
-                const uint32_t own = upper ? (uint32_t)place : (uint32_t)(place >> 32);
-                uint32_t diff = 0u;
-#pragma unroll
-                for (int ch = 0; ch < kChunks; ++ch) {
-                    near[ch] = least[ch] <= lim ? near[ch] : 0u;
-                    diff |= near[ch] ^ ((prev >> 6) == (uint32_t)ch ? own : 0u);
-                }
-                if ((__ballot(diff != 0u) | undecided) == 0) continue;
-                const uint32_t live32 = live_rows(nt);
-                int cnt = 0, at = 0;                       // marks of this lane half, stored label of one of them
-#pragma unroll
-                for (int ch = 0; ch < kChunks; ++ch) {
-                    cnt += __popc(near[ch]);
-                    at = near[ch] ? 64 * ch + (upper ? 32 : 0) + __clz((int)near[ch]) : at;
-                }
-                unsigned c_lo, c_hi, at_lo, at_hi;
-                both_halves((unsigned)cnt, c_lo, c_hi);
-                both_halves((unsigned)at, at_lo, at_hi);
-                const bool live = (live32 >> n32) & 1u;
-                const bool flagged = live && c_lo + c_hi != 1u;
-                const uint32_t fm = (uint32_t)__ballot(flagged);
-                if (fm) {
-                    if (flagged) {
-                        const int rs = nrec + __popc(fm & ((1u << n32) - 1u));
-                        if (!upper) Q.rec_pid()[rs] = (unsigned short)(nt * 32 + n32);
-                        unsigned pos = atomicAdd(Q.n_pairs(), (unsigned)cnt);
-#pragma unroll
-                        for (int ch = 0; ch < kChunks; ++ch) {
-                            uint32_t m = near[ch];
-                            while (m) {
-                                const int q = __clz((int)m);
-                                m &= ~(0x80000000u >> q);
-                                const int c = 64 * ch + slot_centroid(q, upper ? 1 : 0);
-                                if (pos < (unsigned)Queue::kPairs) Q.pairs()[pos] = (unsigned)(rs << 8 | c);
-                                ++pos;
-                            }
-                        }
-                        if (pos > (unsigned)Queue::kPairs) all_pairs = true;
-                    }
-                    // no candidate at all cannot happen (the smallest score is always one); if it does, every centroid is one
-                    if (flagged && c_lo + c_hi == 0u) all_pairs = true;
-                    nrec += __popc(fm);
-                    if (nrec > Queue::kCap - 32) {         // the next tile might not fit
-                        resolve_pairs<DK>(Q, nrec, __any(all_pairs), packed, U.mu64T, U.ojf, KP, k, d, lane);
-                        nrec = 0;
-                        all_pairs = false;
-                        if (lane == 0) *Q.n_pairs() = 0u;
-                        __builtin_amdgcn_wave_barrier();
-                    }
-                }
-                const uint32_t now = !live ? 0xFFu : (flagged ? 0xFEu : (c_lo ? at_lo : at_hi));
-                // (a row resolved just now has its label already)
-                if (!upper && now != 0xFEu) Q.lab_new()[nt * 32 + n32] = (unsigned char)now;
-            }
-            if (nrec) resolve_pairs<DK>(Q, nrec, __any(all_pairs), packed, U.mu64T, U.ojf, KP, k, d, lane);
+            decide_tiles_many<DK, false, false>(Q, tiles, nrec, U.mu64T, U.ojf, KP, k, d, opaque(lane_id));
         } else {
-        // The tile loop from tile nt on, compiled once per number of live registers of the last m-tile (4, 8, 12 or 16), so that
-        // the epilogue has no branches.  Returns the tile to go on with: ntiles, or an earlier one when the queue has to be emptied.
-        auto tile_pass = [&](auto live_tag, auto two_tag, int nt) -> int {
-            constexpr int LREGS = decltype(live_tag)::value;
-            constexpr bool two = decltype(two_tag)::value;
-            constexpr int kAhead = rows_ahead(DK, two, SEP);
-            const int lane = opaque(lane_id), n32 = lane & 31;
-            const bool upper = lane >= 32;
-            const unsigned lane_off = (unsigned)(16 * lane);
-            half8 Bq[kAhead][NS];                // rows of tiles nt .. nt + kAhead - 1
-#pragma unroll
-            for (int u = 0; u < kAhead; ++u) fetch(Bq[u], packed + (nt + u) * kTileBytes, lane_off);
-            const unsigned char *ahead = packed + (nt + kAhead) * kTileBytes;
-            int end = ntiles;                    // where this call stops
-            const unsigned char *labs = Q.lab() + nt * 32 + n32;
-            // A fragments of this pass (the bias slot included)
-            half8 A0[NSA], A1[NSA];
-#pragma unroll
-            for (int s = 0; s < NS2; ++s) {
-                A0[s] = U.afrag[s * 64 + lane];
-                A1[s] = two ? U.afrag[(NS2 + s) * 64 + lane] : A0[s];
-            }
-            // the bias step: 256 against hi (slot 0) and lo (slot 1), the same for every row
-            half8 bias_b;
-            if constexpr (SEP) {
-                A0[NS2] = U.abias[lane];
-                A1[NS2] = two ? U.abias[64 + lane] : A0[NS2];
-#pragma unroll
-                for (int i = 0; i < 8; ++i) bias_b[i] = (_Float16)(i < 2 && lane < 32 ? kBiasScale : 0.0f);
-            }
-
-            float16v accA, accB;
-            const float16v zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-            // one matrix instruction of the chain of a 32x32 tile (the first one behind the bias step)
-            auto mma = [&](float16v &acc, const half8 (&Af)[NSA], const half8 (&Bt)[NS], int s) {
-                if constexpr (SEP) {
-                    if (s == 0) acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(Af[NS2], bias_b, zero16, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(Af[s], Bt[s % NS], acc, 0, 0, 0);
-                    return;
-                }
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(Af[s], Bt[s % NS], s == 0 ? zero16 : acc, 0, 0, 0);
-            };
-            // mark scores [i0, i0 + CH): bit set = below the threshold
-            auto mark = [&](uint32_t &near, const float16v &acc, float thr, int i0) {
-#pragma unroll
-                for (int i = 0; i < CH; ++i)
-                    if (i0 + i < 16) near = __builtin_amdgcn_alignbit(near, __float_as_uint(acc[i0 + i] - thr), 31);
-            };
-            // minimum over the first nreg registers (nreg = 4, 8, 12 or 16)
-            auto min_live = [&](const float16v &acc, auto nreg_tag) {
-                constexpr int nreg = decltype(nreg_tag)::value;
-                float b = vmin(vmin3(acc[0], acc[1], acc[2]), acc[3]);
-                if (nreg > 4) b = vmin3(vmin3(b, acc[4], acc[5]), acc[6], acc[7]);
-                if (nreg > 8) b = vmin3(vmin3(b, acc[8], acc[9]), acc[10], acc[11]);
-                if (nreg > 12) b = vmin3(vmin3(b, acc[12], acc[13]), acc[14], acc[15]);
-                return b;
-            };
-            // both lane halves' minima of a row -> the row's minimum
-            auto row_min = [&](float v) {
-                unsigned lo, hi;
-                both_halves(__float_as_uint(v), lo, hi);
-                return vmin(__uint_as_float(lo), __uint_as_float(hi));
-            };
-            // After the masks of tile nt: a tile whose rows all have exactly their current label marked is done (but in the first
-            // pass).  Otherwise the tile's rows are decided: a row with exactly one candidate takes it, any other row is queued
-            // for the exact evaluation after the tile loop (label 0xFE until then).  (The matrix instructions of the next tile are under way meanwhile.)
-            auto settle = [&](uint32_t cand, uint32_t prev, int nt) {       // cand: bit 31 = position 0
-                const uint64_t place = 0x8000000000000000ull >> (prev & 63u);
-                const uint32_t own = upper ? (uint32_t)place : (uint32_t)(place >> 32);
-                if ((__ballot(cand != own) | undecided) == 0) return;
-                const uint32_t live32 = live_rows(nt);
-                uint32_t cand_lo, cand_hi;
-                both_halves(cand, cand_lo, cand_hi);
-                const int total = __popc(cand_lo) + __popc(cand_hi);
-                const bool live = (live32 >> n32) & 1u;
-                const bool flagged = live && total != 1;
-                const uint32_t fm = (uint32_t)__ballot(flagged);
-                if (fm) {
-                    if (flagged) {
-                        const int rs = nrec + __popc(fm & ((1u << n32) - 1u));
-                        // no candidate at all cannot happen (the smallest score is always one); if it does, every centroid is one
-                        Q.rec_mask()[rs * 2 + (upper ? 1 : 0)] = total ? cand : 0xFFFFFFFFu;
-                        if (!upper) Q.rec_pid()[rs] = (unsigned short)(nt * 32 + n32);
-                    }
-                    nrec += __popc(fm);
-                    if (nrec > Queue::kCap - 32) end = nt + 1;      // the next tile might not fit
-                }
-                const uint32_t lab = cand_lo ? (uint32_t)__clz((int)cand_lo) : 32u + ((uint32_t)__clz((int)cand_hi) & 31u);
-                const uint32_t now = !live ? 0xFFu : (flagged ? 0xFEu : lab);
-                if (!upper) Q.lab_new()[nt * 32 + n32] = (unsigned char)now;
-            };
-
-            if constexpr (two) {
-                // accA = centroids 0..31 (all sixteen registers live), accB = centroids 32..k-1 of the current tile; Bn = rows of
-                // the next tile, Bf = free for those of the tile kAhead further on
-                auto step = [&](half8 (&Bn)[NS], half8 (&Bf)[NS]) {
-                    fetch(Bf, ahead, lane_off);
-                    ahead += kTileBytes;
-                    const uint32_t prev = *labs;
-                    labs += 32;
-                    const float best = row_min(vmin(min_live(accA, std::integral_constant<int, 16>{}), min_live(accB, live_tag)));
-                    const float thr = best + bound;
-                    uint32_t near = 0;
-#pragma unroll
-                    for (int s = 0; s < NS2; ++s) mark(near, accA, thr, s * CH);
-                    // accA is consumed: its next chain runs under the marking of accB
-#pragma unroll
-                    for (int s = 0; s < NS2; ++s) {
-                        __builtin_amdgcn_sched_barrier(0);
-                        mma(accA, A0, Bn, s);
-                        __builtin_amdgcn_sched_barrier(0);
-                        if (s * CH < LREGS) mark(near, accB, thr, s * CH);
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                    for (int s = 0; s < NS2; ++s) mma(accB, A1, Bn, s);
-                    // (registers of accB that were not walked hold padding only)
-                    constexpr int live_marks = CH * ((LREGS + CH - 1) / CH);
-                    settle(near << (16 - live_marks), prev, nt);
-                    __builtin_amdgcn_sched_barrier(0);
-                    asm volatile("" : "+v"(accB));      // (as below)
-                };
-#pragma unroll
-                for (int s = 0; s < NS2; ++s) mma(accA, A0, Bq[0], s);
-#pragma unroll
-                for (int s = 0; s < NS2; ++s) mma(accB, A1, Bq[0], s);
-                for (;;) {
-#pragma unroll
-                    for (int u = 0; u < kAhead; ++u) {
-                        step(Bq[(u + 1) % kAhead], Bq[u]);
-                        if (++nt >= end) return nt;
-                    }
-                }
-            } else {
-                // one m-tile: the accumulators alternate, the next tile's chain runs under this epilogue
-                auto step = [&](float16v &cur, float16v &nxt, half8 (&Bn)[NS], half8 (&Bf)[NS]) {
-                    fetch(Bf, ahead, lane_off);
-                    ahead += kTileBytes;
-                    const uint32_t prev = *labs;
-                    labs += 32;
-                    const float best = row_min(min_live(cur, live_tag));
-                    const float thr = best + bound;
-                    uint32_t near = 0;
-#pragma unroll
-                    for (int s = 0; s < NS2; ++s) {
-                        __builtin_amdgcn_sched_barrier(0);
-                        mma(nxt, A0, Bn, s);
-                        __builtin_amdgcn_sched_barrier(0);
-                        if (s * CH < LREGS) mark(near, cur, thr, s * CH);
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-                    constexpr int live_marks = CH * ((LREGS + CH - 1) / CH);
-                    settle(near << (32 - live_marks), prev, nt);
-                    __builtin_amdgcn_sched_barrier(0);
-                    // registers of dead scores are not used for anything else meanwhile: that would wait for the chain's end
-                    asm volatile("" : "+v"(nxt));
-                };
-#pragma unroll
-                for (int s = 0; s < NS2; ++s) mma(accA, A0, Bq[0], s);
-                for (;;) {
-#pragma unroll
-                    for (int u = 0; u < kAhead; ++u) {
-                        step(u & 1 ? accB : accA, u & 1 ? accA : accB, Bq[(u + 1) % kAhead], Bq[u]);
-                        if (++nt >= end) return nt;
-                    }
-                }
-            }
-        };
         if (wave_live) {
             int nt = 0;
             do {
                 auto live_pass = [&](auto two_tag) {
                     switch (lregs) {
-                    case 4: nt = tile_pass(std::integral_constant<int, 4>{}, two_tag, nt); break;
-                    case 8: nt = tile_pass(std::integral_constant<int, 8>{}, two_tag, nt); break;
-                    case 12: nt = tile_pass(std::integral_constant<int, 12>{}, two_tag, nt); break;
-                    default: nt = tile_pass(std::integral_constant<int, 16>{}, two_tag, nt); break;
+                    case 4: nt = decide_tiles<DK, SEP, false, false, 4, decltype(two_tag)::value>(Q, tiles, nt, nrec, opaque(lane_id)); break;
+                    case 8: nt = decide_tiles<DK, SEP, false, false, 8, decltype(two_tag)::value>(Q, tiles, nt, nrec, opaque(lane_id)); break;
+                    case 12: nt = decide_tiles<DK, SEP, false, false, 12, decltype(two_tag)::value>(Q, tiles, nt, nrec, opaque(lane_id)); break;
+                    default: nt = decide_tiles<DK, SEP, false, false, 16, decltype(two_tag)::value>(Q, tiles, nt, nrec, opaque(lane_id)); break;
                     }
                 };
                 if constexpr (kAllowTwo) {
@@ -2133,21 +1292,8 @@ __device__ __forceinline__ void run_unit_fetched(const SweepArgs &a, unsigned ch
                 } else {
                     live_pass(std::false_type{});
                 }
-                // the undecided rows: their knobs from the packed copy, then the exact evaluation
-                if (nrec) {
-                    constexpr int LPR = DK / 8;              // lanes per row, 16 bytes each
-                    const int lane = opaque(lane_id);
-                    Queue part = Q;
-                    for (part.first = 0; part.first < nrec; part.first += Queue::kBatch) {
-                        const int left = nrec - part.first, rows = left < Queue::kBatch ? left : Queue::kBatch;
-                        __builtin_amdgcn_wave_barrier();
-                        for (int e = lane; e < rows * LPR; e += 64)
-                            *reinterpret_cast<half8 *>(part.rec_x() + 8 * e) =
-                                *reinterpret_cast<const half8 *>(packed + packed_at(part.rec_pid()[e / LPR], e % LPR, DK));
-                        resolve_queue<DK>(part, rows, U.mu64T, U.ojf, KP, k, d);
-                    }
-                    nrec = 0;
-                }
+                if (nrec) resolve_batches<DK>(Q, nrec, packed, U.mu64T, U.ojf, KP, k, d, opaque(lane_id));
+                nrec = 0;
             } while (nt < ntiles);
         }
         }
@@ -2183,7 +1329,7 @@ __device__ __forceinline__ void run_unit_fetched(const SweepArgs &a, unsigned ch
                     if (changed) {
                         const unsigned cur = (cur4 >> (8 * i)) & 0xFFu, prev = (prev4 >> (8 * i)) & 0xFFu;
                         Q.changes()[cnt + __popcll(cm & below)] =
-                            Queue::centroid(cur) | (prev == 0xFFu ? 0xFFu : Queue::centroid(prev)) << 8 | (at + i) << 16;
+                            Queue::centroid(cur) | (prev == 0xFFu ? 0x80000000u : Queue::centroid(prev) << 8) | (at + i) << 16;
                     }
                     cnt += add;
                 }

@@ -16,30 +16,29 @@
 #include "cham_device.h"
 #include "cham_internal.h"
 #include "mfma_common.h"
+#include "fetched_tiles.h"
 
 namespace cham {
 
 namespace {
 
-constexpr int kMaxTiles = 8;         // 32-row tiles a wave handles per step, at most
-constexpr int kStepRows = kMaxTiles * 32;
-constexpr int kStreamRec = 32;       // queued rows whose knob values are kept in LDS
-constexpr int kWavesPerWg = 4;
-constexpr int kPairCap = 128;        // (queued row, candidate centroid) pairs evaluated per step and wave
+constexpr int kWavesPerWg = 8;
+constexpr int kLossWaves = 4;
 constexpr int kLossRows = 4096;      // rows of a partial sum of the loss, whatever an assigning workgroup walks
 constexpr float kPadScore = 1.0e30f; // score of a padding centroid row (real scores stay below 4 * 32 * 255^2)
 
-// Tiles of 32 rows a wave of the assignment takes per step for a unit of k centroids.
+// Knobs in 16-wide rows may fill every slot: |mu'|^2 starts the accumulator (fp32), which 32-wide rows have no registers for; those
+// have a slot to spare (d <= 31) and carry it there.
 template <int DK>
-__host__ __device__ constexpr int tiles_per_step(int k) { return k <= 64 && DK == 16 ? 8 : 4; }
+constexpr bool starts_from_bias() { return DK == 16; }
 
 // Per-unit state in global memory.  KPM = kmax rounded up to 32.
 struct UnitState {
     int *S;            // [KPM][32]      integer sums
     int *n;            // [KPM]          counts
     double *mu;        // [32][KPM]      exact centroids, transposed
-    half8 *afrag;      // [KPM/32][4][64] A fragments (hi steps then lo steps; NS2 <= 4)
-    float *bias;       // [KPM]          |mu'|^2 (fp32), huge for padding rows: initial accumulator values
+    half8 *afrag;      // [KPM/32][4][64] A fragments (hi steps then lo steps; NS2 <= 4), centroid c in row frag_row(c)
+    float *bias;       // [KPM]          |mu'|^2 (fp32), huge for padding rows, in the order of the accumulator's registers
 };
 
 __device__ __forceinline__ UnitState unit_state(const StreamArgs &a, int u)
@@ -85,13 +84,13 @@ __global__ __launch_bounds__(256) void stream_offsets_kernel(const StreamArgs a)
     }
 }
 
-// Centred f16 copy of the rows (row-major, DK halfs per row, absent knobs zero) and the squared
+// Centred f16 copy of the rows in tiles (packed_at; absent knobs zero, 32-wide rows with the bias slot's constant) and the squared
 // norm of every centred row.
 template <int DK>
 __global__ void stream_pack_kernel(const StreamArgs a, int64_t n_rows)
 {
     const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= n_rows) return;
+    if (r >= n_rows || r < a.task_off[0]) return;        // (rows before the first task have no place among the tiles)
     int lo = 0, hi = a.T;                      // task of row r: last t with task_off[t] <= r
     while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;
@@ -99,7 +98,8 @@ __global__ void stream_pack_kernel(const StreamArgs a, int64_t n_rows)
     }
     const float *o = a.ojf + lo * 32;
     float x2 = 0.0f;
-    _Float16 *dst = reinterpret_cast<_Float16 *>(a.xh) + r * DK;
+    unsigned char *dst = reinterpret_cast<unsigned char *>(a.xh) + ((a.task_off[lo] >> 5) + lo) * (32 * DK * 2);
+    const int in_task = (int)(r - a.task_off[lo]);
 #pragma unroll
     for (int g = 0; g < DK / 8; ++g) {
         half8 v;
@@ -111,7 +111,8 @@ __global__ void stream_pack_kernel(const StreamArgs a, int64_t n_rows)
             x2 = __builtin_fmaf(f, f, x2);
             v[i] = (_Float16)f;
         }
-        *reinterpret_cast<half8 *>(dst + 8 * g) = v;
+        if (!starts_from_bias<DK>() && g == DK / 8 - 1) v[7] = (_Float16)bias_scale(true);
+        *reinterpret_cast<half8 *>(dst + packed_at(in_task, g, DK)) = v;
     }
     a.x2[r] = x2;
 }
@@ -234,16 +235,22 @@ __global__ __launch_bounds__(32 * (DK / 8)) void stream_update_kernel(const Stre
     // |mu'|^2 over all knob groups of the centroid (the G lanes of a centroid are neighbours)
 #pragma unroll
     for (int off = G / 2; off >= 1; off >>= 1) b = b + __shfl_xor(b, off, 64);
-    // |mu'|^2 starts the accumulator; padding centroid rows get a score above all others
-    if (g == G - 1) st.bias[c] = c < k ? (float)b : kPadScore;
+    // padding centroid rows get a score above all others
+    if (starts_from_bias<DK>()) {
+        if (g == G - 1) st.bias[mt * 32 + 16 * (c & 1) + (m32 >> 1)] = c < k ? (float)b : kPadScore;
+    } else if (g == G - 1) {
+        const float bs = c < k ? __builtin_fminf((float)b * (1.0f / bias_scale(true)), kHalfMax) : kHalfMax;
+        hi8[7] = (_Float16)bs;
+        lo8[7] = (_Float16)(bs - (float)hi8[7]);
+    }
     const int hh = g & 1, fstep = g >> 1;
-    st.afrag[(mt * 4 + fstep) * 64 + 32 * hh + m32] = hi8;
-    st.afrag[(mt * 4 + NS + fstep) * 64 + 32 * hh + m32] = lo8;
+    st.afrag[(mt * 4 + fstep) * 64 + 32 * hh + frag_row(m32)] = hi8;
+    st.afrag[(mt * 4 + NS + fstep) * 64 + 32 * hh + frag_row(m32)] = lo8;
 
     float bmax = c < k ? __double2float_ru(b) * 1.0000005f : 0.0f;
     // a start (or an empty cluster still there) so far off that an operand may have been clamped: every centroid
     // is a candidate of every row
-    if (!(bmax <= kHalfMax * kHalfMax / 4.0f)) bmax = 1.0e30f;
+    if (!(bmax <= (starts_from_bias<DK>() ? kHalfMax * kHalfMax / 4.0f : max_screened(true)))) bmax = 1.0e30f;
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) bmax = __builtin_fmaxf(bmax, __shfl_xor(bmax, off, 64));
     if ((tid & 63) == 0) red[tid >> 6] = bmax;
@@ -257,52 +264,50 @@ __global__ __launch_bounds__(32 * (DK / 8)) void stream_update_kernel(const Stre
 
 template <int DK>
 struct StreamLds {
-    half8 *afrag;        // [KPM/32][4][64]
-    int *S;              // [KPM][DK] changes of the sums made by this workgroup
-    int *n;              // [KPM]
-    float *ojf;          // [DK]
+    half8 *afrag;        // [KPM/32][2*DK/16][64]
     float *bias;         // [KPM]
+    int *S;              // [KPM][DK+1] changes of the sums made by this workgroup
+    int *n;              // [KPM]
+    int *dirty;          // [KPM] (written beside the sizes; not used here)
+    float *ojf;          // [DK]
     unsigned char *wave_base;
-    // per wave: knob values of queued rows, their row slots, resolved labels, label changes
-    // ... and for the exact evaluation of queued rows: (record, centroid) pairs, per record the
-    // smallest distance (bits) and the lowest centroid attaining it, the pair counter
-    static constexpr size_t kWaveBytes = (size_t)kStreamRec * DK * 2 + kStepRows * 2 + kStepRows +
-                                         kStreamRec * 4 + kPairCap * 2 + kStepRows * 8 + kStepRows * 4 + 16;
+    static __host__ __device__ size_t wave_bytes(bool many) { return many ? ManyQueue<DK>::bytes(kWavesPerWg) : FetchedQueue<DK>::kBytes; }
     __host__ __device__ static size_t bytes(int kpm)
     {
-        size_t b = 16 * (size_t)(kpm / 32) * 4 * 64 + sizeof(int) * (size_t)kpm * DK + sizeof(int) * kpm +
-                   sizeof(float) * DK + sizeof(float) * kpm + 16;
+        size_t b = 16 * (size_t)(kpm / 32) * (2 * DK / 16) * 64 + sizeof(float) * kpm + sizeof(int) * (size_t)kpm * (DK + 1) +
+                   sizeof(int) * kpm * 2 + sizeof(float) * DK;
         b = (b + 15) & ~(size_t)15;
-        return b + ((kWaveBytes + 15) & ~(size_t)15) * kWavesPerWg;
+        const size_t wave = wave_bytes(false);
+        return b + (kpm > 64 && wave_bytes(true) > wave ? wave_bytes(true) : wave) * kWavesPerWg;      // (units of either form)
     }
     __device__ StreamLds(unsigned char *base, int kpm)
     {
         size_t o = 0;
-        afrag = reinterpret_cast<half8 *>(base + o);  o += 16 * (size_t)(kpm / 32) * 4 * 64;
-        S = reinterpret_cast<int *>(base + o);        o += sizeof(int) * (size_t)kpm * DK;
-        n = reinterpret_cast<int *>(base + o);        o += sizeof(int) * kpm;
-        ojf = reinterpret_cast<float *>(base + o);    o += sizeof(float) * DK;
-        o = (o + 15) & ~(size_t)15;
+        afrag = reinterpret_cast<half8 *>(base + o);  o += 16 * (size_t)(kpm / 32) * (2 * DK / 16) * 64;
         bias = reinterpret_cast<float *>(base + o);   o += sizeof(float) * kpm;
+        S = reinterpret_cast<int *>(base + o);        o += sizeof(int) * (size_t)kpm * (DK + 1);
+        n = reinterpret_cast<int *>(base + o);        o += sizeof(int) * kpm;
+        dirty = reinterpret_cast<int *>(base + o);    o += sizeof(int) * kpm;
+        ojf = reinterpret_cast<float *>(base + o);    o += sizeof(float) * DK;
         o = (o + 15) & ~(size_t)15;
         wave_base = base + o;
     }
 };
 
-// One (unit, row chunk) workgroup of the assignment.  NCH = chunks of 64 centroids of the unit
-// (compiled for 1, 2 or 4), TILES = 32-row tiles a wave handles per step: the more rows a step
-// holds, the fewer chains of dependent short phases (decision, exact evaluation, label changes) a
-// workgroup goes through, within what the registers hold beside the per-chunk marks.
-template <int DK, int NCH, int TILES>
+// One (unit, row chunk) workgroup of the assignment: a pass of the resident kernel that fetches its rows, over at most 512 rows
+// per wave, with the unit's state in global memory.  128 registers a wave let two workgroups of eight waves share a compute unit
+// where LDS holds them (k <= 192, or d <= 16): with four waves of 256 registers, steps of four or eight tiles and every row
+// decided afresh in every pass, the vector ALU was busy less than half of the time.  MANY: k > 64.
+template <int DK, bool MANY>
 __device__ __forceinline__ void assign_unit(const StreamArgs &a, int unit_idx)
 {
-    constexpr int NS = DK / 16, NS2 = 2 * NS;
+    constexpr int NS2 = 2 * DK / 16;
+    constexpr bool CIN = starts_from_bias<DK>();
+    typedef typename std::conditional<MANY, ManyQueue<DK>, FetchedQueue<DK>>::type Queue;
     extern __shared__ __align__(16) unsigned char smem[];
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = tid >> 6;
-    const int n32 = lane & 31;
-    const int h = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wgi = blockIdx.x - a.wg_off[unit_idx];
     const int u = a.u_begin + unit_idx;
     const int ki = a.n_k - 1 - u / a.T;
@@ -319,425 +324,109 @@ __device__ __forceinline__ void assign_unit(const StreamArgs &a, int unit_idx)
     // every pass.
     int *moved_at = a.passes + (int64_t)t * a.n_k + ki;
     if (a.it > 0 && !a.trace && *moved_at < a.it) return;
-    bool moved = false;
     for (int i = 1; i < kpu / 32; ++i) m2 = __builtin_fmaxf(m2, a.m2[u * kM2Tiles + i]);
     const UnitState st = unit_state(a, u);
     StreamLds<DK> L(smem, kpm);
+    auto region = [&]() {
+        if constexpr (MANY) return Queue(L.wave_base + Queue::bytes(kWavesPerWg) * wave, kWavesPerWg);
+        else return Queue(L.wave_base + Queue::kBytes * wave);
+    };
+    const Queue Q = region();
 
     const int64_t t0 = a.task_off[t], t1 = a.task_off[t + 1];
-    const int64_t rpw = a.rows_per_wg;
-    const int64_t r0 = t0 + (int64_t)wgi * rpw;
-    const int64_t r1 = (r0 + rpw < t1) ? r0 + rpw : t1;
-    uint8_t *labrow = a.labbuf + (int64_t)ki * a.ld;
+    const int first_row = wgi * a.rows_per_wg;                     // of the chunk, within the task
+    const int left = (int)(t1 - t0) - first_row;
+    const int run = a.rows_per_wg / kWavesPerWg;                   // rows of a wave: whole groups of 64
+    const int wave_row0 = first_row + wave * run;
+    const int here = (left < a.rows_per_wg ? left : a.rows_per_wg) - wave * run;
+    const int rows_wave = here < 0 ? 0 : (here < run ? here : run);
     const bool first = a.it == 0;
-    unsigned char *wb = L.wave_base + ((StreamLds<DK>::kWaveBytes + 15) & ~(size_t)15) * wave;
-    _Float16 *rec_x = reinterpret_cast<_Float16 *>(wb);                                          // [kStreamRec][DK]
-    unsigned short *rec_slot = reinterpret_cast<unsigned short *>(wb + (size_t)kStreamRec * DK * 2);   // [kStepRows]
-    unsigned char *lab_res = wb + (size_t)kStreamRec * DK * 2 + kStepRows * 2;                    // [kStepRows]
-    unsigned *chg = reinterpret_cast<unsigned *>(lab_res + kStepRows);                             // [kStreamRec] cur | prev << 8 | first << 16
-    unsigned short *pairs = reinterpret_cast<unsigned short *>(chg + kStreamRec);                  // [kPairCap] record << 8 | centroid
-    unsigned long long *best_bits = reinterpret_cast<unsigned long long *>(pairs + kPairCap);      // [kStepRows]
-    int *best_c = reinterpret_cast<int *>(best_bits + kStepRows);                                  // [kStepRows]
-    unsigned *npairs = reinterpret_cast<unsigned *>(best_c + kStepRows);
+    uint8_t *labrow = a.labbuf + (int64_t)ki * a.ld + t0 + wave_row0;
+    const unsigned char *packed = reinterpret_cast<const unsigned char *>(a.xh) + ((t0 >> 5) + t) * (32 * DK * 2) +
+                                  (size_t)(rows_wave ? wave_row0 : 0) * (DK * 2);
 
-    const _Float16 *xh = reinterpret_cast<const _Float16 *>(a.xh);
-    const int nch = (k + 63) >> 6;
-
-    const int64_t step_rows = (int64_t)kWavesPerWg * TILES * 32;
-
-    // rows of one step of this wave: B fragments, squared norms, previous labels
-    struct StepRows {
-        half8 B[TILES][NS];
-        float x2[TILES];
-        int prev[TILES];
-    };
-    auto load_step = [&](int64_t wrow0, StepRows &R) {
+    // the labels so far (0xFF: none): both tables, in their stored form
+    {
+        unsigned char c[8];
 #pragma unroll
-        for (int tt = 0; tt < TILES; ++tt) {
-            const int64_t row = wrow0 + tt * 32 + n32;
-            const bool lv = row < r1;
-            const int64_t rr = lv ? row : (wrow0 < r1 ? wrow0 : r0);     // a valid row either way
+        for (int i = 0; i < 8; ++i) c[i] = !first && 64 * i + lane < rows_wave ? labrow[64 * i + lane] : 0;
 #pragma unroll
-            for (int f = 0; f < NS; ++f) {
-                half8 v = *reinterpret_cast<const half8 *>(xh + rr * DK + 16 * f + 8 * h);
-                if (!lv) {
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) v[i] = (_Float16)0.0f;
-                }
-                R.B[tt][f] = v;
-            }
-            R.x2[tt] = a.x2[rr];
-            R.prev[tt] = first ? 0 : (int)labrow[rr];
+        for (int i = 0; i < 8; ++i) {
+            const int r = 64 * i + lane;
+            const unsigned char v = !first && r < rows_wave ? (unsigned char)Queue::stored(c[i]) : 0xFFu;
+            Q.lab()[r] = v;
+            Q.lab_new()[r] = v;
         }
-    };
-
-    StepRows nxt;
-    if (r0 < r1) load_step(r0 + (int64_t)wave * TILES * 32, nxt);    // under way during the set-up below
-
-    for (int e = tid; e < (kpu / 32) * NS2 * 64; e += blockDim.x) {      // the NS2 slots in use of every m-tile
-        const int src = (e / (NS2 * 64)) * 4 * 64 + e % (NS2 * 64);
-        L.afrag[src] = st.afrag[src];
     }
-    for (int e = tid; e < kpu; e += blockDim.x) L.bias[e] = st.bias[e];
-    for (int e = tid; e < k * DK; e += blockDim.x) L.S[e] = 0;
+    for (int e = tid; e < (kpu / 32) * NS2 * 64; e += blockDim.x)        // the NS2 slots in use of every m-tile
+        L.afrag[e] = st.afrag[(e / (NS2 * 64)) * 4 * 64 + e % (NS2 * 64)];
+    if (CIN)
+        for (int e = tid; e < kpu; e += blockDim.x) L.bias[e] = st.bias[e];
+    for (int e = tid; e < k * (DK + 1); e += blockDim.x) L.S[e] = 0;
     for (int c = tid; c < k; c += blockDim.x) L.n[c] = 0;
-    if (tid < DK) L.ojf[tid] = tid < 32 ? a.ojf[t * 32 + tid] : 0.0f;
+    if (tid < DK) L.ojf[tid] = a.ojf[t * 32 + tid];
     __syncthreads();
 
-    for (int64_t base = r0; base < r1; base += step_rows) {
-        const int64_t wrow0 = base + (int64_t)wave * TILES * 32;      // first row of this wave's step
-        const StepRows cur = nxt;
-        if (base + step_rows < r1) load_step(wrow0 + step_rows, nxt);  // next step's rows load under this step
-        if (wrow0 >= r1) continue;                                      // wave-uniform
-        bool live[TILES];
-#pragma unroll
-        for (int tt = 0; tt < TILES; ++tt) live[tt] = (wrow0 + tt * 32 + n32) < r1;
-
-        constexpr int kMaxCh = NCH;                  // chunks of 64 centroids
-        int cnt[TILES], candq[TILES];
-        uint32_t cmask[TILES][kMaxCh];             // candidate centroids of this lane half, per chunk
-#pragma unroll
-        for (int tt = 0; tt < TILES; ++tt) {
-            cnt[tt] = 0;
-            candq[tt] = 0;
-#pragma unroll
-            for (int ch = 0; ch < kMaxCh; ++ch) cmask[tt][ch] = 0u;
-        }
-        if (lane == 0) *npairs = 0u;
-        // fragments of the two m-tiles of chunk ch and the initial accumulator values (|mu'|^2 of the
-        // centroid rows this lane's registers belong to: rows 8 g + 4 h + (0..3) for registers 4 g + (0..3))
-        auto load_a = [&](int ch, bool has1, half8 (&A0)[NS2], half8 (&A1)[NS2], float16v &c0, float16v &c1) {
-#pragma unroll
-            for (int s = 0; s < NS2; ++s) {
-                A0[s] = L.afrag[((2 * ch) * 4 + s) * 64 + lane];        // slots 0..NS-1 hi parts, NS..2NS-1 lo parts
-                A1[s] = has1 ? L.afrag[((2 * ch + 1) * 4 + s) * 64 + lane] : A0[s];
-            }
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const float4 b0 = *reinterpret_cast<const float4 *>(L.bias + (2 * ch) * 32 + 8 * g + 4 * h);
-                const float4 b1 = has1 ? *reinterpret_cast<const float4 *>(L.bias + (2 * ch + 1) * 32 + 8 * g + 4 * h) : b0;
-                c0[4 * g + 0] = b0.x; c0[4 * g + 1] = b0.y; c0[4 * g + 2] = b0.z; c0[4 * g + 3] = b0.w;
-                c1[4 * g + 0] = b1.x; c1[4 * g + 1] = b1.y; c1[4 * g + 2] = b1.z; c1[4 * g + 3] = b1.w;
-            }
-        };
-        // one matrix instruction of the chain of a 32x32 tile
-        auto mma = [&](float16v &acc, const half8 (&Af)[NS2], const half8 (&Bt)[NS], const float16v &cinit, int s) {
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(Af[s], Bt[s % NS], s == 0 ? cinit : acc, 0, 0, 0);
-        };
-        auto min16 = [&](const float16v &acc) {
-            float m = min3f(acc[0], acc[1], acc[2]);
-#pragma unroll
-            for (int i = 3; i < 15; i += 2) m = min3f(m, acc[i], acc[i + 1]);
-            return __builtin_fminf(m, acc[15]);
-        };
-        // mark scores [i0, i0 + CH): bit set = above the threshold
-        constexpr int CH = 16 / NS2;
-        auto mark = [&](uint32_t &far, const float16v &acc, float thr, int i0) {
-#pragma unroll
-            for (int i = 0; i < CH; ++i)
-                far = __builtin_amdgcn_alignbit(far, __float_as_uint(thr - acc[i0 + i]), 31);
-        };
-
-        // One sweep over the chunks of 64 centroids.  Every chunk leaves its own minimum (over both
-        // lane halves) and the marks within the bound of that minimum; afterwards a chunk's marks
-        // count iff its minimum lies within the bound of the overall minimum.  The centroids
-        // within the bound of the overall minimum are all among them (their chunk's minimum is
-        // no larger than their score), at worst joined by some up to two bounds away, which
-        // only sends a few more rows to the exact evaluation.  Within a chunk the tiles are
-        // pipelined: the chain of the next tile is issued under the marking of the current one.
-        float bch[TILES][kMaxCh];
-        float bnd[TILES];
-#pragma unroll
-        for (int tt = 0; tt < TILES; ++tt) bnd[tt] = mfma_bound<NS2>(cur.x2[tt], m2);
-#pragma unroll
-        for (int ch = 0; ch < kMaxCh; ++ch) {
-            if (ch < nch) {
-                const bool has1 = (2 * ch + 1) * 32 < kpu;
-                half8 A0[NS2], A1[NS2];
-                float16v cin0, cin1;
-                load_a(ch, has1, A0, A1, cin0, cin1);
-                float16v accA, accB;
-                constexpr int kLast = TILES - 1;
-                if (has1) {
-                    // accA = centroids 0..31, accB = centroids 32..63 of the chunk
-#pragma unroll
-                    for (int s = 0; s < NS2; ++s) mma(accA, A0, cur.B[0], cin0, s);
-#pragma unroll
-                    for (int s = 0; s < NS2; ++s) mma(accB, A1, cur.B[0], cin1, s);
-#pragma unroll
-                    for (int tt = 0; tt < TILES; ++tt) {
-                        const int nx = tt < kLast ? tt + 1 : tt;
-                        const float m = min_halves(__builtin_fminf(min16(accA), min16(accB)));
-                        const float thr = m + bnd[tt];
-                        uint32_t far = 0;
-#pragma unroll
-                        for (int s = 0; s < NS2; ++s) mark(far, accA, thr, s * CH);
-                        // accA is consumed: its next chain runs under the marking of accB
-#pragma unroll
-                        for (int s = 0; s < NS2; ++s) {
-                            __builtin_amdgcn_sched_barrier(0);
-                            if (tt < kLast) mma(accA, A0, cur.B[nx], cin0, s);
-                            __builtin_amdgcn_sched_barrier(0);
-                            mark(far, accB, thr, s * CH);
-                        }
-                        __builtin_amdgcn_sched_barrier(0);
-                        if (tt < kLast) {
-#pragma unroll
-                            for (int s = 0; s < NS2; ++s) mma(accB, A1, cur.B[nx], cin1, s);
-                        }
-                        bch[tt][ch] = m;
-                        cmask[tt][ch] = ~far;
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
-                } else {
-                    // one block of 32 centroids: the accumulators alternate
-#pragma unroll
-                    for (int s = 0; s < NS2; ++s) mma(accA, A0, cur.B[0], cin0, s);
-#pragma unroll
-                    for (int tt = 0; tt < TILES; ++tt) {
-                        const int nx = tt < kLast ? tt + 1 : tt;
-                        float16v &now = (tt & 1) ? accB : accA;
-                        float16v &nxt2 = (tt & 1) ? accA : accB;
-                        const float m = min_halves(min16(now));
-                        const float thr = m + bnd[tt];
-                        uint32_t far = 0;
-#pragma unroll
-                        for (int s = 0; s < NS2; ++s) {
-                            __builtin_amdgcn_sched_barrier(0);
-                            if (tt < kLast) mma(nxt2, A0, cur.B[nx], cin0, s);
-                            __builtin_amdgcn_sched_barrier(0);
-                            mark(far, now, thr, s * CH);
-                        }
-                        __builtin_amdgcn_sched_barrier(0);
-                        bch[tt][ch] = m;
-                        cmask[tt][ch] = ~((far << 16) | 0xFFFFu);
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
+    // the bound of a row, as a constant and a multiple of its squared norm
+    constexpr float kPerNorm = mfma_bound_slope<NS2>();
+    const Tiles tiles = {packed, L.afrag, nullptr, L.bias, a.x2 + t0 + wave_row0, mfma_bound<NS2>(0.0f, m2), kPerNorm, bias_scale(true),
+                         (rows_wave + 31) >> 5, rows_wave, first ? ~0ull : 0ull};
+    int nrec = 0;
+    if constexpr (MANY) {
+        decide_tiles_many<DK, CIN, true>(Q, tiles, nrec, st.mu, L.ojf, kpm, k, d, lane);
+    } else if (rows_wave) {
+        const bool two = k > 32;
+        const int lregs = (((two ? k - 32 : k) + 1) / 2 + 3) & ~3;       // live accumulator registers of the last m-tile
+        int nt = 0;
+        do {
+            auto live_pass = [&](auto two_tag) {
+                constexpr bool TWO = decltype(two_tag)::value;
+                switch (lregs) {
+                case 4: nt = decide_tiles<DK, false, CIN, true, 4, TWO>(Q, tiles, nt, nrec, lane); break;
+                case 8: nt = decide_tiles<DK, false, CIN, true, 8, TWO>(Q, tiles, nt, nrec, lane); break;
+                case 12: nt = decide_tiles<DK, false, CIN, true, 12, TWO>(Q, tiles, nt, nrec, lane); break;
+                default: nt = decide_tiles<DK, false, CIN, true, 16, TWO>(Q, tiles, nt, nrec, lane); break;
                 }
-            } else {
-#pragma unroll
-                for (int tt = 0; tt < TILES; ++tt) bch[tt][ch] = __builtin_inff();
-            }
-        }
-#pragma unroll
-        for (int tt = 0; tt < TILES; ++tt) {
-            float best = bch[tt][0];
-#pragma unroll
-            for (int ch = 1; ch < kMaxCh; ++ch) best = __builtin_fminf(best, bch[tt][ch]);
-            const float lim = best + bnd[tt];
-#pragma unroll
-            for (int ch = 0; ch < kMaxCh; ++ch) {
-                const uint32_t cand = bch[tt][ch] <= lim ? cmask[tt][ch] : 0u;
-                cnt[tt] += __popc(cand);
-                candq[tt] = cand ? (ch * 32 + __clz((int)cand)) : candq[tt];
-                cmask[tt][ch] = cand;
-            }
-        }
-        // decide, or queue for the exact evaluation
-        int lab[TILES];
-        uint32_t flagged_mask = 0;
-        int nrec = 0;
-        bool no_candidate = false;          // a queued row without any candidate (cannot happen with a valid bound)
-        __builtin_amdgcn_wave_barrier();    // the pair counter is zero
-#pragma unroll
-        for (int tt = 0; tt < TILES; ++tt) {
-            unsigned c_lo, c_hi, q_lo, q_hi;
-            both_halves((unsigned)cnt[tt], c_lo, c_hi);
-            both_halves((unsigned)candq[tt], q_lo, q_hi);
-            const int total = (int)(c_lo + c_hi);
-            const int hh = c_lo ? 0 : 1;
-            const int qg = (int)(c_lo ? q_lo : q_hi);
-            lab[tt] = 64 * (qg >> 5) + centroid_of(qg & 31, hh);
-            const bool flagged = live[tt] && total != 1;
-            const uint64_t fm = __ballot(flagged) & 0xFFFFFFFFull;
-            if (fm) {
-                if (flagged) {
-                    flagged_mask |= 1u << tt;
-                    const int rs = nrec + __popcll(fm & ((1ull << n32) - 1ull));
-                    if (rs < kStreamRec) {
-#pragma unroll
-                        for (int f = 0; f < NS; ++f)
-                            *reinterpret_cast<half8 *>(rec_x + (size_t)rs * DK + 16 * f + 8 * h) = cur.B[tt][f];
-                    }
-                    if (h == 0) rec_slot[rs] = (unsigned short)(tt * 32 + n32);
-                    // this lane half's candidates of the row join the list of (record, centroid) pairs
-                    unsigned pos = atomicAdd(npairs, (unsigned)cnt[tt]);
-#pragma unroll
-                    for (int ch = 0; ch < kMaxCh; ++ch) {
-                        uint32_t m = cmask[tt][ch];
-                        while (m) {
-                            const int q = __clz((int)m);
-                            m &= ~(0x80000000u >> q);
-                            if (pos < (unsigned)kPairCap)
-                                pairs[pos] = (unsigned short)((rs << 8) | (64 * ch + centroid_of(q, h)));
-                            ++pos;
-                        }
-                    }
-                }
-                no_candidate = no_candidate || (flagged && total == 0);
-                nrec += __popcll(fm);
-            }
-        }
+            };
+            if (two) live_pass(std::true_type{});
+            else live_pass(std::false_type{});
+            resolve_batches<DK>(Q, nrec, packed, st.mu, L.ojf, kpm, k, d, lane);
+            nrec = 0;
+        } while (nt < tiles.ntiles);
+    }
+
+    // ---- label changes -> labels in memory, changes of the sums in LDS; a lane compares four rows at a time
+    bool moved = false;
+    {
+        const uint64_t below = (1ull << lane) - 1ull;
+        int cnt = 0;
         __builtin_amdgcn_wave_barrier();
-        const unsigned np = nrec ? *npairs : 0u;
-        const bool full_eval = nrec && (np > (unsigned)kPairCap || __ballot(no_candidate) != 0ull);
-        if (nrec && !full_eval) {
-            // Exact evaluation of the queued rows against their candidates only: one lane per
-            // (row, centroid) pair, the distance as sum_j ((double)x_j - mu_j)^2 with j ascending;
-            // per row the smallest distance, then the lowest centroid attaining it.
-            for (int r = lane; r < nrec; r += 64) {
-                best_bits[r] = ~0ull;
-                best_c[r] = 0x7fffffff;
-            }
-            __builtin_amdgcn_wave_barrier();
-            unsigned long long mine[kPairCap / 64];
-            int mine_rc[kPairCap / 64];
+        for (int base = 0; base < rows_wave; base += 256) {
+            const int at = base + 4 * lane;
+            const unsigned cur4 = *reinterpret_cast<const unsigned *>(Q.lab_new() + at);
+            const unsigned prev4 = *reinterpret_cast<const unsigned *>(Q.lab() + at);
 #pragma unroll
-            for (int rd = 0; rd < kPairCap / 64; ++rd) {
-                const unsigned p = rd * 64 + lane;
-                mine[rd] = ~0ull;
-                mine_rc[rd] = -1;
-                if (p < np) {
-                    const int pr = pairs[p];
-                    const int r = pr >> 8, c = pr & 0xFF;
-                    const int sl = rec_slot[r];
-                    double sd = 0.0;
-                    for (int j0 = 0; j0 < d; j0 += 8) {
-                        double mu[8];
-                        half8 xq;
-                        if (r < kStreamRec) xq = *reinterpret_cast<const half8 *>(rec_x + (size_t)r * DK + j0);
-                        else xq = *reinterpret_cast<const half8 *>(xh + (wrow0 + sl) * DK + j0);
-#pragma unroll
-                        for (int i = 0; i < 8; ++i) mu[i] = (j0 + i < d) ? st.mu[(size_t)(j0 + i) * kpm + c] : 0.0;
-#pragma unroll
-                        for (int i = 0; i < 8; ++i) {
-                            if (j0 + i < d) {
-                                const double tq = (double)((float)xq[i] + L.ojf[j0 + i]) - mu[i];
-                                sd = sd + tq * tq;
-                            }
-                        }
-                    }
-                    mine[rd] = (unsigned long long)__double_as_longlong(sd);
-                    mine_rc[rd] = pr;
-                    atomicMin(&best_bits[r], mine[rd]);
-                }
-            }
-            __builtin_amdgcn_wave_barrier();
-#pragma unroll
-            for (int rd = 0; rd < kPairCap / 64; ++rd) {
-                if (mine_rc[rd] >= 0 && best_bits[mine_rc[rd] >> 8] == mine[rd])
-                    atomicMin(&best_c[mine_rc[rd] >> 8], mine_rc[rd] & 0xFF);
-            }
-            __builtin_amdgcn_wave_barrier();
-            for (int r = lane; r < nrec; r += 64) {
-                const int bc = best_c[r];
-                lab_res[rec_slot[r]] = (unsigned char)(bc < k ? bc : 0);
-            }
-            __builtin_amdgcn_wave_barrier();
-        }
-        if (nrec && full_eval) {
-            // exact evaluation of the queued rows against all k centroids, one centroid per lane;
-            // the centroid loads of 8 knobs are issued together
-            __builtin_amdgcn_wave_barrier();
-            for (int r = 0; r < nrec; ++r) {
-                const int sl = rec_slot[r];
-                double bs = __builtin_inf();
-                int bc = 0x7fffffff;
-                for (int c0 = 0; c0 < k; c0 += 64) {
-                    int c = c0 + lane;
-                    const int cc = c < k ? c : k - 1;
-                    double s = 0.0;
-                    for (int j0 = 0; j0 < d; j0 += 8) {
-                        double mu[8];
-                        half8 xq;
-                        if (r < kStreamRec) xq = *reinterpret_cast<const half8 *>(rec_x + (size_t)r * DK + j0);
-                        else xq = *reinterpret_cast<const half8 *>(xh + (wrow0 + sl) * DK + j0);
-#pragma unroll
-                        for (int i = 0; i < 8; ++i) mu[i] = (j0 + i < d) ? st.mu[(size_t)(j0 + i) * kpm + cc] : 0.0;
-#pragma unroll
-                        for (int i = 0; i < 8; ++i) {
-                            if (j0 + i < d) {
-                                const double tq = (double)((float)xq[i] + L.ojf[j0 + i]) - mu[i];
-                                s = s + tq * tq;
-                            }
-                        }
-                    }
-                    if (c >= k) {
-                        s = __builtin_inf();
-                        c = 0x7fffffff;
-                    }
-                    wave_argmin(s, c);
-                    if (s < bs) {
-                        bs = s;
-                        bc = c;
-                    }
-                }
-                if (lane == 0) lab_res[sl] = (unsigned char)(bc < k ? bc : 0);
-            }
-            __builtin_amdgcn_wave_barrier();
-        }
-        // Label changes -> sums of this workgroup (LDS).  The rows of the step whose label changed
-        // are listed with their knob values (kStreamRec of them at most, then the list is applied
-        // and starts again) and applied together, one lane per (row, group of 4 knobs): one chain
-        // of dependent LDS accesses per step when few rows move, however many tiles hold one.
-        auto apply_changes = [&](int count) {
-            __builtin_amdgcn_wave_barrier();
-            constexpr int LPR = DK / 4, EPI = 64 / LPR;
-            const int j0 = 4 * (lane % LPR);
-            for (int e0 = 0; e0 < count; e0 += EPI) {
-                const int e = e0 + lane / LPR;
-                if (e < count && j0 < d) {
-                    const unsigned w = chg[e];
-                    const int cc = w & 0xFF, pp = (w >> 8) & 0xFF;
-                    const bool had = ((w >> 16) & 1u) == 0u;     // the row had a label before
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        if (j0 + i < d) {
-                            const int xi = (int)((float)rec_x[(size_t)e * DK + j0 + i] + L.ojf[j0 + i]);
-                            atomicAdd(&L.S[cc * DK + j0 + i], xi);
-                            if (had) atomicSub(&L.S[pp * DK + j0 + i], xi);
-                        }
-                    }
-                    if (j0 == 0) {
-                        atomicAdd(&L.n[cc], 1);
-                        if (had) atomicSub(&L.n[pp], 1);
-                    }
-                }
-            }
-            __builtin_amdgcn_wave_barrier();
-        };
-        int nchg = 0;
-#pragma unroll
-        for (int tt = 0; tt < TILES; ++tt) {
-            const int64_t row = wrow0 + tt * 32 + n32;
-            int cl = lab[tt];
-            if ((flagged_mask >> tt) & 1u) cl = lab_res[tt * 32 + n32];
-            const int prev = cur.prev[tt];
-            const bool changed = live[tt] && (first || cl != prev);
-            const uint64_t cm = __ballot(changed) & 0xFFFFFFFFull;
-            if (cm) {
-                const int c = __popcll(cm);
-                if (nchg + c > kStreamRec) {                       // wave-uniform
-                    apply_changes(nchg);
-                    nchg = 0;
+            for (int i = 0; i < 4; ++i) {
+                const unsigned cur = (cur4 >> (8 * i)) & 0xFFu, prev = (prev4 >> (8 * i)) & 0xFFu;
+                const bool changed = first ? at + i < rows_wave : cur != prev;
+                const uint64_t cm = __ballot(changed);
+                if (!cm) continue;
+                const int add = __popcll(cm);
+                moved = true;
+                if (cnt + add > Queue::kChanges) {
+                    apply_listed<DK>(Q, cnt, packed, L.S, L.n, L.dirty, L.ojf, d, 0);
+                    cnt = 0;
                 }
                 if (changed) {
-                    const int rs = nchg + __popcll(cm & ((1ull << n32) - 1ull));
-#pragma unroll
-                    for (int f = 0; f < NS; ++f)
-                        *reinterpret_cast<half8 *>(rec_x + (size_t)rs * DK + 16 * f + 8 * h) = cur.B[tt][f];
-                    if (h == 0) {
-                        chg[rs] = (unsigned)cl | ((unsigned)prev << 8) | (first ? 0x10000u : 0u);
-                        labrow[row] = (uint8_t)cl;
-                    }
+                    const unsigned c = Queue::centroid(cur);
+                    labrow[at + i] = (uint8_t)c;
+                    // (a first label is told by a place of its own: the number 255 is a centroid here)
+                    Q.changes()[cnt + __popcll(cm & below)] = c | (first ? 0u : Queue::centroid(prev)) << 8 | (unsigned)(at + i) << 16 | (first ? 0x80000000u : 0u);
                 }
-                nchg += c;
+                cnt += add;
             }
         }
-        if (nchg) {
-            apply_changes(nchg);
-            moved = true;
-        }
+        if (cnt) apply_listed<DK>(Q, cnt, packed, L.S, L.n, L.dirty, L.ojf, d, 0);
     }
 
     const bool any_moved = __syncthreads_or(moved ? 1 : 0) != 0;
@@ -745,7 +434,7 @@ __device__ __forceinline__ void assign_unit(const StreamArgs &a, int unit_idx)
     if (any_moved && !a.final_pass) {
         if (tid == 0) *moved_at = a.it + 1;
         for (int e = tid; e < k * DK; e += blockDim.x) {
-            const int v = L.S[e];
+            const int v = L.S[(e / DK) * (DK + 1) + e % DK];
             if (v != 0) atomicAdd(&st.S[(e / DK) * 32 + (e % DK)], v);
         }
     }
@@ -780,24 +469,21 @@ __device__ __forceinline__ int unit_of_block(const StreamArgs &a, int *unit_sh)
 }
 
 template <int DK>
-__global__ __launch_bounds__(kWavesPerWg * 64, 2) void stream_assign_kernel(const StreamArgs a)
+__global__ __launch_bounds__(kWavesPerWg * 64, 4) void stream_assign_kernel(const StreamArgs a)
 {
     __shared__ int unit_sh;
     const int unit_idx = unit_of_block(a, &unit_sh);
     const int u = a.u_begin + unit_idx;
     const int k = a.ks[a.n_k - 1 - u / a.T];
     // the unit index goes through an opaque copy per variant: what a variant derives from it stays inside
-    // its branch instead of being computed for all three ahead of the branch (scalar registers)
+    // its branch instead of being computed for both ahead of the branch (scalar registers)
     int ui = unit_idx;
     if (k <= 64) {
         asm volatile("" : "+s"(ui));
-        assign_unit<DK, 1, tiles_per_step<DK>(64)>(a, ui);
-    } else if (k <= 128) {
-        asm volatile("" : "+s"(ui));
-        assign_unit<DK, 2, tiles_per_step<DK>(128)>(a, ui);
+        assign_unit<DK, false>(a, ui);
     } else {
         asm volatile("" : "+s"(ui));
-        assign_unit<DK, 4, tiles_per_step<DK>(256)>(a, ui);
+        assign_unit<DK, true>(a, ui);
     }
 }
 
@@ -805,7 +491,7 @@ __global__ __launch_bounds__(kWavesPerWg * 64, 2) void stream_assign_kernel(cons
 // workgroup per kLossRows rows of a unit, whatever the assigning workgroups walk.  How the rows are split
 // among those depends on the batch and on the chunk of the list of k, and the knee rule compares the losses,
 // so the order of the sum must not: the terms of all rows go to LDS, then lane l of four waves adds up rows l,
-// l + 64, ... of its wave's runs of consecutive rows (the runs a wave of the assignment takes per step), then
+// l + 64, ... of its wave's runs of consecutive rows (128, or 256 with at most 16 knobs and k <= 64), then
 // the lanes, the waves and, in the update kernel, the blocks of kLossRows.  Bound by the latency of the
 // centroids' gathers, hence from LDS: a step of 171 256 x 14, k = 64 and 128 (84 workgroups), takes 529 us, 545 us
 // with gathers from memory and 536 us with the loss inside the assignment, where it cost registers.
@@ -817,7 +503,7 @@ __global__ __launch_bounds__(1024) void stream_loss_kernel(const StreamArgs a)
     extern __shared__ __align__(16) unsigned char smem[];
     double *term = reinterpret_cast<double *>(smem);               // [kLossRows]
     double *mu_sh = term + kLossRows;                              // [d][KPM] centroids
-    __shared__ double red[kWavesPerWg];
+    __shared__ double red[kLossWaves];
     __shared__ int unit_sh;
     const int tid = threadIdx.x;
     const int unit_idx = unit_of_block(a, &unit_sh);
@@ -851,10 +537,10 @@ __global__ __launch_bounds__(1024) void stream_loss_kernel(const StreamArgs a)
         term[r] = s;
     }
     __syncthreads();
-    if (tid < kWavesPerWg * 64) {
-        const int run = 32 * tiles_per_step<DK>(k);
+    if (tid < kLossWaves * 64) {
+        const int run = k <= 64 && DK == 16 ? 256 : 128;
         double part = 0.0;
-        for (int base = (tid >> 6) * run; base < n; base += kWavesPerWg * run)
+        for (int base = (tid >> 6) * run; base < n; base += kLossWaves * run)
             for (int r = base + (tid & 63); r < base + run; r += 64)
                 if (r < n) part = part + term[r];
         const double ws = wave_sum(part);
@@ -863,7 +549,7 @@ __global__ __launch_bounds__(1024) void stream_loss_kernel(const StreamArgs a)
     __syncthreads();
     if (tid == 0) {
         double s = 0.0;
-        for (int w = 0; w < kWavesPerWg; ++w) s = s + red[w];
+        for (int w = 0; w < kLossWaves; ++w) s = s + red[w];
         // with fewer rows per workgroup the partials stand in the unit's sums, which nothing reads any more
         if (a.rows_per_wg < kLossRows) reinterpret_cast<double *>(st.S)[first / kLossRows] = s;
         else a.loss_part[blockIdx.x] = s;

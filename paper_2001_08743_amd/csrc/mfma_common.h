@@ -35,6 +35,9 @@ __device__ __forceinline__ float mfma_bound(float x2, float m2)
     return kE * (x2 + 2.0f * m2) + (BYTE_KNOBS ? 4.0e-5f : 2.5e-3f);
 }
 
+template <int NS2>
+constexpr float mfma_bound_slope() { return 2.5f * (float)(18 * NS2 + 6) * 5.9604644775390625e-8f; }      // ... per |x'|^2
+
 __device__ __forceinline__ float min3f(float a, float b, float c)
 {
     return __builtin_fminf(__builtin_fminf(a, b), c);
