@@ -244,8 +244,16 @@ bool many_centroids(const Plan &pl, SweepPath path, int d, int flags)
     return path == SweepPath::kStream && !(flags & CHAM_F_STREAMING) && mfma_many_fits(d, pl.kmax, pl.n_max);
 }
 
+// The vector path's two-byte sweeps (no flag asks for the vector kernel): the matrix-core kernel that fetches its rows, on knob values
+// in two parts.  f16 values per packed row, 0: not used.
+int two_part_halfs(const Plan &pl, SweepPath path, int xbytes, int d, int flags)
+{
+    if (xbytes != 2 || path != SweepPath::kVectorResident || (flags & (CHAM_F_FORCE_EXACT | CHAM_F_NO_MFMA))) return 0;
+    return mfma_two_part_halfs(d, pl.kmax, pl.n_max);
+}
+
 struct SweepWs {
-    int64_t blob = 0, init_rows = 0, ndist = 0, passes = 0, counters = 0, xh = 0, task_ojf = 0, norms = 0, labbuf = 0, total = 0;
+    int64_t blob = 0, init_rows = 0, ndist = 0, passes = 0, counters = 0, xh = 0, task_ojf = 0, norms = 0, two_part = 0, labbuf = 0, total = 0;
     int64_t fetched = 0;           // of the total: what the matrix-core kernel that fetches its rows needs beside them
     // streaming path
     int64_t x2 = 0, ojf = 0, Sg = 0, ng = 0, mu = 0, afrag = 0, biasf = 0, m2 = 0, wg_off = 0, loss = 0;
@@ -255,7 +263,7 @@ struct SweepWs {
 // xh_halfs: f16 values per row of the packed copy of the rows (0: the path needs none).  fetched: the matrix-core kernel that
 // fetches its rows in every pass runs (or, two-byte knobs, would run if the caller promised values below 2048).
 SweepWs sweep_ws(const Plan &pl, int64_t ld, bool own_labels, bool stream, const int64_t *task_off,
-                 int xh_halfs, bool fetched, int tile_halfs)
+                 int xh_halfs, bool fetched, int tile_halfs, int two_part)
 {
     SweepWs w;
     int64_t o = 0;
@@ -271,7 +279,10 @@ SweepWs sweep_ws(const Plan &pl, int64_t ld, bool own_labels, bool stream, const
     o += up(((int64_t)pl.n_k * kUnitQueues + 1) * 4); // (+ the flag of a two-byte value too large for the f16 rows)
     w.xh = o;
     o += up(ld * xh_halfs * 2);
-    if (fetched || stream) {
+    w.two_part = o;
+    o += up(ld * two_part * 2);
+    if (tile_halfs < two_part) tile_halfs = two_part;
+    if (fetched || stream || two_part) {
         // packed in tiles of 32 rows every task may need one more than its rows fill; behind them the offsets and norms of the
         // tasks' centred rows, and room to read on for (four tiles of 2 KiB, or two of 4 KiB, are fetched ahead)
         const int64_t rows_end = o;
@@ -352,6 +363,12 @@ static bool fetched_rows(const Plan &pl, SweepPath path, int xbytes, int d, int 
     return (xbytes == 2 ? mfma_path_fits_u16(d, pl.kmax, pl.n_max) : path == SweepPath::kMfmaResident) && mfma_fetches_rows(d, pl.n_max);
 }
 
+// Two-byte knobs: room for the values in two parts whatever the promise.
+static int ws_two_part(const Plan &pl, int xbytes, int d, int flags)
+{
+    return two_part_halfs(pl, SweepPath::kVectorResident, xbytes, d, flags);
+}
+
 // fetched: set to what of it SweepWs::fetched names.
 static int64_t sweep_ws_bytes(int xbytes, int64_t ld, int32_t d, const int64_t *task_off, int32_t T,
                               const int32_t *ks, int32_t n_k, int32_t flags, bool no_heap = false, int64_t *fetched = nullptr)
@@ -362,7 +379,8 @@ static int64_t sweep_ws_bytes(int xbytes, int64_t ld, int32_t d, const int64_t *
     if (rc != CHAM_OK) return rc;
     const SweepPath path = choose_path(pl, d, flags, xbytes);
     if (xbytes == 2 && path == SweepPath::kVectorResident && !u16_fits(pl)) return CHAM_E_BAD_K;
-    const SweepWs w = sweep_ws(pl, ld, true, path == SweepPath::kStream && !many_centroids(pl, path, d, flags), task_off, xh_halfs_of(path, xbytes, d), fetched_rows(pl, path, xbytes, d, flags), d <= 32 ? 32 : 64);
+    const SweepWs w = sweep_ws(pl, ld, true, path == SweepPath::kStream && !many_centroids(pl, path, d, flags), task_off, xh_halfs_of(path, xbytes, d), fetched_rows(pl, path, xbytes, d, flags), d <= 32 ? 32 : 64,
+                               ws_two_part(pl, xbytes, d, flags));
     if (fetched) *fetched = w.fetched;
     return w.total;
 }
@@ -403,7 +421,8 @@ static int32_t sweep_impl(const void *Xv, int xbytes, int64_t ld, int32_t d, con
     if (xbytes == 2 && (flags & CHAM_F_STREAMING)) return CHAM_E_BAD_FLAG;
     const SweepPath path = choose_path(pl, d, flags, xbytes);
     if (xbytes == 2 && path == SweepPath::kVectorResident && !u16_fits(pl)) return CHAM_E_BAD_K;
-    const SweepWs w = sweep_ws(pl, ld, labels == nullptr, path == SweepPath::kStream && !many_centroids(pl, path, d, flags), task_off, xh_halfs_of(path, xbytes, d), fetched_rows(pl, path, xbytes, d, flags), d <= 32 ? 32 : 64);
+    const SweepWs w = sweep_ws(pl, ld, labels == nullptr, path == SweepPath::kStream && !many_centroids(pl, path, d, flags), task_off, xh_halfs_of(path, xbytes, d), fetched_rows(pl, path, xbytes, d, flags), d <= 32 ? 32 : 64,
+                               ws_two_part(pl, xbytes, d, flags));
     const bool chunked = chunk > 0;
     const int64_t done_bytes = chunked ? up((int64_t)T * 4) : 0;
     if (!workspace || workspace_bytes < w.total + done_bytes) return CHAM_E_WORKSPACE;
@@ -463,6 +482,8 @@ static int32_t sweep_impl(const void *Xv, int xbytes, int64_t ld, int32_t d, con
     }
     int cus = 0;
     const bool many = many_centroids(pl, path, d, flags);
+    const bool two_part = two_part_halfs(pl, path, xbytes, d, flags) != 0;
+    if (two_part) a.xh = reinterpret_cast<uint16_t *>(ws + w.two_part);
     if (path == SweepPath::kStream && !many) {
         if (stream_lds_bytes(d, w.kpm) > 160 * 1024) return CHAM_E_BAD_K;
         e = compute_units(cus);
@@ -547,6 +568,8 @@ static int32_t sweep_impl(const void *Xv, int xbytes, int64_t ld, int32_t d, con
             sa.passes = a.passes;
             e = acc > 0 ? launch_stream_sweep(sa, pl.n_total, acc, s) : hipSuccess;
             if (acc == 0) e = launch_resident_sweep(a, pl.nt, s);   // all tasks empty: trivial path
+        } else if (two_part) {
+            e = launch_mfma_two_part(a, pl.n_max, pl.n_total, s);
         } else if (path == SweepPath::kMfmaResident) {
             e = launch_mfma_sweep(a, pl.n_max, pl.n_total, s);
         } else {
@@ -689,7 +712,7 @@ int32_t cham_sweep_passes(const void *workspace, int64_t workspace_bytes, int64_
     if (rc != CHAM_OK) return rc;
     if (!passes) return CHAM_E_NULL;
     // the region sits before every part of the workspace whose size depends on the path or the knob width
-    const SweepWs w = sweep_ws(pl, ld, false, false, task_off, 0, false, 0);
+    const SweepWs w = sweep_ws(pl, ld, false, false, task_off, 0, false, 0, 0);
     if (!workspace || workspace_bytes < w.passes + (int64_t)T * n_k * 4) return CHAM_E_WORKSPACE;
     (void)flags;
     hipError_t e = hipMemcpyAsync(passes, static_cast<const unsigned char *>(workspace) + w.passes,

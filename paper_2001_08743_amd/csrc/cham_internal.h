@@ -172,6 +172,8 @@ bool mfma_path_fits_d32(int d, int kmax, int64_t n_max);
 bool mfma_path_fits_u16(int d, int kmax, int64_t n_max);
 // Whether that kernel fetches its rows in every pass (from tiles of packed rows, with tables per task) or keeps them in registers.
 bool mfma_fetches_rows(int d, int64_t n_max);
+int mfma_two_part_halfs(int d, int kmax, int64_t n_max);       // 0: not usable
+hipError_t launch_mfma_two_part(const SweepArgs &a, int64_t n_max, int64_t n_total, hipStream_t s);
 bool mfma_many_fits(int d, int kmax, int64_t n_max);
 hipError_t launch_mfma_many(const SweepArgs &a, int64_t n_max, int64_t n_total, hipStream_t s);
 hipError_t launch_mfma_sweep(const SweepArgs &a, int64_t n_max, int64_t n_total, hipStream_t s);

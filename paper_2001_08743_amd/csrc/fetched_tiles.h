@@ -120,7 +120,10 @@ __device__ __forceinline__ void resolve_rows(const Queue &Q, int nrec, const dou
             double ss = 0.0;
             // knobs in groups of 8; the loads of a group are independent and overlap
             for (int j0 = 0; j0 < d; j0 += 8) {
-                const half8 xq = *reinterpret_cast<const half8 *>(Q.rec_x() + (size_t)rr * DK + j0);
+                const _Float16 *xr = Q.rec_x() + (size_t)rr * (DK * Queue::kPlanes) + j0;
+                const half8 xq = *reinterpret_cast<const half8 *>(xr);
+                half8 xs = xq;                   // (the second part of a value, where there is one)
+                if (Queue::kPlanes == 2) xs = *reinterpret_cast<const half8 *>(xr + DK);
                 const float4 oa = *reinterpret_cast<const float4 *>(ojf + j0);
                 const float4 ob = *reinterpret_cast<const float4 *>(ojf + j0 + 4);
                 const float of[8] = {oa.x, oa.y, oa.z, oa.w, ob.x, ob.y, ob.z, ob.w};
@@ -131,6 +134,7 @@ __device__ __forceinline__ void resolve_rows(const Queue &Q, int nrec, const dou
                 for (int i = 0; i < 8; ++i) {
                     // queued copies are centred; padded knobs are skipped (the last one carries the bias)
                     float xf = (float)xq[i] + of[i];
+                    if (Queue::kPlanes == 2) xf += (float)xs[i];
                     if (j0 + i >= d) xf = 0.0f;
                     const double tq = (double)xf - mu[i];
                     ss = ss + tq * tq;
@@ -189,8 +193,9 @@ __device__ __forceinline__ void resolve_few(const Queue &Q, int nrec, const doub
         const int pid = Q.rec_pid()[rr];
         // this lane's knobs of the row (the queued copy is centred; the bias slot and padded slots count as zero)
         float xa = 0.0f, xb = 0.0f;
-        if (jl < d) xa = (float)Q.rec_x()[(size_t)rr * DK + jl] + ojf[jl];
-        if (DK == 32 && jl + 16 < d) xb = (float)Q.rec_x()[(size_t)rr * DK + jl + 16] + ojf[jl + 16];
+        const _Float16 *xr = Q.rec_x() + (size_t)rr * (DK * Queue::kPlanes) + jl;
+        if (jl < d) xa = (float)xr[0] + ojf[jl] + (Queue::kPlanes == 2 ? (float)xr[DK] : 0.0f);
+        if (DK == 32 && jl + 16 < d) xb = (float)xr[16] + ojf[jl + 16] + (Queue::kPlanes == 2 ? (float)xr[DK + 16] : 0.0f);
         auto pop = [&]() -> int {
             int c = -1;
             if (rem0) {
@@ -365,24 +370,26 @@ __device__ __forceinline__ void full_sums(const Queue &Q, int *S, int *n, const 
 // label changes of the pass; the knobs of the rows being resolved, a batch at a time, from the packed copy; the labels.  A label is
 // stored as its position among the mask bits of a row (32 * lane half + position in that half's word), so that the mask of a
 // decided row is one shift away.
-template <int DK>
+// PL: f16 parts a knob value is split into (packed rows of PL * DK halfs).
+template <int DK, int PL = 1>
 struct FetchedQueue {
+    static constexpr int kPlanes = PL;
     static constexpr int kRows = DK <= 32 ? 512 : 256;      // rows a wave owns at most
     static constexpr int kCap = 96;                         // (a tile adds at most 32)
     static constexpr int kBatch = 16;
     static constexpr int kChanges = 64;
-    static constexpr size_t kOffFew = (size_t)8 * DK * 2;   // (behind the eight rows there are then at most; up to 32-wide rows)
-    static constexpr size_t kOffMask = DK <= 32 ? kOffFew + 4 * 32 * 8 : (size_t)kBatch * DK * 2;
+    static constexpr size_t kOffFew = (size_t)8 * DK * PL * 2;   // (behind the eight rows there are then at most; up to 32-wide rows)
+    static constexpr size_t kOffMask = DK <= 32 ? (kOffFew + 4 * 32 * 8 > (size_t)kBatch * DK * PL * 2 ? kOffFew + 4 * 32 * 8 : (size_t)kBatch * DK * PL * 2) : (size_t)kBatch * DK * PL * 2;
     static constexpr size_t kOffPid = kOffMask + (size_t)kCap * 8;
     static constexpr size_t kOffLab = kOffPid + (size_t)kCap * 2;
     static constexpr size_t kOffNew = kOffLab + (size_t)kRows;
     static constexpr size_t kBytes = kOffNew + (size_t)kRows;
     static_assert(kBytes % 16 == 0 && kOffLab % 16 == 0, "regions of a wave stay 16-byte aligned");
-    static_assert(kCap * 8 >= kChanges * 4 && kOffMask >= (size_t)kBatch * DK * 2 && kOffMask >= 64 * sizeof(double), "what shares a place fits it");
+    static_assert(kCap * 8 >= kChanges * 4 && kOffMask >= (size_t)kBatch * DK * PL * 2 && kOffMask >= 64 * sizeof(double), "what shares a place fits it");
     unsigned char *base;
     int first;                                              // first row of the batch being resolved
     __device__ explicit FetchedQueue(unsigned char *wb) : base(wb), first(0) {}
-    __device__ _Float16 *rec_x() const { return reinterpret_cast<_Float16 *>(base); }                    // [kBatch][DK]
+    __device__ _Float16 *rec_x() const { return reinterpret_cast<_Float16 *>(base); }                    // [kBatch][PL * DK]
     __device__ unsigned *rec_mask() const { return reinterpret_cast<unsigned *>(base + kOffMask) + 2 * first; }      // [kCap][2]
     __device__ unsigned short *rec_pid() const { return reinterpret_cast<unsigned short *>(base + kOffPid) + first; }
     __device__ double *few() const { return reinterpret_cast<double *>(base + kOffFew); }                 // [4][32]
@@ -398,6 +405,7 @@ struct FetchedQueue {
 constexpr int kManyCentroids = 224;                         // (labels 0xFE and 0xFF mean undecided and none; LDS)
 template <int DK>
 struct ManyQueue {
+    static constexpr int kPlanes = 1;
     static constexpr int kRows = 512;
     static constexpr int kCap = 96;                         // (a tile adds at most 32)
     static constexpr int kPairs = 256;
@@ -502,7 +510,7 @@ __device__ __forceinline__ void apply_listed(const Queue &Q, int cnt, const unsi
     typedef _Float16 half4 __attribute__((ext_vector_type(4)));
     constexpr int LPR = DK / 4;              // lanes per row
     constexpr int EPI = 64 / LPR;            // rows per step
-    constexpr int U = 4;
+    constexpr int U = 4, PL = Queue::kPlanes;
     const int lane = threadIdx.x & 63;
     const int j0 = 4 * (lane % LPR);
     const float4 o4 = *reinterpret_cast<const float4 *>(ojf + j0);
@@ -511,12 +519,13 @@ __device__ __forceinline__ void apply_listed(const Queue &Q, int cnt, const unsi
     __builtin_amdgcn_wave_barrier();
     for (int e0 = 0; e0 < cnt; e0 += U * EPI) {
         unsigned w[U];
-        half4 xq[U];
+        half4 xq[U], xs[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int e = e0 + u * EPI + lane / LPR;
             w[u] = Q.changes()[e < cnt ? e : 0];
-            xq[u] = *reinterpret_cast<const half4 *>(packed + packed_at((w[u] >> 16) & 0x7FFF, j0 >> 3, DK) + 2 * (j0 & 4));
+            xq[u] = *reinterpret_cast<const half4 *>(packed + packed_at((w[u] >> 16) & 0x7FFF, j0 >> 3, DK * PL) + 2 * (j0 & 4));
+            if (PL == 2) xs[u] = *reinterpret_cast<const half4 *>(packed + packed_at((w[u] >> 16) & 0x7FFF, (DK + j0) >> 3, DK * PL) + 2 * (j0 & 4));
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -529,7 +538,7 @@ __device__ __forceinline__ void apply_listed(const Queue &Q, int cnt, const unsi
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     if (j0 + i < d) {
-                        const int xi = (int)((float)xq[u][i] + of[i]);
+                        const int xi = (int)((float)xq[u][i] + of[i] + (PL == 2 ? (float)xs[u][i] : 0.0f));
                         atomicAdd(sc + i, xi);
                         if (!first) atomicSub(sp + i, xi);
                     }
@@ -549,22 +558,22 @@ __device__ __forceinline__ void apply_listed(const Queue &Q, int cnt, const unsi
 }
 
 // Tiles whose rows are fetched ahead (even: the accumulators alternate).
-constexpr int rows_ahead(int DK, bool two, bool SEP, bool CIN) { return (DK == 16 && !CIN) || (DK == 32 && !two) ? 4 : 2; }
+constexpr int rows_ahead(int W, bool two, bool SEP, bool CIN) { return (W == 16 && !CIN) || (W == 32 && !two) ? 4 : 2; }
 
 // The undecided rows of a wave: their knobs from the packed copy, a batch at a time, then the exact evaluation.
-template <int DK>
-__device__ __forceinline__ void resolve_batches(const FetchedQueue<DK> &Q, int nrec, const unsigned char *packed, const double *mu64T,
+template <int DK, int PL>
+__device__ __forceinline__ void resolve_batches(const FetchedQueue<DK, PL> &Q, int nrec, const unsigned char *packed, const double *mu64T,
                                                 const float *ojf, int KP, int k, int d, int lane)
 {
-    typedef FetchedQueue<DK> Queue;
-    constexpr int LPR = DK / 8;              // lanes per row, 16 bytes each
+    typedef FetchedQueue<DK, PL> Queue;
+    constexpr int LPR = DK * PL / 8;              // lanes per row, 16 bytes each
     Queue part = Q;
     for (part.first = 0; part.first < nrec; part.first += Queue::kBatch) {
         const int left = nrec - part.first, rows = left < Queue::kBatch ? left : Queue::kBatch;
         __builtin_amdgcn_wave_barrier();
         for (int e = lane; e < rows * LPR; e += 64)
             *reinterpret_cast<half8 *>(part.rec_x() + 8 * e) =
-                *reinterpret_cast<const half8 *>(packed + packed_at(part.rec_pid()[e / LPR], e % LPR, DK));
+                *reinterpret_cast<const half8 *>(packed + packed_at(part.rec_pid()[e / LPR], e % LPR, DK * PL));
         resolve_queue<DK>(part, rows, mu64T, ojf, KP, k, d);
     }
 }
@@ -620,18 +629,19 @@ template <int DK, bool SEP, bool CIN, bool ROW_BOUND, int LREGS, bool TWO, typen
 __device__ __forceinline__ int decide_tiles(const Queue &Q, const Tiles &T, int nt, int &nrec, int lane)
 {
     constexpr int NS = DK / 16, NS2 = 2 * NS, NSA = NS2 + (SEP ? 1 : 0);
-    constexpr int CH = NS2 == 6 ? 4 : 16 / NS2;   // scores handled between two matrix instructions
-    constexpr unsigned kTileBytes = 32 * DK * 2;
-    constexpr int kAhead = rows_ahead(DK, TWO, SEP, CIN);
+    constexpr int PL = Queue::kPlanes, NB = NS * PL, NC = NS2 * PL;      // B fragments of a row, instructions of a chain
+    constexpr int CH = NC == 6 ? 4 : (NC == 12 ? 2 : 16 / NC);           // scores handled between two matrix instructions
+    constexpr unsigned kTileBytes = 32 * DK * PL * 2;
+    constexpr int kAhead = rows_ahead(DK * PL, TWO, SEP, CIN);
     const std::integral_constant<int, LREGS> live_tag;
     const int n32 = lane & 31;
     const unsigned char *packed = T.packed;
     const bool upper = lane >= 32;
     const unsigned lane_off = (unsigned)(16 * lane);
     const float16v zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    half8 Bq[kAhead][NS];                // rows of tiles nt .. nt + kAhead - 1
+    half8 Bq[kAhead][NB];                // rows of tiles nt .. nt + kAhead - 1
 #pragma unroll
-    for (int u = 0; u < kAhead; ++u) fetch_tile<DK>(Bq[u], packed + (nt + u) * kTileBytes, lane_off);
+    for (int u = 0; u < kAhead; ++u) fetch_tile<DK * PL>(Bq[u], packed + (nt + u) * kTileBytes, lane_off);
     // squared norms of the rows, as far ahead
     float x2q[kAhead];
     const float *norms = T.x2 + 32 * nt + n32;
@@ -661,16 +671,22 @@ __device__ __forceinline__ int decide_tiles(const Queue &Q, const Tiles &T, int 
 
     // the chain starts from zero (the bias is in the operands), or from the bias in fp32
     float16v startA = zero16, startB = zero16;
-    if constexpr (CIN) {
+    if constexpr (CIN && PL == 1) {
         start_scores(startA, T.bias, lane);
         if (TWO) start_scores(startB, T.bias + 32, lane);
     }
     float16v accA, accB;
     // one matrix instruction of the chain of a 32x32 tile (the first one behind the bias step)
-    auto mma = [&](float16v &acc, const half8 (&Af)[NSA], const half8 (&Bt)[NS], const float16v &start, int s) {
+    auto mma = [&](float16v &acc, const half8 (&Af)[NSA], const half8 (&Bt)[NB], const float16v &start, int s) {
         if constexpr (SEP) {
             if (s == 0) acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(Af[NS2], bias_b, zero16, 0, 0, 0);
             acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(Af[s], Bt[s % NS], acc, 0, 0, 0);
+            return;
+        }
+        if constexpr (CIN && PL == 2) {
+            // (no registers to keep the initial scores in: fetched where the chain starts)
+            if (s == 0) start_scores(acc, T.bias + (&Af == &A1 ? 32 : 0), lane);
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(Af[s / PL], Bt[(s / PL) % NS + NS * (s % PL)], acc, 0, 0, 0);
             return;
         }
         acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(Af[s], Bt[s % NS], s == 0 ? start : acc, 0, 0, 0);
@@ -728,8 +744,8 @@ __device__ __forceinline__ int decide_tiles(const Queue &Q, const Tiles &T, int 
     if constexpr (TWO) {
         // accA = centroids 0..31 (all sixteen registers live), accB = centroids 32..k-1 of the current tile; Bn = rows of
         // the next tile, Bf = free for those of the tile kAhead further on
-        auto step = [&](half8 (&Bn)[NS], half8 (&Bf)[NS], float &x2f) {
-            fetch_tile<DK>(Bf, ahead, lane_off);
+        auto step = [&](half8 (&Bn)[NB], half8 (&Bf)[NB], float &x2f) {
+            fetch_tile<DK * PL>(Bf, ahead, lane_off);
             ahead += kTileBytes;
             const float x2 = x2f;
             if (ROW_BOUND) {
@@ -742,10 +758,10 @@ __device__ __forceinline__ int decide_tiles(const Queue &Q, const Tiles &T, int 
             const float thr = best + T.bound + (ROW_BOUND ? T.x2_scale * x2 : 0.0f);
             uint32_t near = 0;
 #pragma unroll
-            for (int s = 0; s < NS2; ++s) mark(near, accA, thr, s * CH);
+            for (int s = 0; s < NC; ++s) mark(near, accA, thr, s * CH);
             // accA is consumed: its next chain runs under the marking of accB
 #pragma unroll
-            for (int s = 0; s < NS2; ++s) {
+            for (int s = 0; s < NC; ++s) {
                 __builtin_amdgcn_sched_barrier(0);
                 mma(accA, A0, Bn, startA, s);
                 __builtin_amdgcn_sched_barrier(0);
@@ -753,7 +769,7 @@ __device__ __forceinline__ int decide_tiles(const Queue &Q, const Tiles &T, int 
             }
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int s = 0; s < NS2; ++s) mma(accB, A1, Bn, startB, s);
+            for (int s = 0; s < NC; ++s) mma(accB, A1, Bn, startB, s);
             // (registers of accB that were not walked hold padding only)
             constexpr int live_marks = CH * ((LREGS + CH - 1) / CH);
             settle(near << (16 - live_marks), prev, nt);
@@ -761,9 +777,9 @@ __device__ __forceinline__ int decide_tiles(const Queue &Q, const Tiles &T, int 
             asm volatile("" : "+v"(accB));      // (as below)
         };
 #pragma unroll
-        for (int s = 0; s < NS2; ++s) mma(accA, A0, Bq[0], startA, s);
+        for (int s = 0; s < NC; ++s) mma(accA, A0, Bq[0], startA, s);
 #pragma unroll
-        for (int s = 0; s < NS2; ++s) mma(accB, A1, Bq[0], startB, s);
+        for (int s = 0; s < NC; ++s) mma(accB, A1, Bq[0], startB, s);
         for (;;) {
 #pragma unroll
             for (int u = 0; u < kAhead; ++u) {
@@ -773,8 +789,8 @@ __device__ __forceinline__ int decide_tiles(const Queue &Q, const Tiles &T, int 
         }
     } else {
         // one m-tile: the accumulators alternate, the next tile's chain runs under this epilogue
-        auto step = [&](float16v &cur, float16v &nxt, half8 (&Bn)[NS], half8 (&Bf)[NS], float &x2f) {
-            fetch_tile<DK>(Bf, ahead, lane_off);
+        auto step = [&](float16v &cur, float16v &nxt, half8 (&Bn)[NB], half8 (&Bf)[NB], float &x2f) {
+            fetch_tile<DK * PL>(Bf, ahead, lane_off);
             ahead += kTileBytes;
             const float x2 = x2f;
             if (ROW_BOUND) {
@@ -787,7 +803,7 @@ __device__ __forceinline__ int decide_tiles(const Queue &Q, const Tiles &T, int 
             const float thr = best + T.bound + (ROW_BOUND ? T.x2_scale * x2 : 0.0f);
             uint32_t near = 0;
 #pragma unroll
-            for (int s = 0; s < NS2; ++s) {
+            for (int s = 0; s < NC; ++s) {
                 __builtin_amdgcn_sched_barrier(0);
                 mma(nxt, A0, Bn, startA, s);
                 __builtin_amdgcn_sched_barrier(0);
@@ -801,7 +817,7 @@ __device__ __forceinline__ int decide_tiles(const Queue &Q, const Tiles &T, int 
             asm volatile("" : "+v"(nxt));
         };
 #pragma unroll
-        for (int s = 0; s < NS2; ++s) mma(accA, A0, Bq[0], startA, s);
+        for (int s = 0; s < NC; ++s) mma(accA, A0, Bq[0], startA, s);
         for (;;) {
 #pragma unroll
             for (int u = 0; u < kAhead; ++u) {

@@ -55,6 +55,7 @@ struct MfmaLds {
     double *mu64T;      // [DK][KP]   exact centroids, transposed
     double *red;        // [32]       partial sums of the loss
     float *bias;        // [KP]       upper bound of |mu - o|^2 per centroid (0 for padding rows)
+    float *start;       // [KP]       initial scores in the order of the accumulator's registers (values in two parts)
     half8 *afrag;       // [KP/32][2*DK/16][64]  A fragments: hi parts then lo parts
     half8 *abias;       // [KP/32][64] A fragments of the bias step (SEP only; directly behind afrag)
     int *S;             // [KP][DK+1] integer cluster sums (row stride DK + 1: rows of different clusters fall into different banks)
@@ -71,7 +72,7 @@ struct MfmaLds {
     // without the per-wave regions
     __host__ __device__ static size_t base_bytes(int KP)
     {
-        size_t b = sizeof(double) * DK * KP + sizeof(double) * 32 + sizeof(float) * KP;
+        size_t b = sizeof(double) * DK * KP + sizeof(double) * 32 + sizeof(float) * KP * 2;
         b += 16 * (size_t)(KP / 32) * (2 * DK / 16 + (SEP ? 1 : 0)) * 64;
         b += sizeof(int) * (size_t)KP * (DK + 1) + sizeof(int) * KP * 2 + sizeof(float) * DK + 32;
         return (b + 15) & ~(size_t)15;
@@ -84,6 +85,7 @@ struct MfmaLds {
         mu64T = reinterpret_cast<double *>(base + o);  o += sizeof(double) * DK * KP;
         red = reinterpret_cast<double *>(base + o);    o += sizeof(double) * 32;
         bias = reinterpret_cast<float *>(base + o);    o += sizeof(float) * KP;
+        start = reinterpret_cast<float *>(base + o);   o += sizeof(float) * KP;
         afrag = reinterpret_cast<half8 *>(base + o);   o += 16 * (size_t)(KP / 32) * (2 * DK / 16) * 64;
         abias = reinterpret_cast<half8 *>(base + o);   o += SEP ? 16 * (size_t)(KP / 32) * 64 : 0;
         S = reinterpret_cast<int *>(base + o);         o += sizeof(int) * (size_t)KP * (DK + 1);
@@ -104,6 +106,7 @@ struct MfmaLds {
 // the mask the lane had when its tile was last decided.
 template <int DK, int NTW>
 struct WaveQueue {
+    static constexpr int kPlanes = 1;
     static constexpr int kRows = NTW * 32;                  // rows a wave owns at most
     static constexpr int kCap = rec_cap(DK, NTW);
     static constexpr size_t kOffMask = (size_t)kCap * DK * 2;
@@ -209,7 +212,10 @@ __device__ __forceinline__ void apply_changes(const Queue &Q, int cnt, int *S, i
 // full_sums for every cluster (each still off by kRawOffset n): every cluster is updated, and the sums
 // are left either corrected (the next pass applies label changes to them) or, with zero_after,
 // cleared together with the sizes (the next pass rebuilds them).
-template <int DK, bool BYTE_KNOBS, bool SEP>
+// PL = 2 (knob values in two parts, below): operands and scores are a quarter of the full ones, so that w fits f16 for any
+// two-byte value, and the bias is an initial score in fp32.
+constexpr float kTwoPartScale = 0.25f;
+template <int DK, bool BYTE_KNOBS, bool SEP, int PL = 1>
 __device__ __forceinline__ void update_centroids(const MfmaLds<DK, SEP> &U, int k, int KP, int d, int stamp, bool all,
                                                  bool raw = false, bool zero_after = false)
 {
@@ -231,6 +237,7 @@ __device__ __forceinline__ void update_centroids(const MfmaLds<DK, SEP> &U, int 
         half4 hi4 = {(_Float16)0.0f, (_Float16)0.0f, (_Float16)0.0f, (_Float16)0.0f};
         half4 lo4 = hi4;
         double b = 0.0;
+        bool clamped = false;
         // The mean S / n with one division per item instead of one per knob: r = fl(1 / n), then
         // q0 = fl(S r), rem = S - q0 n (exact in one fused operation), fl(q0 + rem r).  That this
         // equals the correctly rounded quotient fl(S / n) for every count 1 <= n <= 4096 and every
@@ -261,7 +268,8 @@ __device__ __forceinline__ void update_centroids(const MfmaLds<DK, SEP> &U, int 
                 }
                 const double m = j < d ? mu - (double)U.ojf[j] : 0.0;
                 b = __builtin_fma(m, m, b);
-                float w = (float)(-2.0 * m);
+                float w = (float)((PL == 2 ? -2.0 * kTwoPartScale : -2.0) * m);
+                if (PL == 2 && all && !(__builtin_fabsf(w) <= kHalfMax)) clamped = true;
                 if (all) w = __builtin_amdgcn_fmed3f(w, -kHalfMax, kHalfMax);
                 const _Float16 hi = (_Float16)w;
                 hi4[i] = hi;
@@ -278,7 +286,9 @@ __device__ __forceinline__ void update_centroids(const MfmaLds<DK, SEP> &U, int 
                 if (all) bs = __builtin_fminf(bs, kHalfMax);
                 const _Float16 bhi = (_Float16)bs;
                 const _Float16 blo = (_Float16)(bs - (float)bhi);
-                if constexpr (SEP) {
+                if constexpr (PL == 2) {
+                    U.start[(c >> 5) * 32 + 16 * (c & 1) + ((c & 31) >> 1)] = (float)b * kTwoPartScale;
+                } else if constexpr (SEP) {
                     typedef _Float16 half2v __attribute__((ext_vector_type(2)));
                     *reinterpret_cast<half2v *>(U.abias + (c >> 5) * 64 + frag_row(c)) = half2v{bhi, blo};
                 } else {
@@ -293,6 +303,8 @@ __device__ __forceinline__ void update_centroids(const MfmaLds<DK, SEP> &U, int 
             half4 *fl = reinterpret_cast<half4 *>(U.afrag + (mt * NS2 + NS + fstep) * 64 + 32 * kh + m32) + sub;
             *fh = hi4;
             *fl = lo4;
+            // (beyond the range of the operands: behind the bound's own value, which a lane of this wave has stored)
+            if (PL == 2 && clamped) atomicMax(reinterpret_cast<int *>(U.bias + c), __float_as_int(1.0e30f));
         }
         if (zero_after && item < items) {
 #pragma unroll
@@ -1012,7 +1024,9 @@ __device__ __forceinline__ const unsigned char *packed_task(const SweepArgs &a, 
 // knob: the rounded mean over eight runs of eight rows spread over the task (any integer would do: it keeps the magnitudes
 // small).  Beside the rows, per workgroup: the largest squared norm of a centred row (for the error bound) and
 // the sum of the raw squared norms (for the loss at a fixed point; byte knobs).
-template <int DK, typename XT, bool SEP>
+// PL = 2: any two-byte value, in two parts that are exact in f16, the multiple of 256 below its magnitude and the rest; there
+// is no bias slot.
+template <int DK, typename XT, bool SEP, int PL>
 __global__ __launch_bounds__(kPackRows) void pack_centred_kernel(const SweepArgs a, int per_task)
 {
     constexpr bool kByteKnobs = sizeof(XT) == 1;
@@ -1046,12 +1060,13 @@ __global__ __launch_bounds__(kPackRows) void pack_centred_kernel(const SweepArgs
     }
     __syncthreads();
     const int row = b * kPackRows + tid;
-    unsigned c2 = 0, raw2 = 0, top = 0;
+    float c2 = 0.0f;                                         // (byte knobs and values below 2048: within 2^-20 of exact)
+    unsigned raw2 = 0, top = 0;
     if (row < nrows) {
-        unsigned char *out = const_cast<unsigned char *>(packed_task(a, t, DK));
+        unsigned char *out = const_cast<unsigned char *>(packed_task(a, t, DK * PL));
 #pragma unroll
         for (int g = 0; g < DK / 8; ++g) {
-            half8 v;
+            half8 v, rest;
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
                 const int j = 8 * g + i;
@@ -1059,19 +1074,22 @@ __global__ __launch_bounds__(kPackRows) void pack_centred_kernel(const SweepArgs
                 const int cv = j < d ? xv - off[j] : 0;
                 top = (unsigned)xv > top ? (unsigned)xv : top;
                 raw2 += (unsigned)(xv * xv);
-                c2 += (unsigned)(cv * cv);
-                v[i] = (_Float16)(float)cv;
+                c2 = __builtin_fmaf((float)cv, (float)cv, c2);
+                const int high = PL == 2 ? (cv < 0 ? -(-cv & ~255) : cv & ~255) : cv;
+                v[i] = (_Float16)(float)high;
+                rest[i] = (_Float16)(float)(cv - high);
             }
-            if (!SEP && g == DK / 8 - 1) v[7] = (_Float16)bias_scale(kByteKnobs);
-            *reinterpret_cast<half8 *>(out + packed_at(row, g, DK)) = v;
+            if (!SEP && PL == 1 && g == DK / 8 - 1) v[7] = (_Float16)bias_scale(kByteKnobs);
+            *reinterpret_cast<half8 *>(out + packed_at(row, g, DK * PL)) = v;
+            if (PL == 2) *reinterpret_cast<half8 *>(out + packed_at(row, DK / 8 + g, DK * PL)) = rest;
         }
-        if (!kByteKnobs && top >= 2048u) *a.too_large = 1;
+        if (!kByteKnobs && PL == 1 && top >= 2048u) *a.too_large = 1;
     }
-    atomicMax(&top_sq, c2);
-    atomicAdd(&sum_sq, raw2);                                // (byte knobs: at most 256 * 32 * 255^2 < 2^32)
+    atomicMax(&top_sq, (unsigned)__float_as_int(c2));        // (non-negative floats order like integers)
+    if (kByteKnobs) atomicAdd(&sum_sq, raw2);                // (at most 256 * 32 * 255^2 < 2^32)
     __syncthreads();
     if (tid == 0) {
-        a.norms[t * 32 + b] = __float_as_int((float)top_sq * 1.000001f);
+        a.norms[t * 32 + b] = __float_as_int(__int_as_float((int)top_sq) * 1.00001f);
         a.norms[t * 32 + 16 + b] = (int)sum_sq;
     }
 }
@@ -1090,13 +1108,13 @@ __host__ __device__ constexpr int centroid_rows(int kmax) { return MANY ? (kmax 
 // within the bound of the overall minimum, and some up to two bounds away).  LDS holds one workgroup per compute unit, of
 // sixteen waves up to k = 192.  16 tasks of up to 2500 x 24, k = 72, 96, 128, 20 steps: the streaming kernels' 43
 // launches 645 us a step, one launch of this NEWFIG us.
-template <int DK, typename XT, bool SEP, bool MANY>
+template <int DK, typename XT, bool SEP, bool MANY, int PL>
 __device__ __forceinline__ void run_unit_fetched(const SweepArgs &a, unsigned char *smem, int ki, int t, int k)
 {
     constexpr bool kByteKnobs = sizeof(XT) == 1;
     constexpr float kBiasScale = bias_scale(kByteKnobs);
     constexpr bool kAllowTwo = DK <= 32;      // (k <= 32 with wider rows)
-    typedef typename std::conditional<MANY, ManyQueue<DK>, FetchedQueue<DK>>::type Queue;
+    typedef typename std::conditional<MANY, ManyQueue<DK>, FetchedQueue<DK, PL>>::type Queue;
     const XT *X = reinterpret_cast<const XT *>(a.X);
     const bool two = kAllowTwo && k > 32;
     constexpr int NS = DK / 16;          // distinct B fragments per row
@@ -1136,7 +1154,7 @@ __device__ __forceinline__ void run_unit_fetched(const SweepArgs &a, unsigned ch
     const int rows_wave = nrows - wave_row0 < run ? (nrows - wave_row0 > 0 ? nrows - wave_row0 : 0) : run;
     const bool wave_live = rows_wave > 0;
     const int ntiles = (rows_wave + 31) >> 5;
-    const unsigned char *packed = packed_task(a, t, DK) + (size_t)(wave_live ? wave_row0 : 0) * (DK * 2);      // (whole tiles)
+    const unsigned char *packed = packed_task(a, t, DK * PL) + (size_t)(wave_live ? wave_row0 : 0) * (DK * PL * 2);      // (whole tiles)
 
     const int kk_last = two ? k - 32 : k;                  // centroids in the last (or only) m-tile
     const int lregs = ((kk_last + 1) / 2 + 3) & ~3;        // live accumulator registers, in groups of four
@@ -1168,7 +1186,9 @@ __device__ __forceinline__ void run_unit_fetched(const SweepArgs &a, unsigned ch
     for (int e = lane_id; e < 2 * lab_rows / 4; e += 64) reinterpret_cast<unsigned *>(Q.lab())[e] = 0xFFFFFFFFu;      // no row has a label yet
     __syncthreads();
     // padding centroid rows (beyond k) carry a huge bias so that they never win
-    for (int c = k + tid; c < KP; c += blockDim.x) {
+    if (PL == 2) {
+        for (int c = k + tid; c < KP; c += blockDim.x) U.start[(c >> 5) * 32 + 16 * (c & 1) + ((c & 31) >> 1)] = 1.0e30f;
+    } else for (int c = k + tid; c < KP; c += blockDim.x) {
         _Float16 *bslot = SEP ? reinterpret_cast<_Float16 *>(U.abias + (c >> 5) * 64 + frag_row(c))
                               : reinterpret_cast<_Float16 *>(U.afrag + ((c >> 5) * NS2 + bstep) * 64 + 32 * bhalf + frag_row(c)) + belem;
         bslot[0] = (_Float16)kHalfMax;
@@ -1189,7 +1209,7 @@ __device__ __forceinline__ void run_unit_fetched(const SweepArgs &a, unsigned ch
         U.mu64T[(size_t)j * KP + c] = v;
     }
     __syncthreads();
-    update_centroids<DK, kByteKnobs, SEP>(U, k, KP, d, 0, true);
+    update_centroids<DK, kByteKnobs, SEP, PL>(U, k, KP, d, 0, true);
     __syncthreads();
     // Screen bound of the unit: that of its farthest row.  Largest squared norm a centred centroid can take during the iteration: every
     // later centroid is a mean of rows (inside their convex hull) or stays where it started.
@@ -1202,8 +1222,11 @@ __device__ __forceinline__ void run_unit_fetched(const SweepArgs &a, unsigned ch
         m2 = wave_max_nonneg(m2);
         m2 = __builtin_fmaxf(m2, x2) * 1.000001f;
         // starts beyond the range of the screen (their operands are clamped): every centroid is a candidate of every row
-        if (!(m2 <= max_screened(kByteKnobs))) m2 = 1.0e30f;
-        bound = mfma_bound<NSA, kByteKnobs>(x2, m2);
+        if (!(m2 <= (PL == 2 ? 1.0e13f : max_screened(kByteKnobs)))) m2 = 1.0e30f;
+        // Values in two parts: twice the instructions, a quarter of the score; the absolute term is half the spacing of the low
+        // operands' subnormal values times the sum of the parts' magnitudes, at most sqrt(48) |x'| + 48 * 255.
+        if (PL == 2) bound = kTwoPartScale * mfma_bound_slope<NS2 * PL>() * (x2 + 2.0f * m2) + 7.5e-8f * (7.0f * __builtin_sqrtf(x2) + 12288.0f);
+        else bound = mfma_bound<NSA, kByteKnobs>(x2, m2);
     }
 
     int passes_run = 0;
@@ -1231,8 +1254,8 @@ __device__ __forceinline__ void run_unit_fetched(const SweepArgs &a, unsigned ch
             double part = 0.0;
             const int last = first + part_rows < rows_wave ? first + part_rows : rows_wave;
             for (int nt = first >> 5; 32 * nt < last; ++nt) {
-                half8 bt[NS];
-                fetch_tile<DK>(bt, packed + nt * (32 * DK * 2), (unsigned)(16 * lane));
+                half8 bt[NS * PL];
+                fetch_tile<DK * PL>(bt, packed + nt * (32 * DK * PL * 2), (unsigned)(16 * lane));
                 const uint32_t lab = Q.lab()[nt * 32 + n32];
                 const bool live = lab != 0xFFu;
                 const double *mc = U.mu64T + (live ? Queue::centroid(lab) : 0u) + (size_t)(8 * h) * KP;
@@ -1246,7 +1269,8 @@ __device__ __forceinline__ void run_unit_fetched(const SweepArgs &a, unsigned ch
 #pragma unroll
                     for (int i = 0; i < 8; ++i) {
                         float xf = (float)bt[f][i] + of[f][i];
-                        if (!SEP && f == bstep && i == belem) xf = h == bhalf ? 0.0f : xf;     // the bias slot is no knob
+                        if (PL == 2) xf += (float)bt[NS + f][i];
+                        else if (!SEP && f == bstep && i == belem) xf = h == bhalf ? 0.0f : xf;     // the bias slot is no knob
                         const double tq = (double)xf - mu[i];
                         s = s + tq * tq;
                     }
@@ -1270,7 +1294,7 @@ __device__ __forceinline__ void run_unit_fetched(const SweepArgs &a, unsigned ch
         const bool last_pass = (it == a.n_iter);
         passes_run = it + 1;
         int nrec = 0;                    // queued rows that the screen could not decide
-        const Tiles tiles = {packed, U.afrag, U.abias, nullptr, nullptr, bound, 0.0f, kBiasScale, ntiles, rows_wave, it == 0 ? ~0ull : 0ull};
+        const Tiles tiles = {packed, U.afrag, U.abias, U.start, nullptr, bound, 0.0f, kBiasScale, ntiles, rows_wave, it == 0 ? ~0ull : 0ull};
 
         if constexpr (MANY) {
             decide_tiles_many<DK, false, false>(Q, tiles, nrec, U.mu64T, U.ojf, KP, k, d, opaque(lane_id));
@@ -1280,10 +1304,10 @@ __device__ __forceinline__ void run_unit_fetched(const SweepArgs &a, unsigned ch
             do {
                 auto live_pass = [&](auto two_tag) {
                     switch (lregs) {
-                    case 4: nt = decide_tiles<DK, SEP, false, false, 4, decltype(two_tag)::value>(Q, tiles, nt, nrec, opaque(lane_id)); break;
-                    case 8: nt = decide_tiles<DK, SEP, false, false, 8, decltype(two_tag)::value>(Q, tiles, nt, nrec, opaque(lane_id)); break;
-                    case 12: nt = decide_tiles<DK, SEP, false, false, 12, decltype(two_tag)::value>(Q, tiles, nt, nrec, opaque(lane_id)); break;
-                    default: nt = decide_tiles<DK, SEP, false, false, 16, decltype(two_tag)::value>(Q, tiles, nt, nrec, opaque(lane_id)); break;
+                    case 4: nt = decide_tiles<DK, SEP, PL == 2, false, 4, decltype(two_tag)::value>(Q, tiles, nt, nrec, opaque(lane_id)); break;
+                    case 8: nt = decide_tiles<DK, SEP, PL == 2, false, 8, decltype(two_tag)::value>(Q, tiles, nt, nrec, opaque(lane_id)); break;
+                    case 12: nt = decide_tiles<DK, SEP, PL == 2, false, 12, decltype(two_tag)::value>(Q, tiles, nt, nrec, opaque(lane_id)); break;
+                    default: nt = decide_tiles<DK, SEP, PL == 2, false, 16, decltype(two_tag)::value>(Q, tiles, nt, nrec, opaque(lane_id)); break;
                     }
                 };
                 if constexpr (kAllowTwo) {
@@ -1292,7 +1316,7 @@ __device__ __forceinline__ void run_unit_fetched(const SweepArgs &a, unsigned ch
                 } else {
                     live_pass(std::false_type{});
                 }
-                if (nrec) resolve_batches<DK>(Q, nrec, packed, U.mu64T, U.ojf, KP, k, d, opaque(lane_id));
+                if (nrec) resolve_batches<DK, PL>(Q, nrec, packed, U.mu64T, U.ojf, KP, k, d, opaque(lane_id));
                 nrec = 0;
             } while (nt < ntiles);
         }
@@ -1368,7 +1392,7 @@ __device__ __forceinline__ void run_unit_fetched(const SweepArgs &a, unsigned ch
         if (last_pass || rows_changed == 0) break;
         if (tid == 0) U.stamp[2 + ((it + 1) & 1)] = 0;      // the next pass counts from zero (nobody adds before the barrier below)
         const bool full_next = x_aligned && rows_changed > full_above;
-        update_centroids<DK, kByteKnobs, SEP>(U, k, KP, d, it, false, full_mode, full_next);
+        update_centroids<DK, kByteKnobs, SEP, PL>(U, k, KP, d, it, false, full_mode, full_next);
         full_mode = full_next;
         __syncthreads();
     }
@@ -1444,7 +1468,7 @@ constexpr bool two_workgroups(int DK, int NTW, bool SEP) { return NTW == 0 || DK
 constexpr int kQueueGroup = 4;
 
 // NTW = 0: rows fetched per pass (run_unit_fetched), otherwise tiles of rows a wave keeps in registers (run_unit).
-template <int DK, int NTW, typename XT, bool SEP, bool MANY>
+template <int DK, int NTW, typename XT, bool SEP, bool MANY, int PL>
 __global__ __launch_bounds__(NTW == 0 ? 1024 : 512, two_workgroups(DK, NTW, SEP) ? 4 : 2) void resident_mfma_kernel(const SweepArgs a)
 {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -1509,7 +1533,7 @@ __global__ __launch_bounds__(NTW == 0 ? 1024 : 512, two_workgroups(DK, NTW, SEP)
             if (a.trace)
                 for (int e = tid; e <= a.n_iter; e += blockDim.x) a.trace[slot * (a.n_iter + 1) + e] = 0.0;
         } else {
-            if constexpr (NTW == 0) run_unit_fetched<DK, XT, SEP, MANY>(a, smem, ki, t, k);
+            if constexpr (NTW == 0) run_unit_fetched<DK, XT, SEP, MANY, PL>(a, smem, ki, t, k);
             else run_unit<DK, NTW, XT, SEP>(a, smem, ki, t, k);
         }
         if (tid == 0) next_unit = unit_of(after);   // (read by everyone after the barrier at the loop's head)
@@ -1519,7 +1543,7 @@ __global__ __launch_bounds__(NTW == 0 ? 1024 : 512, two_workgroups(DK, NTW, SEP)
     }
 }
 
-template <int DK, int NTW, typename XT, bool SEP = false, bool MANY = false>
+template <int DK, int NTW, typename XT, bool SEP = false, bool MANY = false, int PL = 1>
 hipError_t launch_mfma_t(const SweepArgs &a, int nwaves, int64_t n_max, int64_t n_total, int cus, hipStream_t s)
 {
     const int KP = centroid_rows<MANY>(a.kmax);
@@ -1527,8 +1551,8 @@ hipError_t launch_mfma_t(const SweepArgs &a, int nwaves, int64_t n_max, int64_t 
     if constexpr (NTW == 0) {
         const unsigned per_task = (unsigned)((n_max + kPackRows - 1) / kPackRows);
         if (per_task && a.ki_begin == 0)
-            hipLaunchKernelGGL((pack_centred_kernel<DK, XT, SEP>), dim3(per_task * (unsigned)a.T), dim3(kPackRows), 0, s, a, (int)per_task);
-        lds = MfmaLds<DK, SEP>::base_bytes(KP) + (MANY ? ManyQueue<DK>::bytes(nwaves) : FetchedQueue<DK>::kBytes) * nwaves;
+            hipLaunchKernelGGL((pack_centred_kernel<DK, XT, SEP, PL>), dim3(per_task * (unsigned)a.T), dim3(kPackRows), 0, s, a, (int)per_task);
+        lds = MfmaLds<DK, SEP>::base_bytes(KP) + (MANY ? ManyQueue<DK>::bytes(nwaves) : FetchedQueue<DK, PL>::kBytes) * nwaves;
     } else {
         const unsigned pb = (unsigned)((n_total + 255) / 256);
         if (pb && a.ki_begin == 0)
@@ -1537,9 +1561,9 @@ hipError_t launch_mfma_t(const SweepArgs &a, int nwaves, int64_t n_max, int64_t 
         lds = MfmaLds<DK, SEP>::bytes(KP, nwaves, NTW);
     }
     SweepArgs b = a;
-    b.n_queues = NTW == 0 && n_total * DK * 2 > 3 * 1024 * 1024 ? kUnitQueues : 1;
+    b.n_queues = NTW == 0 && n_total * DK * PL * 2 > 3 * 1024 * 1024 ? kUnitQueues : 1;
     b.queue_group = b.n_queues == 1 ? a.T : kQueueGroup;
-    auto kern = resident_mfma_kernel<DK, NTW, XT, SEP, MANY>;
+    auto kern = resident_mfma_kernel<DK, NTW, XT, SEP, MANY, PL>;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
@@ -1643,6 +1667,25 @@ hipError_t launch_mfma_many(const SweepArgs &a, int64_t n_max, int64_t n_total, 
     const int nwaves = a.kmax <= 192 ? 16 : 8;             // 160 KiB of LDS hold sixteen waves' regions beside 192 centroids
     if (a.d <= 15) return launch_mfma_t<16, 0, uint8_t, false, true>(a, nwaves, n_max, n_total, cus, s);
     return launch_mfma_t<32, 0, uint8_t, false, true>(a, nwaves, n_max, n_total, cus, s);
+}
+
+// Two-byte values without the promise, in two parts: rows of 64 slots up to 32 knobs, of 96 up to 48 (registers for one tile of 32
+// centroids then).  A short list of small k has too little to gain for the packed rows.
+int mfma_two_part_halfs(int d, int kmax, int64_t n_max)
+{
+    if (kmax < 8 || n_max <= 256) return 0;
+    if (d <= 32) return kmax <= 64 && n_max <= 4096 ? 64 : 0;
+    return d <= 48 && kmax <= 32 && n_max <= 2048 ? 96 : 0;
+}
+
+hipError_t launch_mfma_two_part(const SweepArgs &a, int64_t n_max, int64_t n_total, hipStream_t s)
+{
+    int cus = 0;
+    const hipError_t e = compute_units(cus);
+    if (e != hipSuccess) return e;
+    const int nwaves = (int64_t)a.T * a.n_k <= cus ? 16 : 8;
+    if (a.d <= 32) return launch_mfma_t<32, 0, uint16_t, false, false, 2>(a, nwaves, n_max, n_total, cus, s);
+    return launch_mfma_t<48, 0, uint16_t, false, false, 2>(a, nwaves, n_max, n_total, cus, s);
 }
 
 hipError_t launch_mfma_sweep(const SweepArgs &a, int64_t n_max, int64_t n_total, hipStream_t s)

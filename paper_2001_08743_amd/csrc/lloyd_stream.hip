@@ -390,7 +390,7 @@ __device__ __forceinline__ void assign_unit(const StreamArgs &a, int unit_idx)
             };
             if (two) live_pass(std::true_type{});
             else live_pass(std::false_type{});
-            resolve_batches<DK>(Q, nrec, packed, st.mu, L.ojf, kpm, k, d, lane);
+            resolve_batches<DK, 1>(Q, nrec, packed, st.mu, L.ojf, kpm, k, d, lane);
             nrec = 0;
         } while (nt < tiles.ntiles);
     }
