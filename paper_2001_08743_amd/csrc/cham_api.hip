@@ -253,7 +253,7 @@ int two_part_halfs(const Plan &pl, SweepPath path, int xbytes, int d, int flags)
 }
 
 struct SweepWs {
-    int64_t blob = 0, init_rows = 0, ndist = 0, passes = 0, counters = 0, xh = 0, task_ojf = 0, norms = 0, two_part = 0, labbuf = 0, total = 0;
+    int64_t blob = 0, init_rows = 0, ndist = 0, passes = 0, counters = 0, xh = 0, task_ojf = 0, norms = 0, two_part = 0, xk = 0, labbuf = 0, total = 0;
     int64_t fetched = 0;           // of the total: what the matrix-core kernel that fetches its rows needs beside them
     // streaming path
     int64_t x2 = 0, ojf = 0, Sg = 0, ng = 0, mu = 0, afrag = 0, biasf = 0, m2 = 0, wg_off = 0, loss = 0;
@@ -263,7 +263,7 @@ struct SweepWs {
 // xh_halfs: f16 values per row of the packed copy of the rows (0: the path needs none).  fetched: the matrix-core kernel that
 // fetches its rows in every pass runs (or, two-byte knobs, would run if the caller promised values below 2048).
 SweepWs sweep_ws(const Plan &pl, int64_t ld, bool own_labels, bool stream, const int64_t *task_off,
-                 int xh_halfs, bool fetched, int tile_halfs, int two_part)
+                 int xh_halfs, bool fetched, int tile_halfs, int two_part, int byte_tile)
 {
     SweepWs w;
     int64_t o = 0;
@@ -287,6 +287,8 @@ SweepWs sweep_ws(const Plan &pl, int64_t ld, bool own_labels, bool stream, const
         // tasks' centred rows, and room to read on for (four tiles of 2 KiB, or two of 4 KiB, are fetched ahead)
         const int64_t rows_end = o;
         o += up((int64_t)(pl.T + 1) * 32 * tile_halfs * 2);
+        w.xk = o;
+        if (!stream) o += up((ld / 32 + pl.T + 1) * byte_tile);
         w.task_ojf = o;
         o += up((int64_t)pl.T * 64 * 4);
         w.norms = o;
@@ -363,6 +365,11 @@ static bool fetched_rows(const Plan &pl, SweepPath path, int xbytes, int d, int 
     return (xbytes == 2 ? mfma_path_fits_u16(d, pl.kmax, pl.n_max) : path == SweepPath::kMfmaResident) && mfma_fetches_rows(d, pl.n_max);
 }
 
+// Bytes of 32 rows in the copy that the sums are rebuilt from.
+// (blocks of 32 knobs; all 32 two-byte knobs are packed in 48-wide rows with the promise, which count as two)
+static int byte_tile_of(int xbytes, int d) { return 1024 * xbytes * (xbytes == 2 && d > 31 ? 2 : 1); }
+static int tile_halfs_of(int xbytes, int d) { return xbytes == 1 || d <= 31 ? 32 : 64; }
+
 // Two-byte knobs: room for the values in two parts whatever the promise.
 static int ws_two_part(const Plan &pl, int xbytes, int d, int flags)
 {
@@ -379,8 +386,8 @@ static int64_t sweep_ws_bytes(int xbytes, int64_t ld, int32_t d, const int64_t *
     if (rc != CHAM_OK) return rc;
     const SweepPath path = choose_path(pl, d, flags, xbytes);
     if (xbytes == 2 && path == SweepPath::kVectorResident && !u16_fits(pl)) return CHAM_E_BAD_K;
-    const SweepWs w = sweep_ws(pl, ld, true, path == SweepPath::kStream && !many_centroids(pl, path, d, flags), task_off, xh_halfs_of(path, xbytes, d), fetched_rows(pl, path, xbytes, d, flags), d <= 32 ? 32 : 64,
-                               ws_two_part(pl, xbytes, d, flags));
+    const SweepWs w = sweep_ws(pl, ld, true, path == SweepPath::kStream && !many_centroids(pl, path, d, flags), task_off, xh_halfs_of(path, xbytes, d), fetched_rows(pl, path, xbytes, d, flags), tile_halfs_of(xbytes, d),
+                               ws_two_part(pl, xbytes, d, flags), byte_tile_of(xbytes, d));
     if (fetched) *fetched = w.fetched;
     return w.total;
 }
@@ -421,8 +428,8 @@ static int32_t sweep_impl(const void *Xv, int xbytes, int64_t ld, int32_t d, con
     if (xbytes == 2 && (flags & CHAM_F_STREAMING)) return CHAM_E_BAD_FLAG;
     const SweepPath path = choose_path(pl, d, flags, xbytes);
     if (xbytes == 2 && path == SweepPath::kVectorResident && !u16_fits(pl)) return CHAM_E_BAD_K;
-    const SweepWs w = sweep_ws(pl, ld, labels == nullptr, path == SweepPath::kStream && !many_centroids(pl, path, d, flags), task_off, xh_halfs_of(path, xbytes, d), fetched_rows(pl, path, xbytes, d, flags), d <= 32 ? 32 : 64,
-                               ws_two_part(pl, xbytes, d, flags));
+    const SweepWs w = sweep_ws(pl, ld, labels == nullptr, path == SweepPath::kStream && !many_centroids(pl, path, d, flags), task_off, xh_halfs_of(path, xbytes, d), fetched_rows(pl, path, xbytes, d, flags), tile_halfs_of(xbytes, d),
+                               ws_two_part(pl, xbytes, d, flags), byte_tile_of(xbytes, d));
     const bool chunked = chunk > 0;
     const int64_t done_bytes = chunked ? up((int64_t)T * 4) : 0;
     if (!workspace || workspace_bytes < w.total + done_bytes) return CHAM_E_WORKSPACE;
@@ -465,6 +472,7 @@ static int32_t sweep_impl(const void *Xv, int xbytes, int64_t ld, int32_t d, con
     a.labbuf = labels ? labels : ws + w.labbuf;
     a.trace = inertia_trace;
     a.xh = reinterpret_cast<uint16_t *>(ws + w.xh);
+    a.xk = ws + w.xk;
     a.ojf = reinterpret_cast<float *>(ws + w.task_ojf);
     a.norms = reinterpret_cast<int *>(ws + w.norms);
     a.passes = reinterpret_cast<int *>(ws + w.passes);
@@ -604,9 +612,9 @@ int32_t cham_kmeans_sweep(const uint8_t *X, int64_t ld, int32_t d, const int64_t
 // one array per GPU, inside the loaded code object, kept until the process ends.  The name below
 // is only a host-side handle of the symbol; the array's device address is looked up once per
 // device and every use in host code goes through that address.
-// CHAM_STATIC_SCRATCH_BYTES bounds what the paths need without SweepWs::fetched; that part (byte knobs, fewer than 1024 tasks: 2.5 KiB
-// each and 16 KiB) has the place behind it.
-constexpr int64_t kStaticScratchBytes = (int64_t)CHAM_STATIC_SCRATCH_BYTES + 3 * 1024 * 1024;
+// CHAM_STATIC_SCRATCH_BYTES bounds what the paths need without SweepWs::fetched; that part (byte knobs, fewer than 1024 tasks: 3.5 KiB
+// each, 16 KiB and half of the 8 MiB) has the place behind it.
+constexpr int64_t kStaticScratchBytes = (int64_t)CHAM_STATIC_SCRATCH_BYTES + 8 * 1024 * 1024;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 constexpr int kMaxDevices = 64;
 static void *g_scratch_addr[kMaxDevices];       // device address of `scratch` on each GPU, null until looked up
@@ -712,7 +720,7 @@ int32_t cham_sweep_passes(const void *workspace, int64_t workspace_bytes, int64_
     if (rc != CHAM_OK) return rc;
     if (!passes) return CHAM_E_NULL;
     // the region sits before every part of the workspace whose size depends on the path or the knob width
-    const SweepWs w = sweep_ws(pl, ld, false, false, task_off, 0, false, 0, 0);
+    const SweepWs w = sweep_ws(pl, ld, false, false, task_off, 0, false, 0, 0, 0);
     if (!workspace || workspace_bytes < w.passes + (int64_t)T * n_k * 4) return CHAM_E_WORKSPACE;
     (void)flags;
     hipError_t e = hipMemcpyAsync(passes, static_cast<const unsigned char *>(workspace) + w.passes,

@@ -36,6 +36,7 @@ struct SweepArgs {
     int *passes;                   // [T][n_k] labelling passes actually run (preset to n_iter + 1 by the host code)
     int *too_large;                // matrix-core kernels, two-byte knobs: set by the packing kernel when a value is 2048 or more (null: byte knobs)
     int queue_lds_off;             // vector kernel: LDS offset of the per-wave queues of moved rows, 0 = no room for them
+    uint8_t *xk;                   // byte copy of the rows in tiles of 32 for the rebuild of sums (same kernel)
     float *ojf;                    // [T][64] centring offsets of the rows in xh (matrix-core kernel that fetches its rows in every pass)
     int *norms;                    // [T][32] per 256 rows of a task: [0..15] float bits of the largest squared norm of a centred row, [16..31] sum of the raw squared norms
     int *unit_counter;             // [kUnitQueues] zeroed before the launch: next unit of every queue (matrix-core resident kernel)

@@ -266,102 +266,105 @@ __device__ __forceinline__ void resolve_queue(const Queue &Q, int nrec, const do
 
 // Sums and sizes of every cluster over this wave's rows, from the current labels, on the matrix
 // cores: S^T (knob x centroid) = X^T (knob x row) * onehot (row x centroid), 32 rows per instruction, all in bytes.
-// Lane (m, kh) of the A fragment holds knob m of sixteen consecutive rows, read straight
-// from the knob-major byte matrix (64 consecutive rows = 64 bytes per lane and group of 128 rows, so that a wave uses up the
-// lines it touches; the same row order is used for the labels, so any order would do).  A knob enters as the signed byte
-// x - 128 (x ^ 0x80), a row of the cluster as -128, any other as 0: with t = label ^ centroid (below 128), bit 7 of
-// t + 127 is clear where t is zero.  The sums come out as -128 (S - 128 n), |.| <= 2^26, and the knob rows of absent
-// knobs (all bytes zero) as 2^14 n, of which row 31 serves as the cluster size.  They are added to the sums
-// of the workgroup lowered by 128 n (kRawOffset: the centroid update takes that off) and to the sizes.  In bytes a
-// step of 32 rows takes 20 (k > 32: 32) vector instructions; in f16 (bytes widened by placement, one-hot by a clamped
-// difference) it was 44 (80), and the rebuild 30 000 cycles of the two workgroups of a compute unit for k = 1.
-// Needs 16-byte aligned rows (xw, ld) and reads whole runs of 64 rows: the caller makes sure
-// that the last run of the task still lies inside the matrix (rows of other tasks or padding
-// read there meet the label 0xFF, which matches no centroid).  NG = runs of 64 rows a wave owns
-// at most; the loads of 256 rows are under way at any time.  SEP: every knob row is in use, so the
-// sizes are counted from the labels.
-constexpr int kRawOffset = -128;
-// first: the 64 centroids [first, first + 64) are summed; MANY: there are more than those (labels up to 223).
-template <int DK, int NG, bool SEP, bool MANY = false, typename Queue>
-__device__ __forceinline__ void full_sums(const Queue &Q, int *S, int *n, const uint8_t *xw, int64_t ld,
-                                          int d, int k_all, int rows_here, int lane, int first = 0)
+// Lane (m, kh) of the A fragment holds knob m of sixteen consecutive rows.  A knob (of two-byte knobs, either of its bytes) enters as the
+// signed byte x - 128 (x ^ 0x80), a row of the cluster as -128, any other as 0: with t = label ^ centroid, bit 7 of t + 127 is clear
+// where t is zero (labels below 128; otherwise two more operations).  The sums come out as -128 (S - 128 n), |.| <= 2^26, and the knob
+// rows of absent knobs (all bytes zero) as 2^14 n, of which the last serves as the cluster size; with all knob rows in use the sizes are
+// counted from the labels.  They are added to the sums of the workgroup off by raw_offset n (the centroid update takes that off)
+// and to the sizes.  In bytes a step of 32 rows takes 20 (k > 32: 32) vector instructions; in f16 (bytes widened by
+// placement, one-hot by a clamped difference) it was 44 (80).
+typedef int int4v __attribute__((ext_vector_type(4)));
+typedef int int16v __attribute__((ext_vector_type(16)));
+constexpr int raw_offset(bool byte_knobs) { return byte_knobs ? -128 : -128 * 257; }
+// labels -> -128 for the rows of the centroid, 0 for others
+template <bool MANY>
+__device__ __forceinline__ int4v members(const int4v &l, int c4)
 {
-    typedef int int4v __attribute__((ext_vector_type(4)));
-    typedef int int16v __attribute__((ext_vector_type(16)));
-    constexpr int W = NG % 2 == 0 ? 2 : 1;                  // a lane's 32-row pieces per group of 64 * W rows
-    constexpr int kGroups = NG / W;
-    constexpr int kDepth = kGroups < 4 / W ? kGroups : 4 / W;
+    int4v o;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int t = MANY ? l[e] ^ c4 : (l[e] & 0x7F7F7F7F) ^ c4;
+        o[e] = MANY ? ~(((t & 0x7F7F7F7F) + 0x7F7F7F7F) | t) & (int)0x80808080 : ~(t + 0x7F7F7F7F) & (int)0x80808080;
+    }
+    return o;
+}
+// From the packed byte copy: per 32 rows, NM blocks of 32 knobs, NP bytes of a value (low, high), the 1024 bytes of an A fragment in lane
+// order.  bytes_w: the wave's first tile.  first: the 64 centroids [first, first + 64) are summed; MANY: there are more than those.
+template <int DK, int NM, int NP, bool MANY, typename Queue>
+__device__ __forceinline__ void packed_sums(const Queue &Q, int *S, int *n, const unsigned char *bytes_w, int d, int k_all, int rows_here,
+                                            int lane, int first)
+{
+    constexpr int NF = NM * NP;                    // fragments per 32 rows
+    constexpr int U = NF == 1 ? 4 : (NF == 2 ? 2 : 1);      // steps under way
     const int m32 = lane & 31, kh = lane >> 5;
     const int k = k_all - first;
     S += first * (DK + 1);
     n += first;
-    const bool two = k > 32;
-    const bool knob = m32 < d;
-    const uint8_t *xp = xw + (int64_t)(knob ? m32 : 0) * ld + 32 * W * kh;
-    const unsigned char *lp = Q.lab() + 32 * W * kh;
+    const bool two = k > 32 && NM == 1;            // (k <= 32 with more than 32 knobs)
+    const unsigned char *lp = Q.lab() + 16 * kh;
     const int c4a = (int)(Queue::stored(first + m32) * 0x01010101u), c4b = (int)(Queue::stored(first + m32 + 32) * 0x01010101u);
-    int16v acc0, acc1;
+    int16v acc0[NF], acc1[NF];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        acc0[i] = 0;
-        acc1[i] = 0;
-    }
-    const int runs = (rows_here + 63) >> 6;
-
-    // this lane's bytes of group g (zero where the knob or the run of 64 rows does not exist)
-    auto fetch = [&](int g, int4v (&w)[2 * W]) {
+    for (int f = 0; f < NF; ++f)
 #pragma unroll
-        for (int i = 0; i < 2 * W; ++i) w[i] = int4v{0, 0, 0, 0};
-        if (knob && W * g + (W == 2 ? kh : 0) < runs) {
-#pragma unroll
-            for (int i = 0; i < 2 * W; ++i) w[i] = *reinterpret_cast<const int4v *>(xp + 64 * W * g + 16 * i);
+        for (int i = 0; i < 16; ++i) {
+            acc0[f][i] = 0;
+            acc1[f][i] = 0;
         }
-    };
-    // labels -> -128 for the rows of the centroid, 0 for others
-    auto members = [](const int4v &l, int c4) {
-        int4v o;
+    const int steps = (rows_here + 31) >> 5;
+    const unsigned char *xp = bytes_w + 16 * lane;
+    int4v w[U][NF];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int t = l[e] ^ c4;
-            o[e] = MANY ? ~(((t & 0x7F7F7F7F) + 0x7F7F7F7F) | t) & (int)0x80808080 : ~(t + 0x7F7F7F7F) & (int)0x80808080;
-        }
-        return o;
-    };
-
-    int4v w[kDepth][2 * W];
+    for (int u = 0; u < U; ++u)
 #pragma unroll
-    for (int g = 0; g < kDepth; ++g) fetch(g, w[g]);
+        for (int f = 0; f < NF; ++f) w[u][f] = *reinterpret_cast<const int4v *>(xp + (size_t)((u < steps ? u : 0) * NF + f) * 1024);
+    for (int s0 = 0; s0 < steps; s0 += U) {
 #pragma unroll
-    for (int g = 0; g < kGroups; ++g) {
-        if (W * g < runs) {
+        for (int u = 0; u < U; ++u) {
+            const int s = s0 + u;
+            if (s < steps) {
+                const int4v l = *reinterpret_cast<const int4v *>(lp + 32 * s);
+                const int4v oa = members<MANY>(l, c4a);
+                int4v ob = oa;
+                if (two) ob = members<MANY>(l, c4b);
 #pragma unroll
-            for (int i = 0; i < 2 * W; ++i) {
-                const int4v A = w[g % kDepth][i] ^ (int)0x80808080;
-                int4v l = *reinterpret_cast<const int4v *>(lp + 64 * W * g + 16 * i);
-                if (!MANY) l = l & 0x7F7F7F7F;
-                acc0 = __builtin_amdgcn_mfma_i32_32x32x32_i8(A, members(l, c4a), acc0, 0, 0, 0);
-                if (two) acc1 = __builtin_amdgcn_mfma_i32_32x32x32_i8(A, members(l, c4b), acc1, 0, 0, 0);
+                for (int f = 0; f < NF; ++f) {
+                    const int4v A = w[u][f] ^ (int)0x80808080;
+                    acc0[f] = __builtin_amdgcn_mfma_i32_32x32x32_i8(A, oa, acc0[f], 0, 0, 0);
+                    if (two) acc1[f] = __builtin_amdgcn_mfma_i32_32x32x32_i8(A, ob, acc1[f], 0, 0, 0);
+                }
+                const int ahead = s + U < steps ? s + U : s;
+#pragma unroll
+                for (int f = 0; f < NF; ++f) w[u][f] = *reinterpret_cast<const int4v *>(xp + (size_t)(ahead * NF + f) * 1024);
             }
-            if (g + kDepth < kGroups) fetch(g + kDepth, w[g % kDepth]);
         }
     }
     // accumulator register i of lane (c, kh) = knob (i & 3) + 8 (i >> 2) + 4 kh of centroid c (or 32 + c)
+    const bool count_labels = (d & 31) == 0;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const int m = (i & 3) + 8 * (i >> 2) + 4 * kh;
-        if (m < d) {
-            if (m32 < k) atomicAdd(&S[m32 * (DK + 1) + m], -(acc0[i] >> 7));
-            if (two && m32 + 32 < k) atomicAdd(&S[(m32 + 32) * (DK + 1) + m], -(acc1[i] >> 7));
-        }
-        if (!SEP && i == 15 && kh == 1) {                              // knob row 31: 2^14 per row of the cluster
-            if (m32 < k) atomicAdd(&n[m32], acc0[i] >> 14);
-            if (two && m32 + 32 < k) atomicAdd(&n[m32 + 32], acc1[i] >> 14);
+    for (int q = 0; q < NM; ++q) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int m = 32 * q + (i & 3) + 8 * (i >> 2) + 4 * kh;
+            if (m < d) {
+                int a = -(acc0[q * NP][i] >> 7), b = -(acc1[q * NP][i] >> 7);
+                if (NP == 2) {
+                    a -= 256 * (acc0[q * NP + NP - 1][i] >> 7);
+                    b -= 256 * (acc1[q * NP + NP - 1][i] >> 7);
+                }
+                if (m32 < k) atomicAdd(&S[m32 * (DK + 1) + m], a);
+                if (two && m32 + 32 < k) atomicAdd(&S[(m32 + 32) * (DK + 1) + m], b);
+            }
+            if (q == NM - 1 && !count_labels && i == 15 && kh == 1) {     // the last knob row: 2^14 per row of the cluster
+                if (m32 < k) atomicAdd(&n[m32], acc0[q * NP][i] >> 14);
+                if (two && m32 + 32 < k) atomicAdd(&n[m32 + 32], acc1[q * NP][i] >> 14);
+            }
         }
     }
-    if (SEP) {
+    if (count_labels) {
         for (int e = lane; e < rows_here; e += 64) {
             const unsigned v = Q.lab()[e];
-            if (v < 64u) atomicAdd(&n[Queue::centroid(v)], 1);       // (k <= 64)
+            if (v != 0xFFu && (int)Queue::centroid(v) >= first && (int)Queue::centroid(v) < first + 64) atomicAdd(&n[Queue::centroid(v) - first], 1);
         }
     }
 }

@@ -202,6 +202,78 @@ __device__ __forceinline__ void apply_changes(const Queue &Q, int cnt, int *S, i
     __builtin_amdgcn_wave_barrier();
 }
 
+// As packed_sums, from the knob-major byte matrix: 64 consecutive rows = 64 bytes per lane and group of 128 rows, so that a wave uses
+// up the lines it touches (the labels are taken in the same order).  Needs 16-byte aligned rows (xw, ld) and reads whole runs of 64
+// rows: the caller makes sure that the last run of the task still lies inside the matrix (rows of other tasks or padding read
+// there meet the label 0xFF, which matches no centroid).  NG = runs of 64 rows a wave owns at most; the loads of 256 rows are
+// under way at any time.  SEP: every knob row is in use, so the sizes are counted from the labels.
+template <int DK, int NG, bool SEP, typename Queue>
+__device__ __forceinline__ void full_sums(const Queue &Q, int *S, int *n, const uint8_t *xw, int64_t ld,
+                                          int d, int k, int rows_here, int lane)
+{
+    constexpr int W = NG % 2 == 0 ? 2 : 1;                  // a lane's 32-row pieces per group of 64 * W rows
+    constexpr int kGroups = NG / W;
+    constexpr int kDepth = kGroups < 4 / W ? kGroups : 4 / W;
+    const int m32 = lane & 31, kh = lane >> 5;
+    const bool two = k > 32;
+    const bool knob = m32 < d;
+    const uint8_t *xp = xw + (int64_t)(knob ? m32 : 0) * ld + 32 * W * kh;
+    const unsigned char *lp = Q.lab() + 32 * W * kh;
+    const int c4a = (int)(Queue::stored(m32) * 0x01010101u), c4b = (int)(Queue::stored(m32 + 32) * 0x01010101u);
+    int16v acc0, acc1;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        acc0[i] = 0;
+        acc1[i] = 0;
+    }
+    const int runs = (rows_here + 63) >> 6;
+
+    // this lane's bytes of group g (zero where the knob or the run of 64 rows does not exist)
+    auto fetch = [&](int g, int4v (&w)[2 * W]) {
+#pragma unroll
+        for (int i = 0; i < 2 * W; ++i) w[i] = int4v{0, 0, 0, 0};
+        if (knob && W * g + (W == 2 ? kh : 0) < runs) {
+#pragma unroll
+            for (int i = 0; i < 2 * W; ++i) w[i] = *reinterpret_cast<const int4v *>(xp + 64 * W * g + 16 * i);
+        }
+    };
+    int4v w[kDepth][2 * W];
+#pragma unroll
+    for (int g = 0; g < kDepth; ++g) fetch(g, w[g]);
+#pragma unroll
+    for (int g = 0; g < kGroups; ++g) {
+        if (W * g < runs) {
+#pragma unroll
+            for (int i = 0; i < 2 * W; ++i) {
+                const int4v A = w[g % kDepth][i] ^ (int)0x80808080;
+                const int4v l = *reinterpret_cast<const int4v *>(lp + 64 * W * g + 16 * i);
+                acc0 = __builtin_amdgcn_mfma_i32_32x32x32_i8(A, members<false>(l, c4a), acc0, 0, 0, 0);
+                if (two) acc1 = __builtin_amdgcn_mfma_i32_32x32x32_i8(A, members<false>(l, c4b), acc1, 0, 0, 0);
+            }
+            if (g + kDepth < kGroups) fetch(g + kDepth, w[g % kDepth]);
+        }
+    }
+    // accumulator register i of lane (c, kh) = knob (i & 3) + 8 (i >> 2) + 4 kh of centroid c (or 32 + c)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const int m = (i & 3) + 8 * (i >> 2) + 4 * kh;
+        if (m < d) {
+            if (m32 < k) atomicAdd(&S[m32 * (DK + 1) + m], -(acc0[i] >> 7));
+            if (two && m32 + 32 < k) atomicAdd(&S[(m32 + 32) * (DK + 1) + m], -(acc1[i] >> 7));
+        }
+        if (!SEP && i == 15 && kh == 1) {                              // knob row 31: 2^14 per row of the cluster
+            if (m32 < k) atomicAdd(&n[m32], acc0[i] >> 14);
+            if (two && m32 + 32 < k) atomicAdd(&n[m32 + 32], acc1[i] >> 14);
+        }
+    }
+    if (SEP) {
+        for (int e = lane; e < rows_here; e += 64) {
+            const unsigned v = Q.lab()[e];
+            if (v < 64u) atomicAdd(&n[Queue::centroid(v)], 1);       // (k <= 64)
+        }
+    }
+}
+
 // Centroid update for the clusters touched in this pass, all threads: item (c, q) owns knobs
 // 4q..4q+3 of centroid c: mean = (double)S / (double)n, then the f16 hi/lo fragments of
 // w = -2 (mu - o) (one 8-byte store each).  The DK/4 items of a centroid sit in adjacent lanes and
@@ -209,7 +281,7 @@ __device__ __forceinline__ void apply_changes(const Queue &Q, int cnt, int *S, i
 // SEP slots 0 and 1 of the bias step) and stores the sum / 256 there as hi/lo, and its rounded-up value for the error bound.
 // all: fragments from the centroids as they are (no sums yet); starts from the caller may lie anywhere, so the
 // operands are clamped (a mean of rows is always in range).  raw: the sums were rebuilt by
-// full_sums for every cluster (each still off by kRawOffset n): every cluster is updated, and the sums
+// full_sums or packed_sums for every cluster (each still off by raw_offset n): every cluster is updated, and the sums
 // are left either corrected (the next pass applies label changes to them) or, with zero_after,
 // cleared together with the sizes (the next pass rebuilds them).
 // PL = 2 (knob values in two parts, below): operands and scores are a quarter of the full ones, so that w fits f16 for any
@@ -253,7 +325,7 @@ __device__ __forceinline__ void update_centroids(const MfmaLds<DK, SEP> &U, int 
                 if (!all && j < d) {
                     int sv = U.S[c * (DK + 1) + j];
                     if (raw) {
-                        sv -= kRawOffset * cnt;
+                        sv -= raw_offset(BYTE_KNOBS) * cnt;
                         U.S[c * (DK + 1) + j] = sv;
                     }
                     const double sd = (double)sv;
@@ -960,7 +1032,7 @@ __device__ __forceinline__ void run_unit(const SweepArgs &a, unsigned char *smem
         // |S_c|^2 = q_c n_c + r_c it is the integer (sum |x|^2 - sum q_c) minus the sum of the fractions
         // r_c / n_c, which is exact up to the rounding of those k fractions and of the final
         // subtraction (and exactly zero when every cluster's rows coincide).  The sums left by a
-        // pass that rebuilt them on the matrix cores are still off by kRawOffset n.
+        // pass that rebuilt them on the matrix cores are still off by raw_offset n.
         double *frac0 = WaveQueue<DK, NTW>(U.wave_base).few();     // the queues are idle: [k] doubles of the first wave's region
         for (int c = tid; c < k; c += blockDim.x) {
             const int nc = U.n[c];
@@ -968,7 +1040,7 @@ __device__ __forceinline__ void run_unit(const SweepArgs &a, unsigned char *smem
             if (nc > 0) {
                 unsigned long long ss = 0;
                 for (int j = 0; j < d; ++j) {
-                    const long long sv = (long long)U.S[c * (DK + 1) + j] - (full_mode ? (long long)kRawOffset * nc : 0ll);
+                    const long long sv = (long long)U.S[c * (DK + 1) + j] - (full_mode ? (long long)raw_offset(true) * nc : 0ll);
                     ss += (unsigned long long)(sv * sv);
                 }
                 const unsigned long long qc = ss / (unsigned long long)nc;
@@ -1030,8 +1102,10 @@ template <int DK, typename XT, bool SEP, int PL>
 __global__ __launch_bounds__(kPackRows) void pack_centred_kernel(const SweepArgs a, int per_task)
 {
     constexpr bool kByteKnobs = sizeof(XT) == 1;
+    constexpr int NM = DK > 32 ? 2 : 1, NP = (int)sizeof(XT);
     __shared__ int off[DK];
     __shared__ unsigned top_sq, sum_sq;
+    __shared__ __align__(16) unsigned char raw[NP][32 * NM][kPackRows];
     const int t = (int)(blockIdx.x / (unsigned)per_task), b = (int)(blockIdx.x % (unsigned)per_task);
     const int64_t r0 = a.task_off[t];
     const int nrows = (int)(a.task_off[t + 1] - r0);
@@ -1073,6 +1147,8 @@ __global__ __launch_bounds__(kPackRows) void pack_centred_kernel(const SweepArgs
                 const int xv = j < d ? (int)X[(int64_t)j * a.ld + r0 + row] : 0;
                 const int cv = j < d ? xv - off[j] : 0;
                 top = (unsigned)xv > top ? (unsigned)xv : top;
+                raw[0][j][tid] = (unsigned char)xv;
+                if (NP == 2) raw[NP - 1][j][tid] = (unsigned char)(xv >> 8);
                 raw2 += (unsigned)(xv * xv);
                 c2 = __builtin_fmaf((float)cv, (float)cv, c2);
                 const int high = PL == 2 ? (cv < 0 ? -(-cv & ~255) : cv & ~255) : cv;
@@ -1088,6 +1164,19 @@ __global__ __launch_bounds__(kPackRows) void pack_centred_kernel(const SweepArgs
     atomicMax(&top_sq, (unsigned)__float_as_int(c2));        // (non-negative floats order like integers)
     if (kByteKnobs) atomicAdd(&sum_sq, raw2);                // (at most 256 * 32 * 255^2 < 2^32)
     __syncthreads();
+    // the bytes of 32 rows in the order of A fragments (packed_sums): sixteen rows of a knob at a time
+    {
+        unsigned char *out = reinterpret_cast<unsigned char *>(a.xk) + ((r0 >> 5) + t + b * (kPackRows / 32)) * (int64_t)(1024 * NM * NP);
+        const int tiles = ((nrows - b * kPackRows < kPackRows ? nrows - b * kPackRows : kPackRows) + 31) >> 5;
+        for (int e = tid; e < tiles * 64 * NM * NP; e += kPackRows) {
+            const int f = e >> 6, kh = (e >> 5) & 1, m = e & 31;         // fragment of the workgroup's tiles, lane within it
+            const int tile = f / (NM * NP), q = f / NP % NM, p = f % NP;
+            typedef unsigned uint4v __attribute__((ext_vector_type(4)));
+            uint4v v = {0u, 0u, 0u, 0u};
+            if (32 * q + m < d) v = *reinterpret_cast<const uint4v *>(&raw[p][32 * q + m][32 * tile + 16 * kh]);
+            *reinterpret_cast<uint4v *>(out + (size_t)e * 16) = v;
+        }
+    }
     if (tid == 0) {
         a.norms[t * 32 + b] = __float_as_int(__int_as_float((int)top_sq) * 1.00001f);
         a.norms[t * 32 + 16 + b] = (int)sum_sq;
@@ -1233,11 +1322,9 @@ __device__ __forceinline__ void run_unit_fetched(const SweepArgs &a, unsigned ch
     bool at_fixed_point = false;         // the last pass run moved no row: every centroid is the mean of its cluster
     // A pass after one that moved many rows rebuilds the sums from the labels on the matrix cores
     // instead of applying the changes one by one; the first pass (every row is new) always does.
-    const uint8_t *xw = a.X + r0 + (wave_live ? wave_row0 : 0);
-    const bool x_aligned = kByteKnobs &&                              // (the rebuild reads the byte matrix)
-                           ((reinterpret_cast<uintptr_t>(a.X) | (uintptr_t)a.ld | (uintptr_t)r0) & 15) == 0 &&
-                           r0 + ((nrows + 63) & ~63) <= a.ld;       // ... and its last group of 64 rows lies inside the matrix
-    bool full_mode = x_aligned;
+    constexpr int NM = DK > 32 ? 2 : 1, NP = (int)sizeof(XT);
+    const unsigned char *bytes_w = reinterpret_cast<const unsigned char *>(a.xk) + ((r0 >> 5) + t + (wave_live ? wave_row0 >> 5 : 0)) * (int64_t)(1024 * NM * NP);
+    bool full_mode = true;
     const int full_above = nrows / kFullDivisor;      // changed rows of a pass above which the next one rebuilds
     bool traced_last = false;
 
@@ -1361,12 +1448,8 @@ __device__ __forceinline__ void run_unit_fetched(const SweepArgs &a, unsigned ch
             if (full_mode) {
                 __builtin_amdgcn_wave_barrier();
                 if (wave_live) {
-                    if constexpr (MANY) {
-                        for (int first = 0; first < k; first += 64)
-                            full_sums<DK, Queue::kRows / 64, SEP, true>(Q, U.S, U.n, xw, a.ld, d, k, rows_wave, lane_id, first);
-                    } else {
-                        full_sums<DK, Queue::kRows / 64, SEP>(Q, U.S, U.n, xw, a.ld, d, k, rows_wave, lane_id);
-                    }
+                    for (int first = 0; first < (MANY ? k : 1); first += 64)
+                        packed_sums<DK, NM, NP, MANY>(Q, U.S, U.n, bytes_w, d, k, rows_wave, lane_id, first);
                 }
             } else if (cnt) {
                 apply_listed<DK>(Q, cnt, packed, U.S, U.n, U.dirty, U.ojf, d, it);
@@ -1391,7 +1474,7 @@ __device__ __forceinline__ void run_unit_fetched(const SweepArgs &a, unsigned ch
         at_fixed_point = rows_changed == 0;
         if (last_pass || rows_changed == 0) break;
         if (tid == 0) U.stamp[2 + ((it + 1) & 1)] = 0;      // the next pass counts from zero (nobody adds before the barrier below)
-        const bool full_next = x_aligned && rows_changed > full_above;
+        const bool full_next = rows_changed > full_above;
         update_centroids<DK, kByteKnobs, SEP, PL>(U, k, KP, d, it, false, full_mode, full_next);
         full_mode = full_next;
         __syncthreads();
@@ -1411,7 +1494,7 @@ __device__ __forceinline__ void run_unit_fetched(const SweepArgs &a, unsigned ch
             if (nc > 0) {
                 unsigned long long ss = 0;
                 for (int j = 0; j < d; ++j) {
-                    const long long sv = (long long)U.S[c * (DK + 1) + j] - (full_mode ? (long long)kRawOffset * nc : 0ll);
+                    const long long sv = (long long)U.S[c * (DK + 1) + j] - (full_mode ? (long long)raw_offset(true) * nc : 0ll);
                     ss += (unsigned long long)(sv * sv);
                 }
                 const unsigned long long qc = ss / (unsigned long long)nc;

@@ -65,3 +65,20 @@ def test_chunked_sweep_equals_the_whole(chunk):
     part = binding.cham_kmeans_sweep_knee(dw.X, dw.ld, dw.d, wl.task_off, wl.ks, wl.n_iter, threshold=0.0, chunk=chunk, _sfx="_u16")
     for key in ("status", "counts", "centroids", "inertia"):
         np.testing.assert_array_equal(part[key].cpu().numpy(), whole[key].cpu().numpy(), err_msg=key)
+
+
+@pytest.mark.parametrize("d", [31, 32, 33])
+@pytest.mark.parametrize("flags", [0, binding.F_VALUES_BELOW_2048])
+def test_many_tiny_tasks_beside_a_large_one(d, flags):
+    # every task takes a tile of its own in the packed copies, whatever its rows
+    wl = workloads.wide_space(d, n_tasks=1, n=300 * 3 + 1100, d=d, ks=(2, 8), n_iter=6, card_wide=(64, 2000))
+    wl.task_off = np.concatenate([np.arange(0, 901, 3), [2000]]).astype(np.int64)
+    import torch
+    X = torch.zeros((d, 2048), dtype=torch.int16, device="cuda")
+    X[:, :2000] = torch.from_numpy(np.ascontiguousarray(wl.rows.T).view(np.int16)).cuda()
+    out = binding.cham_kmeans_sweep(X, 2048, d, wl.task_off, wl.ks, wl.n_iter, want_labels=True, flags=flags, _sfx="_u16")
+    torch.cuda.synchronize()
+    ref = oracle.sweep(wl.rows, wl.task_off, wl.ks, wl.n_iter, want_labels=True)
+    np.testing.assert_array_equal(out["status"].cpu().numpy(), ref["status"])
+    np.testing.assert_array_equal(out["counts"].cpu().numpy(), ref["counts"])
+    np.testing.assert_array_equal(out["centroids"].cpu().numpy(), ref["centroids"])
