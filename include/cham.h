@@ -132,8 +132,12 @@ int32_t cham_kmeans_sweep(const uint8_t *X, int64_t ld, int32_t d,
  *   CHAM_PATH_RESIDENT_MFMA    one workgroup per (task, k), distances on the matrix cores
  *                              (d <= 31, tasks of at most 4096 rows, k <= 64; d = 32: 4096 rows with
  *                              k <= 32, or 2048 rows with k <= 64)
- *   CHAM_PATH_STREAM_MFMA      several workgroups per (task, k), one launch pair per pass (d <= 31)
- *   CHAM_PATH_RESIDENT_VECTOR  one workgroup per (task, k), vector ALU
+ *   CHAM_PATH_STREAM_MFMA      several workgroups per (task, k), one launch pair per pass (d <= 31); lists with
+ *                              64 < k <= 224 on tasks of at most 4096 rows, unless CHAM_F_STREAMING is set, in one
+ *                              launch of the resident matrix-core kernel
+ *   CHAM_PATH_RESIDENT_VECTOR  one workgroup per (task, k), vector ALU; two-byte knobs of any value, unless a flag
+ *                              asks for this kernel, on the matrix cores with values in two parts (largest k 8 to 64,
+ *                              d <= 32, tasks of 257 to 4096 rows; largest k at most 32, d <= 48, 2048 rows)
  * cham_sweep_path_kernel gives the name of the family's dominant kernel (a static string).
  */
 #define CHAM_PATH_RESIDENT_MFMA   0
@@ -165,7 +169,8 @@ int32_t cham_sweep_passes(const void *workspace, int64_t workspace_bytes, int64_
  * process ends.  The call allocates nothing, on the device or on the host.
  *   - Limit: cham_sweep_workspace_bytes(...) for the arguments must not exceed
  *     CHAM_STATIC_SCRATCH_BYTES and T + n_k must stay below about a thousand (the host tables
- *     live on the stack); beyond: CHAM_E_TOO_LARGE, nothing is enqueued.
+ *     live on the stack); beyond: CHAM_E_TOO_LARGE, nothing is enqueued.  (For tasks above 1024 rows the
+ *     packed tiles' share of the workspace, up to 8 MiB more, does not count: the array has room for it.)
  *   - The array's device address is looked up on the first call on each GPU (with that GPU
  *     current); cham_static_init() does the lookup ahead of time, e.g. before a graph capture.
  *   - All calls on one GPU share that GPU's array, whatever the stream: calls that overlap in

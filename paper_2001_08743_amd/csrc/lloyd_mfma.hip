@@ -16,15 +16,16 @@
 // four registers, not all sixteen.  Per 32-row tile: minimum over the live registers (v_min3),
 // threshold = minimum + error bound of the row (a constant of the row for the whole unit: the
 // bound uses the largest squared norm that a centroid can have, that of the farthest row), one
-// subtract and one v_alignbit per score for the mask of centroids beyond the threshold.  If every
-// row's mask equals the mask it had when the tile was last decided (and none of its rows was
+// subtract and one v_alignbit per score for the mask of centroids within the threshold.  If every
+// row's mask is that of its label alone (rows in registers: the mask it had when the tile was last decided, and none of its rows was
 // undecided then), every row keeps its label and nothing else happens for the tile.  Otherwise a
 // row with a single centroid inside the threshold takes it; the others are queued per wave and
 // their marked centroids are re-evaluated in double in the oracle's operation order.
 // The matrix instructions of the next tile are issued between the epilogue pieces of the current
-// one.  Rows (as f16 B fragments) and labels stay in registers for all passes; centroids, integer
-// sums and counts stay in LDS; a row touches the sums only when its label changes (exact: the
-// sums are integers), through a dense per-wave queue.
+// one.  Centroids, labels, integer sums and counts stay in LDS; a row touches the sums only when its label changes (exact: the
+// sums are integers), through a dense per-wave queue.  The rows (f16 B fragments) stay in registers for all passes
+// (run_unit: tasks of at most 1024 rows) or are fetched from packed tiles in every pass (run_unit_fetched), which lets two
+// workgroups share a compute unit whatever the size of the task: 256 tasks x 4096 x 24, k = 1..64: 16.9 -> 12.7 ms a step.
 //
 // A pass that changes no label leaves the sums, hence the centroids, hence every later pass as
 // they are: the iteration stops there and reports the state it has, which is what the remaining
@@ -397,8 +398,8 @@ __device__ __forceinline__ void run_unit(const SweepArgs &a, unsigned char *smem
     constexpr bool kByteKnobs = sizeof(XT) == 1;
     constexpr double kMaxValue = kByteKnobs ? 255.0 : 2047.0;
     constexpr float kBiasScale = bias_scale(kByteKnobs);
-    // 64-wide rows leave no registers for a second m-tile, nor do 16 tiles of rows beside the bias step: k <= 32 there
-    constexpr bool kAllowTwo = DK <= 32 && !(SEP && NTW > 8);
+    // 48- and 64-wide rows: k <= 32
+    constexpr bool kAllowTwo = DK <= 32;
     const XT *X = reinterpret_cast<const XT *>(a.X);
     const bool two = kAllowTwo && k > 32;
     constexpr int NS = DK / 16;          // distinct B fragments per row
@@ -1196,7 +1197,7 @@ __host__ __device__ constexpr int centroid_rows(int kmax) { return MANY ? (kmax 
 // bound of it; the marks of a chunk count iff its minimum is within the bound of the overall one (that keeps every centroid
 // within the bound of the overall minimum, and some up to two bounds away).  LDS holds one workgroup per compute unit, of
 // sixteen waves up to k = 192.  16 tasks of up to 2500 x 24, k = 72, 96, 128, 20 steps: the streaming kernels' 43
-// launches 645 us a step, one launch of this NEWFIG us.
+// launches 645 us a step, one launch of this 460 us.
 template <int DK, typename XT, bool SEP, bool MANY, int PL>
 __device__ __forceinline__ void run_unit_fetched(const SweepArgs &a, unsigned char *smem, int ki, int t, int k)
 {
@@ -1248,7 +1249,9 @@ __device__ __forceinline__ void run_unit_fetched(const SweepArgs &a, unsigned ch
     const int kk_last = two ? k - 32 : k;                  // centroids in the last (or only) m-tile
     const int lregs = ((kk_last + 1) / 2 + 3) & ~3;        // live accumulator registers, in groups of four
     constexpr int bstep = NS - 1, bhalf = 1, belem = 7;
-    constexpr int kFullDivisor = 8;
+    // (the rebuild against changes applied one by one after a pass that moved more than 1/3, 1/8, 1/16, 1/32 of the rows: the full model
+    // 12.68 / 12.99 / 13.2 / 13.6 ms a step, 16 x 1900 x 27 two-byte knobs 479 / 510 / 525 / 569 us)
+    constexpr int kFullDivisor = 3;
 
     // ---- set-up
     for (int e = tid; e < DK * KP; e += blockDim.x) U.mu64T[e] = 0.0;

@@ -4,15 +4,14 @@
 // stream_update_kernel over units.  Labels, integer sums and counts live in global memory and are
 // updated incrementally (a row touches the sums only when its label changes: exact, integers).
 //
-// The screen is an f16 hi/lo matrix-core screen as in the resident kernel, for up to 256
-// centroids, with every knob slot of the fragments holding a knob (d <= 16 takes one 16-wide
-// step per part): |mu'|^2 enters as the initial value of the accumulator, in fp32.  Centroids
-// are taken in chunks of 64 (two 32-row m-tiles); one sweep over the chunks leaves, per chunk, the
+// The assignment is a pass of the resident kernel that fetches its rows (fetched_tiles.h), for up to 256
+// centroids.  With at most 16 knobs every slot of the fragments holds a knob (one 16-wide
+// step per part) and |mu'|^2 enters as the initial value of the accumulator, in fp32; otherwise it takes the last slot.  Up to 64
+// centroids are swept at once; more are taken in chunks of 64: every chunk leaves the
 // minimum score of every row and the scores within the error bound of that minimum, and the chunks
 // whose minimum lies within the bound of the overall minimum contribute their marks.  A row with
 // exactly one marked score is decided; any other row is re-evaluated in double against its marked
-// centroids (one lane per (row, centroid) pair; knobs ascending, no fused multiply-add, lowest
-// index on ties), or against all k centroids when the pairs do not fit.
+// centroids (knobs ascending, no fused multiply-add, lowest index on ties).
 #include "cham_device.h"
 #include "cham_internal.h"
 #include "mfma_common.h"
