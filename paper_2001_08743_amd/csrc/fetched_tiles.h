@@ -858,7 +858,7 @@ __device__ __forceinline__ void decide_tiles_many(const ManyQueue<DK> &Q, const 
     }
     for (int nt = 0; nt < T.ntiles; ++nt) {
         half8 Bt[NS];
-    #pragma unroll
+#pragma unroll
         for (int f = 0; f < NS; ++f) Bt[f] = Bn[f];
         fetch_tile<DK>(Bn, packed + (nt + 1) * kTileBytes, lane_off);
         const float bound = T.bound + (ROW_BOUND ? T.x2_scale * x2n : 0.0f);
@@ -867,7 +867,7 @@ __device__ __forceinline__ void decide_tiles_many(const ManyQueue<DK> &Q, const 
         uint32_t near[kChunks];
         float least[kChunks];
         float best = __builtin_inff();
-    #pragma unroll
+#pragma unroll
         for (int ch = 0; ch < kChunks; ++ch) {
             near[ch] = 0u;
             least[ch] = __builtin_inff();
@@ -878,17 +878,17 @@ __device__ __forceinline__ void decide_tiles_many(const ManyQueue<DK> &Q, const 
                     start_scores(accA, T.bias + 64 * ch, lane);
                     if (has1) start_scores(accB, T.bias + 64 * ch + 32, lane);
                 }
-    #pragma unroll
+#pragma unroll
                 for (int s = 0; s < NS2; ++s)
                     accA = __builtin_amdgcn_mfma_f32_32x32x16_f16(T.afrag[((2 * ch) * NS2 + s) * 64 + lane], Bt[s % NS], accA, 0, 0, 0);
                 if (has1) {
-    #pragma unroll
+#pragma unroll
                     for (int s = 0; s < NS2; ++s)
                         accB = __builtin_amdgcn_mfma_f32_32x32x16_f16(T.afrag[((2 * ch + 1) * NS2 + s) * 64 + lane], Bt[s % NS], accB, 0, 0, 0);
                 }
                 auto min16 = [](const float16v &acc) {
                     float m = vmin3(acc[0], acc[1], acc[2]);
-    #pragma unroll
+#pragma unroll
                     for (int i = 3; i < 15; i += 2) m = vmin3(m, acc[i], acc[i + 1]);
                     return vmin(m, acc[15]);
                 };
@@ -899,10 +899,10 @@ __device__ __forceinline__ void decide_tiles_many(const ManyQueue<DK> &Q, const 
                 m = vmin(__uint_as_float(lo), __uint_as_float(hi));
                 const float thr = m + bound;
                 uint32_t bits = 0;
-    #pragma unroll
+#pragma unroll
                 for (int i = 0; i < 16; ++i) bits = __builtin_amdgcn_alignbit(bits, __float_as_uint(accA[i] - thr), 31);
                 if (has1) {
-    #pragma unroll
+#pragma unroll
                     for (int i = 0; i < 16; ++i) bits = __builtin_amdgcn_alignbit(bits, __float_as_uint(accB[i] - thr), 31);
                 } else {
                     bits <<= 16;
@@ -917,7 +917,7 @@ __device__ __forceinline__ void decide_tiles_many(const ManyQueue<DK> &Q, const 
         const uint64_t place = 0x8000000000000000ull >> (prev & 63u);
         const uint32_t own = upper ? (uint32_t)place : (uint32_t)(place >> 32);
         uint32_t diff = 0u;
-    #pragma unroll
+#pragma unroll
         for (int ch = 0; ch < kChunks; ++ch) {
             near[ch] = least[ch] <= lim ? near[ch] : 0u;
             diff |= near[ch] ^ ((prev >> 6) == (uint32_t)ch ? own : 0u);
@@ -925,7 +925,7 @@ __device__ __forceinline__ void decide_tiles_many(const ManyQueue<DK> &Q, const 
         if ((__ballot(diff != 0u) | T.undecided) == 0) continue;
         const uint32_t live32 = live_rows(T.rows_wave, nt);
         int cnt = 0, at = 0;                       // marks of this lane half, stored label of one of them
-    #pragma unroll
+#pragma unroll
         for (int ch = 0; ch < kChunks; ++ch) {
             cnt += __popc(near[ch]);
             at = near[ch] ? 64 * ch + (upper ? 32 : 0) + __clz((int)near[ch]) : at;
@@ -941,7 +941,7 @@ __device__ __forceinline__ void decide_tiles_many(const ManyQueue<DK> &Q, const 
                 const int rs = nrec + __popc(fm & ((1u << n32) - 1u));
                 if (!upper) Q.rec_pid()[rs] = (unsigned short)(nt * 32 + n32);
                 unsigned pos = atomicAdd(Q.n_pairs(), (unsigned)cnt);
-    #pragma unroll
+#pragma unroll
                 for (int ch = 0; ch < kChunks; ++ch) {
                     uint32_t m = near[ch];
                     while (m) {

@@ -1150,7 +1150,7 @@ __global__ __launch_bounds__(kPackRows) void pack_centred_kernel(const SweepArgs
                 top = (unsigned)xv > top ? (unsigned)xv : top;
                 raw[0][j][tid] = (unsigned char)xv;
                 if (NP == 2) raw[NP - 1][j][tid] = (unsigned char)(xv >> 8);
-                raw2 += (unsigned)(xv * xv);
+                if (kByteKnobs) raw2 += (unsigned)(xv * xv);
                 c2 = __builtin_fmaf((float)cv, (float)cv, c2);
                 const int high = PL == 2 ? (cv < 0 ? -(-cv & ~255) : cv & ~255) : cv;
                 v[i] = (_Float16)(float)high;
