@@ -132,9 +132,9 @@ int32_t cham_kmeans_sweep(const uint8_t *X, int64_t ld, int32_t d,
  *   CHAM_PATH_RESIDENT_MFMA    one workgroup per (task, k), distances on the matrix cores
  *                              (d <= 31, tasks of at most 4096 rows, k <= 64; d = 32: 4096 rows with
  *                              k <= 32, or 2048 rows with k <= 64)
- *   CHAM_PATH_STREAM_MFMA      several workgroups per (task, k), one launch pair per pass (d <= 31); lists with
- *                              64 < k <= 224 on tasks of at most 4096 rows, unless CHAM_F_STREAMING is set, in one
- *                              launch of the resident matrix-core kernel
+ *   CHAM_PATH_STREAM_MFMA      several workgroups per (task, k), one launch pair per pass (d <= 31); with a
+ *                              largest k of 65 to 224 and at most 7000 rows x ceil(k / 64), unless CHAM_F_STREAMING
+ *                              is set, one launch of the resident matrix-core kernel
  *   CHAM_PATH_RESIDENT_VECTOR  one workgroup per (task, k), vector ALU; two-byte knobs of any value, unless a flag
  *                              asks for this kernel, on the matrix cores with values in two parts (largest k 8 to 64,
  *                              d <= 32, tasks of 257 to 4096 rows; largest k at most 32, d <= 48, 2048 rows)

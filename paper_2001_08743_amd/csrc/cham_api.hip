@@ -237,7 +237,7 @@ SweepPath choose_path(const Plan &pl, int d, int flags, int xbytes = 1)
     return SweepPath::kStream;
 }
 
-// The streaming path's lists of k for tasks of at most 4096 rows (no flag asks for the streaming kernels): one launch of the
+// The streaming path's lists of k for small tasks (no flag asks for the streaming kernels): one launch of the
 // resident matrix-core kernel in its form for many centroids.
 bool many_centroids(const Plan &pl, SweepPath path, int d, int flags)
 {

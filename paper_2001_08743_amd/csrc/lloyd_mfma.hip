@@ -1739,10 +1739,14 @@ static hipError_t launch_mfma_sweep_t(const SweepArgs &a, int64_t n_max, int64_t
     return hipErrorInvalidValue;
 }
 
-// k beyond 64 (byte knobs, d <= 31): within what LDS holds beside a wave's labels.
+// k beyond 64 (byte knobs, d <= 31): within what LDS holds beside a wave's labels, and up to 7000 rows x chunks of 64 centroids. One
+// compute unit has a unit's rows to itself here, the streaming kernels spread them over the chip at two launches a pass.
+// us a step, this / streaming, 20 steps, 24 knobs, 2 and 16 tasks: k = 72, 96, 128: 1500 rows 346 / 507 and 369 / 576, 2500 rows 498 / 602 and
+// 525 / 618, 4096 rows 691 / 628 and 728 / 706; k = 100, 200: 1500 rows 486 / 515 and 529 / 639, 2500 rows 726 / 632 and 996 / 799.  (With
+// 96 units of 4096 rows and k up to 128 this would be ahead again, 743 / 974, but the order of a loss would then depend on the batch.)
 bool mfma_many_fits(int d, int kmax, int64_t n_max)
 {
-    return d >= 1 && d <= 31 && kmax > 64 && kmax <= kManyCentroids && n_max <= 4096;
+    return d >= 1 && d <= 31 && kmax > 64 && kmax <= kManyCentroids && n_max * ((kmax + 63) / 64) <= 7000;
 }
 
 hipError_t launch_mfma_many(const SweepArgs &a, int64_t n_max, int64_t n_total, hipStream_t s)

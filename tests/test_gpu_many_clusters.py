@@ -1,6 +1,6 @@
-"""Lists of k beyond 64 on tasks of at most 4096 rows, without a flag: the resident matrix-core kernel's form for many centroids, up to
-k = 224.  Sizes around the chunks of 64 centroids, the waves' rows and the LDS limits, against the oracle; losses of chunks of the
-list against the whole list's."""
+"""Lists of k beyond 64 without a flag: the resident matrix-core kernel's form for many centroids, up to k = 224 and 7000 rows x chunks of 64
+centroids, and the streaming kernels behind that.  Sizes around the chunks, the waves' rows, the LDS limits and the limit
+between the two, against the oracle; losses of chunks of the list against the whole list's."""
 import numpy as np
 import pytest
 
@@ -22,7 +22,7 @@ def _sweep(wl, want_trace=False, init=None):
     return dw, out
 
 
-@pytest.mark.parametrize("n", [66, 300, 1023, 1025, 2500, 4095, 4096])
+@pytest.mark.parametrize("n", [66, 300, 1023, 1025, 1749, 1751, 2333, 2334, 3499, 3501, 4096])
 @pytest.mark.parametrize("d,ks", [(9, (5, 64, 65)), (15, (96, 97, 128)), (16, (33, 129, 160)), (24, (2, 191, 192)), (31, (193, 224))])
 def test_sizes(n, d, ks):
     wl = workloads.random_task(3 * n + d, n, d, card_hi=20, n_blobs=9, sigma=0.8, ks=ks, n_iter=12, n_tasks=3, ragged=n % 2 == 1)
