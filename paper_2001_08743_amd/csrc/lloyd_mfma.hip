@@ -1710,9 +1710,11 @@ static hipError_t launch_mfma_sweep_t(const SweepArgs &a, int64_t n_max, int64_t
     if (e != hipSuccess) return e;
     const int64_t units = (int64_t)a.T * a.n_k;            // of the whole list of k: a chunk of it is run the same way
     if (mfma_fetches_rows(a.d, n_max)) {
-        // One workgroup per compute unit at most: sixteen waves hide what two workgroups of eight would (4096 x 12, k = 2..64, 63
-        // units: 8 / 16 waves 519 / 483 us a step).
-        const int nwaves = units <= cus ? 16 : 8;
+        // One workgroup per compute unit at most: sixteen waves hide what two workgroups of eight would, if each has work enough.
+        // 8 / 16 waves, us a step: one task of 4096 x 12, k = 2..64, 519 / 483, of 4096 x 24 524 / 494, of 2000 x 14 239 / 232; 4 tasks of
+        // 1100 x 12 191 / 182, 6 of 2000 x 24 360 / 363.  At 32 byte knobs from more than 2048 rows on: 4 tasks of 3000 rows 390 / 375,
+        // but 7 of 2000 292 / 309, 10 of up to 1200 191 / 216.
+        const int nwaves = units <= cus && !(sep && n_max <= 2048) ? 16 : 8;
         if (sep) return launch_mfma_t<32, 0, uint8_t, true>(a, nwaves, n_max, n_total, cus, s);
         if (DK == 16) return launch_mfma_t<16, 0, XT>(a, nwaves, n_max, n_total, cus, s);
         if (DK == 32) return launch_mfma_t<32, 0, XT>(a, nwaves, n_max, n_total, cus, s);
@@ -1773,9 +1775,11 @@ hipError_t launch_mfma_two_part(const SweepArgs &a, int64_t n_max, int64_t n_tot
     int cus = 0;
     const hipError_t e = compute_units(cus);
     if (e != hipSuccess) return e;
+    // Few units, 8 / 16 waves, us a step: 4 tasks of 1500 x 31, k = 2..40, 431 / 411; above 32 knobs, with at most 2048 rows and 32
+    // centroids, 4 of 1900 x 40 475 / 518, 2 of 2000 x 45 457 / 496.
+    if (a.d > 32) return launch_mfma_t<48, 0, uint16_t, false, false, 2>(a, 8, n_max, n_total, cus, s);
     const int nwaves = (int64_t)a.T * a.n_k <= cus ? 16 : 8;
-    if (a.d <= 32) return launch_mfma_t<32, 0, uint16_t, false, false, 2>(a, nwaves, n_max, n_total, cus, s);
-    return launch_mfma_t<48, 0, uint16_t, false, false, 2>(a, nwaves, n_max, n_total, cus, s);
+    return launch_mfma_t<32, 0, uint16_t, false, false, 2>(a, nwaves, n_max, n_total, cus, s);
 }
 
 hipError_t launch_mfma_sweep(const SweepArgs &a, int64_t n_max, int64_t n_total, hipStream_t s)
