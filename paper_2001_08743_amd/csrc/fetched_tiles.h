@@ -61,6 +61,12 @@ __device__ __forceinline__ float vmin3(float a, float b, float c) { return __bui
 // Score position -> centroid.  Position q = 16 * m-tile + accumulator register (the order in which
 // the mask bits are collected, most significant first), hh = lane half.
 __device__ __forceinline__ int slot_centroid(int q, int hh) { return 2 * q + hh; }
+// Mask of the positions (bit 31 = position 0) of lane half hh that hold centroids below kk.
+__device__ __forceinline__ uint32_t marks_below(int kk, int hh)
+{
+    const int n = (kk + 1 - hh) >> 1;
+    return n <= 0 ? 0u : (n >= 32 ? 0xFFFFFFFFu : ~(0xFFFFFFFFu >> n));
+}
 // Row of the 32-row A fragment that holds centroid c of its m-tile.
 __device__ __forceinline__ int frag_row(int c)
 {
@@ -940,6 +946,14 @@ __device__ __forceinline__ void decide_tiles_many(const ManyQueue<DK> &Q, const 
             if (flagged) {
                 const int rs = nrec + __popc(fm & ((1u << n32) - 1u));
                 if (!upper) Q.rec_pid()[rs] = (unsigned short)(nt * 32 + n32);
+                // Starts beyond the range of the operands have every score within the bound, those of the padding rows
+                // k .. 32 ceil(k / 32) - 1 too: no candidates (their centroids are zero, or whatever memory held).
+                cnt = 0;
+#pragma unroll
+                for (int ch = 0; ch < kChunks; ++ch) {
+                    near[ch] &= marks_below(k - 64 * ch, upper ? 1 : 0);
+                    cnt += __popc(near[ch]);
+                }
                 unsigned pos = atomicAdd(Q.n_pairs(), (unsigned)cnt);
 #pragma unroll
                 for (int ch = 0; ch < kChunks; ++ch) {

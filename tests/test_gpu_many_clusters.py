@@ -56,3 +56,34 @@ def test_chunked_sweep_equals_the_whole(chunk):
     part = binding.cham_kmeans_sweep_knee(dw.X, dw.ld, dw.d, wl.task_off, wl.ks, wl.n_iter, threshold=0.0, chunk=chunk, want_labels=True)
     for key in ("status", "counts", "centroids", "labels", "inertia"):
         np.testing.assert_array_equal(part[key].cpu().numpy(), whole[key].cpu().numpy(), err_msg=key)
+
+
+def _far_starts(wl, ks, far):
+    # every start outside the range of the screen's operands (some 2300 from the rows), so that every score is within the bound
+    rng = np.random.default_rng(wl.n_total)
+    return 128.0 + far * (1.0 + 0.1 * rng.random((wl.T, sum(ks), 1))) * rng.choice([-1.0, 1.0], size=(wl.T, sum(ks), wl.d))
+
+
+@pytest.mark.parametrize("far", [5.0e3, 1.0e6])
+@pytest.mark.parametrize("d", [9, 24])
+@pytest.mark.parametrize("n,k", [(65, 70), (130, 70), (641, 70), (642, 70), (641, 100), (642, 100), (641, 129), (1281, 193)])
+def test_candidates_without_number_listed_pair_by_pair(n, k, d, far):
+    # the last wave owns one or two rows: their candidates fit the list of pairs, which holds no centroid beyond k
+    wl = workloads.random_task(n + d, n, d, card_lo=100, card_hi=256, n_blobs=9, sigma=20.0, ks=(k,), n_iter=2, n_tasks=2)
+    _sweep(wl, init=_far_starts(wl, (k,), far))
+
+
+@pytest.mark.parametrize("byte", [0x00, 0xFF, 0x40])
+@pytest.mark.parametrize("d", [9, 24])
+@pytest.mark.parametrize("n,k", [(65, 70), (641, 70), (642, 100), (641, 129), (641, 250)])
+def test_streaming_candidates_without_number_listed_pair_by_pair(n, k, d, byte):
+    # ... whatever the workspace held before
+    import torch
+    wl = workloads.random_task(n + d, n, d, card_lo=100, card_hi=256, n_blobs=9, sigma=20.0, ks=(k,), n_iter=2, n_tasks=2)
+    init = _far_starts(wl, (k,), 1.0e5)
+    dw = binding.DeviceWorkload(wl)
+    size = binding.cham_sweep_workspace_bytes(dw.ld, d, wl.task_off, wl.ks, wl.n_iter, binding.F_STREAMING)
+    out = binding.cham_kmeans_sweep(dw.X, dw.ld, d, wl.task_off, wl.ks, wl.n_iter, init_centroids=torch.from_numpy(init).to(dw.X.device), want_labels=True,
+                                    flags=binding.F_STREAMING, workspace=torch.full((size,), byte, dtype=torch.uint8, device=dw.X.device))
+    torch.cuda.synchronize()
+    check_sweep(wl, out, oracle.sweep(wl.rows, wl.task_off, wl.ks, wl.n_iter, init=init, want_labels=True), dw.ld)
