@@ -360,7 +360,9 @@ __device__ __forceinline__ void update_centroids(const MfmaLds<DK, SEP> &U, int 
                 const _Float16 bhi = (_Float16)bs;
                 const _Float16 blo = (_Float16)(bs - (float)bhi);
                 if constexpr (PL == 2) {
-                    U.start[(c >> 5) * 32 + 16 * (c & 1) + ((c & 31) >> 1)] = (float)b * kTwoPartScale;
+                    float st = (float)b * kTwoPartScale;
+                    if (all) st = __builtin_fminf(st, kFarScore);
+                    U.start[(c >> 5) * 32 + 16 * (c & 1) + ((c & 31) >> 1)] = st;
                 } else if constexpr (SEP) {
                     typedef _Float16 half2v __attribute__((ext_vector_type(2)));
                     *reinterpret_cast<half2v *>(U.abias + (c >> 5) * 64 + frag_row(c)) = half2v{bhi, blo};
@@ -377,7 +379,7 @@ __device__ __forceinline__ void update_centroids(const MfmaLds<DK, SEP> &U, int 
             *fh = hi4;
             *fl = lo4;
             // (beyond the range of the operands: behind the bound's own value, which a lane of this wave has stored)
-            if (PL == 2 && clamped) atomicMax(reinterpret_cast<int *>(U.bias + c), __float_as_int(1.0e30f));
+            if (PL == 2 && clamped) atomicMax(reinterpret_cast<int *>(U.bias + c), __float_as_int(kFarNorm));
         }
         if (zero_after && item < items) {
 #pragma unroll
@@ -597,7 +599,7 @@ __device__ __forceinline__ void run_unit(const SweepArgs &a, unsigned char *smem
         float m2 = wave_max_nonneg(lane < k ? U.bias[lane] : 0.0f);
         m2 = __builtin_fmaxf(m2, __int_as_float(U.stamp[1])) * 1.000001f;
         // starts beyond the range of the screen (their operands are clamped): every centroid is a candidate of every row
-        if (!(m2 <= max_screened(kByteKnobs))) m2 = 1.0e30f;
+        if (!(m2 <= max_screened(kByteKnobs))) m2 = kFarNorm;
 #pragma unroll
         for (int nt = 0; nt < NTW; ++nt)
             if (h == 0) Q.eb()[nt * 32 + n32] = mfma_bound<NSA, kByteKnobs>(x2row[nt], m2);
@@ -1279,7 +1281,7 @@ __device__ __forceinline__ void run_unit_fetched(const SweepArgs &a, unsigned ch
     __syncthreads();
     // padding centroid rows (beyond k) carry a huge bias so that they never win
     if (PL == 2) {
-        for (int c = k + tid; c < KP; c += blockDim.x) U.start[(c >> 5) * 32 + 16 * (c & 1) + ((c & 31) >> 1)] = 1.0e30f;
+        for (int c = k + tid; c < KP; c += blockDim.x) U.start[(c >> 5) * 32 + 16 * (c & 1) + ((c & 31) >> 1)] = kPadScore;
     } else for (int c = k + tid; c < KP; c += blockDim.x) {
         _Float16 *bslot = SEP ? reinterpret_cast<_Float16 *>(U.abias + (c >> 5) * 64 + frag_row(c))
                               : reinterpret_cast<_Float16 *>(U.afrag + ((c >> 5) * NS2 + bstep) * 64 + 32 * bhalf + frag_row(c)) + belem;
@@ -1314,7 +1316,7 @@ __device__ __forceinline__ void run_unit_fetched(const SweepArgs &a, unsigned ch
         m2 = wave_max_nonneg(m2);
         m2 = __builtin_fmaxf(m2, x2) * 1.000001f;
         // starts beyond the range of the screen (their operands are clamped): every centroid is a candidate of every row
-        if (!(m2 <= (PL == 2 ? 1.0e13f : max_screened(kByteKnobs)))) m2 = 1.0e30f;
+        if (!(m2 <= (PL == 2 ? 1.0e13f : max_screened(kByteKnobs)))) m2 = kFarNorm;
         // Values in two parts: twice the instructions, a quarter of the score; the absolute term is half the spacing of the low
         // operands' subnormal values times the sum of the parts' magnitudes, at most sqrt(48) |x'| + 48 * 255.
         if (PL == 2) bound = kTwoPartScale * mfma_bound_slope<NS2 * PL>() * (x2 + 2.0f * m2) + 7.5e-8f * (7.0f * __builtin_sqrtf(x2) + 12288.0f);

@@ -24,7 +24,6 @@ namespace {
 constexpr int kWavesPerWg = 8;
 constexpr int kLossWaves = 4;
 constexpr int kLossRows = 4096;      // rows of a partial sum of the loss, whatever an assigning workgroup walks
-constexpr float kPadScore = 1.0e30f; // score of a padding centroid row (real scores stay below 4 * 32 * 255^2)
 
 // Knobs in 16-wide rows may fill every slot: |mu'|^2 starts the accumulator (fp32), which 32-wide rows have no registers for; those
 // have a slot to spare (d <= 31) and carry it there.
@@ -236,7 +235,7 @@ __global__ __launch_bounds__(32 * (DK / 8)) void stream_update_kernel(const Stre
     for (int off = G / 2; off >= 1; off >>= 1) b = b + __shfl_xor(b, off, 64);
     // padding centroid rows get a score above all others
     if (starts_from_bias<DK>()) {
-        if (g == G - 1) st.bias[mt * 32 + 16 * (c & 1) + (m32 >> 1)] = c < k ? (float)b : kPadScore;
+        if (g == G - 1) st.bias[mt * 32 + 16 * (c & 1) + (m32 >> 1)] = c < k ? __builtin_fminf((float)b, kFarScore) : kPadScore;
     } else if (g == G - 1) {
         const float bs = c < k ? __builtin_fminf((float)b * (1.0f / bias_scale(true)), kHalfMax) : kHalfMax;
         hi8[7] = (_Float16)bs;
@@ -249,7 +248,7 @@ __global__ __launch_bounds__(32 * (DK / 8)) void stream_update_kernel(const Stre
     float bmax = c < k ? __double2float_ru(b) * 1.0000005f : 0.0f;
     // a start (or an empty cluster still there) so far off that an operand may have been clamped: every centroid
     // is a candidate of every row
-    if (!(bmax <= (starts_from_bias<DK>() ? kHalfMax * kHalfMax / 4.0f : max_screened(true)))) bmax = 1.0e30f;
+    if (!(bmax <= (starts_from_bias<DK>() ? kHalfMax * kHalfMax / 4.0f : max_screened(true)))) bmax = kFarNorm;
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) bmax = __builtin_fmaxf(bmax, __shfl_xor(bmax, off, 64));
     if ((tid & 63) == 0) red[tid >> 6] = bmax;

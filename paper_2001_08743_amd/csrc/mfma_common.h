@@ -21,6 +21,11 @@ constexpr float bias_scale(bool byte_knobs) { return byte_knobs ? 256.0f : 16384
 constexpr float max_screened(bool byte_knobs) { return bias_scale(byte_knobs) * kHalfMax / 3.2f; }
 static_assert(max_screened(true) > 32.0f * 255.0f * 255.0f && max_screened(false) > 63.0f * 2047.0f * 2047.0f, "rows never leave the range");
 
+// Where the chain starts from |mu'|^2 in fp32, padding centroid rows start from kPadScore (real scores of usable starts stay far
+// below: 4 * 32 * 255^2 for byte knobs).  Starts beyond the range of the operands take kFarNorm for their squared norm in the bound,
+// which makes some 1e25 of it, and their scores are cut off at kFarScore: every centroid is a candidate of every row and padding never is.
+constexpr float kPadScore = 1.0e30f, kFarNorm = 1.0e30f, kFarScore = 1.0e13f;
+
 // Error bound of the matrix-core screen, relative to (|x'|^2 + 2 max|mu'|^2), in units of 2^-24:
 // w = fl32(-2mu') and the bias are rounded once (1 each) and hi + lo keeps 22 bits (4);
 // each instruction adds 16 exact products to the running value: the hardware aligns the 17 addends

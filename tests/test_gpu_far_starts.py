@@ -101,3 +101,33 @@ def test_most_rows_on_the_far_side_of_the_first_ones(d):
     rows[50:60] = rng.integers(0, 40, size=(10, d))
     wl.cards[:] = 2048
     _sweep(wl, flags=binding.F_VALUES_BELOW_2048, sfx="_u16")
+
+
+def _all_far(wl, far, same_norm):
+    # nothing near the rows; with equal norms the order of two starts hangs on x . mu alone
+    rng = np.random.default_rng(wl.n_total)
+    shape = (wl.T, sum(wl.ks), wl.d)
+    size = far if same_norm else far * (1.0 + rng.random(shape[:2]))[:, :, None]
+    return 128.0 + size * rng.choice([-1.0, 1.0], size=shape)
+
+
+@pytest.mark.parametrize("same_norm", [True, False])
+@pytest.mark.parametrize("far", [1e8, 3e15, 1e16, 1e18, 1e25, 1e200])
+@pytest.mark.parametrize("d,n,ks", [(9, 700, (3, 31, 63)), (16, 641, (40, 70)), (24, 900, (5, 33))])
+def test_streaming_starts_beyond_the_padding_scores(d, n, ks, far, same_norm):
+    # an unclamped |mu'|^2 exceeds the score of padding rows, and its rounding the bound under which every centroid is a candidate
+    wl = workloads.random_task(n, n, d, card_lo=100, card_hi=256, n_blobs=9, sigma=30.0, ks=ks, n_iter=3, n_tasks=2)
+    _sweep(wl, init=_all_far(wl, far, same_norm), flags=binding.F_STREAMING, path=1)
+
+
+@pytest.mark.parametrize("same_norm", [True, False])
+@pytest.mark.parametrize("far", [1e8, 3e15, 1e16, 1e18, 1e25, 1e200])
+@pytest.mark.parametrize("d,n,ks", [(7, 700, (3, 31, 63)), (32, 1100, (8, 64)), (45, 600, (5, 30))])
+def test_two_part_starts_beyond_the_padding_scores(d, n, ks, far, same_norm):
+    import torch
+    wl = workloads.wide_space(n + d, n_tasks=2, n=n, d=d, ks=ks, n_iter=3, card_wide=(64, 9000))
+    init = _all_far(wl, far, same_norm)
+    dw = binding.DeviceWorkload(wl)
+    out = binding.cham_kmeans_sweep(dw.X, dw.ld, d, wl.task_off, wl.ks, wl.n_iter, init_centroids=torch.from_numpy(init).to(dw.X.device), want_labels=True,
+                                    _sfx="_u16")
+    check_sweep(wl, out, oracle.sweep(wl.rows, wl.task_off, wl.ks, wl.n_iter, init=init, want_labels=True), dw.ld)
