@@ -7,6 +7,10 @@ namespace cham {
 
 constexpr int kUnitQueues = 8;         // one per XCD
 
+// A loss of the streaming kernels is added up by this many waves, each over runs of consecutive rows in turn.
+constexpr int kLossWaves = 4;
+__host__ __device__ constexpr int loss_run(int d, int k) { return d <= 16 && k <= 64 ? 256 : 128; }
+
 // Arguments of the sweep kernels.  Pointers are device pointers.
 struct SweepArgs {
     const uint8_t *X;              // knob values, [d][ld] items of xbytes bytes each

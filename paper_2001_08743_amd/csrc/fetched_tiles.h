@@ -424,7 +424,7 @@ struct ManyQueue {
     static constexpr size_t kOffPairs = kOffPid + (size_t)kCap * 2;
     static constexpr size_t kOffCount = kOffPairs + (size_t)kPairs * 4;
     static constexpr size_t kOffLab = kOffCount + 16;
-    static_assert(kPairs >= kChanges && kOffLab % 16 == 0, "the label changes fit the pairs' place");
+    static_assert(kPairs >= kChanges && kOffLab % 16 == 0 && kOffLab >= 256 * sizeof(double), "the label changes fit the pairs' place, the terms of a loss the queue's");
     static __host__ __device__ size_t bytes(int nwaves) { return kOffLab + 2 * (size_t)(nwaves == 16 ? kRows / 2 : kRows); }
     unsigned char *base;
     int rows;                                               // rows a wave owns at most

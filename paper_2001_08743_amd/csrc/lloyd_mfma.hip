@@ -1289,7 +1289,7 @@ __device__ __forceinline__ void run_unit_fetched(const SweepArgs &a, unsigned ch
     }
     if (tid < (nrows + kPackRows - 1) / kPackRows) {
         atomicMax(&U.stamp[1], a.norms[t * 32 + tid]);           // non-negative floats order like integers
-        if (kByteKnobs) atomicAdd(&U.acc64[0], (unsigned long long)(unsigned)a.norms[t * 32 + 16 + tid]);
+        if (kByteKnobs && !MANY) atomicAdd(&U.acc64[0], (unsigned long long)(unsigned)a.norms[t * 32 + 16 + tid]);
     }
     for (int e = tid; e < k * d; e += blockDim.x) {
         const int c = e / d, j = e % d;
@@ -1382,6 +1382,48 @@ __device__ __forceinline__ void run_unit_fetched(const SweepArgs &a, unsigned ch
         }
     };
 
+    // MANY: the same terms in the order of the streaming kernels (stream_loss_kernel, tasks of one block of 4096 rows), which run such
+    // lists of k when a task of the batch is larger: a loss does not depend on the form.  Every wave leaves the terms of its rows in its
+    // queue's place; four waves add up, their sums land in U.red[at .. at + 4).
+    auto many_loss = [&](int at) {
+        const int lane = opaque(lane_id);
+        double *term = reinterpret_cast<double *>(Q.base);
+        for (int r = lane; r < rows_wave; r += 64) {
+            const double *mc = U.mu64T + Queue::centroid(Q.lab()[r]);
+            const unsigned char *x = packed + packed_at(r, 0, DK);
+            double s = 0.0;
+            for (int j0 = 0; j0 < d; j0 += 8) {
+                const half8 xq = *reinterpret_cast<const half8 *>(x + packed_at(0, j0 >> 3, DK));
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    if (j0 + i < d) {
+                        const double tq = (double)((float)xq[i] + U.ojf[j0 + i]) - mc[(size_t)(j0 + i) * KP];
+                        s = s + tq * tq;
+                    }
+                }
+            }
+            term[r] = s;
+        }
+        __syncthreads();
+        if (wave < kLossWaves) {
+            const int consecutive = loss_run(d, k);
+            double part = 0.0;
+            for (int base = wave * consecutive; base < nrows; base += kLossWaves * consecutive)
+                for (int first = base; first < base + consecutive && first < nrows; first += 64) {
+                    const int owner = first / run;                 // (whole groups of 64 rows a wave)
+                    if (first + lane < nrows)
+                        part = part + reinterpret_cast<const double *>(U.wave_base + ManyQueue<DK>::bytes(nwaves) * owner)[first - owner * run + lane];
+                }
+            const double ws = wave_sum(part);
+            if (lane == 0) U.red[at + wave] = ws;
+        }
+    };
+    constexpr int kSums = MANY ? kLossWaves : kParts;
+    auto sum_losses = [&](int at) {
+        if constexpr (MANY) many_loss(at);
+        else wave_loss(at);
+    };
+
     for (int it = 0; it <= a.n_iter; ++it) {
         const bool last_pass = (it == a.n_iter);
         passes_run = it + 1;
@@ -1463,13 +1505,13 @@ __device__ __forceinline__ void run_unit_fetched(const SweepArgs &a, unsigned ch
         if (wave_changed && lane_id == 0) atomicAdd(&U.stamp[2 + (it & 1)], wave_changed);
         traced_last = false;
         if (a.trace) {
-            wave_loss((it & 1) * kParts);
+            sum_losses((it & 1) * kParts);
             traced_last = true;
         }
         __syncthreads();
         if (a.trace && tid == 0) {
             double s = 0.0;
-            for (int p = 0; p < kParts; ++p) s = s + U.red[(it & 1) * kParts + p];
+            for (int p = 0; p < kSums; ++p) s = s + U.red[(it & 1) * kParts + p];
             a.trace[slot * (a.n_iter + 1) + it] = s;
         }
         // A pass that moved no row leaves every sum, hence every centroid, as it was: the labels are
@@ -1490,7 +1532,7 @@ __device__ __forceinline__ void run_unit_fetched(const SweepArgs &a, unsigned ch
     // the loss of the final labels: the per-wave sums of the last traced pass are still in place
     int loss_slot = ((passes_run - 1) & 1) * kParts;
     double loss = 0.0;
-    if (kByteKnobs && !traced_last && at_fixed_point) {
+    if (kByteKnobs && !MANY && !traced_last && at_fixed_point) {
         // At a fixed point every non-empty centroid is the mean S / n of its cluster: the loss in integers, as in run_unit
         double *frac0 = reinterpret_cast<double *>(U.wave_base);     // the queues are idle: [k] doubles of the first wave's region
         for (int c = tid; c < k; c += blockDim.x) {
@@ -1518,11 +1560,11 @@ __device__ __forceinline__ void run_unit_fetched(const SweepArgs &a, unsigned ch
     } else {
         if (!traced_last) {
             loss_slot = 0;
-            wave_loss(0);
+            sum_losses(0);
             __syncthreads();
         }
         if (tid == 0)
-            for (int p = 0; p < kParts; ++p) loss = loss + U.red[loss_slot + p];
+            for (int p = 0; p < kSums; ++p) loss = loss + U.red[loss_slot + p];
     }
     if (a.trace && tid == 0) {
         // the passes that were not run would have seen the same labels and centroids

@@ -22,7 +22,6 @@ namespace cham {
 namespace {
 
 constexpr int kWavesPerWg = 8;
-constexpr int kLossWaves = 4;
 constexpr int kLossRows = 4096;      // rows of a partial sum of the loss, whatever an assigning workgroup walks
 
 // Knobs in 16-wide rows may fill every slot: |mu'|^2 starts the accumulator (fp32), which 32-wide rows have no registers for; those
@@ -536,7 +535,7 @@ __global__ __launch_bounds__(1024) void stream_loss_kernel(const StreamArgs a)
     }
     __syncthreads();
     if (tid < kLossWaves * 64) {
-        const int run = k <= 64 && DK == 16 ? 256 : 128;
+        const int run = loss_run(d, k);
         double part = 0.0;
         for (int base = (tid >> 6) * run; base < n; base += kLossWaves * run)
             for (int r = base + (tid & 63); r < base + run; r += 64)

@@ -87,3 +87,46 @@ def test_streaming_candidates_without_number_listed_pair_by_pair(n, k, d, byte):
                                     flags=binding.F_STREAMING, workspace=torch.full((size,), byte, dtype=torch.uint8, device=dw.X.device))
     torch.cuda.synchronize()
     check_sweep(wl, out, oracle.sweep(wl.rows, wl.task_off, wl.ks, wl.n_iter, init=init, want_labels=True), dw.ld)
+
+
+def _same_bits(a, b, keys):
+    for key in keys:
+        np.testing.assert_array_equal(a[key].cpu().numpy(), b[key].cpu().numpy(), err_msg=key)
+
+
+@pytest.mark.parametrize("n_iter", [2, 25])
+@pytest.mark.parametrize("n,d,ks", [(65, 5, (65,)), (300, 15, (3, 64, 65)), (1025, 16, (40, 100)), (2333, 17, (64, 150)), (3499, 16, (30, 128)), (1750, 31, (9, 224)),
+                                    (3500, 24, (63, 65))])
+def test_loss_is_that_of_the_streaming_kernels(n, d, ks, n_iter):
+    # the knee rule compares losses: they belong to a task and its k, whichever of the two forms the batch runs on, with and without a trace,
+    # at the fixed point or not
+    wl = workloads.random_task(n + d, n, d, card_hi=30, n_blobs=7, sigma=1.1, ks=ks, n_iter=n_iter, n_tasks=2, ragged=True)
+    dw = binding.DeviceWorkload(wl)
+    sweep = lambda **kw: binding.cham_kmeans_sweep(dw.X, dw.ld, d, wl.task_off, ks, n_iter, **kw)
+    plain, traced, streamed = sweep(), sweep(want_trace=True), sweep(want_trace=True, flags=binding.F_STREAMING)
+    _same_bits(plain, streamed, ("status", "centroids", "counts", "inertia"))
+    _same_bits(traced, streamed, ("inertia", "trace"))
+
+
+def test_loss_does_not_depend_on_the_batch():
+    wl = workloads.random_task(11, 4096, 14, card_hi=18, n_blobs=6, sigma=0.9, ks=(8, 65, 130), n_iter=3, n_tasks=6, ragged=True)
+    off = wl.task_off
+    dw = binding.DeviceWorkload(wl)
+    whole = binding.cham_kmeans_sweep(dw.X, dw.ld, dw.d, off, wl.ks, wl.n_iter)["inertia"].cpu().numpy()
+    sizes = np.diff(off)
+    assert sizes.max() * 3 > 7000 > sizes.min() * 3         # together they stream, the smaller ones alone do not
+    for t in range(wl.T):
+        alone = binding.cham_kmeans_sweep(dw.X, dw.ld, dw.d, off[t:t + 2], wl.ks, wl.n_iter)["inertia"].cpu().numpy()
+        np.testing.assert_array_equal(alone[0], whole[t])
+
+
+def test_loss_of_tasks_without_rows():
+    import torch
+    wl = workloads.random_task(12, 200, 6, card_hi=9, n_blobs=3, sigma=1.0, ks=(66,), n_iter=2, n_tasks=2)
+    off = np.array([0, 0, 3, 3, 200], dtype=np.int64)
+    dw = binding.DeviceWorkload(wl)
+    init = np.random.default_rng(1).uniform(0, 9, size=(4, 66, 6))
+    out = binding.cham_kmeans_sweep(dw.X, dw.ld, 6, off, wl.ks, 2, init_centroids=torch.from_numpy(init).to(dw.X.device))
+    ref = oracle.sweep(wl.rows[:200], off, wl.ks, 2, init=init)
+    np.testing.assert_allclose(out["inertia"].cpu().numpy(), ref["inertia"], rtol=1e-12, atol=0)
+    np.testing.assert_array_equal(out["counts"].cpu().numpy(), ref["counts"])
