@@ -1615,6 +1615,7 @@ __global__ __launch_bounds__(NTW == 0 ? 1024 : 512, two_workgroups(DK, NTW, SEP)
     // (thread 0) place in a queue -> unit, moving on to the next queue when this one is empty; -1: all are
     int q = (int)blockIdx.x % a.n_queues, hops = 0;
     auto unit_of = [&](int v) -> int {
+        if constexpr (NTW != 0) return v < a.T * nk ? a.T * nk - 1 - v : -1;       // one queue
         for (;;) {
             const int tasks = (a.T - q + a.n_queues - 1) / a.n_queues;
             if (v < tasks * nk) {
