@@ -1101,6 +1101,10 @@ __device__ __forceinline__ const unsigned char *packed_task(const SweepArgs &a, 
 // the sum of the raw squared norms (for the loss at a fixed point; byte knobs).
 // PL = 2: any two-byte value, in two parts that are exact in f16, the multiple of 256 below its magnitude and the rest; there
 // is no bias slot.
+// Bound by its chain of latencies (task, offsets, rows, LDS) in small calls, so the row's knobs are asked for first, and by bank conflicts of
+// the byte copy, whose lanes read 256 bytes apart but for the padding.  Us, with both / with neither: 32 tasks of 2000 x 32
+// bytes 10.9 / 13.5, one of 2000 x 24 8.8 / 10.4, 64 of up to 600 x 48 two-byte knobs 12.6 / 20.0, of up to 2048 x 32 13.7 / 19.8, values in
+// two parts 13.4 / 15.5.
 template <int DK, typename XT, bool SEP, int PL>
 __global__ __launch_bounds__(kPackRows) void pack_centred_kernel(const SweepArgs a, int per_task)
 {
@@ -1108,17 +1112,22 @@ __global__ __launch_bounds__(kPackRows) void pack_centred_kernel(const SweepArgs
     constexpr int NM = DK > 32 ? 2 : 1, NP = (int)sizeof(XT);
     __shared__ int off[DK];
     __shared__ unsigned top_sq, sum_sq;
-    __shared__ __align__(16) unsigned char raw[NP][32 * NM][kPackRows];
+    __shared__ __align__(16) unsigned char raw[NP][32 * NM][kPackRows + 16];      // (16: the lanes of a fragment read different banks)
     const int t = (int)(blockIdx.x / (unsigned)per_task), b = (int)(blockIdx.x % (unsigned)per_task);
     const int64_t r0 = a.task_off[t];
     const int nrows = (int)(a.task_off[t + 1] - r0);
     if (b * kPackRows >= nrows) return;
     const XT *X = reinterpret_cast<const XT *>(a.X);
     const int tid = threadIdx.x, d = a.d;
+    const int row = b * kPackRows + tid;
     if (tid == 0) {
         top_sq = 0u;
         sum_sq = 0u;
     }
+    // the row's knobs are on their way while the offsets are found
+    XT x[DK];
+#pragma unroll
+    for (int j = 0; j < DK; ++j) x[j] = j < d && row < nrows ? X[(int64_t)j * a.ld + r0 + row] : (XT)0;
     for (int e = tid; e < DK * 8; e += kPackRows) {          // (uniform within a wave: every lane exchanges)
         const int j = e >> 3, part = e & 7;
         int sum = 0;
@@ -1136,7 +1145,6 @@ __global__ __launch_bounds__(kPackRows) void pack_centred_kernel(const SweepArgs
         }
     }
     __syncthreads();
-    const int row = b * kPackRows + tid;
     float c2 = 0.0f;                                         // (byte knobs and values below 2048: within 2^-20 of exact)
     unsigned raw2 = 0, top = 0;
     if (row < nrows) {
@@ -1147,7 +1155,7 @@ __global__ __launch_bounds__(kPackRows) void pack_centred_kernel(const SweepArgs
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
                 const int j = 8 * g + i;
-                const int xv = j < d ? (int)X[(int64_t)j * a.ld + r0 + row] : 0;
+                const int xv = (int)x[j];
                 const int cv = j < d ? xv - off[j] : 0;
                 top = (unsigned)xv > top ? (unsigned)xv : top;
                 raw[0][j][tid] = (unsigned char)xv;
