@@ -480,6 +480,7 @@ static int32_t sweep_impl(const void *Xv, int xbytes, int64_t ld, int32_t d, con
     a.too_large = (xbytes == 2 && path == SweepPath::kMfmaResident) ? reinterpret_cast<int *>(ws + w.counters) + (int64_t)n_k * kUnitQueues : nullptr;
     a.n_queues = 1;
     a.queue_group = T;
+    a.loss_parts = 0;
     a.ki_begin = 0;
     a.ki_end = n_k;
     a.done = nullptr;

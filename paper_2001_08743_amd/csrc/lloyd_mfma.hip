@@ -49,6 +49,10 @@ __host__ __device__ constexpr int rec_cap(int DK, int ntw) { return DK == 32 && 
 // sums the loss in its order.
 constexpr bool paired_loss(int DK, int ntw) { return DK == 16 && ntw == 2; }
 
+// A loss is summed by equal parts of the task's rows where the number of units chooses between rows in registers and rows fetched.
+constexpr int kParts = 16;
+__device__ __forceinline__ int rows_of_part(int nrows) { return nrows > 64 * kParts ? (nrows + 64 * kParts - 1) / (64 * kParts) * 64 : 64; }
+
 // LDS carve-up.  DK = padded knob count (16, 32, 48 or 64), KP = padded centroid count (32 or 64); SEP: the
 // bias has fragments of its own.
 template <int DK, bool SEP = false>
@@ -653,11 +657,29 @@ __device__ __forceinline__ void run_unit(const SweepArgs &a, unsigned char *smem
     // through its idle queue to the wave before it, whose lanes add up what they would with twice the tiles.
     constexpr bool kPaired = paired_loss(DK, NTW);
     static_assert(!kPaired || (size_t)NTW * 64 * sizeof(double) <= WaveQueue<DK, NTW>::kOffMask, "the terms fit the queue's rows");
-    const int n_parts = kPaired ? (nwaves + 1) / 2 : nwaves;
-    auto wave_loss = [&](int slot8) {
+    // kCanPart: the sums of the task's parts (kParts, of 64 or 128 rows, so that a wave has whole ones), as run_unit_fetched adds them up.
+    constexpr bool kCanPart = NTW == 8 || (DK > 32 && NTW == 4);
+    const bool parted = kCanPart && (NTW == 8 || a.loss_parts != 0);
+    const int part_rows = parted ? rows_of_part(nrows) : NTW * 32;
+    const int all_parts = parted ? nwaves * NTW * 32 / part_rows : (kPaired ? (nwaves + 1) / 2 : nwaves);
+    const int n_parts = all_parts < kParts ? all_parts : kParts;
+    auto wave_loss = [&](int first_slot) {
         double part = 0.0;
         const bool handed_over = kPaired && (wave & 1) != 0;
         const int lane = opaque(lane_id), n32 = lane & 31, h = lane >> 5;
+        // a total in the fixed order lane ^ 32, 16, ..., 1 (partner indices from the local lane index)
+        auto put = [&](double ws, int place) {
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) {
+                const long long b = __double_as_longlong(ws);
+                const int plo = __builtin_amdgcn_ds_bpermute((lane ^ off) << 2, (int)(b & 0xFFFFFFFFll));
+                const int phi = __builtin_amdgcn_ds_bpermute((lane ^ off) << 2, (int)(b >> 32));
+                ws = ws + __longlong_as_double(((long long)phi << 32) | (unsigned int)plo);
+            }
+            if (lane == 0 && place < kParts) U.red[first_slot + place] = ws;
+        };
+        double ends[NTW / 2] = {};                                  // sums up to every second tile
+        auto ends_part = [&](int nt) { return ((nt + 1) * 32 & (part_rows - 1)) == 0; };
         if (wave_live) {
             float of[NS][8];
 #pragma unroll
@@ -689,6 +711,10 @@ __device__ __forceinline__ void run_unit(const SweepArgs &a, unsigned char *smem
                     }
                 if (handed_over) reinterpret_cast<double *>(Q.rec_x())[nt * 64 + lane] = live ? s : 0.0;
                 else part = part + (live ? s : 0.0);
+                if (kCanPart && (nt & 1)) {
+                    ends[nt / 2] = part;
+                    part = ends_part(nt) ? 0.0 : part;
+                }
             }
         }
         if constexpr (kPaired) {
@@ -699,16 +725,13 @@ __device__ __forceinline__ void run_unit(const SweepArgs &a, unsigned char *smem
                 for (int nt = 0; nt < NTW; ++nt) part = part + terms[nt * 64 + lane];
             }
         }
-        // the wave's total in the fixed order lane ^ 32, 16, ..., 1 (partner indices from the local lane index)
-        double ws = part;
+        if constexpr (kCanPart) {
 #pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) {
-            const long long b = __double_as_longlong(ws);
-            const int plo = __builtin_amdgcn_ds_bpermute((lane ^ off) << 2, (int)(b & 0xFFFFFFFFll));
-            const int phi = __builtin_amdgcn_ds_bpermute((lane ^ off) << 2, (int)(b >> 32));
-            ws = ws + __longlong_as_double(((long long)phi << 32) | (unsigned int)plo);
+            for (int q = 0; q < NTW / 2; ++q)
+                if (ends_part(2 * q + 1)) put(ends[q], (wave_row0 + q * 64) / part_rows);
+        } else if (!handed_over) {
+            put(part, kPaired ? wave >> 1 : wave);
         }
-        if (lane == 0 && !handed_over) U.red[slot8 + (kPaired ? wave >> 1 : wave)] = ws;
     };
 
     for (int it = 0; it <= a.n_iter; ++it) {
@@ -997,13 +1020,13 @@ __device__ __forceinline__ void run_unit(const SweepArgs &a, unsigned char *smem
         if (wave_changed && lane_id == 0) atomicAdd(&U.stamp[2 + (it & 1)], wave_changed);
         traced_last = false;
         if (a.trace) {
-            wave_loss((it & 1) * 8);
+            wave_loss((it & 1) * kParts);
             traced_last = true;
         }
         __syncthreads();
         if (a.trace && tid == 0) {
             double s = 0.0;
-            for (int w = 0; w < n_parts; ++w) s = s + U.red[(it & 1) * 8 + w];
+            for (int w = 0; w < n_parts; ++w) s = s + U.red[(it & 1) * kParts + w];
             a.trace[slot * (a.n_iter + 1) + it] = s;
         }
         // A pass that moved no row leaves every sum, hence every centroid, as it was: the labels are
@@ -1027,7 +1050,7 @@ __device__ __forceinline__ void run_unit(const SweepArgs &a, unsigned char *smem
         }
     }
     // the loss of the final labels: the per-wave sums of the last traced pass are still in place
-    int loss_slot = ((passes_run - 1) & 1) * 8;
+    int loss_slot = ((passes_run - 1) & 1) * kParts;
     double loss = 0.0;
     if (kByteKnobs && !traced_last && at_fixed_point) {
         // At a fixed point every non-empty centroid is the mean S / n of its cluster, so the loss is
@@ -1194,8 +1217,6 @@ __global__ __launch_bounds__(kPackRows) void pack_centred_kernel(const SweepArgs
     }
 }
 
-constexpr int kParts = 16;
-
 // Centroid rows LDS holds (KP).
 template <bool MANY>
 __host__ __device__ constexpr int centroid_rows(int kmax) { return MANY ? (kmax + 31) / 32 * 32 : (kmax > 32 ? 64 : 32); }
@@ -1248,7 +1269,7 @@ __device__ __forceinline__ void run_unit_fetched(const SweepArgs &a, unsigned ch
     const int lab_rows = nwaves == 16 && MANY ? Queue::kRows / 2 : Queue::kRows;       // rows the label tables hold
     // Rows of the task in kParts equal parts of whole groups of 64; a wave has one, or two in a row.  The loss is summed part by
     // part, so that its order does not depend on the number of waves.
-    const int part_rows = nrows > 64 * kParts ? (nrows + 64 * kParts - 1) / (64 * kParts) * 64 : 64;
+    const int part_rows = rows_of_part(nrows);
     const int run = part_rows * (kParts / nwaves);
     const int wave_row0 = wave * run;
     const int rows_wave = nrows - wave_row0 < run ? (nrows - wave_row0 > 0 ? nrows - wave_row0 : 0) : run;
@@ -1702,6 +1723,7 @@ hipError_t launch_mfma_t(const SweepArgs &a, int nwaves, int64_t n_max, int64_t 
     SweepArgs b = a;
     b.n_queues = NTW == 0 && n_total * DK * PL * 2 > 3 * 1024 * 1024 ? kUnitQueues : 1;
     b.queue_group = b.n_queues == 1 ? a.T : kQueueGroup;
+    b.loss_parts = mfma_fetches_rows(a.d, n_max) ? 1 : 0;
     auto kern = resident_mfma_kernel<DK, NTW, XT, SEP, MANY, PL>;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -1762,7 +1784,12 @@ static hipError_t launch_mfma_sweep_t(const SweepArgs &a, int64_t n_max, int64_t
     const hipError_t e = compute_units(cus);
     if (e != hipSuccess) return e;
     const int64_t units = (int64_t)a.T * a.n_k;            // of the whole list of k: a chunk of it is run the same way
-    if (mfma_fetches_rows(a.d, n_max)) {
+    // Few units (at most one on every second compute unit) of rows that fit the registers beside them: a sweep is then the latency of its
+    // passes, and fetching pays only from there on.  us a sweep, registers / fetched, 20 steps: 16 tasks of 2048 x 32 bytes, k = 16, 167 / 200;
+    // 32 tasks, k = 8, 32, 196 / 222; 64 tasks of 1536, k = 8, 32, 60 (192 units), 285 / 265; two-byte knobs: 64 tasks of up to 600 x 48, k = 2, 8,
+    // 140 / 169, 8 of 600 x 40, k = 4, 16, 32, 119 / 138, but 32 of 900 x 40, k = 2..32 (992 units), 536 / 493.
+    const bool few = units <= cus / 2 && ((sep && n_max <= 2048) || (a.d > 32 && n_max <= 1024));
+    if (mfma_fetches_rows(a.d, n_max) && !few) {
         // One workgroup per compute unit at most: sixteen waves hide what two workgroups of eight would, if each has work enough.
         // 8 / 16 waves, us a step: one task of 4096 x 12, k = 2..64, 519 / 483, of 4096 x 24 524 / 494, of 2000 x 14 239 / 232; 4 tasks of
         // 1100 x 12 191 / 182, 6 of 2000 x 24 360 / 363.  At 32 byte knobs from more than 2048 rows on: 4 tasks of 3000 rows 390 / 375,
@@ -1780,10 +1807,11 @@ static hipError_t launch_mfma_sweep_t(const SweepArgs &a, int64_t n_max, int64_t
     // Rows in registers: four tiles per wave hold 1024 rows in eight waves.  Two where one task's latency counts (no more units than
     // compute units), DK = 16, up to 512 rows: 256 rows 121 / 102 us a step, 500 rows 137 / 109 us; with many
     // units four are as good (64 tasks x 500 rows 271 / 277 us).
-    const int ntw = n_max <= 512 && DK == 16 && (int64_t)a.T * (a.ki_end - a.ki_begin) <= cus ? 2 : 4;
+    const int ntw = n_max <= 512 && DK == 16 && (int64_t)a.T * (a.ki_end - a.ki_begin) <= cus ? 2 : (few && sep && n_max > 1024 ? 8 : 4);
     int nwaves = (int)((n_max + 32 * ntw - 1) / (32 * ntw));
     if (nwaves < 1) nwaves = 1;
-    if (sep) return launch_mfma_t<32, 4, uint8_t, true>(a, nwaves, n_max, n_total, cus, s);
+    if (sep)
+        return ntw == 8 ? launch_mfma_t<32, 8, uint8_t, true>(a, nwaves, n_max, n_total, cus, s) : launch_mfma_t<32, 4, uint8_t, true>(a, nwaves, n_max, n_total, cus, s);
     if (DK == 16)
         return ntw == 2 ? launch_mfma_t<16, 2, XT>(a, nwaves, n_max, n_total, cus, s) : launch_mfma_t<16, 4, XT>(a, nwaves, n_max, n_total, cus, s);
     if (DK == 32) return launch_mfma_t<32, 4, XT>(a, nwaves, n_max, n_total, cus, s);

@@ -130,3 +130,37 @@ def test_resident_loss_does_not_depend_on_the_batch(n, d, ks):
         alone = binding.cham_kmeans_sweep(dw.X, dw.ld, d, wl.task_off[t:t + 2], ks, wl.n_iter, want_trace=True)
         for key in ("inertia", "trace"):
             np.testing.assert_array_equal(alone[key][0].cpu().numpy(), whole[key][t].cpu().numpy())
+
+
+def _subset_has_the_whole_batchs_losses(wl, ks, n_iter, flags, sfx):
+    """Two tasks next to each other, the largest of the batch among them: few units, another form of the kernel."""
+    dw = binding.DeviceWorkload(wl)
+    off = np.asarray(wl.task_off)
+    whole = binding.cham_kmeans_sweep(dw.X, dw.ld, dw.d, off, ks, n_iter, want_trace=True, flags=flags, _sfx=sfx)
+    plain = binding.cham_kmeans_sweep(dw.X, dw.ld, dw.d, off, ks, n_iter, flags=flags, _sfx=sfx)
+    big = int(np.argmax(np.diff(off)))
+    for t in {max(0, big - 1), min(big, wl.T - 2)}:
+        two = off[t:t + 3]
+        alone = binding.cham_kmeans_sweep(dw.X, dw.ld, dw.d, two, ks, n_iter, want_trace=True, flags=flags, _sfx=sfx)
+        quiet = binding.cham_kmeans_sweep(dw.X, dw.ld, dw.d, two, ks, n_iter, flags=flags, _sfx=sfx)
+        for key in ("status", "counts", "centroids", "inertia", "trace"):
+            np.testing.assert_array_equal(alone[key].cpu().numpy(), whole[key][t:t + 2].cpu().numpy(), err_msg=key)
+        np.testing.assert_array_equal(quiet["inertia"].cpu().numpy(), plain["inertia"][t:t + 2].cpu().numpy())
+
+
+@pytest.mark.parametrize("n_iter", [3, 30])
+@pytest.mark.parametrize("n", [1025, 1300, 1537, 2048])
+def test_loss_of_all_byte_knobs_does_not_depend_on_the_batch(n, n_iter):
+    wl = workloads.random_task(n, n, 32, card_hi=24, n_blobs=9, sigma=1.2, ks=(2, 9, 33, 50), n_iter=n_iter, n_tasks=80, ragged=True)
+    _subset_has_the_whole_batchs_losses(wl, wl.ks, n_iter, 0, "")
+
+
+@pytest.mark.parametrize("n_iter", [3, 30])
+@pytest.mark.parametrize("n,d", [(513, 40), (700, 33), (900, 47), (1024, 48), (1000, 63)])
+def test_loss_of_many_two_byte_knobs_does_not_depend_on_the_batch(n, d, n_iter):
+    wl = workloads.wide_space(n, n_tasks=80, n=n, d=d, ks=(2, 9, 32), n_iter=n_iter, ragged=True)
+    # (ragged sizes: the largest task stays above 512 rows)
+    off = np.asarray(wl.task_off)
+    if np.diff(off).max() <= 512:
+        wl = workloads.wide_space(n, n_tasks=80, n=n, d=d, ks=(2, 9, 32), n_iter=n_iter)
+    _subset_has_the_whole_batchs_losses(wl, wl.ks, n_iter, binding.F_VALUES_BELOW_2048, "_u16")
