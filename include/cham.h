@@ -137,7 +137,9 @@ int32_t cham_kmeans_sweep(const uint8_t *X, int64_t ld, int32_t d,
  *                              is set, one launch of the resident matrix-core kernel
  *   CHAM_PATH_RESIDENT_VECTOR  one workgroup per (task, k), vector ALU; two-byte knobs of any value, unless a flag
  *                              asks for this kernel, on the matrix cores with values in two parts (largest k 8 to 64,
- *                              d <= 32, tasks of 257 to 4096 rows; largest k at most 32, d <= 48, 2048 rows)
+ *                              d <= 32, tasks of 257 to 4096 rows; largest k at most 32, d <= 48, 2048 rows; up to 16
+ *                              knobs from a larger k on: 24 up to 8 knobs, and with a largest task of 1025 to 2048 rows
+ *                              33 up to 8 and 16 up to 16)
  * cham_sweep_path_kernel gives the name of the family's dominant kernel (a static string).
  */
 #define CHAM_PATH_RESIDENT_MFMA   0

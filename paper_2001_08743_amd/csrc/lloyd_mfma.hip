@@ -1843,10 +1843,18 @@ hipError_t launch_mfma_many(const SweepArgs &a, int64_t n_max, int64_t n_total, 
 }
 
 // Two-byte values without the promise, in two parts: rows of 64 slots up to 32 knobs, of 96 up to 48 (registers for one tile of 32
-// centroids then).  A short list of small k has too little to gain for the packed rows.
+// centroids then).  The matrix kernel works for 32 (48) knobs whatever their number, the vector kernel for the next multiple of eight,
+// and with 1025 to 2048 rows every lane of it has its four rows of the one step there is.  So up to 16 knobs a longer list is asked for;
+// time of the vector kernel over this one's (one task and 64, cardinalities up to 32, 600 and 6000): 4 to 8 knobs, largest k 8, 0.90 at 260
+// rows, 0.82 at 700, 0.68 at 2048, 0.77 at 4096; k 24, 1.1 to 1.2 up to 700 rows, 1.0 at 1100, 0.92 at 2048, 1.1 to 1.3 above; k 48, 1.15 at
+// 1500.  9 to 16 knobs, k 8: 1.05 to 1.1 up to 700 rows, 0.92 to 1.03 at 1100, 0.85 to 0.94 at 2048, 1.05 to 1.25 above; k 16, 1.02 at 2048.
+// 17 to 48 knobs, k 8: 1.15 to 1.9 everywhere.  (Up to 256 rows and below k = 8 calls stay where they are, on the vector kernel: even or behind up
+// to 16 knobs, 1.05 to 1.4 could be had above.)
 int mfma_two_part_halfs(int d, int kmax, int64_t n_max)
 {
-    if (kmax < 8 || n_max <= 256) return 0;
+    const bool one_step = n_max > 1024 && n_max <= 2048;
+    const int least = d <= 8 ? (one_step ? 33 : 24) : (d <= 16 && one_step ? 16 : 8);
+    if (kmax < least || n_max <= 256) return 0;
     if (d <= 32) return kmax <= 64 && n_max <= 4096 ? 64 : 0;
     return d <= 48 && kmax <= 32 && n_max <= 2048 ? 96 : 0;
 }
