@@ -135,20 +135,19 @@ def main():
     # evaluation: d multiply-adds of the expanded form plus the bias add and the compare = 2d + 2 flops.
     # The matrix-core kernels run the contraction in f16 (hi/lo split), so they are priced against the dense
     # f16 MFMA peak; the vector kernel against the fp32 vector peak.
-    path = binding.cham_sweep_path(dw.ld, dw.d, wl.task_off, wl.ks, flags=args.sweep_flags)
-    kernel = binding.cham_sweep_path_kernel(path)
-    uses_mfma = path in (0, 1)
+    kernel = binding.cham_sweep_kernel(dw.ld, dw.d, wl.task_off, wl.ks, flags=args.sweep_flags)
+    uses_mfma = kernel != "resident_sweep_kernel"
     flops_per_eval = 2 * wl.d + 2
     achieved_tflops = executed * flops_per_eval / (sweep_ms * 1e-3) / 1e12
     nominal_tflops = nominal * flops_per_eval / (sweep_ms * 1e-3) / 1e12
     peak = PEAK_F16_MFMA_TFLOPS if uses_mfma else PEAK_FP32_VECTOR_TFLOPS
     # HBM traffic of the sweep kernel as the launch shape implies it (every unit reads its task's packed
-    # rows once, 2 bytes per padded knob; centroids, counts and working labels are written once); the
+    # rows once, 2 bytes per padded knob, and finds them in its L2 in later passes; centroids, counts and working labels are written once); the
     # counter figures of the rocprofv3 --pmc runs are under profiles/ and cannot be read from in here.
     dk = 16 if wl.d <= 15 else 32
     sizes = np.diff(wl.task_off).astype(np.float64)
     traffic_model = float(sizes.sum() * len(wl.ks) * (dk * 2 + 1) + wl.T * sum(wl.ks) * (wl.d * 8 + 4)) \
-        if path == 0 else None
+        if kernel == "resident_mfma_kernel" else None
     roofline = dict(bound="mfma" if uses_mfma else "alu", achieved=round(achieved_tflops, 3), peak=peak,
                     unit="TFLOP/s", frac=round(achieved_tflops / peak, 4), traffic=None,
                     traffic_model=traffic_model, kernel=kernel,
@@ -268,9 +267,8 @@ def main():
         # cardinalities of at most 2048: the harness promises values below 2048 and the sweep may run on the
         # matrix cores (the library says which kernel it is)
         w_promise = args.wide_flags | (binding.F_VALUES_BELOW_2048 if int(ww.cards.max()) <= 2048 else 0)
-        w_path = binding.cham_sweep_path_u16((ww.n_total + 63) // 64 * 64, ww.d, ww.task_off, ww.ks, flags=w_promise)
-        wide["kernel"] = binding.cham_sweep_path_kernel(w_path)
-        if w_path == 0:
+        wide["kernel"] = binding.cham_sweep_kernel_u16((ww.n_total + 63) // 64 * 64, ww.d, ww.task_off, ww.ks, flags=w_promise)
+        if wide["kernel"] == "resident_mfma_kernel":
             wide["frac_of_f16_mfma_peak"] = round(w_exec * (2 * ww.d + 2) / (w_ms * 1e-3) / 1e12
                                                   / PEAK_F16_MFMA_TFLOPS, 4)
 
@@ -280,9 +278,9 @@ def main():
     if args.large_single and args.cfg != 4:
         wl4 = workloads.make_config(4, 0)
         l_ms, l_exec, l_nom = side_workload(wl4, reps=3)
-        p4 = binding.cham_sweep_path((wl4.n_total + 63) // 64 * 64, wl4.d, wl4.task_off, wl4.ks)
+        kernel4 = binding.cham_sweep_kernel((wl4.n_total + 63) // 64 * 64, wl4.d, wl4.task_off, wl4.ks)
         large = dict(workload=f"{wl4.name}: N={wl4.n_total} rows x d={wl4.d}, k={list(wl4.ks)}, {wl4.n_iter} Lloyd steps "
-                              f"+ final pass", kernel=binding.cham_sweep_path_kernel(p4),
+                              f"+ final pass", kernel=kernel4,
                      ms_per_step=round(l_ms, 3), evals_per_step=l_exec, evals_per_s=round(l_exec / (l_ms * 1e-3), 1),
                      frac_of_f16_mfma_peak=round(l_exec * (2 * wl4.d + 2) / (l_ms * 1e-3) / 1e12
                                                  / PEAK_F16_MFMA_TFLOPS, 4))

@@ -126,21 +126,23 @@ int32_t cham_kmeans_sweep(const uint8_t *X, int64_t ld, int32_t d,
                           void *workspace, int64_t workspace_bytes, int32_t flags, void *stream);
 
 /*
- * Which kernel family cham_kmeans_sweep runs for these arguments (all HOST), or a negative error:
+ * Which path cham_kmeans_sweep takes for these arguments (all HOST), or a negative error:
  * the choice depends only on d, the largest task, the largest k and flags (Sec. 3.3's k-means,
  * "K-means.run" of Algorithm 1, is the same computation on every path).
  *   CHAM_PATH_RESIDENT_MFMA    one workgroup per (task, k), distances on the matrix cores
  *                              (d <= 31, tasks of at most 4096 rows, k <= 64; d = 32: 4096 rows with
  *                              k <= 32, or 2048 rows with k <= 64)
- *   CHAM_PATH_STREAM_MFMA      several workgroups per (task, k), one launch pair per pass (d <= 31); with a
+ *   CHAM_PATH_STREAM_MFMA      several workgroups per (task, k), one launch pair per pass (d <= 31).  With a
  *                              largest k of 65 to 224 and at most 7000 rows x ceil(k / 64), unless CHAM_F_STREAMING
- *                              is set, one launch of the resident matrix-core kernel
- *   CHAM_PATH_RESIDENT_VECTOR  one workgroup per (task, k), vector ALU; two-byte knobs of any value, unless a flag
- *                              asks for this kernel, on the matrix cores with values in two parts (largest k 8 to 64,
- *                              d <= 32, tasks of 257 to 4096 rows; largest k at most 32, d <= 48, 2048 rows; up to 16
- *                              knobs from a larger k on: 24 up to 8 knobs, and with a largest task of 1025 to 2048 rows
- *                              33 up to 8 and 16 up to 16)
- * cham_sweep_path_kernel gives the name of the family's dominant kernel (a static string).
+ *                              is set, one launch of the resident matrix-core kernel instead
+ *   CHAM_PATH_RESIDENT_VECTOR  one workgroup per (task, k), vector ALU.  Two-byte knobs of any value, unless a flag
+ *                              asks for the vector kernel, on the matrix cores with values in two parts instead: largest
+ *                              k 8 to 64, d <= 32, largest task of 257 to 4096 rows; largest k 8 to 32, d <= 48, 257 to
+ *                              2048 rows; with few knobs from a larger k on: 24 up to 8 knobs, and with a largest task
+ *                              of 1025 to 2048 rows 33 up to 8 and 16 up to 16
+ * cham_sweep_path_kernel gives the name of the kernel a path is named after (a static string).
+ * cham_sweep_kernel gives the name of the kernel that does the sweep for these arguments, "instead" of above
+ * included (a static string; NULL where cham_sweep_path gives an error).
  */
 #define CHAM_PATH_RESIDENT_MFMA   0
 #define CHAM_PATH_STREAM_MFMA     1
@@ -148,6 +150,8 @@ int32_t cham_kmeans_sweep(const uint8_t *X, int64_t ld, int32_t d,
 int32_t     cham_sweep_path(int64_t ld, int32_t d, const int64_t *task_off, int32_t T,
                             const int32_t *ks, int32_t n_k, int32_t flags);
 const char *cham_sweep_path_kernel(int32_t path);
+const char *cham_sweep_kernel(int64_t ld, int32_t d, const int64_t *task_off, int32_t T,
+                              const int32_t *ks, int32_t n_k, int32_t flags);
 
 /*
  * Labelling passes the last sweep that used `workspace` really ran, per (task, k): passes
@@ -377,6 +381,8 @@ int32_t cham_hash_rows(const uint8_t *rows, int64_t n, int32_t d, const uint64_t
  */
 int64_t cham_sweep_workspace_bytes_u16(int64_t ld, int32_t d, const int64_t *task_off, int32_t T,
                                        const int32_t *ks, int32_t n_k, int32_t n_iter, int32_t flags);
+const char *cham_sweep_kernel_u16(int64_t ld, int32_t d, const int64_t *task_off, int32_t T,
+                                  const int32_t *ks, int32_t n_k, int32_t flags);
 int32_t cham_sweep_path_u16(int64_t ld, int32_t d, const int64_t *task_off, int32_t T,
                             const int32_t *ks, int32_t n_k, int32_t flags);
 int32_t cham_kmeans_sweep_u16(const uint16_t *X, int64_t ld, int32_t d,

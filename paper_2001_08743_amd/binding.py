@@ -25,9 +25,9 @@ EXPORTS = [
     "cham_snap_centroids", "cham_synth_workspace_bytes", "cham_synthesize", "cham_hash_config",
     "cham_hash_rows", "cham_sweep_knee_workspace_bytes", "cham_kmeans_sweep_knee", "cham_synthesize_table",
     "cham_visited_table_clear", "cham_visited_table_insert_hashes", "cham_visited_table_insert_configs",
-    "cham_update_configs", "cham_sweep_path", "cham_sweep_path_kernel", "cham_sweep_passes",
+    "cham_update_configs", "cham_sweep_path", "cham_sweep_path_kernel", "cham_sweep_kernel", "cham_sweep_passes",
     "cham_static_init", "cham_kmeans_sweep_static",
-    "cham_sweep_workspace_bytes_u16", "cham_sweep_path_u16", "cham_kmeans_sweep_u16", "cham_sweep_knee_workspace_bytes_u16",
+    "cham_sweep_workspace_bytes_u16", "cham_sweep_path_u16", "cham_sweep_kernel_u16", "cham_kmeans_sweep_u16", "cham_sweep_knee_workspace_bytes_u16",
     "cham_kmeans_sweep_knee_u16", "cham_snap_workspace_bytes_u16", "cham_snap_centroids_u16",
     "cham_synth_workspace_bytes_u16", "cham_synthesize_u16", "cham_synthesize_table_u16",
     "cham_visited_table_insert_configs_u16", "cham_hash_config_u16", "cham_hash_rows_u16",
@@ -70,6 +70,9 @@ def load() -> C.CDLL:
         lib.cham_sweep_path_u16.argtypes = [i64, i32, vp, i32, vp, i32, i32]
         lib.cham_sweep_path_kernel.restype = C.c_char_p
         lib.cham_sweep_path_kernel.argtypes = [i32]
+        for name in ("cham_sweep_kernel", "cham_sweep_kernel_u16"):
+            getattr(lib, name).restype = C.c_char_p
+            getattr(lib, name).argtypes = [i64, i32, vp, i32, vp, i32, i32]
         lib.cham_sweep_passes.restype = i32
         lib.cham_sweep_passes.argtypes = [vp, i64, i64, i32, vp, i32, vp, i32, i32, vp, vp]
         lib.cham_static_init.restype = i32
@@ -286,6 +289,21 @@ def cham_sweep_path_u16(ld: int, d: int, task_off, ks, flags: int = 0) -> int:
 
 def cham_sweep_path_kernel(path: int) -> str:
     return load().cham_sweep_path_kernel(C.c_int32(path)).decode()
+
+
+def cham_sweep_kernel(ld: int, d: int, task_off, ks, flags: int = 0, _sfx: str = "") -> str:
+    """Name of the kernel that does the sweep for these arguments."""
+    to, k = _host_lists(task_off, ks)
+    name = getattr(load(), "cham_sweep_kernel" + _sfx)(C.c_int64(ld), C.c_int32(d), _hp(to), C.c_int32(len(to) - 1), _hp(k), C.c_int32(len(k)),
+                                                       C.c_int32(flags))
+    if name is None:
+        cham_sweep_path(ld, d, task_off, ks, flags, _sfx)                   # raises the error
+        raise ChamError("cham_sweep_kernel: no kernel for these arguments")
+    return name.decode()
+
+
+def cham_sweep_kernel_u16(ld: int, d: int, task_off, ks, flags: int = 0) -> str:
+    return cham_sweep_kernel(ld, d, task_off, ks, flags, _sfx="_u16")
 
 
 def cham_sweep_passes(workspace, ld: int, d: int, task_off, ks, flags: int = 0, passes=None):

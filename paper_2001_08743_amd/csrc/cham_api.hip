@@ -712,6 +712,30 @@ const char *cham_sweep_path_kernel(int32_t path)
     }
 }
 
+// (the launch's own predicates)
+static const char *sweep_kernel_impl(int xbytes, int64_t ld, int32_t d, const int64_t *task_off, int32_t T,
+                                     const int32_t *ks, int32_t n_k, int32_t flags)
+{
+    const int32_t family = sweep_path_impl(xbytes, ld, d, task_off, T, ks, n_k, flags);
+    Plan pl;
+    if (family < 0 || check_common(nullptr, ld, d, task_off, T, ks, n_k, false, pl, xbytes) != CHAM_OK) return nullptr;
+    const SweepPath path = choose_path(pl, d, flags, xbytes);
+    const bool matrix = many_centroids(pl, path, d, flags) || two_part_halfs(pl, path, xbytes, d, flags) != 0;
+    return cham_sweep_path_kernel(matrix ? CHAM_PATH_RESIDENT_MFMA : family);
+}
+
+const char *cham_sweep_kernel(int64_t ld, int32_t d, const int64_t *task_off, int32_t T, const int32_t *ks, int32_t n_k,
+                              int32_t flags)
+{
+    return sweep_kernel_impl(1, ld, d, task_off, T, ks, n_k, flags);
+}
+
+const char *cham_sweep_kernel_u16(int64_t ld, int32_t d, const int64_t *task_off, int32_t T, const int32_t *ks,
+                                  int32_t n_k, int32_t flags)
+{
+    return sweep_kernel_impl(2, ld, d, task_off, T, ks, n_k, flags);
+}
+
 int32_t cham_sweep_passes(const void *workspace, int64_t workspace_bytes, int64_t ld, int32_t d,
                           const int64_t *task_off, int32_t T, const int32_t *ks, int32_t n_k, int32_t flags,
                           int32_t *passes, void *stream)

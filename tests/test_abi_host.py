@@ -247,3 +247,35 @@ def test_static_sweep_rejects_bad_arguments_and_sizes_before_any_device_work(lib
     limit = int(m.group(1)) * int(m.group(2)) * int(m.group(3))
     ks = list(range(2, 33))
     assert binding.cham_sweep_workspace_bytes(65536, 12, np.arange(0, 65537, 1024), ks, 30) <= limit
+
+
+def test_sweep_kernel_query(lib):
+    """The kernel that does the sweep, which is not always the one its path is named after."""
+    resident, stream, vector = "resident_mfma_kernel", "stream_assign_kernel", "resident_sweep_kernel"
+
+    def kernel(n, d, ks, flags=0, sfx=""):
+        return binding.cham_sweep_kernel((n + 3) // 4 * 4, d, [0, n], ks, flags, _sfx=sfx)
+
+    assert kernel(4096, 24, range(1, 65)) == resident
+    # lists of k beyond 64: up to k = 224 and 7000 rows x chunks of 64 centroids
+    assert kernel(3500, 24, [8, 128]) == resident and kernel(3501, 24, [8, 128]) == stream
+    assert kernel(1750, 31, [224]) == resident and kernel(1751, 31, [224]) == stream and kernel(1000, 31, [225]) == stream
+    assert kernel(2333, 9, [192]) == resident and kernel(2334, 9, [192]) == stream
+    assert kernel(1000, 24, [70], binding.F_STREAMING) == stream and kernel(1000, 24, [70], binding.F_RESIDENT) == vector
+    assert kernel(1000, 32, [70]) == vector and kernel(5000, 24, [8]) == stream
+    # two-byte values in two parts
+    u16 = dict(sfx="_u16")
+    assert kernel(257, 24, [8], **u16) == resident and kernel(256, 24, [8], **u16) == vector and kernel(257, 24, [7], **u16) == vector
+    assert kernel(4096, 32, [64], **u16) == resident and kernel(4097, 32, [64], **u16) == vector and kernel(4096, 32, [65], **u16) == vector
+    assert kernel(2048, 48, [32], **u16) == resident and kernel(2049, 48, [32], **u16) == vector and kernel(2048, 48, [33], **u16) == vector
+    assert kernel(2048, 49, [32], **u16) == vector
+    for n, few, some in ((257, 24, 8), (1024, 24, 8), (1025, 33, 16), (2048, 33, 16), (2049, 24, 8)):
+        assert kernel(n, 8, [few], **u16) == resident and kernel(n, 8, [few - 1], **u16) == vector
+        assert kernel(n, 9, [some], **u16) == resident and kernel(n, 16, [some - 1], **u16) == vector
+        assert kernel(n, 17, [8], **u16) == resident
+    for flag in (binding.F_NO_MFMA, binding.F_FORCE_EXACT):
+        assert kernel(1000, 24, [8], flag, **u16) == vector
+    assert kernel(1000, 24, [8], binding.F_VALUES_BELOW_2048, **u16) == resident
+    for bad in (dict(ks=[3, 2]), dict(ks=[3], flags=1 << 20), dict(ks=[126], d=64, sfx="_u16"), dict(ks=[3], flags=binding.F_STREAMING, sfx="_u16")):
+        with pytest.raises(binding.ChamError):
+            kernel(1000, **{"d": 24, **bad})

@@ -14,6 +14,8 @@ pytestmark = pytest.mark.gpu
 def _sweep(wl, want_trace=False, init=None):
     import torch
     dw = binding.DeviceWorkload(wl)
+    resident = max(wl.ks) <= 224 and int(np.diff(wl.task_off).max()) * -(-max(wl.ks) // 64) <= 7000
+    assert binding.cham_sweep_kernel(dw.ld, dw.d, wl.task_off, wl.ks) == ("resident_mfma_kernel" if resident else "stream_assign_kernel")
     kw = {} if init is None else dict(init_centroids=torch.from_numpy(init).to(dw.X.device))
     out = binding.cham_kmeans_sweep(dw.X, dw.ld, dw.d, wl.task_off, wl.ks, wl.n_iter, want_labels=True, want_trace=want_trace, **kw)
     torch.cuda.synchronize()

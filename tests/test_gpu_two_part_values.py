@@ -13,6 +13,8 @@ pytestmark = pytest.mark.gpu
 def _sweep(wl, init=None, want_trace=False):
     import torch
     dw = binding.DeviceWorkload(wl)
+    in_two_parts = int(np.diff(wl.task_off).max()) > 256       # (a ragged batch of nominally 257 rows stays on the vector kernel)
+    assert binding.cham_sweep_kernel_u16(dw.ld, dw.d, wl.task_off, wl.ks) == ("resident_mfma_kernel" if in_two_parts else "resident_sweep_kernel")
     kw = {} if init is None else dict(init_centroids=torch.from_numpy(init).to(dw.X.device))
     out = binding.cham_kmeans_sweep(dw.X, dw.ld, dw.d, wl.task_off, wl.ks, wl.n_iter, want_labels=True, want_trace=want_trace, _sfx="_u16", **kw)
     vec = binding.cham_kmeans_sweep(dw.X, dw.ld, dw.d, wl.task_off, wl.ks, wl.n_iter, want_labels=True, flags=binding.F_NO_MFMA, _sfx="_u16", **kw)
@@ -82,3 +84,11 @@ def test_many_tiny_tasks_beside_a_large_one(d, flags):
     np.testing.assert_array_equal(out["status"].cpu().numpy(), ref["status"])
     np.testing.assert_array_equal(out["counts"].cpu().numpy(), ref["counts"])
     np.testing.assert_array_equal(out["centroids"].cpu().numpy(), ref["centroids"])
+
+
+@pytest.mark.parametrize("n,d,ks", [(257, 5, (2, 24)), (257, 16, (8,)), (257, 32, (3, 64)), (257, 48, (5, 32)), (1025, 8, (33,)), (1025, 16, (16,)), (4096, 17, (8, 64)),
+                                    (2048, 33, (8,))])
+def test_edges_of_the_rule(n, d, ks):
+    wl = workloads.wide_space(n + d, n_tasks=2, n=n, d=d, ks=ks, n_iter=7, card_wide=(64, 8000), ragged=False)
+    assert int(np.diff(wl.task_off).max()) == n
+    _sweep(wl, want_trace=True)
