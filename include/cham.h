@@ -171,12 +171,14 @@ int32_t cham_sweep_passes(const void *workspace, int64_t workspace_bytes, int64_
  * cham_kmeans_sweep for callers that cannot allocate device memory or pass a workspace: code
  * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments
  * (minus the workspace), same results bit for bit, same kernels; the scratch memory is a static
- * device array of CHAM_STATIC_SCRATCH_BYTES inside the library, one per GPU, held until the
+ * device array of 16 MiB inside the library, one per GPU, held until the
  * process ends.  The call allocates nothing, on the device or on the host.
- *   - Limit: cham_sweep_workspace_bytes(...) for the arguments must not exceed
- *     CHAM_STATIC_SCRATCH_BYTES and T + n_k must stay below about a thousand (the host tables
- *     live on the stack); beyond: CHAM_E_TOO_LARGE, nothing is enqueued.  (For tasks above 1024 rows the
- *     packed tiles' share of the workspace, up to 8 MiB more, does not count: the array has room for it.)
+ *   - Limit: cham_static_bytes(...) for the arguments must not exceed CHAM_STATIC_SCRATCH_BYTES (half of the
+ *     array) and T + n_k must stay below about a thousand (the host tables live on the stack);
+ *     beyond: CHAM_E_TOO_LARGE, nothing is enqueued.  cham_static_bytes is cham_sweep_workspace_bytes
+ *     without the share of the work queues and, where the kernel fetches packed rows in every pass (tasks above 1024 rows,
+ *     the streaming path, a largest k beyond 64), of the tiles and tables that takes, for which the other half has room;
+ *     CHAM_E_TOO_LARGE (for the host tables) and the argument errors as from the sweep.
  *   - The array's device address is looked up on the first call on each GPU (with that GPU
  *     current); cham_static_init() does the lookup ahead of time, e.g. before a graph capture.
  *   - All calls on one GPU share that GPU's array, whatever the stream: calls that overlap in
@@ -184,6 +186,8 @@ int32_t cham_sweep_passes(const void *workspace, int64_t workspace_bytes, int64_
  *     reads it has written first.
  */
 #define CHAM_STATIC_SCRATCH_BYTES (8 * 1024 * 1024)
+int64_t cham_static_bytes(int64_t ld, int32_t d, const int64_t *task_off, int32_t T, const int32_t *ks, int32_t n_k,
+                          int32_t flags);
 int32_t cham_static_init(void);
 int32_t cham_kmeans_sweep_static(const uint8_t *X, int64_t ld, int32_t d,
                                  const int64_t *task_off, int32_t T,

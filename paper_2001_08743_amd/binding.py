@@ -26,7 +26,7 @@ EXPORTS = [
     "cham_hash_rows", "cham_sweep_knee_workspace_bytes", "cham_kmeans_sweep_knee", "cham_synthesize_table",
     "cham_visited_table_clear", "cham_visited_table_insert_hashes", "cham_visited_table_insert_configs",
     "cham_update_configs", "cham_sweep_path", "cham_sweep_path_kernel", "cham_sweep_kernel", "cham_sweep_passes",
-    "cham_static_init", "cham_kmeans_sweep_static",
+    "cham_static_bytes", "cham_static_init", "cham_kmeans_sweep_static",
     "cham_sweep_workspace_bytes_u16", "cham_sweep_path_u16", "cham_sweep_kernel_u16", "cham_kmeans_sweep_u16", "cham_sweep_knee_workspace_bytes_u16",
     "cham_kmeans_sweep_knee_u16", "cham_snap_workspace_bytes_u16", "cham_snap_centroids_u16",
     "cham_synth_workspace_bytes_u16", "cham_synthesize_u16", "cham_synthesize_table_u16",
@@ -75,6 +75,8 @@ def load() -> C.CDLL:
             getattr(lib, name).argtypes = [i64, i32, vp, i32, vp, i32, i32]
         lib.cham_sweep_passes.restype = i32
         lib.cham_sweep_passes.argtypes = [vp, i64, i64, i32, vp, i32, vp, i32, i32, vp, vp]
+        lib.cham_static_bytes.restype = i64
+        lib.cham_static_bytes.argtypes = [i64, i32, vp, i32, vp, i32, i32]
         lib.cham_static_init.restype = i32
         lib.cham_static_init.argtypes = []
         lib.cham_kmeans_sweep_static.restype = i32
@@ -317,6 +319,12 @@ def cham_sweep_passes(workspace, ld: int, d: int, task_off, ks, flags: int = 0, 
                                     _hp(to), C.c_int32(T), _hp(k), C.c_int32(n_k), C.c_int32(flags), _dp(passes),
                                     _stream()))
     return passes
+
+
+def cham_static_bytes(ld: int, d: int, task_off, ks, flags: int = 0) -> int:
+    """What cham_kmeans_sweep_static counts against its limit for these arguments."""
+    to, k = _host_lists(task_off, ks)
+    return _check(load().cham_static_bytes(C.c_int64(ld), C.c_int32(d), _hp(to), C.c_int32(len(to) - 1), _hp(k), C.c_int32(len(k)), C.c_int32(flags)))
 
 
 def cham_static_init() -> None:

@@ -254,7 +254,7 @@ int two_part_halfs(const Plan &pl, SweepPath path, int xbytes, int d, int flags)
 
 struct SweepWs {
     int64_t blob = 0, init_rows = 0, ndist = 0, passes = 0, counters = 0, xh = 0, task_ojf = 0, norms = 0, two_part = 0, xk = 0, labbuf = 0, total = 0;
-    int64_t fetched = 0;           // of the total: what the matrix-core kernel that fetches its rows needs beside them
+    int64_t fetched = 0;           // of the total: the queues beyond one, and what the kernels that fetch their rows need beside them
     // streaming path
     int64_t x2 = 0, ojf = 0, Sg = 0, ng = 0, mu = 0, afrag = 0, biasf = 0, m2 = 0, wg_off = 0, loss = 0;
     int kpm = 0, n_units = 0, total_wgs = 0;
@@ -276,7 +276,9 @@ SweepWs sweep_ws(const Plan &pl, int64_t ld, bool own_labels, bool stream, const
     w.passes = o;
     o += up((int64_t)pl.T * pl.n_k * 4);
     w.counters = o;                                   // work counters, kUnitQueues per launch of a chunked sweep
-    o += up(((int64_t)pl.n_k * kUnitQueues + 1) * 4); // (+ the flag of a two-byte value too large for the f16 rows)
+    const int64_t queues = up(((int64_t)pl.n_k * kUnitQueues + 1) * 4); // (+ the flag of a two-byte value too large for the f16 rows)
+    o += queues;
+    w.fetched = queues - up(((int64_t)pl.n_k + 1) * 4);
     w.xh = o;
     o += up(ld * xh_halfs * 2);
     w.two_part = o;
@@ -293,7 +295,7 @@ SweepWs sweep_ws(const Plan &pl, int64_t ld, bool own_labels, bool stream, const
         o += up((int64_t)pl.T * 64 * 4);
         w.norms = o;
         o += up((int64_t)pl.T * 32 * 4) + 16 * 1024;
-        w.fetched = o - rows_end;
+        w.fetched += o - rows_end;
     }
     w.labbuf = o;
     if (own_labels) o += up((int64_t)pl.n_k * ld);
@@ -614,7 +616,7 @@ int32_t cham_kmeans_sweep(const uint8_t *X, int64_t ld, int32_t d, const int64_t
 // is only a host-side handle of the symbol; the array's device address is looked up once per
 // device and every use in host code goes through that address.
 // CHAM_STATIC_SCRATCH_BYTES bounds what the paths need without SweepWs::fetched; that part (byte knobs, fewer than 1024 tasks: 3.5 KiB
-// each, 16 KiB and half of the 8 MiB) has the place behind it.
+// each, 24 KiB and half of the 8 MiB) has the place behind it.
 constexpr int64_t kStaticScratchBytes = (int64_t)CHAM_STATIC_SCRATCH_BYTES + 8 * 1024 * 1024;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 constexpr int kMaxDevices = 64;
@@ -637,6 +639,18 @@ static int32_t static_scratch_address(void **out)
     return CHAM_OK;
 }
 
+int64_t cham_static_bytes(int64_t ld, int32_t d, const int64_t *task_off, int32_t T, const int32_t *ks, int32_t n_k,
+                          int32_t flags)
+{
+    // argument errors come out of the size query exactly as they would out of the sweep
+    int64_t fetched = 0;
+    const int64_t need = sweep_ws_bytes(1, ld, d, task_off, T, ks, n_k, flags, true, &fetched);
+    if (need == CHAM_E_NOMEM) return CHAM_E_TOO_LARGE;      // tables beyond the part kept on the stack
+    if (need < 0) return need;
+    if (flags & ~kSweepFlags) return CHAM_E_BAD_FLAG;
+    return need - fetched;
+}
+
 int32_t cham_static_init(void)
 {
     void *p = nullptr;
@@ -649,13 +663,9 @@ int32_t cham_kmeans_sweep_static(const uint8_t *X, int64_t ld, int32_t d, const 
                                  double *inertia, int32_t *status, uint8_t *labels, double *inertia_trace,
                                  int32_t flags, void *stream)
 {
-    // argument errors come out of the size query exactly as they would out of the sweep
-    int64_t fetched = 0;
-    const int64_t need = sweep_ws_bytes(1, ld, d, task_off, T, ks, n_k, flags, true, &fetched);
-    if (need == CHAM_E_NOMEM) return CHAM_E_TOO_LARGE;      // tables beyond the part kept on the stack
-    if (need < 0) return (int32_t)need;
-    if (flags & ~kSweepFlags) return CHAM_E_BAD_FLAG;
-    if (need - fetched > (int64_t)CHAM_STATIC_SCRATCH_BYTES || need > kStaticScratchBytes) return CHAM_E_TOO_LARGE;
+    const int64_t counted = cham_static_bytes(ld, d, task_off, T, ks, n_k, flags);
+    if (counted < 0) return (int32_t)counted;
+    if (counted > (int64_t)CHAM_STATIC_SCRATCH_BYTES) return CHAM_E_TOO_LARGE;
     void *ws = nullptr;
     int32_t rc = static_scratch_address(&ws);
     if (rc != CHAM_OK) return rc;

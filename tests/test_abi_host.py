@@ -279,3 +279,30 @@ def test_sweep_kernel_query(lib):
     for bad in (dict(ks=[3, 2]), dict(ks=[3], flags=1 << 20), dict(ks=[126], d=64, sfx="_u16"), dict(ks=[3], flags=binding.F_STREAMING, sfx="_u16")):
         with pytest.raises(binding.ChamError):
             kernel(1000, **{"d": 24, **bad})
+
+
+def test_static_limit_counts_neither_queues_nor_packed_tiles(lib):
+    up = lambda v: (v + 255) // 256 * 256
+    limit = 8 * 1024 * 1024
+
+    def resident(ld, T, ks, halfs=32):
+        blob = 8 * (T + 1 + (len(ks) + 1) // 2 + (len(ks) + 2) // 2)
+        return up(blob) + up(4 * T * ks[-1]) + up(4 * T) + up(4 * T * len(ks)) + up(4 * (len(ks) + 1)) + up(2 * halfs * ld) + up(len(ks) * ld)
+
+    for d, T, n, ks in ((12, 1, 900, [3]), (24, 16, 4096, list(range(1, 65))), (32, 3, 2000, list(range(2, 40))), (9, 500, 77, [2, 64]),
+                        (24, 8, 2500, [72, 96, 128])):
+        ld = (T * n + 3) // 4 * 4
+        off = [n * t for t in range(T + 1)]
+        want = resident(ld, T, ks)
+        assert binding.cham_static_bytes(ld, d, off, ks) == want
+        assert binding.cham_sweep_workspace_bytes(ld, d, off, ks, 5) >= want
+    # the counted size decides to the last byte: 64 values of k, rows up to the limit
+    ks = list(range(1, 65))
+    n = next(n for n in range(65536, 0, -4) if resident(n, 16, ks) <= limit)
+    assert limit - resident(n, 16, ks) < 1024
+    off = [0] + [min(n, 4096 * t) for t in range(1, 16)] + [n]
+    assert binding.cham_static_bytes(n, 24, off, ks) <= limit
+    with pytest.raises(binding.ChamError):
+        binding.cham_static_bytes(4000, 4, range(0, 4002, 2), [1, 2])           # host tables beyond the stack's part
+    with pytest.raises(binding.ChamError):
+        binding.cham_static_bytes(64, 4, [0, 10], [1, 2], 1 << 20)
