@@ -1129,14 +1129,14 @@ __device__ __forceinline__ const unsigned char *packed_task(const SweepArgs &a, 
 // bytes 10.9 / 13.5, one of 2000 x 24 8.8 / 10.4, 64 of up to 600 x 48 two-byte knobs 12.6 / 20.0, of up to 2048 x 32 13.7 / 19.8, values in
 // two parts 13.4 / 15.5.
 template <int DK, typename XT, bool SEP, int PL>
-__global__ __launch_bounds__(kPackRows) void pack_centred_kernel(const SweepArgs a, int per_task)
+__global__ __launch_bounds__(kPackRows) void pack_centred_kernel(const SweepArgs a, int per_task, int first_task)
 {
     constexpr bool kByteKnobs = sizeof(XT) == 1;
     constexpr int NM = DK > 32 ? 2 : 1, NP = (int)sizeof(XT);
     __shared__ int off[DK];
     __shared__ unsigned top_sq, sum_sq;
     __shared__ __align__(16) unsigned char raw[NP][32 * NM][kPackRows + 16];      // (16: the lanes of a fragment read different banks)
-    const int t = (int)(blockIdx.x / (unsigned)per_task), b = (int)(blockIdx.x % (unsigned)per_task);
+    const int t = first_task + (int)(blockIdx.x / (unsigned)per_task), b = (int)(blockIdx.x % (unsigned)per_task);
     const int64_t r0 = a.task_off[t];
     const int nrows = (int)(a.task_off[t + 1] - r0);
     if (b * kPackRows >= nrows) return;
@@ -1710,8 +1710,16 @@ hipError_t launch_mfma_t(const SweepArgs &a, int nwaves, int64_t n_max, int64_t 
     size_t lds;
     if constexpr (NTW == 0) {
         const unsigned per_task = (unsigned)((n_max + kPackRows - 1) / kPackRows);
-        if (per_task && a.ki_begin == 0)
-            hipLaunchKernelGGL((pack_centred_kernel<DK, XT, SEP, PL>), dim3(per_task * (unsigned)a.T), dim3(kPackRows), 0, s, a, (int)per_task);
+        if (per_task && a.ki_begin == 0) {
+            // (a launch takes less than 2^32 threads: 2^20 tasks of sixteen workgroups and more go in parts)
+            const int tasks = (int)((1u << 23) / per_task);
+            for (int first = 0; first < a.T; first += tasks) {
+                const unsigned here = (unsigned)(a.T - first < tasks ? a.T - first : tasks);
+                hipLaunchKernelGGL((pack_centred_kernel<DK, XT, SEP, PL>), dim3(per_task * here), dim3(kPackRows), 0, s, a, (int)per_task, first);
+                const hipError_t e = hipGetLastError();
+                if (e != hipSuccess) return e;
+            }
+        }
         lds = MfmaLds<DK, SEP>::base_bytes(KP) + (MANY ? ManyQueue<DK>::bytes(nwaves) : FetchedQueue<DK, PL>::kBytes) * nwaves;
     } else {
         const unsigned pb = (unsigned)((n_total + 255) / 256);
