@@ -45,10 +45,10 @@ struct SweepArgs {
     int *norms;                    // [T][32] per 256 rows of a task: [0..15] float bits of the largest squared norm of a centred row, [16..31] sum of the raw squared norms
     int *unit_counter;             // [kUnitQueues] zeroed before the launch: next unit of every queue (matrix-core resident kernel)
     int n_queues;                  // 1, or kUnitQueues: task t belongs to queue t % n_queues
-    int loss_parts;                // matrix-core kernel, rows in registers: 1 = the loss by parts of a task, as where rows are fetched
     int queue_group;               // tasks of a queue whose units are handed out together, largest k first
     int ki_begin, ki_end;          // this launch runs ks[ki_begin .. ki_end) (the whole list by default)
     const int *done;               // [T] or null: tasks whose sweep has already stopped; their units are skipped (status 3)
+    int loss_parts;                // matrix-core kernel, rows in registers: 1 = the loss by parts of a task, as where rows are fetched
 };
 
 // LDS bytes the resident kernel needs for padded knob count DP and largest k.
