@@ -352,7 +352,7 @@ const char *cham_strerror(int32_t code)
     }
 }
 
-// Two-byte knobs always run the vector resident kernel; its LDS need bounds k * padded knob count.
+// The LDS need of the vector resident kernel on two-byte knobs bounds k * padded knob count (also of calls that run values in two parts).
 static bool u16_fits(const Plan &pl) { return resident_lds_bytes(pl.DP, pl.kmax, 8) <= 160 * 1024; }
 
 static int xh_halfs_of(SweepPath path, int xbytes, int d)

@@ -14,7 +14,7 @@ __host__ __device__ constexpr int loss_run(int d, int k) { return d <= 16 && k <
 // Arguments of the sweep kernels.  Pointers are device pointers.
 struct SweepArgs {
     const uint8_t *X;              // knob values, [d][ld] items of xbytes bytes each
-    int xbytes;                    // 1: byte knobs; 2: two-byte knobs (vector resident kernel only)
+    int xbytes;                    // 1: byte knobs; 2: two-byte knobs (resident kernels)
     int64_t ld;
     int d;
     int T;

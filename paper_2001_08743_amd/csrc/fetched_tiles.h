@@ -565,7 +565,7 @@ __device__ __forceinline__ void apply_listed(const Queue &Q, int cnt, const unsi
 }
 
 // Tiles whose rows are fetched ahead (even: the accumulators alternate).
-constexpr int rows_ahead(int W, bool two, bool SEP, bool CIN) { return (W == 16 && !CIN) || (W == 32 && !two) ? 4 : 2; }
+constexpr int rows_ahead(int W, bool two, bool CIN) { return (W == 16 && !CIN) || (W == 32 && !two) ? 4 : 2; }
 
 // The undecided rows of a wave: their knobs from the packed copy, a batch at a time, then the exact evaluation.
 template <int DK, int PL>
@@ -639,7 +639,7 @@ __device__ __forceinline__ int decide_tiles(const Queue &Q, const Tiles &T, int 
     constexpr int PL = Queue::kPlanes, NB = NS * PL, NC = NS2 * PL;      // B fragments of a row, instructions of a chain
     constexpr int CH = NC == 6 ? 4 : (NC == 12 ? 2 : 16 / NC);           // scores handled between two matrix instructions
     constexpr unsigned kTileBytes = 32 * DK * PL * 2;
-    constexpr int kAhead = rows_ahead(DK * PL, TWO, SEP, CIN);
+    constexpr int kAhead = rows_ahead(DK * PL, TWO, CIN);
     const std::integral_constant<int, LREGS> live_tag;
     const int n32 = lane & 31;
     const unsigned char *packed = T.packed;

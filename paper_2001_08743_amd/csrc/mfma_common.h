@@ -1,5 +1,5 @@
 // Pieces shared by the matrix-core kernels (resident and streaming): fragment types, the error
-// bound of the f16 hi/lo screen, half-wave exchange and score-index decoding.
+// bound of the f16 hi/lo screen and the exchange between half-waves.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -43,11 +43,6 @@ __device__ __forceinline__ float mfma_bound(float x2, float m2)
 template <int NS2>
 constexpr float mfma_bound_slope() { return 2.5f * (float)(18 * NS2 + 6) * 5.9604644775390625e-8f; }      // ... per |x'|^2
 
-__device__ __forceinline__ float min3f(float a, float b, float c)
-{
-    return __builtin_fminf(__builtin_fminf(a, b), c);
-}
-
 // Both 32-lane halves of a value: lo = the value held by lanes 0..31, hi = by lanes 32..63
 // (v_permlane32_swap: a VALU exchange, no LDS round trip).
 __device__ __forceinline__ void both_halves(unsigned v, unsigned &lo, unsigned &hi)
@@ -55,18 +50,6 @@ __device__ __forceinline__ void both_halves(unsigned v, unsigned &lo, unsigned &
     const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
     lo = r[0];
     hi = r[1];
-}
-__device__ __forceinline__ float min_halves(float v)
-{
-    unsigned lo, hi;
-    both_halves(__float_as_uint(v), lo, hi);
-    return __builtin_fminf(__uint_as_float(lo), __uint_as_float(hi));
-}
-
-// centroid index of score q (processing order: m-tile, then accumulator register) in lane half hh
-__device__ __forceinline__ int centroid_of(int q, int hh)
-{
-    return 32 * (q >> 4) + 8 * ((q & 15) >> 2) + 4 * hh + (q & 3);
 }
 
 }  // namespace cham
