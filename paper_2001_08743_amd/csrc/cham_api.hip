@@ -184,13 +184,12 @@ int32_t check_common(const void *X, int64_t ld, int32_t d, const int64_t *task_o
 
 constexpr int kStreamRowsPerWg = 4096;      // rows per workgroup of the streaming assignment, at most
 
-// Rows one workgroup of the streaming assignment walks: 4096, halved (down to the 512 rows that one step
-// of its four waves holds) while the launch has fewer than two workgroups per compute unit.  Measured per
-// sampling step on 256 of them, 4096 / 2048 / 1024 / 512 rows: 48 units of 900 to 2500 rows 1064 / 1023 / 801 / 676 us; 42 units of 21 000 to 60 000 rows (385 / 770 / 1540 / 3080 workgroups)
-// 1749 / 1418 / 1476 / 1777 us; 5 units of 2^20 rows (1280 / 2560 workgroups) 2890 / 3052 us.  Two also where LDS holds
-// one at a time: 111 760 x 18, k = 16..256, 2048 / 1024 rows (275 / 550 workgroups) 1137 / 993 us.  Not below what
-// gives a task 512 workgroups: one unit of 300 000 x 16 with k = 64, 1024 / 512 rows (293 / 586 workgroups) 520 / 789 us
-// (its steps hold 1024 rows).  The order of the loss does not depend on it; below 4096 rows its partials, one
+// Rows one workgroup of the streaming assignment walks: 4096, halved (down to 512, 64 for each of its eight waves) while the
+// launch has fewer than two workgroups per compute unit.  us a sweep on 256 of them, 4096 / 2048 / 1024 / 512 rows: 48 units of 900
+// to 2500 x 24 771 / 631 / 531 / 475; 42 units of 21 000 to 60 000 x 23 (385 / 770 / 1540 / 3080 workgroups) 1047 / 1072 / 1159 / 1526; 5 units
+// of 2^20 x 16 (1280 / 2560 / 5120 / 10 240) 2038 / 2349 / 3069 / 4626.  Two also where LDS holds one at a time: 111 760 x 18, k = 16..256
+// (140 / 275 / 550 / 1095) 1356 / 964 / 918 / 1242.  Not below what gives a task 512 workgroups: one unit of 300 000 x 16 with
+// k = 64 (74 / 147 / 293 / 586) 548 / 489 / 550 / 677.  The order of the loss does not depend on it; below 4096 rows its partials, one
 // per 4096 rows, stand in the unit's sums, which hold 512 of them at least.  A traced sweep has them in every
 // pass and keeps 4096.
 int stream_rows_per_wg(const Plan &pl, const int64_t *task_off, int n_ks, bool traced, int cus)

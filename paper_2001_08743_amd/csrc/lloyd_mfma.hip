@@ -24,7 +24,7 @@
 // The matrix instructions of the next tile are issued between the epilogue pieces of the current
 // one.  Centroids, labels, integer sums and counts stay in LDS; a row touches the sums only when its label changes (exact: the
 // sums are integers), through a dense per-wave queue.  The rows (f16 B fragments) stay in registers for all passes
-// (run_unit: tasks of at most 1024 rows) or are fetched from packed tiles in every pass (run_unit_fetched), which lets two
+// (run_unit: tasks of at most 1024 rows, and where few units run also larger ones) or are fetched from packed tiles in every pass (run_unit_fetched), which lets two
 // workgroups share a compute unit whatever the size of the task: 256 tasks x 4096 x 24, k = 1..64: 16.9 -> 12.7 ms a step.
 //
 // A pass that changes no label leaves the sums, hence the centroids, hence every later pass as
@@ -1245,7 +1245,7 @@ __host__ __device__ constexpr int centroid_rows(int kmax) { return MANY ? (kmax 
 // bound of it; the marks of a chunk count iff its minimum is within the bound of the overall one (that keeps every centroid
 // within the bound of the overall minimum, and some up to two bounds away).  LDS holds one workgroup per compute unit, of
 // sixteen waves up to k = 192.  16 tasks of up to 2500 x 24, k = 72, 96, 128, 20 steps: the streaming kernels' 43
-// launches 645 us a step, one launch of this 460 us.
+// launches 645 us a step, one launch of this 450 us.
 template <int DK, typename XT, bool SEP, bool MANY, int PL>
 __device__ __forceinline__ void run_unit_fetched(const SweepArgs &a, unsigned char *smem, int ki, int t, int k)
 {
@@ -1351,7 +1351,7 @@ __device__ __forceinline__ void run_unit_fetched(const SweepArgs &a, unsigned ch
     __syncthreads();
     update_centroids<DK, kByteKnobs, SEP, PL>(U, k, KP, d, 0, true);
     __syncthreads();
-    // Screen bound of the unit: that of its farthest row.  Largest squared norm a centred centroid can take during the iteration: every
+    // Screen bound of the unit: that of its farthest row, half as much again as the origin's at most (m2 counts twice).  Largest squared norm a centred centroid can take during the iteration: every
     // later centroid is a mean of rows (inside their convex hull) or stays where it started.
     float bound;
     {
@@ -1831,7 +1831,7 @@ static hipError_t launch_mfma_sweep_t(const SweepArgs &a, int64_t n_max, int64_t
         }
         return hipErrorInvalidValue;        // (byte knobs never come with more than 32 knobs)
     }
-    // Rows in registers: four tiles per wave hold 1024 rows in eight waves.  Two where one task's latency counts (no more units than
+    // Rows in registers: four tiles per wave hold 1024 rows in eight waves, eight 2048 (32 byte knobs, few units).  Two where one task's latency counts (no more units than
     // compute units), DK = 16, up to 512 rows: 256 rows 121 / 102 us a step, 500 rows 137 / 109 us; with many
     // units four are as good (64 tasks x 500 rows 271 / 277 us).
     const int ntw = n_max <= 512 && DK == 16 && (int64_t)a.T * (a.ki_end - a.ki_begin) <= cus ? 2 : (few && sep && n_max > 1024 ? 8 : 4);
@@ -1851,9 +1851,10 @@ static hipError_t launch_mfma_sweep_t(const SweepArgs &a, int64_t n_max, int64_t
 
 // k beyond 64 (byte knobs, d <= 31): within what LDS holds beside a wave's labels, and up to 7000 rows x chunks of 64 centroids. One
 // compute unit has a unit's rows to itself here, the streaming kernels spread them over the chip at two launches a pass.
-// us a step, this / streaming, 20 steps, 24 knobs, 2 and 16 tasks: k = 72, 96, 128: 1500 rows 346 / 507 and 369 / 576, 2500 rows 498 / 602 and
-// 525 / 618, 4096 rows 691 / 628 and 728 / 706; k = 100, 200: 1500 rows 486 / 515 and 529 / 639, 2500 rows 726 / 632 and 996 / 799.  (With
-// 96 units of 4096 rows and k up to 128 this would be ahead again, 743 / 974, but the order of a loss would then depend on the batch.)
+// us a sweep, this / streaming, 20 steps, 24 knobs, 2 and 16 tasks: k = 72, 96, 128: 1500 rows 230 / 379 and 244 / 444, 2500 rows 360 / 450 and
+// 387 / 508, 4096 rows 552 / 485 and 557 / 580; k = 100, 200: 1500 rows 264 / 345 and 350 / 484, 2000 rows 363 / 397 and 448 / 459.  At the limit,
+// one task of 3500 rows, k = 66: 451 / 431; 100 tasks of up to 3400, k = 65: 503 / 764.  (With 96 units of 4096 rows and k up to 128 this would be
+// ahead again, 567 / 799.)
 bool mfma_many_fits(int d, int kmax, int64_t n_max)
 {
     return d >= 1 && d <= 31 && kmax > 64 && kmax <= kManyCentroids && n_max * ((kmax + 63) / 64) <= 7000;
