@@ -482,7 +482,7 @@ __device__ __forceinline__ void resolve_pairs(const ManyQueue<DK> &Q, int nrec, 
     };
     // 64 pairs at a time: where they lower a row's smallest distance, the centroids that attained the one before no longer count
     // (A distance is evaluated once.  With a second walk for the centroids behind one for the distances, and full lists more often (below):
-    // starts 3000 from the rows, 8 tasks of 2500 x 24, k = 72 and 128, 17 700 / 11 100 us a sweep; few values per knob, 84 shapes, 8 % more.)
+    // starts 3000 from the rows, streaming, 60 000 x 24, k = 64 and 128, 5110 / 2890 us a sweep; few values per knob, 84 shapes, 8 % more.)
     for (unsigned p0 = 0; p0 < np; p0 += 64) {
         const bool have = p0 + lane < np;
         int r = 0, c = 0;

@@ -91,6 +91,31 @@ def test_streaming_candidates_without_number_listed_pair_by_pair(n, k, d, byte):
     check_sweep(wl, out, oracle.sweep(wl.rows, wl.task_off, wl.ks, wl.n_iter, init=init, want_labels=True), dw.ld)
 
 
+@pytest.mark.parametrize("n,d,k", [(641, 9, 70), (1500, 24, 100), (2333, 15, 129), (1281, 31, 193)])
+@pytest.mark.parametrize("near", [0, 1, 40])
+def test_starts_no_row_can_be_nearest_to(n, d, k, near):
+    # from three times the farthest row's (or the nearest start's) distance on a start takes no part in the screen: starts on both sides of that, from
+    # just outside the rows to 1e200, centroid 0 among them, with none, one and many starts among the rows
+    wl = workloads.random_task(n + d + near, n, d, card_lo=100, card_hi=256, n_blobs=9, sigma=20.0, ks=(64, k), n_iter=6, n_tasks=2)
+    rng = np.random.default_rng(n)
+    away = np.concatenate([np.geomspace(0.8, 4.0, 24), np.geomspace(10.0, 1.0e4, 12), [1.0e9, 1.0e17, 1.0e200]])
+    init = np.empty((2, 64 + k, d))
+    for t in range(2):
+        rows = wl.rows[wl.task_off[t]:wl.task_off[t + 1]].astype(np.float64)
+        centre = rows.mean(axis=0)
+        reach = np.sqrt(((rows - centre) ** 2).sum(axis=1).max())
+        way = rng.normal(size=(64 + k, d))
+        init[t] = centre + way / np.linalg.norm(way, axis=1, keepdims=True) * reach * rng.choice(away, size=(64 + k, 1))
+        for first, kk in ((0, 64), (64, k)):
+            init[t, first + kk - near:first + kk] = rows[:near]
+    _sweep(wl, want_trace=True, init=init)
+    import torch
+    dw = binding.DeviceWorkload(wl)
+    both = [binding.cham_kmeans_sweep(dw.X, dw.ld, d, wl.task_off, wl.ks, wl.n_iter, init_centroids=torch.from_numpy(init).to(dw.X.device), want_labels=True, flags=f)
+            for f in (0, binding.F_STREAMING)]
+    _same_bits(*both, ("status", "centroids", "counts", "inertia"))
+
+
 def _same_bits(a, b, keys):
     for key in keys:
         np.testing.assert_array_equal(a[key].cpu().numpy(), b[key].cpu().numpy(), err_msg=key)
